@@ -75,6 +75,9 @@ struct SearchArgs {
   u32* out_ids;
   void* out_dists;
   DevCounters* counters;  // may be null
+  // for the host's choice of kernel
+  u64 n;             // vertices of the graph
+  u32 filter_given;  // non-zero: the filter's size is the caller's choice and stays
 };
 
 // The walk of a query through the upper layers of the layered index (Sec. 4.2): a search with

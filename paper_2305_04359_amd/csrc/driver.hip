@@ -323,6 +323,8 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   sa.k = 1;
   sa.hash_buckets = search_hash_buckets(L, g->hash_bits);
   search_filter_mode(g->n, sa.hash_buckets, &sa.id_bits, &sa.tag_width);
+  sa.n = g->n;
+  sa.filter_given = g->hash_bits;
   sa.batch_counters = small;
   sa.eps16 = -1;
   sa.epsf = 0.0f;
@@ -601,6 +603,8 @@ int query_launch(const ann_graph* g, const void* pts, const void* queries, const
   sa.k = k;
   sa.hash_buckets = search_hash_buckets(L, g->hash_bits);
   search_filter_mode(g->n, sa.hash_buckets, &sa.id_bits, &sa.tag_width);
+  sa.n = g->n;
+  sa.filter_given = g->hash_bits;
   sa.eps16 = eps >= 0.0f ? llround((double)eps * 65536.0) : -1;
   sa.epsf = eps >= 0.0f ? eps : 0.0f;
   sa.out_ids = out_ids;

@@ -18,6 +18,7 @@
 
 #include "ann_device.hpp"
 #include "ann_internal.hpp"
+#include "wave_sort.hpp"
 
 namespace annmi {
 
@@ -39,6 +40,262 @@ __device__ __forceinline__ u32 umulhi24(u32 a, u32 b) {
 typedef unsigned short us2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u32 pk_min_u16(u32 a, u32 b) {
   return __builtin_bit_cast(u32, __builtin_elementwise_min(__builtin_bit_cast(us2_t, a), __builtin_bit_cast(us2_t, b)));
+}
+
+// The key no candidate may reach to enter a beam of L entries of which `size` are taken.  (FLAGS:
+// the low bits of a beam entry that are no part of its key.)
+template <int NSLOT, u64 FLAGS>
+__device__ __forceinline__ u64 beam_worst(const u64 (&A)[NSLOT], u32 L, u32 size) {
+  u64 worst = KEY_INF;
+  if (size == L) {
+#pragma unroll
+    for (int s = 0; s < NSLOT; ++s)
+      if ((int)((L - 1) >> 6) == s) worst = readlane_u64(A[s], (int)((L - 1) & 63)) | FLAGS;
+  }
+  return worst;
+}
+
+// the wave's keys moved down by one lane: lane l gets lane l + 1's, lane 63 gets `top`
+__device__ __forceinline__ u64 shift_down_one(u64 k, u64 top) {
+  const u32 lo = (u32)__builtin_amdgcn_update_dpp((int)(u32)top, (int)(u32)k, 0x130, 0xF, 0xF, false);
+  const u32 hi = (u32)__builtin_amdgcn_update_dpp((int)(u32)(top >> 32), (int)(u32)(k >> 32), 0x130, 0xF, 0xF, false);
+  return ((u64)hi << 32) | lo;
+}
+
+// beam <- the L closest of the beam and `ns` survivors (KEY_INF in the other lanes), by a sorting
+// network: the smaller of each pair (entry of the beam's last slot, survivor in descending order),
+// then a merge.  LAST_ROW: the survivors are in lanes 48 to 63.  False, and the beam unchanged, if
+// a survivor is in the beam already (the filter lost it): it then stands next to the entry it repeats,
+// in the beam or at its end.
+template <int NSLOT, u64 FLAGS, bool LAST_ROW>
+__device__ __forceinline__ bool insert_sorted(u64 (&A)[NSLOT], u64 survivor, u32 ns, u32 L, u32& size, int lane) {
+  u64 B[NSLOT];
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) B[s] = A[s];
+  u64 v[1] = {survivor};
+  if constexpr (LAST_ROW)
+    BitonicStage<1, 2, false, 16>::run(v);  // the rows of odd number end in descending order
+  else
+    BitonicStage<1, 2, true, 64>::run(v);
+  const u64 last = B[NSLOT - 1];
+  const bool keep = last < v[0];
+  const u64 out = keep ? v[0] : last;
+  B[NSLOT - 1] = keep ? last : v[0];
+  bitonic_merge<NSLOT>(B);
+  u64 next_first = KEY_INF;  // the smallest key of the next slot, for lane 63
+  bool dup = false;
+#pragma unroll
+  for (int s = NSLOT - 1; s >= 0; --s) {
+    const u64 up = shift_down_one(B[s], next_first);
+    dup = dup || (B[s] != KEY_INF && (up | FLAGS) == (B[s] | FLAGS));
+    next_first = readlane_u64(B[s], 0);
+  }
+  const u64 end = readlane_u64(B[NSLOT - 1], 63);
+  dup = dup || (out != KEY_INF && (out | FLAGS) == (end | FLAGS));
+  if (ballot(dup) != 0) return false;
+  size = size + ns < L ? size + ns : L;
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) A[s] = (u32)(s * 64 + lane) < size ? B[s] : KEY_INF;
+  return true;
+}
+
+// beam <- the L closest of the beam and the lanes' candidates (KEY_INF: none); returns how many
+// candidates were below the beam's last entry and not in the beam already.  Called by one whole
+// wave; `sync` orders its LDS accesses before and after against each other.
+//
+// With the chip full the sorting network takes as many vector instructions as ranks by bisection
+// and counting at 45 survivors of a two-slot beam, at 20 of a one-slot beam, and is used from there
+// in one-slot beams only (10,000 queries at L = 16: 207 -> 196 us; two slots, build of a million
+// points: 79.3 -> 80.0 ms).
+template <int NSLOT, class Sync>
+__device__ __forceinline__ u32 beam_insert(u64 (&A)[NSLOT], u64* beam, u64* skeys, u64 mykey, u32 L, u32& size,
+                                           int lane, Sync sync) {
+  constexpr u64 FLAGS = 1;
+  const u64 worst = beam_worst<NSLOT, FLAGS>(A, L, size);
+  bool surv = mykey < worst;
+  u64 sm = ballot(surv);
+  u32 ns = 0;
+  if (NSLOT == 1 && __builtin_popcountll(sm) >= 20) {
+    ns = (u32)__builtin_popcountll(sm);
+    if (insert_sorted<NSLOT, FLAGS, false>(A, surv ? mykey : KEY_INF, ns, L, size, lane)) {
+#pragma unroll
+      for (int s = 0; s < NSLOT; ++s) beam[s * 64 + lane] = A[s];
+      sync();
+      return ns;
+    }
+    ns = 0;
+  }
+  if (sm) {
+    u32 myrA = 0, myrB = 0;
+    u32 shift[NSLOT];
+#pragma unroll
+    for (int s = 0; s < NSLOT; ++s) shift[s] = 0;
+    if (__builtin_popcountll(sm) >= 4) {
+      // many survivors: each finds its rank among the beam entries by bisection in the LDS
+      // copy of the beam; a survivor that is already in the beam (the filter lost it) sits
+      // exactly at its rank there and is dropped
+      // the rank is at most 64 * NSLOT - 1 (a survivor lies below the last entry of a full
+      // beam): one step per bit of it, each keeping the bit if that many entries lie below
+      // the key; entries past `size` are never counted (the read stays inside the array)
+      constexpr int BITS = (NSLOT == 1 ? 6 : NSLOT == 2 ? 7 : NSLOT == 4 ? 8 : NSLOT == 8 ? 9 : NSLOT == 16 ? 10 : 11);
+      const u64 sk1 = mykey | FLAGS;
+      u32 lo = 0;
+#pragma unroll
+      for (int bit = BITS - 1; bit >= 0; --bit) {
+        const u32 t = lo + (1u << bit);
+        const u64 v = beam[t - 1u] | FLAGS;
+        lo = (t <= size && v < sk1) ? t : lo;
+      }
+      myrA = lo;
+      if (surv && lo < size && (beam[lo] | FLAGS) == sk1) surv = false;
+      sm = ballot(surv);
+      ns = (u32)__builtin_popcountll(sm);
+      if (surv) skeys[__builtin_popcountll(sm & lanemask_lt(lane))] = mykey;
+      sync();
+      // ranks among the survivors, and how far each beam entry moves
+      // (a lane without a survivor counts too: its sum is never read)
+      for (u32 j = 0; j < ns; ++j) {
+        const u64 sj = skeys[j];
+        myrB += (sj < mykey) ? 1u : 0u;
+#pragma unroll
+        for (int s = 0; s < NSLOT; ++s) shift[s] += (sj < A[s]) ? 1u : 0u;
+      }
+      sync();
+    } else {
+      // few survivors: one at a time, ranks from wave-wide compares
+      for (u64 it = sm; it; it &= it - 1) {
+        const int l = __builtin_ctzll(it);
+        const u64 sk = readlane_u64(mykey, l);
+        u32 rA = 0;
+#pragma unroll
+        for (int s = 0; s < NSLOT; ++s) rA += __builtin_popcountll(ballot(A[s] < sk));
+        u64 at = KEY_INF;
+#pragma unroll
+        for (int s = 0; s < NSLOT; ++s)
+          if ((int)(rA >> 6) == s) at = readlane_u64(A[s], (int)(rA & 63));
+        const bool dup = (at | FLAGS) == (sk | FLAGS);
+        if (lane == l) {
+          myrA = rA;
+          if (dup) surv = false;
+        }
+      }
+      sm = ballot(surv);
+      for (u64 it = sm; it; it &= it - 1) {
+        const int l = __builtin_ctzll(it);
+        const u64 sk = readlane_u64(mykey, l);
+        const u32 rB = __builtin_popcountll(ballot(surv && mykey < sk));
+#pragma unroll
+        for (int s = 0; s < NSLOT; ++s) shift[s] += (sk < A[s]) ? 1u : 0u;
+        if (lane == l) myrB = rB;
+        ++ns;
+      }
+    }
+    if (sm) {
+#pragma unroll
+      for (int s = 0; s < NSLOT; ++s) {
+        const u32 np = (u32)(s * 64 + lane) + shift[s];
+        if (A[s] != KEY_INF && np < L) beam[np] = A[s];
+      }
+      if (surv) {
+        const u32 np = myrA + myrB;
+        if (np < L) beam[np] = mykey;
+      }
+      size = size + ns < L ? size + ns : L;
+      sync();
+#pragma unroll
+      for (int s = 0; s < NSLOT; ++s) {
+        const u32 idx = (u32)(s * 64 + lane);
+        A[s] = idx < size ? beam[idx] : KEY_INF;
+      }
+      sync();
+    }
+  }
+  return ns;
+}
+
+// An entry pk of the beam is beyond the bound that its k-th entry kk sets.
+// Integers: d * 2^16 > d_k * (2^16 + eps16), exact; floats: d > d_k + eps * |d_k|, one fp32
+// product and one fp32 sum.
+template <int KIND>
+__device__ __forceinline__ bool beyond_eps(u64 pk, u64 kk, const SearchArgs& a) {
+  if constexpr (KindTraits<KIND>::is_int) {
+    const long long d = int_from_dkey(key_dkey(pk)), dk = int_from_dkey(key_dkey(kk));
+    return d * 65536ll > dk * (65536ll + a.eps16);
+  } else {
+    const float d = float_from_dkey(key_dkey(pk)), dk = float_from_dkey(key_dkey(kk));
+    return d > __fadd_rn(dk, __fmul_rn(a.epsf, __builtin_fabsf(dk)));
+  }
+}
+// entry i of the beam (wave-uniform)
+template <int NSLOT>
+__device__ __forceinline__ u64 beam_entry(const u64 (&A)[NSLOT], u32 i) {
+  u64 k = 0;
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s)
+    if ((int)(i >> 6) == s) k = readlane_u64(A[s], (int)(i & 63u));
+  return k;
+}
+
+// Entry nv of search qi's visited list.  (vptr, vcap) are wave-uniform; vptr turns null when the
+// list is lost (it fits neither its slot nor a spill chunk: the prune kernel sees nv > room and
+// reports it).
+__device__ __forceinline__ void visited_append(const SearchArgs& a, u32 qi, u64*& vptr, u32& vcap, u32 nv, u64 pk,
+                                               int lane) {
+  if (vptr == nullptr) return;
+  if (nv == vcap) {  // the list is full
+    u64* moved = nullptr;
+    u32 newcap = 0;
+    if (vcap == a.vis_cap && a.spill != nullptr) {  // still in its slot: move to a spill chunk
+      const u64 need = (u64)vcap + a.spill_chunk;
+      unsigned long long off = 0;
+      if (lane == 0) off = atomicAdd(a.spill_top, (unsigned long long)need);
+      off = readlane_u64(off, 0);
+      if (off + need <= a.spill_cap) {
+        __threadfence();
+        u64* dst = a.spill + off;
+        for (u32 i = lane; i < vcap; i += 64)
+          dst[i] = __hip_atomic_load(vptr + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) a.vis_where[qi] = off;
+        moved = dst;
+        newcap = (u32)need;
+      }
+    }
+    vptr = reinterpret_cast<u64*>(readlane_u64(reinterpret_cast<u64>(moved), 0));
+    vcap = readlane_u32(newcap, 0);
+  }
+  if (vptr != nullptr && lane == 0) vptr[nv] = pk;
+}
+
+// The first k entries of the beam as search qi's results.
+template <int KIND, int NSLOT>
+__device__ __forceinline__ void write_results(const u64 (&A)[NSLOT], const SearchArgs& a, u32 qi, int lane) {
+  if (a.out_ids == nullptr) return;
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) {
+    const u32 idx = (u32)(s * 64 + lane);
+    if (idx < a.k) {
+      const bool ok = A[s] != KEY_INF;
+      const u64 o = (u64)qi * a.k + idx;
+      a.out_ids[o] = ok ? key_id(A[s]) : NONE_ID;
+      if (a.out_dists != nullptr) {
+        if constexpr (KindTraits<KIND>::is_int)
+          reinterpret_cast<i32*>(a.out_dists)[o] = ok ? int_from_dkey(key_dkey(A[s])) : 0x7FFFFFFF;
+        else
+          reinterpret_cast<float*>(a.out_dists)[o] = ok ? float_from_dkey(key_dkey(A[s])) : __builtin_inff();
+      }
+    }
+  }
+}
+
+// the words of a batch's counters that the steps after the searches count in
+__device__ __forceinline__ void zero_batch_counters(u32* c) {
+  c[0] = 0;
+  c[4] = 0;
+  c[5] = 0;
+  c[8] = 0;
+  c[9] = 0;
+  c[10] = 0;
+  c[11] = 0;
 }
 
 // EPS: the (1 + eps) rule is compiled in.  TAG16: the filter holds 16-bit tags (graphs of up to
@@ -78,15 +335,7 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
       load_query<KIND, VEC, NCH>(a.queries + (u64)qrow * a.qrow_bytes, T.npieces, lane);
 
   for (u32 i = lane; i < hsize; i += 64) hash[i] = NONE_ID;
-  if (a.batch_counters != nullptr && qi == 0 && lane == 0) {
-    a.batch_counters[0] = 0;
-    a.batch_counters[4] = 0;
-    a.batch_counters[5] = 0;
-    a.batch_counters[8] = 0;
-    a.batch_counters[9] = 0;
-    a.batch_counters[10] = 0;
-    a.batch_counters[11] = 0;
-  }
+  if (a.batch_counters != nullptr && qi == 0 && lane == 0) zero_batch_counters(a.batch_counters);
 
   u64 A[NSLOT];
 #pragma unroll
@@ -144,50 +393,13 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
     if (pos < 0) break;
     // (1 + eps) rule of Sec. 4.5: p* is searched only while its distance is within the bound of
     // the beam's k-th entry; the beam is sorted and that entry never moves away, so the first
-    // failure ends the search.  Integers: d * 2^16 > d_k * (2^16 + eps16), exact; floats:
-    // d > d_k + eps * |d_k|, one fp32 product and one fp32 sum.
+    // failure ends the search.
     if (EPS && size >= a.k) {  // compiled in only for searches that use the rule
-      u64 kk = 0;
-#pragma unroll
-      for (int s = 0; s < NSLOT; ++s)
-        if ((int)((a.k - 1u) >> 6) == s) kk = readlane_u64(A[s], (int)((a.k - 1u) & 63u));
-      bool beyond;
-      if constexpr (KindTraits<KIND>::is_int) {
-        const long long d = int_from_dkey(key_dkey(pk)), dk = int_from_dkey(key_dkey(kk));
-        beyond = d * 65536ll > dk * (65536ll + a.eps16);
-      } else {
-        const float d = float_from_dkey(key_dkey(pk)), dk = float_from_dkey(key_dkey(kk));
-        beyond = d > __fadd_rn(dk, __fmul_rn(a.epsf, __builtin_fabsf(dk)));
-      }
+      const bool beyond = beyond_eps<KIND>(pk, beam_entry<NSLOT>(A, a.k - 1u), a);
       if (beyond) break;  // (p* keeps its flag: nothing reads it once the search is over)
     }
     const u32 pstar = key_id(pk);
-    // visited list: (vptr, vcap) are wave-uniform; vptr turns null when the list is lost (it fits
-    // neither its slot nor a spill chunk: the prune kernel sees nv > room and reports it)
-    if (vptr != nullptr) {
-      if (nv == vcap) {  // the list is full
-        u64* moved = nullptr;
-        u32 newcap = 0;
-        if (vcap == a.vis_cap && a.spill != nullptr) {  // still in its slot: move to a spill chunk
-          const u64 need = (u64)vcap + a.spill_chunk;
-          unsigned long long off = 0;
-          if (lane == 0) off = atomicAdd(a.spill_top, (unsigned long long)need);
-          off = readlane_u64(off, 0);
-          if (off + need <= a.spill_cap) {
-            __threadfence();
-            u64* dst = a.spill + off;
-            for (u32 i = lane; i < vcap; i += 64)
-              dst[i] = __hip_atomic_load(vptr + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (lane == 0) a.vis_where[qi] = off;
-            moved = dst;
-            newcap = (u32)need;
-          }
-        }
-        vptr = reinterpret_cast<u64*>(readlane_u64(reinterpret_cast<u64>(moved), 0));
-        vcap = readlane_u32(newcap, 0);
-      }
-      if (vptr != nullptr && lane == 0) vptr[nv] = pk;
-    }
+    visited_append(a, qi, vptr, vcap, nv, pk, lane);
     ++nv;
 
     // beam <- beam U N_out(p*), keep the L closest
@@ -260,101 +472,9 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
         evals += m;
         n_pass += (m + 7u) >> 3;
 
-        u64 worst = KEY_INF;
-        if (size == L) {
-#pragma unroll
-          for (int s = 0; s < NSLOT; ++s)
-            if ((int)((L - 1) >> 6) == s) worst = readlane_u64(A[s], (int)((L - 1) & 63)) | 1ull;
-        }
-        bool surv = mykey < worst;
-        u64 sm = ballot(surv);
-        if (sm) {
-          u32 myrA = 0, myrB = 0, ns = 0;
-          u32 shift[NSLOT];
-#pragma unroll
-          for (int s = 0; s < NSLOT; ++s) shift[s] = 0;
-          if (__builtin_popcountll(sm) >= 4) {
-            // many survivors: each finds its rank among the beam entries by bisection in the LDS
-            // copy of the beam; a survivor that is already in the beam (the filter lost it) sits
-            // exactly at its rank there and is dropped
-            // the rank is at most 64 * NSLOT - 1 (a survivor lies below the last entry of a full
-            // beam): one step per bit of it, each keeping the bit if that many entries lie below
-            // the key; entries past `size` are never counted (the read stays inside the array)
-            constexpr int BITS = (NSLOT == 1 ? 6 : NSLOT == 2 ? 7 : NSLOT == 4 ? 8 : NSLOT == 8 ? 9 : NSLOT == 16 ? 10 : 11);
-            const u64 sk1 = mykey | 1ull;
-            u32 lo = 0;
-#pragma unroll
-            for (int bit = BITS - 1; bit >= 0; --bit) {
-              const u32 t = lo + (1u << bit);
-              const u64 v = beam[t - 1u] | 1ull;
-              lo = (t <= size && v < sk1) ? t : lo;
-            }
-            myrA = lo;
-            if (surv && lo < size && (beam[lo] | 1ull) == sk1) surv = false;
-            sm = ballot(surv);
-            ns = (u32)__builtin_popcountll(sm);
-            if (surv) skeys[__builtin_popcountll(sm & lanemask_lt(lane))] = mykey;
-            __syncthreads();
-            // ranks among the survivors, and how far each beam entry moves
-            // (a lane without a survivor counts too: its sum is never read)
-            for (u32 j = 0; j < ns; ++j) {
-              const u64 sj = skeys[j];
-              myrB += (sj < mykey) ? 1u : 0u;
-#pragma unroll
-              for (int s = 0; s < NSLOT; ++s) shift[s] += (sj < A[s]) ? 1u : 0u;
-            }
-            __syncthreads();
-          } else {
-            // few survivors: one at a time, ranks from wave-wide compares
-            for (u64 it = sm; it; it &= it - 1) {
-              const int l = __builtin_ctzll(it);
-              const u64 sk = readlane_u64(mykey, l);
-              u32 rA = 0;
-#pragma unroll
-              for (int s = 0; s < NSLOT; ++s) rA += __builtin_popcountll(ballot(A[s] < sk));
-              u64 at = KEY_INF;
-#pragma unroll
-              for (int s = 0; s < NSLOT; ++s)
-                if ((int)(rA >> 6) == s) at = readlane_u64(A[s], (int)(rA & 63));
-              const bool dup = (at | 1ull) == (sk | 1ull);
-              if (lane == l) {
-                myrA = rA;
-                if (dup) surv = false;
-              }
-            }
-            sm = ballot(surv);
-            for (u64 it = sm; it; it &= it - 1) {
-              const int l = __builtin_ctzll(it);
-              const u64 sk = readlane_u64(mykey, l);
-              const u32 rB = __builtin_popcountll(ballot(surv && mykey < sk));
-#pragma unroll
-              for (int s = 0; s < NSLOT; ++s) shift[s] += (sk < A[s]) ? 1u : 0u;
-              if (lane == l) myrB = rB;
-              ++ns;
-            }
-          }
-          if (sm) {
-#pragma unroll
-            for (int s = 0; s < NSLOT; ++s) {
-              const u32 np = (u32)(s * 64 + lane) + shift[s];
-              if (A[s] != KEY_INF && np < L) beam[np] = A[s];
-            }
-            if (surv) {
-              const u32 np = myrA + myrB;
-              if (np < L) beam[np] = mykey;
-            }
-            n_surv += ns;
-            ++n_ins;
-            size = size + ns < L ? size + ns : L;
-            __syncthreads();
-#pragma unroll
-            for (int s = 0; s < NSLOT; ++s) {
-              const u32 idx = (u32)(s * 64 + lane);
-              A[s] = idx < size ? beam[idx] : KEY_INF;
-            }
-            __syncthreads();
-          }
-        }
+        const u32 ns = beam_insert<NSLOT>(A, beam, skeys, mykey, L, size, lane, [] { __syncthreads(); });
+        n_surv += ns;
+        n_ins += ns != 0u ? 1u : 0u;
       }
       if (present != ~0ull) break;  // rows are compact: the first gap ends the row
     }
@@ -377,23 +497,7 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
       }
     }
   }
-  if (a.out_ids != nullptr) {
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-      const u32 idx = (u32)(s * 64 + lane);
-      if (idx < a.k) {
-        const bool ok = A[s] != KEY_INF;
-        const u64 o = (u64)qi * a.k + idx;
-        a.out_ids[o] = ok ? key_id(A[s]) : NONE_ID;
-        if (a.out_dists != nullptr) {
-          if constexpr (KindTraits<KIND>::is_int)
-            reinterpret_cast<i32*>(a.out_dists)[o] = ok ? int_from_dkey(key_dkey(A[s])) : 0x7FFFFFFF;
-          else
-            reinterpret_cast<float*>(a.out_dists)[o] = ok ? float_from_dkey(key_dkey(A[s])) : __builtin_inff();
-        }
-      }
-    }
-  }
+  write_results<KIND, NSLOT>(A, a, qi, lane);
   if (a.counters != nullptr && lane == 0) {
     atomicAdd(&block_counters(a.counters)->searches, 1ull);
     atomicAdd(&block_counters(a.counters)->hops, (unsigned long long)nv);
@@ -410,6 +514,11 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
 hipError_t launch_search_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
 hipError_t launch_search_own(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
 hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
+// Several waves per search (search_wide.hip): rows of at most 64 ids, beams of at most 256, ids of
+// at most 24 bits (beam entries and the 16-bit tags of a filter of 512 buckets).
+constexpr u32 WIDE_BUCKETS = 512;
+constexpr u64 WIDE_MAX_POINTS = 1ull << 24;
+hipError_t launch_search_wide(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, u32 waves, hipStream_t s);
 
 // beam slots per lane: the smallest power of two that holds L entries (beams of up to 2,048)
 inline u32 search_nslot_for(u32 L) {
