@@ -14,9 +14,13 @@
       case K_I8 * 1000 + 164: return FN<K_I8, 16, 4>(__VA_ARGS__);                             \
       case K_F32_L2 * 1000 + 162: return FN<K_F32_L2, 16, 2>(__VA_ARGS__);                     \
       case K_F32_L2 * 1000 + 164: return FN<K_F32_L2, 16, 4>(__VA_ARGS__);                     \
+      case K_F32_L2 * 1000 + 166: return FN<K_F32_L2, 16, 6>(__VA_ARGS__);                     \
+      case K_F32_L2 * 1000 + 167: return FN<K_F32_L2, 16, 7>(__VA_ARGS__);                     \
       case K_F32_L2 * 1000 + 168: return FN<K_F32_L2, 16, 8>(__VA_ARGS__);                     \
       case K_F32_IP * 1000 + 162: return FN<K_F32_IP, 16, 2>(__VA_ARGS__);                     \
       case K_F32_IP * 1000 + 164: return FN<K_F32_IP, 16, 4>(__VA_ARGS__);                     \
+      case K_F32_IP * 1000 + 166: return FN<K_F32_IP, 16, 6>(__VA_ARGS__);                     \
+      case K_F32_IP * 1000 + 167: return FN<K_F32_IP, 16, 7>(__VA_ARGS__);                     \
       case K_F32_IP * 1000 + 168: return FN<K_F32_IP, 16, 8>(__VA_ARGS__);                     \
       default: return hipErrorInvalidConfiguration;                                            \
     }                                                                                          \
