@@ -13,7 +13,7 @@ using u64 = uint64_t;
 struct DistCfg {
   int kind;       // Kind
   int vec;        // bytes per load: 16 or 4
-  int nch;        // pieces per lane: 1, 2, 4 or 8
+  int nch;        // pieces per lane: 1, 2, 4, 6, 7 or 8
   u32 npieces;    // pieces per row
   u64 row_bytes;  // d * sizeof(element)
 };

@@ -69,18 +69,22 @@ static hipError_t launch_search_plain(const DistCfg& cfg, const SearchArgs& a, c
 // its own chain of hops: four to eight waves take a search of a million 128-d uint8 points from 96
 // to 70 us at L = 64 and from 166 to 116 at L = 128 (one query), 512 of them from 175 to 130 and 414
 // to 299, 1,000 of them (four waves) from 188 to 146 and 419 to 322.  2,000 searches with four waves
-// each run out of wave slots (422 -> 439 us at L = 128).  Beams below 32 are over before the work
+// each run out of wave slots (422 -> 439 us at L = 128), and so do 800 on a graph that the last-level
+// cache holds, where hops wait less (build searches, L = 128, 40,000 to 90,000 points: 232 us by one
+// wave each, 242 by four; 480 of them by eight 230 -> 199).  Beams below 32 are over before the work
 // ahead pays (L = 16: 37.4 and 37.7 us for one query, 61.2 and 62.3 for 256).
-static u32 search_waves(const SearchArgs& a) {
+constexpr u64 LAST_LEVEL_CACHE = 256ull << 20;
+static u32 search_waves(const DistCfg& cfg, const SearchArgs& a) {
   const bool fits = a.R <= 64u && a.L <= 256u && a.n <= WIDE_MAX_POINTS && !a.filter_given;
   if (!fits || a.L < 32u || a.nq > 1024u) return 1;
-  return a.nq <= 512u ? 8 : 4;
+  if (a.nq <= 512u) return 8;
+  return a.n * (cfg.row_bytes + 4ull * a.R) > LAST_LEVEL_CACHE ? 4 : 1;
 }
 
 hipError_t launch_search(const DistCfg& cfg, const SearchArgs& a, hipStream_t s) {
   if (a.nq == 0) return hipSuccess;
   VecTable T{a.points, (u32)cfg.row_bytes, cfg.npieces};
-  const u32 waves = search_waves(a);
+  const u32 waves = search_waves(cfg, a);
   if (waves > 1u) return launch_search_wide(cfg, a, T, waves, s);
   const bool own = a.starts != nullptr || a.next_start != nullptr;
   if (own) return a.eps16 >= 0 ? launch_search_own_eps(cfg, a, T, s) : launch_search_own(cfg, a, T, s);

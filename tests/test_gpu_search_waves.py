@@ -37,7 +37,7 @@ def test_waves_per_search_do_not_show(env, kind, R, Lb):
     pts, qs = dev(torch, pts_h), dev(torch, qs_h)
     g = A.ann_build(pts, R, Lb, 1.0 if metric else 1.2, seed=4, metric=metric)
     rows, start = g.neighbors(), int(g.info().start)
-    cuts = [0, 1, 38, 550, 1100]  # 1, 37, 512 and 550 queries: eight waves, and four
+    cuts = [0, 1, 38, 550, 1100]  # 1, 37, 512 queries: eight waves; 550: one, the graph is small
     for L in (31, 32, 64, 65, 128, 129, 256):
         for k, eps in ((10, -1.0), (L, -1.0), (10, 0.0), (10, 0.1)):
             say(f"waves {kind} L={L} k={k} eps={eps}")
@@ -63,3 +63,26 @@ def test_waves_per_search_visited_lists(env):
         if "batch_cap" in kw:
             og, _ = O.build(O.Dataset(pts_h, 0), 24, 48, 1.2, seed=2, theta=kw["batch_cap"], threads=0)
         assert (g.neighbors() == og).all()
+
+
+def test_four_waves_per_search(env):
+    """Between 512 and 1,024 searches of a graph beyond the last-level cache share four waves."""
+    torch, A, _ = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    c = 40 * torch.randn((300, 128), generator=g, device="cuda")
+
+    def rows(n):
+        x = c[torch.randint(300, (n,), generator=g, device="cuda")]
+        return (x + 25 * torch.randn((n, 128), generator=g, device="cuda")).round_().clamp_(-127, 127).to(torch.int8)
+
+    n = (256 << 20) // (128 + 4 * 64) + 1  # the smallest such graph
+    pts, qs = rows(n), rows(1025)
+    graph = A.ann_build(pts, 64, 64, 1.2, seed=6)
+    for L in (32, 64, 65, 129, 256):
+        for eps in (-1.0, 0.1):
+            say(f"four waves L={L} eps={eps}")
+            ids, dists = A.ann_search_eps(graph, pts, qs, 10, L, eps)
+            for nq in (513, 1024):
+                i, d = A.ann_search_eps(graph, pts, qs[:nq], 10, L, eps)
+                assert torch.equal(i, ids[:nq]) and torch.equal(d, dists[:nq])
