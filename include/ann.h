@@ -354,7 +354,8 @@ int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total
 /* Wraps an index given on the host: level_host (n), the entry point (a point
  * of the highest level), and rows_host[l] for l = 0..max level, each n x
  * (l ? m : 2m) adjacency rows of point ids, ANN_NONE padded (the rows of
- * points below layer l are ignored).  points_dev as ann_hnsw_build.  Blocks. */
+ * points below layer l are ignored; an id that a row names more than once is
+ * taken once).  points_dev as ann_hnsw_build.  Blocks.                       */
 int ann_hnsw_from_host(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, ann_metric metric,
                        uint32_t m, const uint32_t* level_host, uint32_t entry,
                        const uint32_t* const* rows_host, void* stream, ann_hnsw** out);

@@ -580,6 +580,7 @@ int ann_hnsw_from_host(const void* points_dev, uint64_t n, uint32_t d, ann_dtype
     const u32 R = g->R;
     const std::vector<u32>& mine = h->ids[l];
     std::vector<u32> rows((size_t)g->n * R, ANN_NONE);
+    std::vector<u32> named_by(g->n, ANN_NONE);  // the last row that named this member
     for (u64 c = 0; c < g->n; ++c) {
       const u64 p = l ? mine[c] : c;
       const u32* src = rows_host[l] + p * R;
@@ -587,7 +588,10 @@ int ann_hnsw_from_host(const void* points_dev, uint64_t n, uint32_t d, ann_dtype
       for (u32 j = 0; j < R && src[j] != ANN_NONE; ++j) {
         const u32 q = src[j];
         if (q >= n || h->level[q] < l) return fail(ANN_EINVAL, "neighbour id out of range or not on the layer");
-        rows[c * R + deg++] = l ? (u32)(std::lower_bound(mine.begin(), mine.end(), q) - mine.begin()) : q;
+        const u32 x = l ? (u32)(std::lower_bound(mine.begin(), mine.end(), q) - mine.begin()) : q;
+        if (named_by[x] == (u32)c) continue;  // a search takes the neighbours of a vertex as distinct candidates
+        named_by[x] = (u32)c;
+        rows[c * R + deg++] = x;
       }
     }
     HIP_TRY(hipMemcpyAsync(g->rows, rows.data(), rows.size() * sizeof(u32), hipMemcpyHostToDevice, st));

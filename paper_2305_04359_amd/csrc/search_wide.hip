@@ -109,11 +109,12 @@ __device__ __forceinline__ u32 wide_insert(u64 (&A)[NSLOT], u64 mykey, bool last
     if (last_row ? insert_sorted<NSLOT, WIDE_FLAGS, true>(A, mykey, ns, L, size, lane)
                  : insert_sorted<NSLOT, WIDE_FLAGS, false>(A, mykey, ns, L, size, lane))
       return ns;
-    // some are in the beam already (the filter lost them): drop those
+    // some are in the beam already (the filter lost them): drop those, and those that a lower lane
+    // has, so that the second attempt finds no repeat whatever the rows hold
     for (u64 it = sm; it; it &= it - 1) {
       const int l = __builtin_ctzll(it);
       const u64 k = readlane_u64(mykey, l) | WIDE_FLAGS;
-      bool same = false;
+      bool same = lane < l && (mykey | WIDE_FLAGS) == k;
 #pragma unroll
       for (int s = 0; s < NSLOT; ++s) same = same || (A[s] | WIDE_FLAGS) == k;
       if (ballot(same) != 0 && lane == l) mykey = KEY_INF;

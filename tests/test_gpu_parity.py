@@ -918,6 +918,36 @@ def test_hnsw_from_host_round_trip(env, c1):
         A.ann_hnsw_from_host(pts, 5, oh.level, int(np.flatnonzero(oh.level == 0)[0]), oh.layers)
 
 
+@pytest.mark.parametrize("nq", [37, 1100])
+def test_hnsw_from_host_repeated_neighbours(env, c1, nq):
+    """Rows that name a vertex more than once answer like rows that name it once, whether one wave
+    takes a search (1,100 queries, short beams) or several share it."""
+    torch, A, O = env
+    n = 6000
+    ds = O.Dataset(c1.points[:n], 0)
+    oh = O.hnsw_build(ds, 8, 32, 1.2, seed=9, threads=0)
+    once, twice = [], []
+    for rows in oh.layers:  # the first half of every row, alone and with all of it repeated behind it
+        half = rows.shape[1] // 2
+        a, b = np.full_like(rows, NONE), np.full_like(rows, NONE)
+        a[:, :half] = rows[:, :half]
+        for v in range(n):
+            ids = rows[v, :half][rows[v, :half] != NONE]
+            b[v, :2 * len(ids)] = np.concatenate([ids, ids[::-1]])
+        once.append(a)
+        twice.append(b)
+    pts = dev(torch, c1.points[:n])
+    qs_h = c1.queries[np.arange(nq) % len(c1.queries)]
+    h = A.ann_hnsw_from_host(pts, 8, oh.level, oh.entry, twice)
+    want = O.Hnsw(8, oh.level, once, oh.entry)
+    _check_hnsw_against(h, want, n)
+    for L in (8, 40, 128, 256):
+        say(f"repeated neighbours nq={nq} L={L}")
+        ids, dists = A.ann_hnsw_search(h, pts, dev(torch, qs_h), 8, L)
+        oi, od, _ = O.hnsw_search_batch(ds, want, qs_h, 8, L, threads=0)
+        assert (ids.cpu().numpy().view(np.uint32) == oi).all() and (dists.cpu().numpy() == od).all()
+
+
 # ------------------------------------------------------------------------------------------
 # clustering-based builder (Sec. 3.2 and 4.3, ParlayHCNNG)
 # ------------------------------------------------------------------------------------------
