@@ -51,8 +51,9 @@ struct WideCtrl {
   u32 count[WIDE_MAX_LISTS];  // length of every list
   u32 go;
   u32 done;
-  u32 pad_[2];
+  u32 pad_[4];
 };
+static_assert(sizeof(WideCtrl) % 16 == 0, "the filter's 16-byte buckets lie behind it");
 __device__ __forceinline__ u32 lds_acquire(const u32* p) {
   return readlane_u32(__hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP), 0);
 }
