@@ -103,30 +103,29 @@ __device__ __forceinline__ bool insert_sorted(u64 (&A)[NSLOT], u64 survivor, u32
 // candidates were below the beam's last entry and not in the beam already.  Called by one whole
 // wave; `sync` orders its LDS accesses before and after against each other.
 //
-// With the chip full the sorting network takes as many vector instructions as ranks by bisection
-// and counting at 45 survivors of a two-slot beam, at 20 of a one-slot beam, and is used from there
-// in one-slot beams only (10,000 queries at L = 16: 207 -> 196 us; two slots, build of a million
-// points: 79.3 -> 80.0 ms).
-template <int NSLOT, class Sync>
-__device__ __forceinline__ u32 beam_insert(u64 (&A)[NSLOT], u64* beam, u64* skeys, u64 mykey, u32 L, u32& size,
-                                           int lane, Sync sync) {
+// NETWORK: from 20 survivors on they go in by the sorting network (search_network says when).  With
+// the chip full it takes as many vector instructions as ranks by bisection and counting at 45
+// survivors of a two-slot beam, at 20 of a one-slot beam.
+template <int NSLOT, bool NETWORK, class Sync>
+__device__ __forceinline__ void beam_insert(u64 (&A)[NSLOT], u64* beam, u64* skeys, u64 mykey, u32 L, u32& size,
+                                            u32& n_surv, u32& n_ins, int lane, Sync sync) {
   constexpr u64 FLAGS = 1;
   const u64 worst = beam_worst<NSLOT, FLAGS>(A, L, size);
   bool surv = mykey < worst;
   u64 sm = ballot(surv);
-  u32 ns = 0;
-  if (NSLOT == 1 && __builtin_popcountll(sm) >= 20) {
-    ns = (u32)__builtin_popcountll(sm);
+  if (NETWORK && __builtin_popcountll(sm) >= 20) {
+    const u32 ns = (u32)__builtin_popcountll(sm);
     if (insert_sorted<NSLOT, FLAGS, false>(A, surv ? mykey : KEY_INF, ns, L, size, lane)) {
 #pragma unroll
       for (int s = 0; s < NSLOT; ++s) beam[s * 64 + lane] = A[s];
       sync();
-      return ns;
+      n_surv += ns;
+      ++n_ins;
+      return;
     }
-    ns = 0;
   }
   if (sm) {
-    u32 myrA = 0, myrB = 0;
+    u32 myrA = 0, myrB = 0, ns = 0;
     u32 shift[NSLOT];
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) shift[s] = 0;
@@ -200,6 +199,8 @@ __device__ __forceinline__ u32 beam_insert(u64 (&A)[NSLOT], u64* beam, u64* skey
         const u32 np = myrA + myrB;
         if (np < L) beam[np] = mykey;
       }
+      n_surv += ns;
+      ++n_ins;
       size = size + ns < L ? size + ns : L;
       sync();
 #pragma unroll
@@ -210,7 +211,6 @@ __device__ __forceinline__ u32 beam_insert(u64 (&A)[NSLOT], u64* beam, u64* skey
       sync();
     }
   }
-  return ns;
 }
 
 // An entry pk of the beam is beyond the bound that its k-th entry kk sets.
@@ -303,7 +303,8 @@ __device__ __forceinline__ void zero_batch_counters(u32* c) {
 // not weigh on the registers of the first.
 // OWN: every search has a start vertex of its own and reports the closest vertex it found (the
 // layered index); compiled apart so that the flat graph's searches do not carry its arguments.
-template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN>
+// NETWORK: see beam_insert.
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK>
 __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
   extern __shared__ __align__(16) unsigned char smem[];
   u64* beam = reinterpret_cast<u64*>(smem);
@@ -472,9 +473,7 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
         evals += m;
         n_pass += (m + 7u) >> 3;
 
-        const u32 ns = beam_insert<NSLOT>(A, beam, skeys, mykey, L, size, lane, [] { __syncthreads(); });
-        n_surv += ns;
-        n_ins += ns != 0u ? 1u : 0u;
+        beam_insert<NSLOT, NETWORK>(A, beam, skeys, mykey, L, size, n_surv, n_ins, lane, [] { __syncthreads(); });
       }
       if (present != ~0ull) break;  // rows are compact: the first gap ends the row
     }
@@ -527,24 +526,42 @@ inline u32 search_nslot_for(u32 L) {
   return ns;
 }
 
+// Whether searches with one-slot beams carry the sorting network.  It pays where 20 survivors of one
+// row are common: long rows, or a beam that is still filling (10,000 uint8 queries, a million points,
+// R = 64: 182 -> 174 us at L = 16, 416 -> 410 at L = 64; 200,000 points, R = 48: 183 -> 176 at L = 16,
+// 385 -> 394 at L = 64).  Rows of 32 ids never repay the second path that the loop then holds (20,000
+// uint8 points, 40,000 queries at L = 64: 753 -> 780 us; 48 floats, 2,000 queries: 151 -> 157).
+// In the float variants with start vertices of their own, rows of up to 64 elements, it would also
+// cost the wave per SIMD that they hold at 64 registers.
+template <int KIND, int NCH, bool OWN>
+constexpr bool search_network_compiled = !(OWN && !KindTraits<KIND>::is_int && NCH <= 2);
+inline bool search_network(const SearchArgs& a) { return a.R >= 64u || (a.R > 32u && a.L <= 24u); }
+
 // One launch for a fixed choice of EPS and OWN; the beam slots and the filter layout are picked here.
 template <int KIND, int VEC, int NCH, bool EPS, bool OWN>
 inline hipError_t launch_search_variant(const SearchArgs& a, const VecTable& T, hipStream_t s) {
   const u32 lds = search_lds_bytes(a.L, a.hash_buckets);
   const dim3 grid(a.nq), block(64);
   const bool t16 = a.tag_width == 16u;
-#define ANN_LAUNCH_SEARCH(NS)                                                                            \
-  if (t16)                                                                                               \
-    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NS, EPS, true, OWN>), grid, block, lds, s, a, T);  \
-  else                                                                                                   \
-    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NS, EPS, false, OWN>), grid, block, lds, s, a, T)
+#define ANN_LAUNCH_SEARCH(NS, NET)                                                                            \
+  if (t16)                                                                                                    \
+    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NS, EPS, true, OWN, NET>), grid, block, lds, s, a, T);  \
+  else                                                                                                        \
+    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NS, EPS, false, OWN, NET>), grid, block, lds, s, a, T)
+  constexpr bool NETWORK = search_network_compiled<KIND, NCH, OWN>;
   switch (search_nslot_for(a.L)) {
-    case 1: ANN_LAUNCH_SEARCH(1); break;
-    case 2: ANN_LAUNCH_SEARCH(2); break;
-    case 4: ANN_LAUNCH_SEARCH(4); break;
-    case 8: ANN_LAUNCH_SEARCH(8); break;
-    case 16: ANN_LAUNCH_SEARCH(16); break;
-    default: ANN_LAUNCH_SEARCH(32); break;
+    case 1:
+      if (NETWORK && search_network(a)) {
+        ANN_LAUNCH_SEARCH(1, NETWORK);
+      } else {
+        ANN_LAUNCH_SEARCH(1, false);
+      }
+      break;
+    case 2: ANN_LAUNCH_SEARCH(2, false); break;
+    case 4: ANN_LAUNCH_SEARCH(4, false); break;
+    case 8: ANN_LAUNCH_SEARCH(8, false); break;
+    case 16: ANN_LAUNCH_SEARCH(16, false); break;
+    default: ANN_LAUNCH_SEARCH(32, false); break;
   }
 #undef ANN_LAUNCH_SEARCH
   return hipGetLastError();
