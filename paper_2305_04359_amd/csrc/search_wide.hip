@@ -27,7 +27,7 @@
 
 namespace annmi {
 
-constexpr u32 WIDE_MAX_WAVES = 16;
+constexpr u32 WIDE_MAX_WAVES = 8;
 constexpr u32 WIDE_MAX_LISTS = 32;
 constexpr u64 WIDE_FLAGS = 0xFF;
 // states: not expanded; 1 + i: expanded into list i; STATE_TAKEN + i: being expanded into list i;
@@ -131,8 +131,12 @@ __device__ __forceinline__ const SearchArgs& args_here() {
   return *reinterpret_cast<const SearchArgs*>(p);
 }
 
+// Four waves per SIMD: 512 searches of eight waves, or 1,024 of four, are then on the chip at once.  It
+// holds the kernel to 128 registers, and three float instances of 8 pieces per lane spill 2 to 7 of
+// them.  Free to take up to 139 they do not spill, but beyond 384 searches a second generation
+// waits for the first (300,000 points of 256 floats, R = 32, 512 searches, L = 100: 556 -> 810 us).
 template <int KIND, int VEC, int NCH, int NSLOT>
-__global__ __launch_bounds__(1024) void search_wide_kernel(SearchArgs a, VecTable T, u32 nlists) {
+__global__ __launch_bounds__(64 * WIDE_MAX_WAVES, 4) void search_wide_kernel(SearchArgs a, VecTable T, u32 nlists) {
   extern __shared__ __align__(16) unsigned char smem[];
   u64* lists = reinterpret_cast<u64*>(smem);  // nlists x 64
   WideCtrl* ctrl = reinterpret_cast<WideCtrl*>(lists + (u64)nlists * 64);
@@ -403,6 +407,7 @@ static hipError_t launch_wide(const SearchArgs& a, const VecTable& T, u32 waves,
 }
 
 hipError_t launch_search_wide(const DistCfg& cfg, const SearchArgs& args, const VecTable& T, u32 waves, hipStream_t s) {
+  if (waves < 2u || waves > WIDE_MAX_WAVES) return hipErrorInvalidConfiguration;
   SearchArgs a = args;
   // a filter of its own size: LDS is no concern with few searches
   a.hash_buckets = WIDE_BUCKETS;
