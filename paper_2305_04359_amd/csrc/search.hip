@@ -66,19 +66,40 @@ static hipError_t launch_search_plain(const DistCfg& cfg, const SearchArgs& a, c
 }
 
 // How many waves share a search.  Up to 1,024 searches leave most of the chip idle, and each waits for
-// its own chain of hops: four to eight waves take a search of a million 128-d uint8 points from 96
-// to 70 us at L = 64 and from 166 to 116 at L = 128 (one query), 512 of them from 175 to 130 and 414
-// to 299, 1,000 of them (four waves) from 188 to 146 and 419 to 322.  2,000 searches with four waves
-// each run out of wave slots (422 -> 439 us at L = 128), and so do 800 on a graph that the last-level
-// cache holds, where hops wait less (build searches, L = 128, 40,000 to 90,000 points: 232 us by one
-// wave each, 242 by four; 480 of them by eight 230 -> 199).  Beams below 32 are over before the work
-// ahead pays (L = 16: 37.4 and 37.7 us for one query, 61.2 and 62.3 for 256).
-constexpr u64 LAST_LEVEL_CACHE = 256ull << 20;
+// its own chain of hops: four to eight waves take a search of a million 128-d uint8 points, R = 64,
+// from 125 to 97 us at L = 64 and from 170 to 135 at L = 100 (one query), 512 of them from 242 to 168
+// and 338 to 281, 1,000 of them (four waves) from 245 to 193 and 342 to 291.  2,000 searches of four
+// waves do not fit the chip at once (422 -> 439 us at L = 128), and 513 to 1,024 of four waves gain
+// nothing on a graph that the last-level cache holds (800 at L = 128, 40,000 to 90,000 points: 232 us
+// by one wave each, 242 by four).
+//
+// Work ahead pays by the trips to memory it hides, and costs the first wave a longer chain per hop
+// (lists, hand-over, a sorting network over all of the beam per insertion).  Measured over 5,000 to
+// 1.5 million points, speed against one wave each:
+//  - beams below 32 are over before it pays (L = 16: 37.4 and 37.7 us for one query), rows of 16 ids
+//    bring too little work (uint8: 0.66 to 1.08, nearly all below 1);
+//  - beams above 128, four slots: rows of 48 ids and more, for byte rows on graphs beyond the last-level
+//    cache (float 1.06 to 1.6, uint8 there 1.0 to 1.3; with R = 32 0.7 to 1.2, byte rows on 50,000
+//    points 0.8 to 1.2);
+//  - rows below 48 ids, beams above 64: byte rows of up to 128 bytes on graphs beyond 16 MB (0.92 to
+//    1.21; 0.87 to 1.0 for rows of 256 bytes, 0.8 to 1.1 on 5,000 points), float rows of up to 7
+//    pieces per lane (1.0 to 1.4; 8 pieces 0.87 to 1.04);
+//  - rows below 48 ids, beams below 48: byte rows gain for a few searches only (one to 16: 0.95 to 1.2;
+//    more: 0.91 to 1.1);
+//  - byte rows on graphs that one L2 holds: up to 256 searches (beyond: 0.8 to 1.05), beams above 64
+//    with rows of 64 ids (0.97 to 1.4; R = 48 0.9 to 1.04).
+constexpr u64 LAST_LEVEL_CACHE = 256ull << 20, ONE_L2 = 4ull << 20;
 static u32 search_waves(const DistCfg& cfg, const SearchArgs& a) {
   const bool fits = a.R <= 64u && a.L <= 256u && a.n <= WIDE_MAX_POINTS && !a.filter_given;
-  if (!fits || a.L < 32u || a.nq > 1024u) return 1;
+  if (!fits || a.L < 32u || a.R < 32u || a.nq > 1024u) return 1;
+  const u64 graph = a.n * (cfg.row_bytes + 4ull * a.R);
+  const bool byte_rows = cfg.kind == K_U8 || cfg.kind == K_I8, short_rows = a.R < 48u;
+  if (a.L > 128u && (short_rows || (byte_rows && graph <= LAST_LEVEL_CACHE))) return 1;
+  if (short_rows && a.L > 64u && (byte_rows ? cfg.nch > 1 || graph <= 4u * ONE_L2 : cfg.nch > 7)) return 1;
+  if (short_rows && a.L < 48u && byte_rows && a.nq > 16u) return 1;
+  if (byte_rows && graph <= ONE_L2 && (a.nq > 256u || (a.L > 64u && a.R < 64u))) return 1;
   if (a.nq <= 512u) return 8;
-  return a.n * (cfg.row_bytes + 4ull * a.R) > LAST_LEVEL_CACHE ? 4 : 1;
+  return graph > LAST_LEVEL_CACHE ? 4 : 1;
 }
 
 hipError_t launch_search(const DistCfg& cfg, const SearchArgs& a, hipStream_t s) {

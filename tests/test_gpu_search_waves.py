@@ -86,3 +86,26 @@ def test_four_waves_per_search(env):
             for nq in (513, 1024):
                 i, d = A.ann_search_eps(graph, pts, qs[:nq], 10, L, eps)
                 assert torch.equal(i, ids[:nq]) and torch.equal(d, dists[:nq])
+
+
+@pytest.mark.parametrize("n", [(1 << 20) + 1, (1 << 22) + 1])
+def test_waves_per_search_many_points(env, n):
+    """Ids of 21 and 23 bits: the several-waves kernel's filter keeps 16-bit tags, the one-wave kernel's
+    smaller one does so for the first graph only."""
+    torch, A, _ = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    c = torch.randint(256, (3000, 16), generator=g, device="cuda")
+
+    def rows(m):
+        x = c[torch.randint(3000, (m,), generator=g, device="cuda")] + torch.randint(-40, 41, (m, 16), generator=g, device="cuda")
+        return x.clamp_(0, 255).to(torch.uint8)
+
+    pts, qs = rows(n), rows(1100)
+    graph = A.ann_build(pts, 48, 48, 1.2, seed=6)
+    for L in (32, 64, 128, 256):
+        say(f"several waves n={n} L={L}")
+        ids, dists = A.ann_search(graph, pts, qs, 10, L)
+        for nq in (1, 37, 512, 1000):
+            i, d = A.ann_search(graph, pts, qs[:nq], 10, L)
+            assert torch.equal(i, ids[:nq]) and torch.equal(d, dists[:nq])
