@@ -120,7 +120,9 @@ typedef struct {
 typedef struct {
   uint64_t searches;    /* greedy searches run                                   */
   uint64_t hops;        /* vertices processed, summed over searches (|V|)        */
-  uint64_t evals;       /* distances taken in searches, re-evaluations included  */
+  uint64_t evals;       /* distances taken in searches, re-evaluations included; where
+                           several waves share a search, also those taken ahead of
+                           their turn (their number depends on timing)            */
   uint64_t prunes;      /* step-1 prunes                                         */
   uint64_t reprunes;    /* step-2 prunes of overflowing rows                     */
   uint64_t appends;     /* step-2 rows that only appended                        */
