@@ -14,7 +14,7 @@ READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     """{(name, template arguments): {"vgpr_count": ..., "vgpr_spill_count": ...}}"""
-    data = open(B.build_library(force=False), "rb").read()
+    data = open(B.library_path(), "rb").read()
     magic, out = b"__CLANG_OFFLOAD_BUNDLE__", {}
     path = str(tmp_path_factory.mktemp("co") / "code.o")
     for m in re.finditer(magic, data):
