@@ -110,15 +110,26 @@ __device__ __forceinline__ u32 wide_insert(u64 (&A)[NSLOT], u64 mykey, bool last
     if (last_row ? insert_sorted<NSLOT, WIDE_FLAGS, true>(A, mykey, ns, L, size, lane)
                  : insert_sorted<NSLOT, WIDE_FLAGS, false>(A, mykey, ns, L, size, lane))
       return ns;
-    // some are in the beam already (the filter lost them): drop those, and those that a lower lane
-    // has, so that the second attempt finds no repeat whatever the rows hold
+    // some are in the beam already (the filter lost them): drop those
+    bool dropped = false;
     for (u64 it = sm; it; it &= it - 1) {
       const int l = __builtin_ctzll(it);
       const u64 k = readlane_u64(mykey, l) | WIDE_FLAGS;
-      bool same = lane < l && (mykey | WIDE_FLAGS) == k;
+      bool same = false;
 #pragma unroll
       for (int s = 0; s < NSLOT; ++s) same = same || (A[s] | WIDE_FLAGS) == k;
-      if (ballot(same) != 0 && lane == l) mykey = KEY_INF;
+      if (ballot(same) != 0) {
+        dropped = true;
+        if (lane == l) mykey = KEY_INF;
+      }
+    }
+    // A row named a vertex twice: drop all but its last, so that the loop ends whatever the rows hold.  (Apart
+    // from the drop above, which is taken often: in it, the test cost 1 to 3 % of a search.)
+    if (!dropped) {
+      for (u64 it = sm; it; it &= it - 1) {
+        const u64 k = readlane_u64(mykey, __builtin_ctzll(it));
+        if (mykey == k && lane < 63 - __builtin_clzll(ballot(mykey == k))) mykey = KEY_INF;
+      }
     }
   }
 }
