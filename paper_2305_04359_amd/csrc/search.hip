@@ -88,6 +88,8 @@ static hipError_t launch_search_plain(const DistCfg& cfg, const SearchArgs& a, c
 //    more: 0.91 to 1.1);
 //  - byte rows on graphs that one L2 holds: up to 256 searches (beyond: 0.8 to 1.05), beams above 64
 //    with rows of 64 ids (0.97 to 1.4; R = 48 0.9 to 1.04).
+// Up to eight searches of byte rows gain on both sides of these lines (1.02 to 1.27), but for four slots
+// on short rows.
 // Build searches run on a graph that is still smaller and write visited lists; the last line does not
 // hold for them (2,000 points, R = 48, L = 128: build 9.5 ms, 10.9 with one wave each), the one on short
 // rows from 128 searches on (R = 32, L = 128: 2,000 points 9.9 and 11.0 ms, 20,000 points 16.1 and 15.4).
@@ -97,13 +99,13 @@ static u32 search_waves(const DistCfg& cfg, const SearchArgs& a) {
   if (!fits || a.L < 32u || a.R < 32u || a.nq > 1024u) return 1;
   const u64 graph = a.n * (cfg.row_bytes + 4ull * a.R);
   const bool byte_rows = cfg.kind == K_U8 || cfg.kind == K_I8, short_rows = a.R < 48u;
-  if (a.L > 128u && (short_rows || (byte_rows && graph <= LAST_LEVEL_CACHE))) return 1;
-  const bool build = a.vis != nullptr;
-  if (short_rows && a.L > 64u && (byte_rows ? cfg.nch > 1 || graph <= 4u * ONE_L2 : cfg.nch > 7) &&
+  const bool build = a.vis != nullptr, lone = a.nq <= 8u;
+  if (a.L > 128u && (short_rows || (byte_rows && graph <= LAST_LEVEL_CACHE && !lone))) return 1;
+  if (short_rows && a.L > 64u && (byte_rows ? !lone && (cfg.nch > 1 || graph <= 4u * ONE_L2) : cfg.nch > 7) &&
       !(build && a.nq <= 128u))
     return 1;
   if (short_rows && a.L < 48u && byte_rows && a.nq > 16u) return 1;
-  if (!build && byte_rows && graph <= ONE_L2 && (a.nq > 256u || (a.L > 64u && a.R < 64u))) return 1;
+  if (!build && !lone && byte_rows && graph <= ONE_L2 && (a.nq > 256u || (a.L > 64u && a.R < 64u))) return 1;
   if (a.nq <= 512u) return 8;
   return graph > LAST_LEVEL_CACHE ? 4 : 1;
 }

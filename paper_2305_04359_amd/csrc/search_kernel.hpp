@@ -535,7 +535,13 @@ inline u32 search_nslot_for(u32 L) {
 // cost the wave per SIMD that they hold at 64 registers.
 template <int KIND, int NCH, bool OWN>
 constexpr bool search_network_compiled = !(OWN && !KindTraits<KIND>::is_int && NCH <= 2);
-inline bool search_network(const SearchArgs& a) { return a.R >= 64u || (a.R > 32u && a.L <= 24u); }
+// The second path is repaid all the same where the searches are few and wait for their own chains, of
+// which the network's is the shorter (56,000 uint8 points, R = 32, 7 queries at L = 18, eps = 0.25: 36.5 ->
+// 34.3), and with the (1 + eps) rule, where a search ends soon after its beam has filled (341,000 uint8
+// points, R = 48, 2,698 queries at L = 34, eps = 0.05: 115.5 -> 109.6).
+inline bool search_network(const SearchArgs& a) {
+  return a.R >= 64u || (a.R > 32u && (a.L <= 24u || a.eps16 >= 0)) || a.nq <= 256u;
+}
 
 // One launch for a fixed choice of EPS and OWN; the beam slots and the filter layout are picked here.
 template <int KIND, int VEC, int NCH, bool EPS, bool OWN>
