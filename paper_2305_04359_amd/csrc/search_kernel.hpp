@@ -236,6 +236,13 @@ __device__ __forceinline__ u64 beam_entry(const u64 (&A)[NSLOT], u32 i) {
   return k;
 }
 
+// Stands at the end of a branch that some lanes take, where uniform branches around it end too.  Without
+// it the compiler lets all of them end in one place, and takes a value that differs between the
+// uniform paths to that place (a list's pointer, a count) for one that differs between lanes: it, the
+// branches it decides and in the end the state of the loop then live in vector registers and
+// execution masks.
+__device__ __forceinline__ void keep_join() { __builtin_amdgcn_wave_barrier(); }
+
 // Entry nv of search qi's visited list.  (vptr, vcap) are wave-uniform; vptr turns null when the
 // list is lost (it fits neither its slot nor a spill chunk: the prune kernel sees nv > room and
 // reports it).
@@ -264,6 +271,7 @@ __device__ __forceinline__ void visited_append(const SearchArgs& a, u32 qi, u64*
     vcap = readlane_u32(newcap, 0);
   }
   if (vptr != nullptr && lane == 0) vptr[nv] = pk;
+  keep_join();
 }
 
 // The first k entries of the beam as search qi's results.
