@@ -78,6 +78,7 @@ struct SearchArgs {
   // for the host's choice of kernel
   u64 n;             // vertices of the graph
   u32 filter_given;  // non-zero: the filter's size is the caller's choice and stays
+  u32 shares_chip;   // non-zero: other searches run beside these (parts of a batch)
 };
 
 // The walk of a query through the upper layers of the layered index (Sec. 4.2): a search with

@@ -363,6 +363,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     SearchArgs sc = sa;
     sc.qidx = ids_dev + cut[c];
     sc.nq = (u32)(cut[c + 1] - cut[c]);
+    sc.shares_chip = nparts > 1 ? 1u : 0u;
     sc.vis = sa.vis + cut[c] * S.vis_cap;
     sc.nvis = sa.nvis + cut[c];
     sc.vis_where = sa.vis_where + cut[c];

@@ -110,11 +110,28 @@ static u32 search_waves(const DistCfg& cfg, const SearchArgs& a) {
   return graph > LAST_LEVEL_CACHE ? 4 : 1;
 }
 
+// Whether the next hops' memory is requested ahead.  It costs registers (five waves per SIMD instead of eight)
+// and instructions (three entries of the beam looked up per hop, one in thirteen expansions undone), and
+// hides one of a hop's two trips to memory: it pays while the chip is half empty.  Speed against one wave
+// each without it, uint8 and int8 rows, 5,000 to 500,000 points, R = 32 to 64:
+//  - 513 to 3,000 searches: 0.98 to 1.28 (2,000 uint8 searches at L = 128, R = 64: 233 -> 203 us on 100,000
+//    points, 374 -> 325 on a million); 4,000: 0.95 to 1.23, 6,000: 0.70 to 1.2, most below 0.9;
+//  - on graphs that one L2 holds a trip is short: 2,000 searches 0.99 to 1.09, 3,000 0.95 to 1.05;
+//  - beams below 32: 0.90 to 1.08; up to 512 searches, which several waves share where that pays, 0.71 to 1.1.
+// Searches that run beside others (parts of a batch) are not alone on the chip, however few.
+static bool search_ahead(const DistCfg& cfg, const SearchArgs& a) {
+  if (a.nq <= 512u || a.R < 32u || a.R > 64u || a.L < 32u || a.L > 128u || a.n > AHEAD_MAX_POINTS || a.filter_given || a.shares_chip) return false;
+  if (cfg.kind != K_U8 && cfg.kind != K_I8) return false;
+  const u64 graph = a.n * (cfg.row_bytes + 4ull * a.R);
+  return a.nq <= (graph > ONE_L2 ? 3072u : 2048u);
+}
+
 hipError_t launch_search(const DistCfg& cfg, const SearchArgs& a, hipStream_t s) {
   if (a.nq == 0) return hipSuccess;
   VecTable T{a.points, (u32)cfg.row_bytes, cfg.npieces};
   const u32 waves = search_waves(cfg, a);
   if (waves > 1u) return launch_search_wide(cfg, a, T, waves, s);
+  if (search_ahead(cfg, a)) return launch_search_ahead(cfg, a, T, s);
   const bool own = a.starts != nullptr || a.next_start != nullptr;
   if (own) return a.eps16 >= 0 ? launch_search_own_eps(cfg, a, T, s) : launch_search_own(cfg, a, T, s);
   return a.eps16 >= 0 ? launch_search_eps(cfg, a, T, s) : launch_search_plain(cfg, a, T, s);

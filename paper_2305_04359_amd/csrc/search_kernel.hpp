@@ -526,6 +526,11 @@ hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const 
 constexpr u32 WIDE_BUCKETS = 512;
 constexpr u64 WIDE_MAX_POINTS = 1ull << 24;
 hipError_t launch_search_wide(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, u32 waves, hipStream_t s);
+// One wave per search with the next hops' memory requested ahead (search_ahead.hip): byte rows, rows of at
+// most 64 ids, beams of at most 128, ids that 16-bit tags of a filter of AHEAD_BUCKETS hold.
+constexpr u32 AHEAD_BUCKETS = 480;
+constexpr u64 AHEAD_MAX_POINTS = 1ull << 23;
+hipError_t launch_search_ahead(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
 
 // beam slots per lane: the smallest power of two that holds L entries (beams of up to 2,048)
 inline u32 search_nslot_for(u32 L) {
