@@ -815,12 +815,18 @@ __global__ __launch_bounds__(64) void merge_generic_kernel(MergeArgs a, VecTable
   constexpr int LIST = CAP == MERGE_SPILL_MIN ? 2 : 3;
   __shared__ u64 cand_lds[CAP];
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr bool kF32 = F32PruneOk<KIND, VEC, NCH>::value;
   u32* out = reinterpret_cast<u32*>(smem);  // R entries
   SelStage st;
   st.stride = stage_stride(T.row_bytes);
   st.xx = out + a.R;
   unsigned char* blk = smem + ((a.R * 8u + 15u) & ~15u);  // 8 rows + 8 norms
   st.vec = a.stage_bytes ? blk + 8u * st.stride + 32u : nullptr;
+  F32Lds F{};
+  if constexpr (kF32) {
+    F = f32_lds_carve(smem, a.R, out);
+    st.vec = nullptr;
+  }
   constexpr bool kMfma = MfmaPruneOk<KIND, VEC, NCH>::value;
   const MfmaLds M = mfma_lds_carve(smem + ((a.R * 4u + 15u) & ~15u), a.R, T.row_bytes);  // used when a.use_mfma
 
@@ -886,7 +892,10 @@ __global__ __launch_bounds__(64) void merge_generic_kernel(MergeArgs a, VecTable
           done = true;
         }
       }
-      if (!done) kept = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand, total, a.R, al, out, lane, pair_evals);
+      if constexpr (kF32)
+        kept = prune_sorted_f32<KIND, VEC, NCH>(T, F, T.base + (u64)b * T.row_bytes, cand, total, a.R, a.af, out, lane, pair_evals);
+      else if (!done)
+        kept = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand, total, a.R, al, out, lane, pair_evals);
     } else {
       // (the staged-vector areas are laid out for the walk in use; the minimum-search walk reads
       // the selected vectors from device memory when the matrix-core layout is active)
@@ -916,7 +925,8 @@ static hipError_t launch_merge_t(const MergeArgs& a, const VecTable& T, u32 grid
                                  hipStream_t s_generic, hipStream_t s_medium) {
   // the generic kernel's few, long items first, so that they start at once instead of waiting
   // for LDS that the other two kernels' workgroups hold; a small grid serves its short list
-  const u32 lds = a.use_mfma ? ((a.R * 4u + 15u) & ~15u) + mfma_lds_bytes(a.R, T.row_bytes)
+  const u32 lds = F32PruneOk<KIND, VEC, NCH>::value ? f32_lds_bytes(a.R, T.npieces)
+                  : a.use_mfma ? ((a.R * 4u + 15u) & ~15u) + mfma_lds_bytes(a.R, T.row_bytes)
                             : ((a.R * 8u + 15u) & ~15u) + 8u * stage_stride(T.row_bytes) + 32u + a.stage_bytes;
   const u32 grid_generic = (grid < 1024u || a.force_prune) ? grid : 1024u;
   hipLaunchKernelGGL((merge_generic_kernel<KIND, VEC, NCH, MERGE_SPILL_MIN>), dim3(grid_generic), dim3(64), lds,

@@ -11,9 +11,10 @@ namespace annmi {
 // step 1: N_out(p) <- prune(p, V, R) for every batch point; emit the reversed edges
 // ---------------------------------------------------------------------------------------------
 template <int KIND, int VEC, int NCH>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void prune_kernel(PruneArgs a, VecTable T) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PruneWaves<KIND, VEC, NCH>::value, PruneWaves<KIND, VEC, NCH>::value))) void prune_kernel(PruneArgs a, VecTable T) {
   __shared__ u64 cand_lds[PRUNE_LDS_CAP];
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr bool kF32 = F32PruneOk<KIND, VEC, NCH>::value;
   u32* out = reinterpret_cast<u32*>(smem);  // R entries
   u32* selxx = out + a.R;                   // R entries
   SelStage st;
@@ -21,6 +22,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   st.xx = selxx;
   unsigned char* blk = smem + ((a.R * 8u + 15u) & ~15u);  // 8 rows + 8 norms
   st.vec = a.stage_bytes ? blk + 8u * st.stride + 32u : nullptr;
+  F32Lds F{};
+  if constexpr (kF32) {
+    F = f32_lds_carve(smem, a.R, out);
+    st.vec = nullptr;
+  }
   constexpr bool kMfma = MfmaPruneOk<KIND, VEC, NCH>::value;
   const MfmaLds M = mfma_lds_carve(smem + ((a.R * 4u + 15u) & ~15u), a.R, T.row_bytes);  // used when a.use_mfma
 
@@ -63,7 +69,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         done = true;
       }
     }
-    if (!done) cnt = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand_lds, nv, a.R, al, out, lane, pair_evals);
+    if constexpr (kF32)
+      cnt = prune_sorted_f32<KIND, VEC, NCH>(T, F, T.base + (u64)p * T.row_bytes, cand_lds, nv, a.R, a.af, out, lane, pair_evals);
+    else if (!done)
+      cnt = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand_lds, nv, a.R, al, out, lane, pair_evals);
   } else {
     for (u32 i = lane; i < nv; i += 64) vis[i] &= ~1ull;
     __syncthreads();
@@ -89,7 +98,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 
 template <int KIND, int VEC, int NCH>
 static hipError_t launch_prune_t(const PruneArgs& a, const VecTable& T, hipStream_t s) {
-  const u32 lds = a.use_mfma ? ((a.R * 4u + 15u) & ~15u) + mfma_lds_bytes(a.R, T.row_bytes)
+  const u32 lds = F32PruneOk<KIND, VEC, NCH>::value ? f32_lds_bytes(a.R, T.npieces)
+                  : a.use_mfma ? ((a.R * 4u + 15u) & ~15u) + mfma_lds_bytes(a.R, T.row_bytes)
                             : ((a.R * 8u + 15u) & ~15u) + 8u * stage_stride(T.row_bytes) + 32u + a.stage_bytes;
   hipLaunchKernelGGL((prune_kernel<KIND, VEC, NCH>), dim3(a.nq), dim3(64), lds, s, a, T);
   return hipGetLastError();

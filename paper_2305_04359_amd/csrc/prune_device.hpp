@@ -189,7 +189,8 @@ __device__ __forceinline__ bool removes_pieces(const RemoveTest<KIND>& rt, const
 }
 
 // cand[0..m): keys (distance to p | id), ids distinct, p absent, SORTED ascending.
-// Selected ids go to out[0..return) in selection order.  blk: LDS for 8 rows of st.stride bytes
+// Selected ids go to out[0..return) in selection order.  Byte rows of more than 128 bytes come here; the
+// walks on the matrix cores further down take the others.  blk: LDS for 8 rows of st.stride bytes
 // plus 8 norms (used even when the selected vectors themselves are not staged).
 template <int KIND, int VEC, int NCH>
 __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& st, unsigned char* blk,
@@ -252,8 +253,6 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
     } else {
       // the rows lie in device memory: several are requested before the first is tested.  One at a
       // time, each waited for its own trip through the cache.
-      // With instances of 7 pieces per lane: a step of 20,000 float points of 200, R = 64, 1,245 -> 850 us
-      // per launch (build of a million: 345 -> 310 ms).
       constexpr u32 AHEAD = NCH <= 2 ? 4 : 2;
       for (u32 t = 0; t < nout; t += AHEAD) {
         Piece<VEC> x[AHEAD][NCH];
@@ -287,8 +286,7 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
       }
     }
     {  // the next block's vectors travel while this block is settled.  Not earlier: rows read from device
-      // memory need the registers (requested first where the rows are staged, the wider instances spill:
-      // build of 50,000 points of 256 floats 111 -> 114.5 ms, of 100,000 of 100 floats 59.9 -> 61.1), and the
+      // memory need the registers, and the
       // tests against staged rows hide nothing that settling does not (100,000 uint8 points of 160 bytes,
       // R = 48: 24.0 ms either way)
       const u32 ci = i0 + 8u + grp;
@@ -585,6 +583,297 @@ __device__ __forceinline__ u32 prune_sorted_mfma(const VecTable& T, const MfmaLd
         *reinterpret_cast<uint4*>(M.sel + slot * MM_STRIDE + 16u * sub) =
             *reinterpret_cast<const uint4*>(M.blk + t * MM_STRIDE + 16u * sub);
       }
+    }
+    nout += nsel;
+    __syncthreads();
+  }
+  return nout;
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same walk for float rows, 16 candidates at a time, with the inner products taken on the matrix
+// cores (v_mfma_f32_16x16x1_4b_f32: four independent 16 x 16 outer products, one fp32 fma per entry).
+//
+// A block of 16 candidates lies in registers as the matrix operand: lane (blk, r) = (lane / 16, lane %
+// 16) holds the 16-byte pieces 8 u + 4 h + blk of candidate r (h = 0, 1; u < NCH).  Piece p is summed by
+// lane p % 8 of a group in distance_key, so one instruction takes the same element of four of those
+// eight partial sums, and an entry's eight sums, added up in the order of group_sum, are bit for bit the
+// inner product that distance_key computes.
+//
+//  - Inner product: the verdicts are those of the vector path.
+//  - Squared L2: distance_key sums (a - b)^2, which is no matrix product.  With a' = a - p the products
+//    give S = |a'|^2 + |b'|^2 - 2 <a', b'>, and |S - D| <= E for the D that distance_key computes (see
+//    GRAM_ERR): S + E and S - E decide nearly every pair, and the rest is measured by distance_key's own
+//    sum.  Both give the vector path's verdicts.  Moving the origin to p makes E small against the
+//    distances of p's neighbourhood wherever the data lies.
+//
+// What bounds it: the matrix cores (NCH * 8 instructions of 32 cycles for 256 pairs); the vector path is
+// bound by the first-level cache, which hands it a piece of a selected row eight times over for eight pairs.
+// Per launch of 20,000 points of 200 floats, R = 64, L = 128, inner product: 850 -> 405 us, the re-prunes
+// beside each other 525 -> 142; builds: a million such points 311 -> 264 ms; squared L2, 100,000 points of 200
+// floats 139 -> 82 ms, of 96 floats (R = 48, L = 96) 37.4 -> 26.3, of 48 (R = 32, L = 64) 18.0 -> 15.6.
+// ---------------------------------------------------------------------------------------------
+typedef float v16f_t __attribute__((ext_vector_type(16)));
+
+// |S - D| <= E = GRAM_ERR * (|a'|^2 + |b'|^2) + GRAM_TINY, both norms as computed.  With u = 2^-24, rows
+// of at most 256 elements and N = |a - p|^2 + |b - p|^2: rounding a' and b' moves the distance by at most
+// 4 u N; the norms (chains of 64 fmas, two sums) are off by 66 u N; the inner product (chains of 32, three
+// sums) by 35 u |a'||b'|, twice of which is 35 u N; putting S together costs 3 u N; and D itself, 38 u of a
+// distance of at most 2 N, 76 u N.  In all 184 u N, where GRAM_ERR is 256 u: the rest covers the roundings
+// of S + E and S - E and of the computed norms.  GRAM_TINY covers products and elements that underflow.
+constexpr float GRAM_ERR = 0x1p-16f, GRAM_TINY = 1e-35f;
+
+template <int KIND, int VEC, int NCH>
+struct F32PruneOk {
+  static constexpr bool value = !KindTraits<KIND>::is_int && VEC == 16 && NCH <= 8;
+};
+
+// Waves per SIMD of the prune kernel.  The float walk holds a block of candidates and a tile of selected
+// rows, 8 * NCH registers each, beside 16 of products: the count at which nothing spills.
+template <int KIND, int VEC, int NCH>
+struct PruneWaves {
+  static constexpr int value = F32PruneOk<KIND, VEC, NCH>::value ? (NCH <= 4 ? 4 : NCH <= 7 ? 3 : 2) : 4;
+};
+
+// LDS of the walk: p's row, zero-padded to 8 * NCH pieces, the block's norms, the selected points' norms
+struct F32Lds {
+  float4* p;
+  float* cnorm;    // 16
+  float* selnorm;  // R
+};
+__host__ __device__ inline u32 f32_lds_bytes(u32 R, u32 npieces) {
+  return ((npieces + 7u) & ~7u) * 16u + 64u + ((R * 4u + 15u) & ~15u) + ((R * 4u + 15u) & ~15u);
+}
+// `base` is 16-byte aligned; `out` gets the first R words
+__device__ __forceinline__ F32Lds f32_lds_carve(unsigned char* base, u32 R, u32*& out) {
+  F32Lds M;
+  const u32 words = (R * 4u + 15u) & ~15u;
+  out = reinterpret_cast<u32*>(base);
+  M.selnorm = reinterpret_cast<float*>(base + words);
+  M.cnorm = reinterpret_cast<float*>(base + 2u * words);
+  M.p = reinterpret_cast<float4*>(base + 2u * words + 64u);
+  return M;
+}
+
+template <int NCH>
+struct F32Operand {
+  float4 x[2][NCH];
+};
+
+// a row's pieces of this lane; L2: less p's
+template <int KIND, int NCH>
+__device__ __forceinline__ void f32_load(F32Operand<NCH>& o, const char* row, u32 npieces, u32 blk) {
+#pragma unroll
+  for (int u = 0; u < NCH; ++u)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const u32 pc = 8u * u + 4u * h + blk;
+      o.x[h][u] = pc < npieces ? *reinterpret_cast<const float4*>(row + (u64)pc * 16u) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+}
+template <int KIND, int NCH>
+__device__ __forceinline__ void f32_centre(F32Operand<NCH>& o, const F32Lds& M, u32 npieces, u32 blk) {
+  if constexpr (KIND == K_F32_L2) {
+#pragma unroll
+    for (int u = 0; u < NCH; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (8u * u + 4u * h < npieces) {  // (uniform; the LDS copy of p has zeros up to a multiple of 8 pieces)
+          const float4 p = M.p[8u * u + 4u * h + blk];
+          o.x[h][u].x -= p.x;
+          o.x[h][u].y -= p.y;
+          o.x[h][u].z -= p.z;
+          o.x[h][u].w -= p.w;
+        }
+      }
+  }
+}
+
+// inner products of rows a (4 * (lane / 16) + v) and columns b (lane % 16)
+template <int NCH>
+__device__ __forceinline__ void f32_products(const F32Operand<NCH>& a, const F32Operand<NCH>& b, u32 npieces,
+                                             float (&dot)[4]) {
+  // one half of the partial sums after the other: the second half's pieces may still be on their way
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    v16f_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+      // (an instance serves rows that leave its last pieces empty: a chain of them adds zeros)
+      if (u + 2 < NCH || 8u * u + 4u * h < npieces) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(a.x[h][u].x, b.x[h][u].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(a.x[h][u].y, b.x[h][u].y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(a.x[h][u].z, b.x[h][u].z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(a.x[h][u].w, b.x[h][u].w, acc, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float half = (acc[v] + acc[4 + v]) + (acc[8 + v] + acc[12 + v]);
+      dot[v] = h == 0 ? half : dot[v] + half;
+    }
+  }
+}
+
+// What the products say of one pair: +1 the first removes the second, -1 it does not, 0 to be measured.
+// na, nb: squared norms (L2); dpc = d(p, second).
+template <int KIND>
+__device__ __forceinline__ int f32_verdict(float dot, float na, float nb, float af, float dpc) {
+  if constexpr (KIND == K_F32_IP) {
+    return af * -dot <= dpc ? 1 : -1;
+  } else {
+    const float n = na + nb;
+    const float S = __builtin_fmaf(-2.0f, dot, n), E = __builtin_fmaf(GRAM_ERR, n, GRAM_TINY);
+    const float lo = S - E, hi = S + E;
+    // (a NaN anywhere, as from an overflow, fails every comparison: measured)
+    if (lo <= hi && af * hi <= dpc) return 1;
+    return af * lo > dpc ? -1 : 0;
+  }
+}
+
+// Which of the candidates first[j], j in `mask`, row `sel` removes, each measured with distance_key's sum.
+__device__ __forceinline__ u32 f32_measured(const VecTable& T, u32 sel, const u64* first, u32 mask, float af, int lane) {
+  const u32 sub = (u32)lane & 7u, grp = (u32)lane >> 3;
+  u32 removed = 0;
+  while (mask) {
+    u32 rest = mask;
+    for (u32 k = 0; k < grp; ++k) rest &= rest - 1u;  // this group's candidate: the grp-th of the mask
+    const bool ok = rest != 0;
+    const u32 j = ok ? (u32)__builtin_ctz(rest) : 0u;
+    const u64 key = first[j];
+    const char* x = T.base + (u64)sel * T.row_bytes;
+    const char* y = T.base + (u64)(ok ? key_id(key) : sel) * T.row_bytes;
+    float d = 0.0f;  // (rare: not worth the registers that all pieces at once would take)
+#pragma unroll 1
+    for (u32 pc = sub; pc < T.npieces; pc += 8u) {
+      const float4 f = *reinterpret_cast<const float4*>(x + (u64)pc * 16u), g = *reinterpret_cast<const float4*>(y + (u64)pc * 16u);
+      const float e0 = f.x - g.x, e1 = f.y - g.y, e2 = f.z - g.z, e3 = f.w - g.w;
+      d = __builtin_fmaf(e3, e3, __builtin_fmaf(e2, e2, __builtin_fmaf(e1, e1, __builtin_fmaf(e0, e0, d))));
+    }
+    d = group_sum(d);
+    const u64 hit = ballot(ok && af * d <= float_from_dkey(key_dkey(key)));
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      if (mask) {  // uniform
+        if ((hit >> (8 * g)) & 1ull) removed |= mask & (0u - mask);
+        mask &= mask - 1u;
+      }
+    }
+  }
+  return removed;
+}
+
+// prow: p's row (L2).  The rest as prune_sorted.
+template <int KIND, int VEC, int NCH>
+__device__ __forceinline__ u32 prune_sorted_f32(const VecTable& T, const F32Lds& M, const char* prow, const u64* cand, u32 m,
+                                                u32 R, float af, u32* out, int lane, u32& pair_evals) {
+  constexpr bool L2 = KIND == K_F32_L2;
+  const u32 blk = (u32)lane >> 4, r = (u32)lane & 15u;
+  u32 nout = 0;
+  if (m == 0) return 0;
+  if constexpr (L2) {
+    const u32 np8 = (T.npieces + 7u) & ~7u;  // (at most 64)
+    if ((u32)lane < np8)
+      M.p[lane] = (u32)lane < T.npieces ? reinterpret_cast<const float4*>(prow)[lane] : make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+  }
+  for (u32 i0 = 0; i0 < m && nout < R; i0 += 16) {
+    const u32 nb = m - i0 < 16u ? m - i0 : 16u;
+    const u64* first = cand + i0;
+    const u64 ckey = first[r < nb ? r : 0u];
+    const float dpc = float_from_dkey(key_dkey(ckey));  // of column r
+    F32Operand<NCH> b;
+    f32_load<KIND, NCH>(b, T.base + (u64)key_id(ckey) * T.row_bytes, T.npieces, blk);
+    f32_centre<KIND, NCH>(b, M, T.npieces, blk);
+    float ncol = 0.0f;
+    if constexpr (L2) {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float4 x = b.x[h][u];
+          ncol = __builtin_fmaf(x.x, x.x, ncol);
+          ncol = __builtin_fmaf(x.y, x.y, ncol);
+          ncol = __builtin_fmaf(x.z, x.z, ncol);
+          ncol = __builtin_fmaf(x.w, x.w, ncol);
+        }
+      ncol += __shfl_xor(ncol, 16, 64);
+      ncol += __shfl_xor(ncol, 32, 64);
+      if (lane < 16) M.cnorm[lane] = ncol;
+    }
+
+    // removed by a point selected before this block?
+    u32 removed = 0;  // bit j: candidate j of the block
+    for (u32 s0 = 0; s0 < nout; s0 += 16) {
+      F32Operand<NCH> a;  // (past the end: the last row again, which changes no verdict)
+      f32_load<KIND, NCH>(a, T.base + (u64)out[s0 + r < nout ? s0 + r : nout - 1u] * T.row_bytes, T.npieces, blk);
+      f32_centre<KIND, NCH>(a, M, T.npieces, blk);
+      float dot[4];
+      f32_products<NCH>(a, b, T.npieces, dot);
+      bool rem = false;
+      u32 open = 0;  // rows whose pair with this lane's column has to be measured
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const u32 row = s0 + 4u * blk + v;
+        const float nrow = L2 ? M.selnorm[row < nout ? row : nout - 1u] : 0.0f;
+        const int verdict = f32_verdict<KIND>(dot[v], nrow, ncol, af, dpc);
+        rem = rem | (verdict > 0);
+        if (L2 && verdict == 0 && row < nout) open |= 1u << v;
+      }
+      const u64 rm = ballot(rem);
+      removed |= (u32)(rm | (rm >> 16) | (rm >> 32) | (rm >> 48)) & 0xFFFFu;
+      if constexpr (L2) {
+        if (ballot(open != 0)) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const u64 om = ballot((open >> v) & 1u);
+            for (u32 q = 0; q < 4; ++q) {
+              const u32 mask = (u32)(om >> (16u * q)) & 0xFFFFu & ~removed & ((1u << nb) - 1u);
+              if (mask) removed |= f32_measured(T, out[s0 + 4u * q + v], first, mask, af, lane);
+            }
+          }
+        }
+      }
+    }
+
+    // which candidate of the block would remove which: rows[v] holds rows v, 4 + v, 8 + v, 12 + v, 16 bits each
+    u64 rows[4], opens[4];
+    {
+      float dot[4];
+      f32_products<NCH>(b, b, T.npieces, dot);
+      __syncthreads();  // (the norms)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float nrow = L2 ? M.cnorm[4u * blk + v] : 0.0f;
+        const int verdict = f32_verdict<KIND>(dot[v], nrow, ncol, af, dpc);
+        rows[v] = ballot(verdict > 0);
+        opens[v] = L2 ? ballot(verdict == 0) : 0ull;
+      }
+    }
+    pair_evals += nb * nout + nb * (nb - 1) / 2;
+
+    // settle the block in order
+    u32 alive = ((1u << nb) - 1u) & ~removed;
+    u32 selmask = 0, nsel = 0;
+    while (alive != 0 && nout + nsel < R) {
+      const u32 t = (u32)__builtin_ctz(alive);
+      selmask |= 1u << t;
+      ++nsel;
+      alive &= ~(1u << t);
+      const u32 v = t & 3u, sh = 16u * (t >> 2);
+      const u64 row = v == 0 ? rows[0] : v == 1 ? rows[1] : v == 2 ? rows[2] : rows[3];
+      alive &= ~((u32)(row >> sh) & 0xFFFFu);
+      if constexpr (L2) {
+        const u64 ow = v == 0 ? opens[0] : v == 1 ? opens[1] : v == 2 ? opens[2] : opens[3];
+        const u32 mask = (u32)(ow >> sh) & alive;
+        if (mask) alive &= ~f32_measured(T, key_id(first[t]), first, mask, af, lane);
+      }
+    }
+    // commit: ids and norms of the selected candidates, in order
+    if (lane < 16 && ((selmask >> lane) & 1u)) {
+      const u32 slot = nout + (u32)__builtin_popcount(selmask & ((1u << lane) - 1u));
+      out[slot] = key_id(ckey);
+      if constexpr (L2) M.selnorm[slot] = ncol;
     }
     nout += nsel;
     __syncthreads();
