@@ -51,10 +51,10 @@ u32 bits_to_hold(u64 count) {  // smallest b with 2^b - 1 >= count: indices belo
   return b;
 }
 
-// A wavefront of the side kernels takes SIDE_PER_WAVE consecutive positions, eight at a time
-// (eight lanes per point).  The node of its first position is found once, by a uniform search
-// that the scalar unit runs; the later positions step forward from there.
-constexpr u32 SIDE_PER_WAVE = 32;
+// A wavefront of the side kernels takes SIDE_PER_WAVE consecutive positions.  The node of its first
+// position is found once, by a uniform search that the scalar unit runs; the later positions step
+// forward from there.
+constexpr u32 SIDE_PER_WAVE = 128, SIDE_PER_WAVE_F32 = 32;
 __device__ inline u32 side_first_node(const u32* off, u32 nseg, u64 w0) {
   u32 lo = 0, hi = nseg;
   while (hi - lo > 1) {
@@ -67,84 +67,109 @@ __device__ inline u32 side_first_node(const u32* off, u32 nseg, u64 w0) {
   return lo;
 }
 
-// One level of one tree.  keys_in[i] = (anything << 32) | id of the point at position i; the
-// nodes of the level are the position ranges off[s]..off[s+1].  A node that splits names the
-// positions of its two pivots; its points get child index base[s] (left: at most as far from the
-// first pivot as from the second) or base[s] + 1.  Other nodes keep their points under base[s].
-// Eight lanes per point.
+// The sides of one level's points: bit i % 32 of right[i / 32] is set if the point at position i is farther
+// from the first pivot of its node than from the second.  ids: the point at each position; the nodes of the
+// level are the position ranges off[s]..off[s+1]; a node that splits names the positions of its two
+// pivots, the points of any other node are all left ones.
+//
+// A wavefront takes SIDE_PER_WAVE consecutive positions, whose vectors are all requested before the first
+// is used, 32 at a time: the pivots of up to 16 nodes are the rows of a matrix product and the 32 points
+// its columns, so that a point costs a quarter of a matrix instruction instead of 16 dot products and
+// their sums across lanes, and hands on one bit instead of its key again.  Nearly always one node covers all 32.
+// What bounds it: 128 bytes gathered per point.  30 trees over a million uint8 points of 128: 365 -> 247 us per
+// level on average (39 levels), with the ids of 4 bytes and the sides of one bit that the split then reads
+// (74 + 29 + 13 -> 52 + 4 + 4 us) the build 65.7 -> 59.4 ms.
 template <bool SIGNED>
-__global__ __launch_bounds__(256) void hc_side_kernel(const unsigned char* pts, u32 row_bytes, const u64* keys_in, u64 n,
+__global__ __launch_bounds__(256) void hc_side_kernel(const unsigned char* pts, u32 row_bytes, const u32* ids, u64 n,
                                                       const u32* off, u32 nseg, const u32* pos1, const u32* pos2,
-                                                      const u32* base, u64* keys_out) {
-  const u32 sub = threadIdx.x & 7u, grp = (threadIdx.x >> 3) & 7u;
+                                                      u32* right) {
+  const int lane = (int)(threadIdx.x & 63u);
+  const u32 half = (u32)lane >> 5, col = (u32)lane & 31u;
   const u64 w0 = ((u64)blockIdx.x * 4u + (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * SIDE_PER_WAVE;
   if (w0 >= n) return;
-  u32 seg = side_first_node(off, nseg, w0);
-  const bool has_piece = sub < row_bytes / 16;  // a row is at most 128 bytes: one 16-byte piece per lane
-  // Four positions of a group at a time, every load of one kind requested for all four before the
-  // first answer is used: the kernel waits for memory, and this way four waits overlap.
-  constexpr u32 NB = 4;
-  for (u32 it0 = 0; it0 < SIDE_PER_WAVE / 8u; it0 += NB) {
-    u64 pos[NB];
-    bool live[NB];
-    u32 id[NB];
+  constexpr u32 NT = SIDE_PER_WAVE / 32u;
+  const u32 npieces = row_bytes / 16u;  // at most 8
+  constexpr u32 flip = SIGNED ? 0u : 0x80808080u;  // uint8 data moved down by 128: distances do not change
+  auto load_row = [&](u32 id, v4i_t (&x)[4]) {
+    const unsigned char* row = pts + (u64)id * row_bytes;
 #pragma unroll
-    for (u32 q = 0; q < NB; ++q) {
-      pos[q] = w0 + 8u * (it0 + q) + grp;
-      live[q] = pos[q] < n;
-      id[q] = live[q] ? (u32)keys_in[pos[q]] : 0u;
-    }
-    u32 idx[NB], p1[NB], p2[NB];
+    for (u32 ks = 0; ks < 4; ++ks)
+      x[ks] = 2u * ks + half < npieces ? *reinterpret_cast<const v4i_t*>(row + 16u * (2u * ks + half)) : v4i_t{0, 0, 0, 0};
+  };
+  auto to_int8 = [&](v4i_t (&x)[4]) {  // (the pieces behind the row's end stay zero)
 #pragma unroll
-    for (u32 q = 0; q < NB; ++q) {
-      if (live[q])
-        while ((u64)off[seg + 1] <= pos[q]) ++seg;
-      idx[q] = base[seg];
-      p1[q] = live[q] ? pos1[seg] : HC_NONE;
-      p2[q] = pos2[seg];
-    }
-    u32 ida[NB], idb[NB];
+    for (u32 ks = 0; ks < 4; ++ks) x[ks] = 2u * ks + half < npieces ? x[ks] ^ (int)flip : x[ks];
+  };
+  u32 id[NT];
 #pragma unroll
-    for (u32 q = 0; q < NB; ++q) {
-      const bool split = p1[q] != HC_NONE;
-      ida[q] = split ? (u32)keys_in[p1[q]] : 0u;
-      idb[q] = split ? (u32)keys_in[p2[q]] : 0u;
-    }
-    uint4 vx[NB], va[NB], vb[NB];
-#pragma unroll
-    for (u32 q = 0; q < NB; ++q) {
-      vx[q] = va[q] = vb[q] = make_uint4(0, 0, 0, 0);
-      if (p1[q] != HC_NONE && has_piece) {
-        vx[q] = reinterpret_cast<const uint4*>(pts + (u64)id[q] * row_bytes)[sub];
-        va[q] = reinterpret_cast<const uint4*>(pts + (u64)ida[q] * row_bytes)[sub];
-        vb[q] = reinterpret_cast<const uint4*>(pts + (u64)idb[q] * row_bytes)[sub];
-      }
-    }
-#pragma unroll
-    for (u32 q = 0; q < NB; ++q) {
-      const u32 wx[4] = {vx[q].x, vx[q].y, vx[q].z, vx[q].w}, wa[4] = {va[q].x, va[q].y, va[q].z, va[q].w},
-                wb[4] = {vb[q].x, vb[q].y, vb[q].z, vb[q].w};
-      i32 xa = 0, xb = 0, aa = 0, bb = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if constexpr (SIGNED) {
-          xa = __builtin_amdgcn_sdot4((i32)wx[k], (i32)wa[k], xa, false);
-          xb = __builtin_amdgcn_sdot4((i32)wx[k], (i32)wb[k], xb, false);
-          aa = __builtin_amdgcn_sdot4((i32)wa[k], (i32)wa[k], aa, false);
-          bb = __builtin_amdgcn_sdot4((i32)wb[k], (i32)wb[k], bb, false);
-        } else {
-          xa = (i32)__builtin_amdgcn_udot4(wx[k], wa[k], (u32)xa, false);
-          xb = (i32)__builtin_amdgcn_udot4(wx[k], wb[k], (u32)xb, false);
-          aa = (i32)__builtin_amdgcn_udot4(wa[k], wa[k], (u32)aa, false);
-          bb = (i32)__builtin_amdgcn_udot4(wb[k], wb[k], (u32)bb, false);
-        }
-      }
-      // |x-a|^2 <= |x-b|^2  <=>  |a|^2 - 2<x,a> <= |b|^2 - 2<x,b>  (a node that does not split: 0 <= 0)
-      const i32 lhs = group_sum(aa - 2 * xa), rhs = group_sum(bb - 2 * xb);
-      if (lhs > rhs) idx[q] += 1;
-      if (live[q] && sub == 0) keys_out[pos[q]] = ((u64)idx[q] << 32) | id[q];
-    }
+  for (u32 q = 0; q < NT; ++q) {
+    const u64 i = w0 + 32u * q + col;
+    id[q] = ids[i < n ? i : n - 1u];
   }
+  v4i_t x[NT][4];
+#pragma unroll
+  for (u32 q = 0; q < NT; ++q) load_row(id[q], x[q]);
+
+  u32 seg = side_first_node(off, nseg, w0);
+  u32 held = HC_NONE;  // the node whose pivots are rows 0 and 1 of the operand
+  v4i_t pv[4];
+  u32 splits = 0;  // row's node splits
+  i32 norm = 0;    // the pivot's squared norm
+  u32 word = 0;    // lane q: the sides of tile q
+#pragma unroll
+  for (u32 q = 0; q < NT; ++q) {
+    const u64 t0 = w0 + 32u * q;
+    if (t0 >= n) break;  // uniform
+    const u64 t1 = t0 + 31u < n ? t0 + 31u : n - 1u;
+    while ((u64)off[seg + 1] <= t0) ++seg;
+    u32 last = seg;  // (a node that splits has 3 points or more, one that does not is deep: at most 12 nodes in 32
+                     // positions, as the level holds only nodes of more points than a leaf)
+    while ((u64)off[last + 1] <= t1) ++last;
+    if (held == HC_NONE || seg < held || last > held + 15u || (seg == last && seg != held)) {  // uniform
+      held = seg;
+      const u32 node = held + (col >> 1) < nseg ? held + (col >> 1) : nseg - 1u;
+      const u32 p = (col & 1u) ? pos2[node] : pos1[node];
+      splits = p != HC_NONE ? 1u : 0u;
+      load_row(splits ? ids[p] : 0u, pv);
+      to_int8(pv);
+      norm = 0;
+#pragma unroll
+      for (u32 ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) norm = __builtin_amdgcn_sdot4(pv[ks][k], pv[ks][k], norm, false);
+      norm += __shfl_xor(norm, 32, 64);
+    }
+    to_int8(x[q]);
+    v16i_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(pv[ks], x[q][ks], acc, 0, 0, 0);
+    // |x-a|^2 <= |x-b|^2  <=>  |a|^2 - |b|^2 - 2 (<x,a> - <x,b>) <= 0.  Register r of a lane is row 8 (r / 4) +
+    // 4 half + r % 4: the pivots of node held + k are registers 4 (k / 4) + 2 (k % 2) and the next, in the
+    // lanes of half (k / 2) % 2.
+    bool far;
+    if (seg == last) {
+      const i32 d = (i32)readlane_u32((u32)norm, 0) - (i32)readlane_u32((u32)norm, 1);
+      far = readlane_u32(splits, 0) != 0 && d - 2 * (acc[0] - acc[1]) > 0;
+    } else {
+      const u64 i = t0 + col;
+      u32 k = seg - held;
+      while (held + k < last && (u64)off[held + k + 1] <= i) ++k;
+      i32 v = 0;
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          if (k == (u32)(4 * g + e) + 2u * half) v = acc[4 * g + 2 * e] - acc[4 * g + 2 * e + 1];
+      const i32 other = __shfl_xor(v, 32, 64);
+      if (((k >> 1) & 1u) != half) v = other;
+      const i32 d = __shfl(norm, (int)(2u * k), 64) - __shfl(norm, (int)(2u * k + 1u), 64);
+      const u32 sp = (u32)__shfl((int)splits, (int)(2u * k), 64);
+      far = sp != 0 && d - 2 * v > 0;
+    }
+    const u32 bits = (u32)ballot(far && half == 0 && t0 + col < n);
+    if ((u32)lane == q) word = bits;
+  }
+  if ((u32)lane < NT && w0 + 32u * (u32)lane < n) right[w0 / 32u + (u32)lane] = word;
 }
 
 // Leaf vectors are kept in tiles of 32 consecutive points of ONE leaf (a leaf's tiles follow one
@@ -370,22 +395,22 @@ __global__ __launch_bounds__(64) void hc_knn_kernel(const unsigned char* leafvec
 typedef float v16f_t __attribute__((ext_vector_type(16)));
 
 template <bool MIPS>
-__global__ __launch_bounds__(256) void hc_side_f32_kernel(const unsigned char* pts, u32 row_bytes, const u64* keys_in,
+__global__ __launch_bounds__(256) void hc_side_f32_kernel(const unsigned char* pts, u32 row_bytes, const u32* ids,
                                                           u64 n, const u32* off, u32 nseg, const u32* pos1,
-                                                          const u32* pos2, const u32* base, u64* keys_out) {
+                                                          const u32* pos2, u32* right) {
   const u32 sub = threadIdx.x & 7u, grp = (threadIdx.x >> 3) & 7u;
-  const u64 w0 = ((u64)blockIdx.x * 4u + (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * SIDE_PER_WAVE;
+  const u64 w0 = ((u64)blockIdx.x * 4u + (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * SIDE_PER_WAVE_F32;
   if (w0 >= n) return;
   u32 seg = side_first_node(off, nseg, w0);
-  for (u32 it = 0; it < SIDE_PER_WAVE / 8u; ++it) {
+  u32 word = 0;
+  for (u32 it = 0; it < SIDE_PER_WAVE_F32 / 8u; ++it) {
     const u64 i = w0 + 8u * it + grp;
-    if (i >= n) break;
-    const u32 id = (u32)keys_in[i];
-    while ((u64)off[seg + 1] <= i) ++seg;
-    u32 idx = base[seg];
+    const u32 id = ids[i < n ? i : n - 1u];
+    while ((u64)off[seg + 1] <= (i < n ? i : n - 1u)) ++seg;
+    bool far = false;
     const u32 p1 = pos1[seg];
     if (p1 != HC_NONE) {
-      const u32 ida = (u32)keys_in[p1], idb = (u32)keys_in[pos2[seg]];
+      const u32 ida = ids[p1], idb = ids[pos2[seg]];
       const float4* x = reinterpret_cast<const float4*>(pts + (u64)id * row_bytes);
       const float4* a = reinterpret_cast<const float4*>(pts + (u64)ida * row_bytes);
       const float4* b = reinterpret_cast<const float4*>(pts + (u64)idb * row_bytes);
@@ -407,10 +432,15 @@ __global__ __launch_bounds__(256) void hc_side_f32_kernel(const unsigned char* p
       }
       da = group_sum(da);
       db = group_sum(db);
-      if (da > db) idx += 1;
+      far = da > db;
     }
-    if (sub == 0) keys_out[i] = ((u64)idx << 32) | id;
+    u64 m = ballot(far && i < n) & 0x0101010101010101ull;  // bit 8 g: point g of the eight
+    m |= m >> 7;
+    m |= m >> 14;
+    m |= m >> 28;
+    word |= ((u32)m & 0xFFu) << (8u * it);
   }
+  if ((threadIdx.x & 63u) == 0) right[w0 / 32u] = word;
 }
 
 // vectors in leaf order (rows of lv_stride bytes, zero tail) and their squared norms
@@ -950,35 +980,43 @@ __global__ __launch_bounds__(256) void uq_scatter_kernel(const u64* keys, u64 n,
 }
 
 // ---- a stable two-way split of every node, without a sort -------------------------------------
-// keys[i] = (side << 32) | id, side 0 = left.  With L(i) = number of left points before position
-// i, a point of the node [a, b) with nl = L(b) - L(a) left points goes to a + (L(i) - L(a)) if it
-// is a left point and to a + nl + (i - a) - (L(i) - L(a)) otherwise.
+// With L(i) = number of left points before position i, a point of the node [a, b) with nl = L(b) - L(a)
+// left points goes to a + (L(i) - L(a)) if it is a left point and to a + nl + (i - a) - (L(i) - L(a))
+// otherwise.  The side kernels leave one bit per position.
 constexpr u32 SP_TILE = 2048;  // positions per workgroup of 256 threads
 
-__global__ __launch_bounds__(256) void hc_count_left_kernel(const u64* keys, u64 m, u32* tile_cnt) {
-  __shared__ u32 total;
-  if (threadIdx.x == 0) total = 0;
-  __syncthreads();
-  const u64 base = (u64)blockIdx.x * SP_TILE + threadIdx.x;  // neighbouring lanes, neighbouring keys
-  u32 c = 0;
+// the left points among the positions 64 w .. 64 w + 63 that lie below `end`, as a mask
+__device__ __forceinline__ u64 left_mask(const u32* right, u64 w, u64 end) {
+  const u64 first = 64u * w;
+  if (first >= end) return 0ull;
+  u64 r = right[2u * w];
+  if (first + 32u < end) r |= (u64)right[2u * w + 1u] << 32;
+  const u64 live = end - first >= 64u ? ~0ull : (1ull << (end - first)) - 1ull;
+  return ~r & live;
+}
+
+__device__ __forceinline__ u32 wave_sum(u32 c) {
 #pragma unroll
-  for (u32 k = 0; k < 8; ++k)
-    if (base + 256u * k < m && (u32)(keys[base + 256u * k] >> 32) == 0u) ++c;
-  atomicAdd(&total, c);
-  __syncthreads();
-  if (threadIdx.x == 0) tile_cnt[blockIdx.x] = total;
+  for (int o = 32; o >= 1; o >>= 1) c += (u32)__shfl_xor((int)c, o, 64);
+  return c;
+}
+
+// left points per tile; one wavefront each
+__global__ __launch_bounds__(64) void hc_count_left_kernel(const u32* right, u64 m, u32* tile_cnt) {
+  u32 c = 0;
+  if (threadIdx.x < SP_TILE / 64u)
+    c = (u32)__builtin_popcountll(left_mask(right, (u64)blockIdx.x * (SP_TILE / 64u) + threadIdx.x, m));
+  c = wave_sum(c);
+  if (threadIdx.x == 0) tile_cnt[blockIdx.x] = c;
 }
 
 // Lb[j] = L(woff[j]) for the nact + 1 node boundaries; one wavefront each
-__global__ __launch_bounds__(64) void hc_seg_left_kernel(const u64* keys, u64 m, const u32* woff, const u32* tile_off,
-                                                         u32* Lb) {
+__global__ __launch_bounds__(64) void hc_seg_left_kernel(const u32* right, const u32* woff, const u32* tile_off, u32* Lb) {
   const u64 a = woff[blockIdx.x];
   const u64 t = a / SP_TILE;
   u32 c = 0;
-  for (u64 i = t * SP_TILE + threadIdx.x; i < a; i += 64)
-    if ((u32)(keys[i] >> 32) == 0u) ++c;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) c += (u32)__shfl_xor((int)c, o, 64);
+  if (threadIdx.x < SP_TILE / 64u) c = (u32)__builtin_popcountll(left_mask(right, t * (SP_TILE / 64u) + threadIdx.x, a));
+  c = wave_sum(c);
   if (threadIdx.x == 0) Lb[blockIdx.x] = tile_off[t] + c;
 }
 
@@ -986,21 +1024,23 @@ __global__ __launch_bounds__(64) void hc_seg_left_kernel(const u64* keys, u64 m,
 // covers sp (children 2 seg and 2 seg + 1 start at cstart[..]) and from there either the final
 // order (a finished child, dest = its first final position) or the next level's work array (top
 // bit of dest set).
-__global__ __launch_bounds__(256) void hc_split_route_kernel(const u64* keys, u64 m, const u32* woff, u32 nact,
-                                                             const u32* Lb, const u32* tile_off, const u32* cstart,
-                                                             const u32* dest, u64* final_keys, u64* next_work) {
-  // The tile's 2,048 positions in eight rows of 256: a wavefront reads 64 neighbouring keys at a
+__global__ __launch_bounds__(256) void hc_split_route_kernel(const u32* ids, const u32* right, u64 m, const u32* woff,
+                                                             u32 nact, const u32* Lb, const u32* tile_off,
+                                                             const u32* cstart, const u32* dest, u64* final_keys,
+                                                             u32* next_work) {
+  // The tile's 2,048 positions in eight rows of 256: a wavefront reads 64 neighbouring ids at a
   // time and writes the left ones (and the right ones) of a node to neighbouring places.
   __shared__ u32 before[32];  // left points of the tile before row k's quarter w, at [4 k + w]
-  const u32 t = threadIdx.x, w = t >> 6;
+  const u32 t = threadIdx.x, w = (u32)__builtin_amdgcn_readfirstlane((int)(t >> 6));
   const int lane = (int)(t & 63u);
   const u64 tile0 = (u64)blockIdx.x * SP_TILE;
-  u64 key[8], lefts[8];
+  u32 id[8];
+  u64 lefts[8];
 #pragma unroll
   for (u32 k = 0; k < 8; ++k) {
     const u64 i = tile0 + 256u * k + t;
-    key[k] = i < m ? keys[i] : ~0ull;
-    lefts[k] = ballot((u32)(key[k] >> 32) == 0u);
+    id[k] = i < m ? ids[i] : 0u;
+    lefts[k] = left_mask(right, tile0 / 64u + 4u * k + w, m);
     if (lane == 0) before[4 * k + w] = (u32)__builtin_popcountll(lefts[k]);
   }
   __syncthreads();
@@ -1023,7 +1063,7 @@ __global__ __launch_bounds__(256) void hc_split_route_kernel(const u64* keys, u6
   for (u32 k = 0; k < 8; ++k) {
     const u64 i = tile0 + 256u * k + t;
     if (i >= m) break;
-    const bool left = (u32)(key[k] >> 32) == 0u;
+    const bool left = (lefts[k] >> lane) & 1ull;
     const u32 L = tile_left + before[4 * k + w] + (u32)__builtin_popcountll(lefts[k] & lanemask_lt(lane));
     while ((u64)woff[lo + 1] <= i) ++lo;
     const u32 a = woff[lo], La = Lb[lo], nl = Lb[lo + 1] - La;
@@ -1032,17 +1072,17 @@ __global__ __launch_bounds__(256) void hc_split_route_kernel(const u64* keys, u6
     const u32 r = sp >= cstart[2 * lo + 1] ? 2 * lo + 1 : 2 * lo;
     const u32 d = dest[r];
     const u64 kk = sp - cstart[r];
-    const u64 id = key[k] & 0xFFFFFFFFull;
     if (d & 0x80000000u)
-      next_work[(u64)(d & 0x7FFFFFFFu) + kk] = id;
+      next_work[(u64)(d & 0x7FFFFFFFu) + kk] = id[k];
     else
-      final_keys[(u64)d + kk] = id;
+      final_keys[(u64)d + kk] = id[k];
   }
 }
 
-__global__ __launch_bounds__(256) void hc_iota_mod_kernel(u64* keys, u64 n, u64 total) {
+template <class Id>
+__global__ __launch_bounds__(256) void hc_iota_mod_kernel(Id* ids, u64 n, u64 total) {
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < total) keys[i] = i % n;
+  if (i < total) ids[i] = (Id)(i % n);
 }
 
 struct Seg {
@@ -1064,7 +1104,7 @@ struct HcCtx {
   const unsigned char* pts = nullptr;
   u32 Ls = 0, s = 0, l = 0;
   u64 seed = 0;
-  DevBuf final_keys, work[2], segbuf, routebuf, tilebuf, first, leafvec, leafnorm, leaf_off, knn_pos, knn_d, pair_cnt, leaf_list;
+  DevBuf final_keys, work[2], right, segbuf, routebuf, tilebuf, first, leafvec, leafnorm, leaf_off, knn_pos, knn_d, pair_cnt, leaf_list;
   u64 pair_cnt_cap = 0;
   u64 leaf_tiles = 0;  // tiles of 32 rows that leafvec holds
   u64 seg_words = 0;
@@ -1075,7 +1115,8 @@ struct HcCtx {
   i32* dump_d = nullptr;
   int alloc() {
     HIP_TRY(final_keys.alloc(N * 8));
-    for (auto& k : work) HIP_TRY(k.alloc(N * 8));
+    for (auto& k : work) HIP_TRY(k.alloc(N * 4));
+    HIP_TRY(right.alloc((N / 32 + 2) * 4));
     // nodes that split at one level: each holds more than Ls points
     const u64 nact = N / ((u64)Ls + 1) + G + 1;
     seg_words = 8 * nact + 16;
@@ -1111,31 +1152,30 @@ int hc_partition(HcCtx& X, u32 tree0, u32 G, std::vector<Leaf>& leaves, hipStrea
   const u64 n = X.n, N = (u64)G * n;
   leaves.clear();
   if (n <= X.Ls) {
-    hipLaunchKernelGGL(hc_iota_mod_kernel, dim3((u32)((N + 255) / 256)), dim3(256), 0, st, X.final_keys.as<u64>(), n, N);
+    hipLaunchKernelGGL(hc_iota_mod_kernel<u64>, dim3((u32)((N + 255) / 256)), dim3(256), 0, st, X.final_keys.as<u64>(), n, N);
     HIP_TRY(hipGetLastError());
     for (u32 g = 0; g < G; ++g) leaves.push_back(Leaf{(u64)g * n, n});
     return ANN_OK;
   }
-  hipLaunchKernelGGL(hc_iota_mod_kernel, dim3((u32)((N + 255) / 256)), dim3(256), 0, st, X.work[0].as<u64>(), n, N);
+  hipLaunchKernelGGL(hc_iota_mod_kernel<u32>, dim3((u32)((N + 255) / 256)), dim3(256), 0, st, X.work[0].as<u32>(), n, N);
   HIP_TRY(hipGetLastError());
   std::vector<Seg> act, next;
   for (u32 g = 0; g < G; ++g) act.push_back(Seg{(u64)g * n, n, 1, (u64)g * n, 0, tree0 + g});
   u64 m = N;
+  u32 in = 0;  // which of the two work arrays holds this level's points
   while (!act.empty()) {
     const u32 nact = (u32)act.size();
     if (8ull * nact + 16 > X.seg_words) return fail(ANN_EINTERNAL, "more splitting nodes than planned for");
-    // woff[nact+1] | pos1[nact] | pos2[nact] | base[nact]
+    // woff[nact+1] | pos1[nact] | pos2[nact]
     // (the host tables are free again: the wait in the middle of the previous level came after
     // this table's copy, and the routing table is not written before this level's wait)
     u32* woff = X.h_up.as<u32>();
-    std::fill(woff, woff + (size_t)4 * nact + 1, HC_NONE);
+    std::fill(woff, woff + (size_t)3 * nact + 1, HC_NONE);
     u32* pos1 = woff + nact + 1;
     u32* pos2 = pos1 + nact;
-    u32* base = pos2 + nact;
     for (u32 j = 0; j < nact; ++j) {
       const Seg& sg = act[j];
       woff[j] = (u32)sg.woff;
-      base[j] = 0;  // the side is all the key carries: 0 left, 1 right
       if (sg.depth < HC_MAX_DEPTH) {
         const u64 k = 2 * (((u64)sg.tree << 40) + sg.node);
         const u64 i1 = mulhi64(stream_output(X.seed, k), sg.cnt);
@@ -1147,11 +1187,14 @@ int hc_partition(HcCtx& X, u32 tree0, u32 G, std::vector<Leaf>& leaves, hipStrea
     }
     woff[nact] = (u32)m;
     u32* d_seg = X.segbuf.as<u32>();
-    HIP_TRY(hipMemcpyAsync(d_seg, woff, ((size_t)4 * nact + 1) * 4, hipMemcpyHostToDevice, st));
-    const u32 grid_side = (u32)((m + 4 * SIDE_PER_WAVE - 1) / (4 * SIDE_PER_WAVE));
-#define HC_SIDE(KERNEL)                                                                                                  \
-  hipLaunchKernelGGL(KERNEL, dim3(grid_side), dim3(256), 0, st, X.pts, X.row_bytes, X.work[0].as<u64>(), m, d_seg, nact, \
-                     d_seg + nact + 1, d_seg + 2 * nact + 1, d_seg + 3 * nact + 1, X.work[1].as<u64>())
+    HIP_TRY(hipMemcpyAsync(d_seg, woff, ((size_t)3 * nact + 1) * 4, hipMemcpyHostToDevice, st));
+    const u32* ids = X.work[in].as<u32>();
+    const u32* right = X.right.as<u32>();
+    const u32 per_block = 4 * (X.is_f32 ? SIDE_PER_WAVE_F32 : SIDE_PER_WAVE);
+    const u32 grid_side = (u32)((m + per_block - 1) / per_block);
+#define HC_SIDE(KERNEL)                                                                                       \
+  hipLaunchKernelGGL(KERNEL, dim3(grid_side), dim3(256), 0, st, X.pts, X.row_bytes, ids, m, d_seg, nact,      \
+                     d_seg + nact + 1, d_seg + 2 * nact + 1, X.right.as<u32>())
     if (X.is_f32 && X.is_mips)
       HC_SIDE(hc_side_f32_kernel<true>);
     else if (X.is_f32)
@@ -1166,9 +1209,9 @@ int hc_partition(HcCtx& X, u32 tree0, u32 G, std::vector<Leaf>& leaves, hipStrea
     const u32 ntiles = (u32)((m + SP_TILE - 1) / SP_TILE);
     u32* d_tile = X.tilebuf.as<u32>();
     u32* d_Lb = X.first.as<u32>();
-    hipLaunchKernelGGL(hc_count_left_kernel, dim3(ntiles), dim3(256), 0, st, X.work[1].as<u64>(), m, d_tile);
+    hipLaunchKernelGGL(hc_count_left_kernel, dim3(ntiles), dim3(64), 0, st, right, m, d_tile);
     hipLaunchKernelGGL(uq_scan_kernel, dim3(1), dim3(1024), 0, st, d_tile, ntiles);
-    hipLaunchKernelGGL(hc_seg_left_kernel, dim3(nact + 1), dim3(64), 0, st, X.work[1].as<u64>(), m, d_seg, d_tile, d_Lb);
+    hipLaunchKernelGGL(hc_seg_left_kernel, dim3(nact + 1), dim3(64), 0, st, right, d_seg, d_tile, d_Lb);
     HIP_TRY(hipGetLastError());
     const u32* h_first = X.h_first.as<u32>();
     HIP_TRY(hipMemcpyAsync(X.h_first.p, d_Lb, ((size_t)nact + 1) * 4, hipMemcpyDeviceToHost, st));
@@ -1204,9 +1247,10 @@ int hc_partition(HcCtx& X, u32 tree0, u32 G, std::vector<Leaf>& leaves, hipStrea
     cstart[2 * nact] = (u32)m;
     u32* d_route = X.routebuf.as<u32>();
     HIP_TRY(hipMemcpyAsync(d_route, cstart, ((size_t)4 * nact + 1) * 4, hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(hc_split_route_kernel, dim3(ntiles), dim3(256), 0, st, X.work[1].as<u64>(), m, d_seg, nact, d_Lb,
-                       d_tile, d_route, d_route + 2 * nact + 1, X.final_keys.as<u64>(), X.work[0].as<u64>());
+    hipLaunchKernelGGL(hc_split_route_kernel, dim3(ntiles), dim3(256), 0, st, ids, right, m, d_seg, nact, d_Lb, d_tile,
+                       d_route, d_route + 2 * nact + 1, X.final_keys.as<u64>(), X.work[1 - in].as<u32>());
     HIP_TRY(hipGetLastError());
+    in = 1 - in;
     act.swap(next);
     m = nm;
   }

@@ -1,0 +1,23 @@
+"""The pivot tests of the cluster trees at the edges of a wavefront's tiles: rows of 1 to 8 pieces, the last one
+padded, numbers of points around 32, 64 and 128, and leaves so small that the 32 points of a tile belong
+to many nodes.  Byte rows are whole numbers: the trees must be the oracle's."""
+import numpy as np
+import pytest
+
+from helpers import dev, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,lo,hi", [(np.uint8, 0, 256), (np.int8, -128, 128)])
+@pytest.mark.parametrize("d", [7, 32, 100, 128])
+def test_trees_equal_the_oracles(env, d, dtype, lo, hi):
+    torch, A, O = env
+    rng = np.random.default_rng(d)
+    pts_h = rng.integers(lo, hi, (4099, d)).astype(dtype)
+    pts_h[::5] = pts_h[2]  # equal points: nodes that nothing separates
+    for n, Ls in ((31, 2), (33, 2), (65, 3), (129, 2), (513, 4), (2049, 2), (4099, 2), (4099, 700)):
+        say(f"cluster tree sides d={d} {dtype.__name__} n={n} Ls={Ls}")
+        perm, off, _ = A.ann_hcnng_tree_edges(dev(torch, pts_h[:n]), Ls, 3, 3, 5, 1)
+        operm, ooff = O.hcnng_tree(O.Dataset(pts_h[:n], 0), Ls, 5, 1)
+        assert (off == ooff[:len(off)]).all() and (perm == operm).all()
