@@ -191,7 +191,7 @@ __device__ inline u32 leaf_of_tile(const u32* tile_of_leaf, u32 nleaves, u32 til
 }
 
 // The vectors in that layout, as int8 (uint8 data moved down by 128: distances do not change),
-// rows of lv_stride bytes (a multiple of 32, zero tail), and their squared norms (times 512) by
+// rows of lv_stride bytes (a multiple of 32, zero tail), and their squared norms (times 512, and a number below 16) by
 // position.  One workgroup per tile, eight lanes per point.
 template <bool SIGNED>
 __global__ __launch_bounds__(256) void hc_gather_kernel(const unsigned char* pts, u32 row_bytes, const u64* keys,
@@ -229,7 +229,8 @@ __global__ __launch_bounds__(256) void hc_gather_kernel(const unsigned char* pts
     nn = __builtin_amdgcn_sdot4((i32)v.w, (i32)v.w, nn, false);
   }
   nn = group_sum(nn);
-  if (sub == 0) leafnorm[i] = nn << 9;  // where the nearest-neighbour kernel's keys hold the distance
+  // where the nearest-neighbour kernel's keys hold the distance, and which of its lane's 16 candidates of a tile it is
+  if (sub == 0) leafnorm[i] = (nn << 9) | (i32)(4u * (r / 8u) + r % 4u);
 }
 
 // Which leaf and which 32 queries of it a block of the nearest-neighbour kernels takes.  A leaf's
@@ -243,14 +244,73 @@ __device__ inline bool knn_block(u32 nleaves, u32 ny, u32& leaf, u32& q0) {
   return leaf < nleaves;
 }
 
+__device__ __forceinline__ u32 med3_u32(u32 a, u32 b, u32 c) {
+  u32 r;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// best <- the N smallest of two ascending lists, ascending: the smaller of one list's i-th and the other's
+// i-th from the end are the N smallest, rising up to some place and falling behind it; a merging network
+// over the next power of two, with zeros in front, sorts them.
+template <int N>
+__device__ __forceinline__ void merge_lists(u64 (&best)[N], const u64 (&other)[N]) {
+  constexpr int P = N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : 32;
+  u64 v[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) v[i] = 0ull;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[P - N + i] = best[i] < other[N - 1 - i] ? best[i] : other[N - 1 - i];
+#pragma unroll
+  for (int j = P / 2; j > 0; j >>= 1)
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      if ((i & j) == 0) {
+        const u64 lo = v[i] < v[i + j] ? v[i] : v[i + j], hi = v[i] < v[i + j] ? v[i + j] : v[i];
+        v[i] = lo;
+        v[i + j] = hi;
+      }
+#pragma unroll
+  for (int i = 0; i < N; ++i) best[i] = v[P - N + i];
+}
+
+// a lane's own keys, ascending: a bitonic network over the next power of two
+template <int N>
+__device__ __forceinline__ void sort_list(u64 (&a)[N]) {
+  constexpr int P = N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : 32;
+  u64 v[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) v[i] = i < P - N ? 0ull : a[i - (P - N)];
+#pragma unroll
+  for (int k = 2; k <= P; k <<= 1)
+#pragma unroll
+    for (int j = k / 2; j > 0; j >>= 1)
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if ((i & j) == 0) {
+          const bool up = (i & k) == 0;
+          const u64 lo = v[i] < v[i + j] ? v[i] : v[i + j], hi = v[i] < v[i + j] ? v[i + j] : v[i];
+          v[i] = up ? lo : hi;
+          v[i + j] = up ? hi : lo;
+        }
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = v[P - N + i];
+}
+
 // The l nearest neighbours, inside its leaf, of each of 32 consecutive points of a leaf (block
 // (leaf, 32-point block), one wavefront).  Matrix-core tile: rows = 32 candidates, columns = the
 // 32 points; lane (half, col) then holds, for point col, the inner products with 16 of the 32
 // candidates, and keeps the LCAP smallest (distance, position) keys it has seen in registers.
 // The two lanes of a point merge their lists at the end.  knn_pos / knn_d: l entries per point,
 // ascending; positions are relative to the leaf.
+//
+// What bounds it: vector instructions (84 % of the cycles), five per candidate to form, test and queue its key
+// and ten (v_med3) per queue entry to put it in the list.  30 trees over a million uint8 points, leaves
+// of up to 1,000, l = 10: 10.9 -> 8.3 ms (insertion by min and max, 100 exchanges per merge and tiles moved
+// between registers before).  Longer queues (32, 40) gain nothing, nor do blocks of four waves that read
+// a leaf side by side (10.9).
 template <int LCAP>
-__global__ __launch_bounds__(64) void hc_knn_kernel(const unsigned char* leafvec, const i32* leafnorm, u32 lv_stride,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LCAP <= 10 ? 4 : 3, LCAP <= 10 ? 4 : 3))) void hc_knn_kernel(const unsigned char* leafvec, const i32* leafnorm, u32 lv_stride,
                                                     const u32* leaf_off, const u32* tile_of_leaf, u32 l,
                                                     unsigned short* knn_pos, i32* knn_d, u32 nleaves, u32 ny) {
   u32 leaf, q0;
@@ -264,7 +324,7 @@ __global__ __launch_bounds__(64) void hc_knn_kernel(const unsigned char* leafvec
   const u32 ksteps = lv_stride / 32u;  // at most 4
   const u32 q = q0 + col;
   const u32 qrow = q < cnt ? q : cnt - 1u;
-  const u32 qn = (u32)leafnorm[off + qrow];  // (times 512, like the candidates' norms)
+  const u32 qn = (u32)leafnorm[off + qrow] & ~511u;  // (times 512, like the candidates' norms)
   v4i_t bq[4];
 #pragma unroll
   for (u32 ks = 0; ks < 4; ++ks) {
@@ -284,75 +344,87 @@ __global__ __launch_bounds__(64) void hc_knn_kernel(const unsigned char* leafvec
   // column per lane) and are inserted when some lane's queue is full: the insertion code then
   // runs a few times per wave with most lanes busy, not once per candidate for one lane's sake.
   constexpr u32 QCAP = 24;  // a tile adds at most 16 per lane; drained once above 8
-  __shared__ u32 pend[QCAP][64];
-  u32 pc = 0;
+  __shared__ __align__(16) unsigned char pend[QCAP * 256];
+  const u32 first = 4u * (u32)lane;
+  u32 at = first;  // (bytes) where the lane's next entry goes
   u32 worst = K32_INF;
   auto drain = [&]() {
+    // into an ascending list: every place takes the middle one of the key, its own entry and the one before
 #pragma unroll 1
-    for (u32 i = 0; i < QCAP; ++i) {
-      if (ballot(i < pc) == 0ull) break;
-      u32 key = i < pc ? pend[i][lane] : K32_INF;
+    for (u32 p = first; p < QCAP * 256u; p += 512u) {
+      if (ballot(p < at) == 0ull) break;
+      const u32 k0 = *reinterpret_cast<const u32*>(pend + p);  // (what lies behind the queue's end is not used)
+      const u32 k1 = *reinterpret_cast<const u32*>(pend + p + 256u);
+      const u32 key[2] = {p < at ? k0 : K32_INF, p + 256u < at ? k1 : K32_INF};
 #pragma unroll
-      for (int t = 0; t < LCAP; ++t) {
-        const u32 hi = key > best32[t] ? key : best32[t];
-        best32[t] = key < best32[t] ? key : best32[t];
-        key = hi;
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int t = LCAP - 1; t > 0; --t) best32[t] = med3_u32(key[h], best32[t - 1], best32[t]);
+        best32[0] = key[h] < best32[0] ? key[h] : best32[0];
       }
     }
-    pc = 0;
-    worst = best32[LCAP - 1];
+    at = first;
+    // The point's other lane has the other half of the candidates: half a list from each of the two is a
+    // whole one, and what is farther than both halves' ends cannot enter it (8.6 -> 8.3 ms).
+    const u32 mine = best32[LCAP / 2 - 1], theirs = (u32)__shfl_xor((int)mine, 32, 64);
+    const u32 end = (mine > theirs ? mine : theirs) | 511u;  // (numbers of two lanes do not compare: all of that distance)
+    worst = end < best32[LCAP - 1] ? end + 1u : best32[LCAP - 1];
   };
 
-  // the tile after the current one is requested before the current one is used
-  v4i_t av[4], cn[4];
-  auto request = [&](u32 c0, v4i_t (&a)[4], v4i_t (&nrm)[4]) {
+  struct Tile {
+    v4i_t av[4], cn[4];
+  };
+  auto request = [&](u32 c0, Tile& t) {
 #pragma unroll
     for (u32 ks = 0; ks < 4; ++ks) {
       const u32 kk = ks < ksteps ? ks : ksteps - 1u;
-      a[ks] = *reinterpret_cast<const v4i_t*>(tiles + (u64)c0 * lv_stride + ((2u * kk + half) * 32u + col) * 16u);
+      t.av[ks] = *reinterpret_cast<const v4i_t*>(tiles + (u64)c0 * lv_stride + ((2u * kk + half) * 32u + col) * 16u);
     }
     // norms of this lane's 16 candidates: rows 8g + 4 half + 0..3, g = 0..3 (the array has a tail
     // of 64 entries, so reading past the leaf's end stays inside it)
 #pragma unroll
-    for (u32 g = 0; g < 4; ++g) nrm[g] = *reinterpret_cast<const v4i_t*>(leafnorm + off + c0 + 8u * g + 4u * half);
+    for (u32 g = 0; g < 4; ++g) t.cn[g] = *reinterpret_cast<const v4i_t*>(leafnorm + off + c0 + 8u * g + 4u * half);
   };
-  request(0, av, cn);
-  for (u32 c0 = 0; c0 < cnt; c0 += 32u) {
-    v4i_t av_next[4], cn_next[4];
-    const u32 cnext = c0 + 32u < cnt ? c0 + 32u : c0;  // (the last tile asks for itself again)
-    request(cnext, av_next, cn_next);
-    if (ballot(pc > QCAP - 16u) != 0ull) drain();  // room for this tile in every lane's queue
+  auto use = [&](u32 c0, const Tile& tile) {
+    if (ballot(at > first + 256u * (QCAP - 16u)) != 0ull) drain();  // room for this tile in every lane's queue
     v16i_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[ks], bq[ks], acc, 0, 0, 0);
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(tile.av[ks], bq[ks], acc, 0, 0, 0);
     // only the tile with the queries themselves and the leaf's last tile hold candidates to skip
     const u32 qn_tile = qn + (c0 >> 1);
-    const int minus_1024 = -1024;
+    int minus_1024;  // (out of the compiler's sight, which makes two instructions of a known power of two)
+    asm("s_movk_i32 %0, -1024" : "=s"(minus_1024));
     auto scan = [&](auto checked) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const u32 cand = c0 + 8u * (r / 4) + 4u * half + (r % 4);
-        // (|q|^2 + |c|^2 - 2<q,c>) << 9 | number, from norms that come shifted: an add and a
-        // multiply-add
-        const u32 base = (u32)cn[r / 4][r % 4] + qn_tile + (u32)r;
-        u32 packed;  // base - 1024 * <q,c>: an inner product over 128 bytes fits 24 bits
-        asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(packed) : "v"(acc[r]), "s"(minus_1024), "v"(base));
+        // (|q|^2 + |c|^2 - 2<q,c>) << 9 | number, from norms that come shifted and with the number in the tile:
+        // a multiplication (an inner product over 128 bytes fits 24 bits) and a sum of three.  (No asm
+        // statement may read the products: the compiler waits for the matrix unit only before its own
+        // instructions.)
+        const u32 packed = (u32)__mul24(acc[r], minus_1024) + ((u32)tile.cn[r / 4][r % 4] + qn_tile);
         const bool valid = !decltype(checked)::value || (cand < cnt && cand != q);
         const u32 key = valid ? packed : K32_INF;
-        // written in any case, kept when the count moves on: no lane is masked, no branch taken
-        pend[pc][lane] = key;
-        pc += key < worst ? 1u : 0u;
+        // written in any case, kept when the place moves on: no lane is masked, no branch taken
+        *reinterpret_cast<u32*>(pend + at) = key;
+        at += key < worst ? 256u : 0u;
       }
     };
     if (c0 == q0 || c0 + 32u > cnt)
       scan(std::true_type{});
     else
       scan(std::false_type{});
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      av[ks] = av_next[ks];
-      cn[ks] = cn_next[ks];
-    }
+  };
+  // the tile after the current one is requested before the current one is used (the last one asks
+  // for itself again); two tiles in turn, so that none is moved from register to register
+  Tile t0, t1;
+  request(0, t0);
+  for (u32 c0 = 0; c0 < cnt; c0 += 64u) {
+    request(c0 + 32u < cnt ? c0 + 32u : c0, t1);
+    use(c0, t0);
+    if (c0 + 32u >= cnt) break;
+    request(c0 + 64u < cnt ? c0 + 64u : c0, t0);
+    use(c0 + 32u, t1);
   }
   drain();
   // back to (distance << 32 | position), then the other half of the candidates from the partner lane
@@ -366,16 +438,7 @@ __global__ __launch_bounds__(64) void hc_knn_kernel(const unsigned char* leafvec
   u64 other[LCAP];
 #pragma unroll
   for (int i = 0; i < LCAP; ++i) other[i] = (u64)__shfl_xor((unsigned long long)best[i], 32, 64);
-#pragma unroll
-  for (int j = 0; j < LCAP; ++j) {
-    u64 key = other[j];
-#pragma unroll
-    for (int i = 0; i < LCAP; ++i) {
-      const u64 lo = key < best[i] ? key : best[i];
-      key = key < best[i] ? best[i] : key;
-      best[i] = lo;
-    }
-  }
+  merge_lists<LCAP>(best, other);
   if (half == 0 && q < cnt) {
 #pragma unroll
     for (int j = 0; j < LCAP; ++j) {
@@ -520,7 +583,10 @@ __global__ __launch_bounds__(64) void hc_knn_f32_kernel(const unsigned char* lea
       }
     }
     pc = 0;
-    worst = best[LCAP - 1];
+    // (half a list from each of the point's two lanes, as above; these keys compare)
+    const u64 mine = best[LCAP / 2 - 1], theirs = (u64)__shfl_xor((unsigned long long)mine, 32, 64);
+    const u64 end = mine > theirs ? mine : theirs;
+    worst = end < best[LCAP - 1] ? end + 1u : best[LCAP - 1];
   };
   for (u32 c0 = 0; c0 < cnt; c0 += 32u) {
     if (ballot(pc > QCAP - 16u) != 0ull) drain();  // room for this tile in every lane's queue
@@ -565,16 +631,7 @@ __global__ __launch_bounds__(64) void hc_knn_f32_kernel(const unsigned char* lea
   u64 other[LCAP];
 #pragma unroll
   for (int i = 0; i < LCAP; ++i) other[i] = (u64)__shfl_xor((unsigned long long)best[i], 32, 64);
-#pragma unroll
-  for (int j = 0; j < LCAP; ++j) {
-    u64 key = other[j];
-#pragma unroll
-    for (int i = 0; i < LCAP; ++i) {
-      const u64 lo = key < best[i] ? key : best[i];
-      key = key < best[i] ? best[i] : key;
-      best[i] = lo;
-    }
-  }
+  merge_lists<LCAP>(best, other);
   if constexpr (!MIPS) {
     // |a|^2 + |b|^2 - 2<a,b> loses the leading digits of a small distance (unit vectors a hundredth
     // apart: errors of a few 1e-5 of the value), which is fine for picking candidates but not for
@@ -613,18 +670,10 @@ __global__ __launch_bounds__(64) void hc_knn_f32_kernel(const unsigned char* lea
     for (int j = 0; j < LCAP; ++j) {
       const u64 o = (u64)__shfl_xor((unsigned long long)fresh[j], 32, 64);
       fresh[j] = ((u32)j & 1u) == half ? fresh[j] : o;
-      best[j] = KEY_INF;
     }
+    sort_list<LCAP>(fresh);
 #pragma unroll
-    for (int j = 0; j < LCAP; ++j) {
-      u64 key = fresh[j];
-#pragma unroll
-      for (int i = 0; i < LCAP; ++i) {
-        const u64 lo = key < best[i] ? key : best[i];
-        key = key < best[i] ? best[i] : key;
-        best[i] = lo;
-      }
-    }
+    for (int j = 0; j < LCAP; ++j) best[j] = fresh[j];
   }
   if (half == 0 && q < cnt) {
 #pragma unroll
