@@ -34,10 +34,9 @@
  *     the padded copies named above, and the scratch of ann_insert_batch /
  *     ann_insert_points (sized for the largest batch so far).  The memory
  *     comes from hipMalloc / hipFree, or from the `alloc` / `free` callbacks
- *     of ann_build_opts / ann_hnsw_opts, which the object then keeps for all
- *     its later allocations and for its own release (the clustering-based
- *     builder always uses hipMalloc).  The caller owns every buffer it
- *     passes in.
+ *     of ann_build_opts / ann_hnsw_opts / ann_hcnng_opts, which the object
+ *     then keeps for all its later allocations and for its own release.  The
+ *     caller owns every buffer it passes in.
  *   - Calls that use one graph or index object must be issued on one stream
  *     (or be ordered by the caller): the object's padded query copy and
  *     insertion scratch are shared by all calls on it.
@@ -420,6 +419,18 @@ void ann_hnsw_free(ann_hnsw* h);
 int ann_hcnng_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, ann_metric metric,
                     uint32_t T, uint32_t Ls, uint32_t s, uint32_t l, uint32_t R, float alpha, uint64_t seed,
                     void* stream, ann_graph** out);
+
+/* The same with the caller's allocator.  A build holds up to 250 bytes per
+ * point and tree (32 million of them at a time) while it runs; hipMalloc and
+ * hipFree of that size now and then take longer than the build itself.       */
+typedef struct {
+  ann_alloc_fn alloc;     /* device memory for the graph and all scratch; NULL =    */
+  ann_free_fn free;       /* hipMalloc / hipFree; both or neither                   */
+  void* alloc_user;
+} ann_hcnng_opts;
+int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, ann_metric metric,
+                         uint32_t T, uint32_t Ls, uint32_t s, uint32_t l, uint32_t R, float alpha, uint64_t seed,
+                         const ann_hcnng_opts* opts, void* stream, ann_graph** out);
 
 /* One cluster tree and its leaves' spanning trees alone (for tests): perm_host
  * receives the n point ids leaf after leaf, leaf_off_host the *nleaves + 1

@@ -64,6 +64,10 @@ class HnswOpts(C.Structure):
                 ("alloc", C.c_void_p), ("free", C.c_void_p), ("alloc_user", C.c_void_p)]
 
 
+class HcnngOpts(C.Structure):
+    _fields_ = [("alloc", C.c_void_p), ("free", C.c_void_p), ("alloc_user", C.c_void_p)]
+
+
 class HnswInfo(C.Structure):
     _fields_ = [("n", C.c_uint64), ("d", C.c_uint32), ("m", C.c_uint32), ("dtype", C.c_uint32),
                 ("metric", C.c_uint32), ("top", C.c_uint32), ("entry", C.c_uint32), ("rounds", C.c_uint64)]
@@ -75,7 +79,7 @@ EXPORTS = [
     "ann_graph_free", "ann_sort_edges", "ann_last_error",
     "ann_hnsw_build", "ann_hnsw_insert_points", "ann_hnsw_from_host", "ann_hnsw_search", "ann_hnsw_info", "ann_hnsw_copy_levels", "ann_hnsw_layer_size",
     "ann_hnsw_copy_layer", "ann_hnsw_get_stats", "ann_hnsw_free",
-    "ann_hcnng_build", "ann_hcnng_tree_edges", "ann_hcnng_leaf_knn",
+    "ann_hcnng_build", "ann_hcnng_build_with", "ann_hcnng_tree_edges", "ann_hcnng_leaf_knn",
 ]
 
 _lib = None
@@ -155,6 +159,9 @@ def lib():
         L.ann_hcnng_build.restype = C.c_int
         L.ann_hcnng_build.argtypes = [vp, u64, u32, C.c_int, C.c_int, u32, u32, u32, u32, u32, C.c_float, u64, vp,
                                       C.POINTER(vp)]
+        L.ann_hcnng_build_with.restype = C.c_int
+        L.ann_hcnng_build_with.argtypes = [vp, u64, u32, C.c_int, C.c_int, u32, u32, u32, u32, u32, C.c_float, u64,
+                                           C.POINTER(HcnngOpts), vp, C.POINTER(vp)]
         L.ann_hcnng_tree_edges.restype = C.c_int
         L.ann_hcnng_tree_edges.argtypes = [vp, u64, u32, C.c_int, C.c_int, u32, u32, u32, u64, u32, vp, vp, vp,
                                            C.POINTER(u64), vp, C.POINTER(u64)]
@@ -197,7 +204,7 @@ FREE_FN = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p)
 
 
 class TorchAllocator:
-    """The `alloc` / `free` callbacks of ann_build_opts / ann_hnsw_opts served by PyTorch's caching
+    """The `alloc` / `free` callbacks of the build options served by PyTorch's caching
     allocator, so that the graph and every scratch buffer of a call are PyTorch's memory.  One
     instance serves any number of calls; it must outlive every object built with it (the
     objects made by this module keep a reference)."""
@@ -556,13 +563,16 @@ def ann_hnsw_search(index: Hnsw, points, queries, k, L, eps=-1.0, ids_out=None, 
     return ids_out, dists_out
 
 
-def ann_hcnng_build(points, T, Ls, s, l, R, alpha, seed=1, metric=L2SQ) -> Graph:
-    """The clustering-based builder of Sec. 4.3 over a device tensor of uint8 or int8 points."""
+def ann_hcnng_build(points, T, Ls, s, l, R, alpha, seed=1, metric=L2SQ, allocator="torch") -> Graph:
+    """The clustering-based builder of Sec. 4.3 over a device tensor of points.
+    The graph and the build's scratch are PyTorch's memory unless allocator=None."""
     points = _dev2d(points, "points")
+    o = HcnngOpts()
+    al = _use_allocator(o, allocator)
     h = C.c_void_p()
-    _check(lib().ann_hcnng_build(points.data_ptr(), points.shape[0], points.shape[1], _dtype_code(points),
-                                 int(metric), T, Ls, s, l, R, float(alpha), seed, _stream_ptr(), C.byref(h)))
-    return Graph(h.value)
+    _check(lib().ann_hcnng_build_with(points.data_ptr(), points.shape[0], points.shape[1], _dtype_code(points), int(metric),
+                                      T, Ls, s, l, R, float(alpha), seed, C.byref(o), _stream_ptr(), C.byref(h)))
+    return Graph(h.value, al)
 
 
 def ann_hcnng_tree_edges(points, Ls, s, l, seed, tree, metric=L2SQ):

@@ -658,9 +658,9 @@ int new_graph(u64 n, u32 d, int dtype, int metric, u32 R, ann_graph** out) {
   g->al = current_allocator();
   hipError_t e = g->al.get(reinterpret_cast<void**>(&g->rows), (size_t)n * R * sizeof(u32));
   if (e == hipSuccess) e = g->al.get(reinterpret_cast<void**>(&g->meta), (size_t)n * sizeof(u32));
-  if (e == hipSuccess) e = hipMemset(g->meta, 0, (size_t)n * sizeof(u32));
+  if (e == hipSuccess) e = g->al.zero(g->meta, (size_t)n * sizeof(u32));
   if (e == hipSuccess) e = g->al.get(reinterpret_cast<void**>(&g->counters), COUNTER_COPIES * sizeof(DevCounters));
-  if (e == hipSuccess) e = hipMemset(g->counters, 0, COUNTER_COPIES * sizeof(DevCounters));
+  if (e == hipSuccess) e = g->al.zero(g->counters, COUNTER_COPIES * sizeof(DevCounters));
   if (e != hipSuccess) {
     ann_graph_free(g);
     return fail(e == hipErrorOutOfMemory ? ANN_ENOMEM : ANN_EHIP, "graph allocation: %s", hipGetErrorString(e));

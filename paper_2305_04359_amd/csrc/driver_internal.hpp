@@ -45,6 +45,11 @@ struct Allocator {
     *p = alloc(bytes, stream, user);
     return *p != nullptr ? hipSuccess : hipErrorOutOfMemory;
   }
+  // Zeroes memory that `get` gave.  Memory of the caller's may still be read or written by work that was
+  // queued on its stream before it was handed on: the clearing goes behind that.
+  hipError_t zero(void* p, size_t bytes) const {
+    return alloc == nullptr ? hipMemset(p, 0, bytes) : hipMemsetAsync(p, 0, bytes, static_cast<hipStream_t>(stream));
+  }
   void put(void* p) const {
     if (p == nullptr) return;
     if (free != nullptr)
@@ -204,7 +209,7 @@ struct BatchScratch {
     HIP_TRY(hist.alloc(radix_hist_entries(E) * 4));
     HIP_TRY(lists.alloc(3 * E * sizeof(MergeItem)));
     HIP_TRY(small.alloc(64));
-    HIP_TRY(hipMemset(small.p, 0, 64));
+    HIP_TRY(small.al.zero(small.p, 64));
     HIP_TRY(ovf_list.alloc(b * 4));
     HIP_TRY(arena.alloc(arena_cap * 8));
     HIP_TRY(spill.alloc(spill_cap * 8));

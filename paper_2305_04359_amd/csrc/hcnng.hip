@@ -1184,7 +1184,7 @@ struct HcCtx {
     if (getenv("ANN_HCNNG_FEW_TILES") != nullptr) leaf_tiles = 1;
     HIP_TRY(leafvec.alloc(leaf_tiles * 32 * lv_stride));
     HIP_TRY(leafnorm.alloc((N + 64) * 4));
-    HIP_TRY(hipMemset(leafnorm.p, 0, (N + 64) * 4));
+    HIP_TRY(leafnorm.al.zero(leafnorm.p, (N + 64) * 4));
     HIP_TRY(leaf_off.alloc(2 * (N + 1) * 4));
     HIP_TRY(knn_pos.alloc(N * l * 2));
     HIP_TRY(knn_d.alloc(N * l * 4));
@@ -1568,7 +1568,13 @@ int ann_hcnng_leaf_knn(const void* points_dev, uint64_t n, uint32_t d, ann_dtype
 
 int ann_hcnng_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, ann_metric metric, uint32_t T,
                     uint32_t Ls, uint32_t s, uint32_t l, uint32_t R, float alpha, uint64_t seed, void* stream,
-                    ann_graph** out) try {
+                    ann_graph** out) {
+  return ann_hcnng_build_with(points_dev, n, d, dtype, metric, T, Ls, s, l, R, alpha, seed, nullptr, stream, out);
+}
+
+int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, ann_metric metric, uint32_t T,
+                         uint32_t Ls, uint32_t s, uint32_t l, uint32_t R, float alpha, uint64_t seed,
+                         const ann_hcnng_opts* opts, void* stream, ann_graph** out) try {
   if (out) *out = nullptr;
   if (!points_dev || !out) return fail(ANN_EINVAL, "null argument");
   int rc = hc_check(n, d, dtype, metric, Ls, s, l);
@@ -1576,6 +1582,10 @@ int ann_hcnng_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dt
   if (T < 1 || T >= (1u << 20)) return fail(ANN_EINVAL, "the number of trees must be in [1, 2^20)");
   if ((u64)T * 2 * n >= (1ull << 32)) return fail(ANN_EINVAL, "trees times points must stay below 2^31");
   hipStream_t st = static_cast<hipStream_t>(stream);
+  Allocator al;
+  if (opts && !allocator_from(opts->alloc, opts->free, opts->alloc_user, stream, &al))
+    return fail(ANN_EINVAL, "alloc and free must be given together");
+  AllocScope scope(al);
   const bool trace = getenv("ANN_TRACE_BUILD") != nullptr;  // wall-clock breakdown on stderr
   auto t_last = std::chrono::steady_clock::now();
   auto mark = [&](const char* what) {

@@ -21,3 +21,29 @@ def test_trees_equal_the_oracles(env, d, dtype, lo, hi):
         perm, off, _ = A.ann_hcnng_tree_edges(dev(torch, pts_h[:n]), Ls, 3, 3, 5, 1)
         operm, ooff = O.hcnng_tree(O.Dataset(pts_h[:n], 0), Ls, 5, 1)
         assert (off == ooff[:len(off)]).all() and (perm == operm).all()
+
+
+def test_allocator_callbacks(env):
+    """Graph and scratch come from the caller's callbacks and go back to them, on the default stream and on
+    another; an allocator that runs dry gives ANN_ENOMEM and gets everything back."""
+    from test_gpu_boundary import CountingAllocator
+    torch, A, O = env
+    rng = np.random.default_rng(5)
+    pts_h = rng.integers(0, 256, (3000, 64)).astype(np.uint8)
+    pts = dev(torch, pts_h)
+    og = O.hcnng_build(O.Dataset(pts_h, 0), 5, 100, 3, 10, 24, 1.2, seed=3, threads=0)
+    for name in (None, "torch"):
+        assert (A.ann_hcnng_build(pts, 5, 100, 3, 10, 24, 1.2, seed=3, allocator=name).neighbors() == og).all()
+    ca = CountingAllocator(A, torch)
+    other = torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(other):
+        g = A.ann_hcnng_build(pts, 5, 100, 3, 10, 24, 1.2, seed=3, allocator=ca)
+    assert (g.neighbors() == og).all() and ca.allocs > 10 and len(ca.live) == 3
+    del g
+    assert len(ca.live) == 0 and ca.allocs == ca.frees
+    for k in (0, 2, 9):
+        dry = CountingAllocator(A, torch, fail_after=k)
+        with pytest.raises(A.AnnError) as e:
+            A.ann_hcnng_build(pts, 5, 100, 3, 10, 24, 1.2, seed=3, allocator=dry)
+        assert e.value.code == -2 and len(dry.live) == 0 and dry.allocs == dry.frees == k
