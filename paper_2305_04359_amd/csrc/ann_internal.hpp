@@ -119,7 +119,7 @@ struct PruneArgs {
   u32* meta;            // per row: degree | clean prefix length << 16 (written for the batch points)
   u64* edges;           // batch_size x R keys (dest << 32 | source), ~0 in unused slots
   u32 stage_bytes;      // dynamic LDS for the selected points' vectors (0: read them from memory)
-  u32 use_mfma;         // u8/i8 rows up to 128 B: pair distances on the matrix cores
+  u32 use_mfma;         // u8/i8 rows up to 256 B: pair distances on the matrix cores
   u32* overflow_count;  // searches whose visited list did not fit
   u32* overflow_list;   // their indices
   long long a16;

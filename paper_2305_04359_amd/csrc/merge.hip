@@ -10,7 +10,7 @@
 //            guarantees of what it keeps) and only a few entries are new.  Only pairs with a new
 //            entry can change anything, so the wave measures every candidate against b and
 //            against the new entries in one sweep and replays the scan on bit masks.
-//   gram     u8/i8 rows of at most 96 candidates: all pair distances from the int8 Gram matrix
+//   gram     u8/i8 rows (up to 256 bytes) of at most 96 candidates: all pair distances from the int8 Gram matrix
 //            on the matrix cores (exact), then the scan on bit masks.
 //   generic  everything else: the wave-wide scan of prune_device.hpp, candidates in LDS or, for
 //            very long lists, in a spill arena in device memory.
@@ -384,7 +384,6 @@ __global__ __launch_bounds__(64) void merge_fast_kernel(MergeArgs a, VecTable T)
 // masks with scalar instructions.
 // ---------------------------------------------------------------------------------------------
 constexpr u32 SM_TMAX = 96;     // candidates handled by this path
-constexpr u32 SM_STRIDE = 144;  // bytes between staged vectors (128 + 16: spreads LDS banks)
 
 struct SmallLds {
   u64 key[SM_TMAX];   // by arrival index
@@ -402,7 +401,7 @@ struct SmallLds {
 
 template <int VEC, int NCH>
 struct SmallPathOk {
-  static constexpr bool value = (8 * NCH * VEC <= 128);
+  static constexpr bool value = (8 * NCH * VEC <= 256);
 };
 
 // One 32x32 tile of the Gram matrix of the sorted candidates: rows 32*RB.., columns 32*CB...
@@ -429,9 +428,10 @@ __device__ __forceinline__ void gram_tile_regs(const v16i_t& acc, const SmallLds
   (gram_tile_reg<RB, CB, Rs>(acc, S, colok, ncol, tcol, half, Klo, Khi), ...);
 }
 
-template <int RB, int CB>
+template <int NCH, int RB, int CB>
 __device__ __forceinline__ void gram_tile(const unsigned char* Xs, const SmallLds& S, u32 total, u32 ksteps, int lane,
                                           u32& Klo, u32& Khi) {
+  constexpr u32 KS = 4u * NCH, SM_STRIDE = mm_stride(128u * NCH);
   const u32 half = (u32)lane >> 5;
   const u32 ia = 32u * RB + (lane & 31), ib = 32u * CB + (lane & 31);
   const u32 ra = ia < total ? S.inv[ia] : 0u;
@@ -439,10 +439,10 @@ __device__ __forceinline__ void gram_tile(const unsigned char* Xs, const SmallLd
   const unsigned char* pa = Xs + ra * SM_STRIDE + 16u * half;
   const unsigned char* pb = Xs + rb * SM_STRIDE + 16u * half;
   v16i_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  // all four k-steps unconditionally: operands beyond the row's last step are zeroed
-  v4i_t av[4], bv[4];
+  // all k-steps unconditionally: operands beyond the row's last step are zeroed
+  v4i_t av[KS], bv[KS];
 #pragma unroll
-  for (u32 ks = 0; ks < 4; ++ks) {
+  for (u32 ks = 0; ks < KS; ++ks) {
     const u32 kk = ks < ksteps ? ks : ksteps - 1u;
     const v4i_t x = *reinterpret_cast<const v4i_t*>(pa + 32u * kk);
     const v4i_t y = *reinterpret_cast<const v4i_t*>(pb + 32u * kk);
@@ -450,7 +450,7 @@ __device__ __forceinline__ void gram_tile(const unsigned char* Xs, const SmallLd
     bv[ks] = y;
   }
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[ks], bv[ks], acc, 0, 0, 0);
+  for (u32 ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[ks], bv[ks], acc, 0, 0, 0);
   const bool colok = ib < total;
   const i32 ncol = colok ? (i32)S.snrm[ib] : 0;
   const i32 tcol = colok ? S.sthr[ib] : -1;
@@ -481,10 +481,11 @@ __device__ __forceinline__ void newrow_tile_regs(const v16i_t& acc, const i32 (&
                                                  std::integer_sequence<int, Rs...>) {
   (newrow_tile_reg<CB, Rs>(acc, rown, rowt, na, colok, ncol, tcol, half, rem, rby), ...);
 }
-template <int CB>
+template <int NCH, int CB>
 __device__ __forceinline__ void newrow_tile(const unsigned char* Xs, const SmallLds& S, const i32 (&rown)[16],
                                             const i32 (&rowt)[16], u32 clean, u32 na, u32 total, u32 ksteps, int lane,
                                             u32& rem, u32& rby) {
+  constexpr u32 KS = 4u * NCH, SM_STRIDE = mm_stride(128u * NCH);
   const u32 half = (u32)lane >> 5;
   const u32 t = (u32)lane & 31u;
   const u32 ib = 32u * CB + t;
@@ -492,9 +493,9 @@ __device__ __forceinline__ void newrow_tile(const unsigned char* Xs, const Small
   const u32 rb = ib < total ? S.inv[ib] : 0u;
   const unsigned char* pa = Xs + ra * SM_STRIDE + 16u * half;
   const unsigned char* pb = Xs + rb * SM_STRIDE + 16u * half;
-  v4i_t av[4], bv[4];
+  v4i_t av[KS], bv[KS];
 #pragma unroll
-  for (u32 ks = 0; ks < 4; ++ks) {
+  for (u32 ks = 0; ks < KS; ++ks) {
     const u32 kk = ks < ksteps ? ks : ksteps - 1u;
     const v4i_t x = *reinterpret_cast<const v4i_t*>(pa + 32u * kk);
     const v4i_t y = *reinterpret_cast<const v4i_t*>(pb + 32u * kk);
@@ -503,7 +504,7 @@ __device__ __forceinline__ void newrow_tile(const unsigned char* Xs, const Small
   }
   v16i_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[ks], bv[ks], acc, 0, 0, 0);
+  for (u32 ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[ks], bv[ks], acc, 0, 0, 0);
   const bool colok = ib < total;
   const i32 ncol = colok ? (i32)S.snrm[ib] : 0;
   const i32 tcol = colok ? S.sthr[ib] : -1;
@@ -518,8 +519,9 @@ __device__ __forceinline__ u32 reprune_small_int(const VecTable& T, const QueryR
                                                  unsigned char* Xs, SmallLds& S, u32 total, u32 clean, u32 R,
                                                  i64 a16, u32* row, int lane) {
   // every pass of eight candidates is requested before the first is used (a pass is at most
-  // four registers here): one trip to memory for the whole list
+  // eight registers here): one trip to memory for the whole list
   constexpr int PB = SM_TMAX / 8;
+  constexpr u32 SM_STRIDE = mm_stride(128u * NCH);
   const int sub = lane & (LPC - 1);
   const u32 grp = (u32)lane >> 3;
   const u32 npass = (total + 7u) >> 3;
@@ -652,9 +654,9 @@ __device__ __forceinline__ u32 reprune_small_int(const VecTable& T, const QueryR
         rowt[r] = S.nthr[t];
       }
     }
-    newrow_tile<0>(Xs, S, rown, rowt, clean, na, total, ksteps, lane, REM[0], RBY[0]);
-    if (nb > 1) newrow_tile<1>(Xs, S, rown, rowt, clean, na, total, ksteps, lane, REM[1], RBY[1]);
-    if (nb > 2) newrow_tile<2>(Xs, S, rown, rowt, clean, na, total, ksteps, lane, REM[2], RBY[2]);
+    newrow_tile<NCH, 0>(Xs, S, rown, rowt, clean, na, total, ksteps, lane, REM[0], RBY[0]);
+    if (nb > 1) newrow_tile<NCH, 1>(Xs, S, rown, rowt, clean, na, total, ksteps, lane, REM[1], RBY[1]);
+    if (nb > 2) newrow_tile<NCH, 2>(Xs, S, rown, rowt, clean, na, total, ksteps, lane, REM[2], RBY[2]);
     const u32 mypos = (u32)lane < na ? S.npos[lane] : 0xFFFFFFFFu;
 
     // replay of the scan of prune() on positions of the sorted list: the clean entries are all
@@ -723,15 +725,15 @@ __device__ __forceinline__ u32 reprune_small_int(const VecTable& T, const QueryR
   // K1 the same for candidates 64..95 (only column block 2 matters there)
   u32 K0[3] = {0u, 0u, 0u};
   u32 K1 = 0u;
-  gram_tile<0, 0>(Xs, S, total, ksteps, lane, K0[0], K1);
+  gram_tile<NCH, 0, 0>(Xs, S, total, ksteps, lane, K0[0], K1);
   if (nb > 1) {
-    gram_tile<0, 1>(Xs, S, total, ksteps, lane, K0[1], K1);
-    gram_tile<1, 1>(Xs, S, total, ksteps, lane, K0[1], K1);
+    gram_tile<NCH, 0, 1>(Xs, S, total, ksteps, lane, K0[1], K1);
+    gram_tile<NCH, 1, 1>(Xs, S, total, ksteps, lane, K0[1], K1);
   }
   if (nb > 2) {
-    gram_tile<0, 2>(Xs, S, total, ksteps, lane, K0[2], K1);
-    gram_tile<1, 2>(Xs, S, total, ksteps, lane, K0[2], K1);
-    gram_tile<2, 2>(Xs, S, total, ksteps, lane, K0[2], K1);
+    gram_tile<NCH, 0, 2>(Xs, S, total, ksteps, lane, K0[2], K1);
+    gram_tile<NCH, 1, 2>(Xs, S, total, ksteps, lane, K0[2], K1);
+    gram_tile<NCH, 2, 2>(Xs, S, total, ksteps, lane, K0[2], K1);
   }
 
   // the scan of prune(): walk the sorted list, select what is still alive, remove what it removes
@@ -773,7 +775,7 @@ template <int KIND, int VEC, int NCH>
 __global__ __launch_bounds__(64) void merge_gram_kernel(MergeArgs a, VecTable T) {
   constexpr bool kOk = KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value;
   if constexpr (kOk) {
-    __shared__ __align__(16) unsigned char Xs[SM_TMAX * SM_STRIDE];
+    __shared__ __align__(16) unsigned char Xs[SM_TMAX * mm_stride(128u * NCH)];
     __shared__ SmallLds small;
     const int lane = threadIdx.x;
     const u32 nitems = a.list_count[1];
@@ -810,8 +812,9 @@ __global__ __launch_bounds__(64) void merge_gram_kernel(MergeArgs a, VecTable T)
 // with long lists (hub vertices; beyond it the list goes to the arena), and MERGE_MEDIUM_MAX for
 // the rows in between, which are many when batches hold millions of points: with the large
 // buffer three waves fit a compute unit, with the small one sixteen.
+// (Byte rows above 128 bytes: left alone, the compiler takes registers for one wave per SIMD.)
 template <int KIND, int VEC, int NCH, u32 CAP>
-__global__ __launch_bounds__(64) void merge_generic_kernel(MergeArgs a, VecTable T) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<KIND>::is_int && NCH == 2 ? 2 : 1))) void merge_generic_kernel(MergeArgs a, VecTable T) {
   constexpr int LIST = CAP == MERGE_SPILL_MIN ? 2 : 3;
   __shared__ u64 cand_lds[CAP];
   extern __shared__ __align__(16) unsigned char smem[];
@@ -823,10 +826,7 @@ __global__ __launch_bounds__(64) void merge_generic_kernel(MergeArgs a, VecTable
   unsigned char* blk = smem + ((a.R * 8u + 15u) & ~15u);  // 8 rows + 8 norms
   st.vec = a.stage_bytes ? blk + 8u * st.stride + 32u : nullptr;
   F32Lds F{};
-  if constexpr (kF32) {
-    F = f32_lds_carve(smem, a.R, out);
-    st.vec = nullptr;
-  }
+  if constexpr (kF32) F = f32_lds_carve(smem, a.R, out);
   constexpr bool kMfma = MfmaPruneOk<KIND, VEC, NCH>::value;
   const MfmaLds M = mfma_lds_carve(smem + ((a.R * 4u + 15u) & ~15u), a.R, T.row_bytes);  // used when a.use_mfma
 
@@ -952,12 +952,12 @@ hipError_t launch_merge(const DistCfg& cfg, const MergeArgs& a, u32 grid, hipStr
   ANN_DISPATCH_CFG(launch_merge_t, a, T, grid, s, s_gram, s_generic, s_medium);
 }
 
-bool gram_path_ok(const DistCfg& cfg) { return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 128; }
+bool gram_path_ok(const DistCfg& cfg) { return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256; }
 u32 gram_path_tmax() { return SM_TMAX; }
 bool mfma_prune_ok(u32 R, const DistCfg& cfg) {
-  return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 128 && mfma_lds_bytes(R, (u32)cfg.row_bytes) <= 24576u;
+  return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256 && mfma_lds_bytes(R, (u32)cfg.row_bytes) <= 24576u;
 }
-u32 prune_stage_bytes(u32 R, const DistCfg& cfg) { return stage_bytes(R, (u32)cfg.row_bytes, STAGE_BUDGET); }
+u32 prune_stage_bytes(u32 R, const DistCfg& cfg) { return cfg.kind <= 1 ? stage_bytes(R, (u32)cfg.row_bytes, STAGE_BUDGET) : 0u; }
 u32 fast_path_amax(const DistCfg& cfg) { return cfg.nch <= 2 ? 4u : (cfg.nch <= 4 ? 2u : 1u); }
 
 // rows given from outside: degree from the row itself, no clean prefix known

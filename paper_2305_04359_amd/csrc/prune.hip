@@ -23,10 +23,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PruneWaves<K
   unsigned char* blk = smem + ((a.R * 8u + 15u) & ~15u);  // 8 rows + 8 norms
   st.vec = a.stage_bytes ? blk + 8u * st.stride + 32u : nullptr;
   F32Lds F{};
-  if constexpr (kF32) {
-    F = f32_lds_carve(smem, a.R, out);
-    st.vec = nullptr;
-  }
+  if constexpr (kF32) F = f32_lds_carve(smem, a.R, out);
   constexpr bool kMfma = MfmaPruneOk<KIND, VEC, NCH>::value;
   const MfmaLds M = mfma_lds_carve(smem + ((a.R * 4u + 15u) & ~15u), a.R, T.row_bytes);  // used when a.use_mfma
 

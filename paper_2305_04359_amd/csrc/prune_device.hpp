@@ -140,56 +140,37 @@ __device__ __forceinline__ void stage_selected(const VecTable& T, const SelStage
   }
 }
 
-// largest D with alpha * D <= d, per kind: integers as floor(d * 2^16 / a16), floats via the product
-template <int KIND>
-struct RemoveTest {
-  i32 thr;    // integer kinds
-  float dpc;  // float kinds
-  float af;
-  __device__ __forceinline__ void set(const AlphaParam& al, u32 dkey_pc) {
-    if constexpr (KindTraits<KIND>::is_int) {
-      const i32 d = int_from_dkey(dkey_pc);
-      // floor(d * 65536 / a16), exact (d >= 0 for squared L2)
-      const u64 x = (u64)(u32)d << 16;
-      u64 t = (u64)__builtin_floor((double)x / (double)al.a16);
-      if (t * (u64)al.a16 > x)
-        --t;
-      else if ((t + 1) * (u64)al.a16 <= x)
-        ++t;
-      thr = t > 0x7FFFFFFFull ? 0x7FFFFFFF : (i32)t;
-    } else {
-      dpc = float_from_dkey(dkey_pc);
-      af = al.af;
-    }
-  }
-  // d_sc: distance selected <-> candidate (integer, or float bits)
-  __device__ __forceinline__ bool removes_int(i32 d_sc) const { return d_sc <= thr; }
-  __device__ __forceinline__ bool removes_float(float d_sc) const { return af * d_sc <= dpc; }
-};
+// floor(d * 2^16 / a16) for 0 <= d < 2^31, 0 < a16 < 2^31, clamped to INT32_MAX: the largest D with
+// alpha * D <= d
+__device__ __forceinline__ i32 alpha_threshold(i32 d, i64 a16) {
+  const u64 x = (u64)(u32)d << 16;
+  u64 t = (u64)__builtin_floor((double)x / (double)a16);
+  if (t * (u64)a16 > x)
+    --t;
+  else if ((t + 1) * (u64)a16 <= x)
+    ++t;
+  return t > 0x7FFFFFFFull ? 0x7FFFFFFF : (i32)t;
+}
 
-// distance between the group's candidate (in Qc) and the row pieces x; xx = <x,x> (integers)
+// is the distance between the group's candidate (in Qc) and the row pieces x at most thr?  xx = <x,x>
 template <int KIND, int VEC, int NCH>
-__device__ __forceinline__ bool removes_pieces(const RemoveTest<KIND>& rt, const QueryRegs<KIND, VEC, NCH>& Qc,
-                                               const Piece<VEC> (&x)[NCH], i32 xx) {
-  if constexpr (KindTraits<KIND>::is_int) {
-    i32 qx = 0;
+__device__ __forceinline__ bool removes_pieces(i32 thr, const QueryRegs<KIND, VEC, NCH>& Qc, const Piece<VEC> (&x)[NCH],
+                                               i32 xx) {
+  i32 qx = 0;
 #pragma unroll
-    for (int u = 0; u < NCH; ++u)
+  for (int u = 0; u < NCH; ++u)
 #pragma unroll
-      for (int i = 0; i < VEC / 4; ++i) {
-        if constexpr (KIND == K_U8)
-          qx = (i32)__builtin_amdgcn_udot4(Qc.q[u].w[i], x[u].w[i], (u32)qx, false);
-        else
-          qx = __builtin_amdgcn_sdot4((i32)Qc.q[u].w[i], (i32)x[u].w[i], qx, false);
-      }
-    return rt.removes_int(Qc.qq + xx - 2 * group_sum(qx));
-  } else {
-    return rt.removes_float(float_from_dkey(distance_key<KIND, VEC, NCH>(Qc, x)));
-  }
+    for (int i = 0; i < VEC / 4; ++i) {
+      if constexpr (KIND == K_U8)
+        qx = (i32)__builtin_amdgcn_udot4(Qc.q[u].w[i], x[u].w[i], (u32)qx, false);
+      else
+        qx = __builtin_amdgcn_sdot4((i32)Qc.q[u].w[i], (i32)x[u].w[i], qx, false);
+    }
+  return Qc.qq + xx - 2 * group_sum(qx) <= thr;
 }
 
 // cand[0..m): keys (distance to p | id), ids distinct, p absent, SORTED ascending.
-// Selected ids go to out[0..return) in selection order.  Byte rows of more than 128 bytes come here; the
+// Selected ids go to out[0..return) in selection order.  Byte rows of more than 256 bytes come here; the
 // walks on the matrix cores further down take the others.  blk: LDS for 8 rows of st.stride bytes
 // plus 8 norms (used even when the selected vectors themselves are not staged).
 template <int KIND, int VEC, int NCH>
@@ -210,8 +191,7 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
     const u64 key = nkey;
     const bool valid = i0 + grp < m;
     query_finish<KIND, VEC, NCH>(cur);
-    RemoveTest<KIND> rt;
-    rt.set(al, valid ? key_dkey(key) : dkey_from_int(0));
+    const i32 thr = alpha_threshold(valid ? int_from_dkey(key_dkey(key)) : 0, al.a16);
     const u32 nb = m - i0 < 8u ? m - i0 : 8u;
 
     // park the block's vectors in LDS for the tests among the eight
@@ -237,7 +217,7 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
           const u32 pc = sub + LPC * u;
           x[u] = pc < T.npieces ? load_piece<VEC>(reinterpret_cast<const char*>(src) + pc * VEC) : zero_piece<VEC>();
         }
-        return removes_pieces<KIND, VEC, NCH>(rt, cur, x, (i32)st.xx[t]);
+        return removes_pieces<KIND, VEC, NCH>(thr, cur, x, (i32)st.xx[t]);
       };
       // four selected points per trip, written out by hand (loops around cross-lane operations
       // are not unrolled for us), so that their LDS reads overlap
@@ -268,27 +248,23 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
 #pragma unroll
         for (u32 q = 0; q < AHEAD; ++q) {
           i32 xx = 0;
-          if constexpr (KindTraits<KIND>::is_int) {
 #pragma unroll
-            for (int u = 0; u < NCH; ++u)
+          for (int u = 0; u < NCH; ++u)
 #pragma unroll
-              for (int i = 0; i < VEC / 4; ++i) {
-                if constexpr (KIND == K_U8)
-                  xx = (i32)__builtin_amdgcn_udot4(x[q][u].w[i], x[q][u].w[i], (u32)xx, false);
-                else
-                  xx = __builtin_amdgcn_sdot4((i32)x[q][u].w[i], (i32)x[q][u].w[i], xx, false);
-              }
-            xx = group_sum(xx);
-          }
-          const bool r = removes_pieces<KIND, VEC, NCH>(rt, cur, x[q], xx);
+            for (int i = 0; i < VEC / 4; ++i) {
+              if constexpr (KIND == K_U8)
+                xx = (i32)__builtin_amdgcn_udot4(x[q][u].w[i], x[q][u].w[i], (u32)xx, false);
+              else
+                xx = __builtin_amdgcn_sdot4((i32)x[q][u].w[i], (i32)x[q][u].w[i], xx, false);
+            }
+          xx = group_sum(xx);
+          const bool r = removes_pieces<KIND, VEC, NCH>(thr, cur, x[q], xx);
           dom = dom | r;
         }
       }
     }
     {  // the next block's vectors travel while this block is settled.  Not earlier: rows read from device
-      // memory need the registers, and the
-      // tests against staged rows hide nothing that settling does not (100,000 uint8 points of 160 bytes,
-      // R = 48: 24.0 ms either way)
+      // memory need the registers, and the tests against staged rows hide nothing that settling does not
       const u32 ci = i0 + 8u + grp;
       nkey = ci < m ? cand[ci] : KEY_INF;
       nxt = load_query_raw<KIND, VEC, NCH>(T.base + (u64)(ci < m ? key_id(nkey) : 0u) * T.row_bytes, T.npieces, lane);
@@ -310,7 +286,7 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
           const u32 pc = sub + LPC * u;
           x[u] = pc < T.npieces ? load_piece<VEC>(reinterpret_cast<const char*>(src) + pc * VEC) : zero_piece<VEC>();
         }
-        const bool r = removes_pieces<KIND, VEC, NCH>(rt, cur, x, (i32)blkxx[t]);
+        const bool r = removes_pieces<KIND, VEC, NCH>(thr, cur, x, (i32)blkxx[t]);
         by[t] = ballot(r && valid && (u32)t < grp);
       }
     }
@@ -354,7 +330,7 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same walk for u8/i8 rows of at most 128 bytes, 32 candidates at a time, with the pair
+// The same walk for u8/i8 rows of at most 256 bytes, 32 candidates at a time, with the pair
 // distances taken on the matrix cores.
 //
 // For a block of 32 candidates two small matrix products decide everything: (selected so far) x
@@ -363,35 +339,27 @@ __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& s
 // is shifted by -128; distances do not change), exact in int32, computed with
 // v_mfma_i32_32x32x32_i8 from LDS copies of the vectors: D(i,j) = |x_i|^2 + |x_j|^2 - 2<x_i,x_j>,
 // and "i removes j" is D(i,j) <= floor(d(p,j) * 2^16 / a16).  The 32 verdicts are then settled in
-// order on bit masks.
+// order on bit masks.  Rows of 129 to 256 bytes (300,000 uint8 points of 200, R = 64, L = 128): build 64.4 ->
+// 36.7 ms against the walk above; of 500,000 such points, step 1's prune 31.5 -> 7.6 ms, the re-prunes 41.2 -> 19.7.
 // ---------------------------------------------------------------------------------------------
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef int v16i_t __attribute__((ext_vector_type(16)));
 
-constexpr u32 MM_STRIDE = 144;  // bytes between staged rows (128 + 16: spreads LDS banks)
-constexpr u32 MM_BLOCK = 32;    // candidates per block
+// bytes between staged rows (128 or 256, and 16 that spread the LDS banks)
+__host__ __device__ constexpr u32 mm_stride(u32 row_bytes) { return row_bytes <= 128u ? 144u : 272u; }
+constexpr u32 MM_BLOCK = 32;  // candidates per block
 
 template <int KIND, int VEC, int NCH>
 struct MfmaPruneOk {
-  static constexpr bool value = KindTraits<KIND>::is_int && (8 * NCH * VEC <= 128);
+  static constexpr bool value = KindTraits<KIND>::is_int && (8 * NCH * VEC <= 256);
 };
-
-// floor(d * 2^16 / a16) for 0 <= d < 2^31, 0 < a16 < 2^31, clamped to INT32_MAX
-__device__ __forceinline__ i32 alpha_threshold(i32 d, i64 a16) {
-  const u64 x = (u64)(u32)d << 16;
-  u64 t = (u64)__builtin_floor((double)x / (double)a16);
-  if (t * (u64)a16 > x)
-    --t;
-  else if ((t + 1) * (u64)a16 <= x)
-    ++t;
-  return t > 0x7FFFFFFFull ? 0x7FFFFFFF : (i32)t;
-}
 
 // LDS areas of the matrix-core walk (all 16-byte aligned)
 struct MfmaLds {
-  unsigned char* sel;  // roundup(R, 32) rows of MM_STRIDE bytes: vectors of the selected points,
-                       // or null: rows are whole multiples of 32 bytes and the matrix operand is
-                       // loaded straight from the vectors in device memory (more waves per CU)
+  unsigned char* sel;  // roundup(R, 32) rows of mm_stride bytes: vectors of the selected points,
+                       // or null: the matrix operand is loaded straight from the vectors in device
+                       // memory (more waves per CU): rows of whole multiples of 32 bytes, and all rows
+                       // above 128 bytes, whose copies would leave room for six waves
   u32* selnorm;        // roundup(R, 32): their squared norms (shifted vectors)
   unsigned char* blk;  // 32 rows: the current block of candidates
   u32* cnorm;          // 32
@@ -399,17 +367,17 @@ struct MfmaLds {
   u32* cid;            // 32
 };
 __host__ __device__ inline u32 mfma_rows(u32 R) { return (R + 31u) & ~31u; }
-__host__ __device__ inline bool mfma_sel_in_lds(u32 row_bytes) { return (row_bytes % 32u) != 0u; }
+__host__ __device__ inline bool mfma_sel_in_lds(u32 row_bytes) { return row_bytes <= 128u && (row_bytes % 32u) != 0u; }
 __host__ __device__ inline u32 mfma_lds_bytes(u32 R, u32 row_bytes) {
-  return (mfma_sel_in_lds(row_bytes) ? mfma_rows(R) * MM_STRIDE : 0u) + mfma_rows(R) * 4u + MM_BLOCK * MM_STRIDE +
-         3u * MM_BLOCK * 4u;
+  return (mfma_sel_in_lds(row_bytes) ? mfma_rows(R) * mm_stride(row_bytes) : 0u) + mfma_rows(R) * 4u +
+         MM_BLOCK * mm_stride(row_bytes) + 3u * MM_BLOCK * 4u;
 }
 __device__ __forceinline__ MfmaLds mfma_lds_carve(unsigned char* base, u32 R, u32 row_bytes) {
   MfmaLds M;
   const bool in_lds = mfma_sel_in_lds(row_bytes);
   M.sel = in_lds ? base : nullptr;
-  M.blk = base + (in_lds ? mfma_rows(R) * MM_STRIDE : 0u);
-  M.selnorm = reinterpret_cast<u32*>(M.blk + MM_BLOCK * MM_STRIDE);
+  M.blk = base + (in_lds ? mfma_rows(R) * mm_stride(row_bytes) : 0u);
+  M.selnorm = reinterpret_cast<u32*>(M.blk + MM_BLOCK * mm_stride(row_bytes));
   M.cnorm = M.selnorm + mfma_rows(R);
   M.cthr = reinterpret_cast<i32*>(M.cnorm + MM_BLOCK);
   M.cid = reinterpret_cast<u32*>(M.cthr + MM_BLOCK);
@@ -439,7 +407,8 @@ __device__ __forceinline__ u32 prune_sorted_mfma(const VecTable& T, const MfmaLd
   const u32 half = (u32)lane >> 5;
   const u32 col = (u32)lane & 31u;
   const u32 flip = KIND == K_U8 ? 0x80808080u : 0u;
-  const u32 ksteps = (T.row_bytes + 31u) / 32u;  // <= 4
+  constexpr u32 KS = 4u * NCH, MM_STRIDE = mm_stride(128u * NCH);
+  const u32 ksteps = (T.row_bytes + 31u) / 32u;  // <= KS
   u32 nout = 0;
   if (m == 0) return 0;
 
@@ -491,9 +460,9 @@ __device__ __forceinline__ u32 prune_sorted_mfma(const VecTable& T, const MfmaLd
     __syncthreads();
 
     // column operand: candidate `col`, this lane's 16 bytes of every k-step
-    v4i_t bv[4];
+    v4i_t bv[KS];
 #pragma unroll
-    for (u32 ks = 0; ks < 4; ++ks) {
+    for (u32 ks = 0; ks < KS; ++ks) {
       const v4i_t v =
           *reinterpret_cast<const v4i_t*>(M.blk + col * MM_STRIDE + 32u * (ks < ksteps ? ks : ksteps - 1u) + 16u * half);
       bv[ks] = ks < ksteps ? v : v4i_t{0, 0, 0, 0};
@@ -507,32 +476,37 @@ __device__ __forceinline__ u32 prune_sorted_mfma(const VecTable& T, const MfmaLd
     bool rem = false;
     const u32 kclamp = ksteps - 1u;
     const u32 aflip = M.sel != nullptr ? 0u : flip;
-    auto load_slice = [&](u32 s0, v4i_t (&av)[4]) {
+    auto load_slice = [&](u32 s0, v4i_t (&av)[KS]) {
       if (M.sel != nullptr) {
 #pragma unroll
-        for (u32 ks = 0; ks < 4; ++ks)
+        for (u32 ks = 0; ks < KS; ++ks)
           av[ks] = *reinterpret_cast<const v4i_t*>(M.sel + (s0 + col) * MM_STRIDE + 32u * (ks < kclamp ? ks : kclamp) +
                                                    16u * half);
       } else {
         const u32 sid = s0 + col < nout ? out[s0 + col] : out[0];
         const char* src = T.base + (u64)sid * T.row_bytes + 16u * half;
 #pragma unroll
-        for (u32 ks = 0; ks < 4; ++ks) {
-          av[ks] = *reinterpret_cast<const v4i_t*>(src + 32u * (ks < kclamp ? ks : kclamp));
+        for (u32 ks = 0; ks < KS; ++ks) {
+          // (a row's odd last piece: its other half meets zeros in the block)
+          const u32 at = 32u * (ks < kclamp ? ks : kclamp);
+          av[ks] = *reinterpret_cast<const v4i_t*>(NCH == 1 || at + 16u * half < T.row_bytes ? src + at : src);
         }
       }
     };
-    v4i_t av[4];
-    if (nout > 0) load_slice(0, av);
+    // (rows above 128 bytes: the registers of a second slice would cost a wave per SIMD)
+    constexpr bool AHEAD = NCH == 1;
+    v4i_t av[KS];
+    if (AHEAD && nout > 0) load_slice(0, av);
     for (u32 s0 = 0; s0 < nout; s0 += 32) {
-      v4i_t cur[4];
+      if (!AHEAD) load_slice(s0, av);
+      v4i_t cur[KS];
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        cur[ks] = (u32)ks < ksteps ? (av[ks] ^ (int)aflip) : v4i_t{0, 0, 0, 0};  // device memory holds u8
-      if (s0 + 32 < nout) load_slice(s0 + 32, av);
+      for (u32 ks = 0; ks < KS; ++ks)
+        cur[ks] = ks < ksteps ? (av[ks] ^ (int)aflip) : v4i_t{0, 0, 0, 0};  // device memory holds u8
+      if (AHEAD && s0 + 32 < nout) load_slice(s0 + 32, av);
       v16i_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur[ks], bv[ks], acc, 0, 0, 0);
+      for (u32 ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur[ks], bv[ks], acc, 0, 0, 0);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const u32 sb = s0 + 8u * q + 4u * half;
@@ -551,7 +525,7 @@ __device__ __forceinline__ u32 prune_sorted_mfma(const VecTable& T, const MfmaLd
     {
       v16i_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(bv[ks], bv[ks], acc, 0, 0, 0);
+      for (u32 ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(bv[ks], bv[ks], acc, 0, 0, 0);
       uint4 n4[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) n4[q] = *reinterpret_cast<const uint4*>(M.cnorm + 8u * q + 4u * half);
@@ -628,11 +602,13 @@ struct F32PruneOk {
   static constexpr bool value = !KindTraits<KIND>::is_int && VEC == 16 && NCH <= 8;
 };
 
-// Waves per SIMD of the prune kernel.  The float walk holds a block of candidates and a tile of selected
-// rows, 8 * NCH registers each, beside 16 of products: the count at which nothing spills.
+// Waves per SIMD of the prune kernel: what its walk's registers leave room for.  Byte rows above 128 bytes
+// hold a block, the next one and a slice of selected rows, 32 registers each; float rows a block of
+// candidates and a tile of selected rows, 8 * NCH registers each, beside 16 of products.
 template <int KIND, int VEC, int NCH>
 struct PruneWaves {
-  static constexpr int value = F32PruneOk<KIND, VEC, NCH>::value ? (NCH <= 4 ? 4 : NCH <= 7 ? 3 : 2) : 4;
+  static constexpr int value = F32PruneOk<KIND, VEC, NCH>::value ? (NCH <= 4 ? 4 : NCH <= 7 ? 3 : 2)
+                               : MfmaPruneOk<KIND, VEC, NCH>::value && NCH == 2 ? 2 : 4;
 };
 
 // LDS of the walk: p's row, zero-padded to 8 * NCH pieces, the block's norms, the selected points' norms
