@@ -194,7 +194,8 @@ hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u6
 hipError_t start_vertex_device(const void* points, u64 n, u32 d, int dtype, hipStream_t s, u32* start_out);
 
 u32 search_lds_bytes(u32 L, u32 hash_buckets);
-u32 search_hash_buckets(u32 L, u32 hash_bits);  // hash_bits: the caller's explicit choice, or 0
+// hash_bits: the caller's explicit choice, or 0; own: searches with start vertices of their own
+u32 search_hash_buckets(const DistCfg& cfg, u64 n, u32 L, u32 hash_bits, bool own);
 // how the visited filter stores vertices of a graph of n points: fills id_bits and tag_width
 void search_filter_mode(u64 n, u32 hash_buckets, u32* id_bits, u32* tag_width);
 

@@ -326,7 +326,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   }
   sa.L = L;
   sa.k = 1;
-  sa.hash_buckets = search_hash_buckets(L, g->hash_bits);
+  sa.hash_buckets = search_hash_buckets(g->cfg, g->n, L, g->hash_bits, starts != nullptr);
   search_filter_mode(g->n, sa.hash_buckets, &sa.id_bits, &sa.tag_width);
   sa.n = g->n;
   sa.filter_given = g->hash_bits;
@@ -607,7 +607,7 @@ int query_launch(const ann_graph* g, const void* pts, const void* queries, const
   }
   sa.L = L;
   sa.k = k;
-  sa.hash_buckets = search_hash_buckets(L, g->hash_bits);
+  sa.hash_buckets = search_hash_buckets(g->cfg, g->n, L, g->hash_bits, starts != nullptr);
   search_filter_mode(g->n, sa.hash_buckets, &sa.id_bits, &sa.tag_width);
   sa.n = g->n;
   sa.filter_given = g->hash_bits;

@@ -10,16 +10,41 @@ namespace annmi {
 u32 search_lds_bytes(u32 L, u32 hash_buckets) { return search_nslot_for(L) * 64 * 8 + 64 * 8 + hash_buckets * 16; }
 
 // Size of the visited filter.  An explicit hash_bits (log2 of the size in 32-bit words) is taken
-// as it is.  Otherwise: 8 words per beam entry, rounded up to a power of two, but never more than
-// 1,024 words (512 for beams above 512 entries), then adjusted so that the wave's LDS lands
-// exactly on the next occupancy step (waves per CU a multiple of four, at most 32, LDS handed
-// out in 512-byte units of 160 KB).  Occupancy is worth more than the evaluations a larger table
-// saves: measured on 128-d uint8 data at beam 128 (a million points), and at beams of 200 to
-// 2,048 on a hundred million points, where tables of 1,024 and 512 words answer 1.7 to 2.3 times
-// the queries per second of tables of 4,096 and 8,192.  The table is never cut below 3/4 of the
-// power of two.
-u32 search_hash_buckets(u32 L, u32 hash_bits) {
+// as it is.  Otherwise, for beams of up to 256: all of the LDS that the waves a SIMD can hold by
+// their registers leave to each, up to 2,048 words: one wave less costs more than a larger table
+// saves, and LDS below that step is free.  A compute unit hands out its 160 KB in units of 1,280 bytes.
+// 10,000 queries, a million 128-d uint8 points (eight waves), R = 64, L = 50: 512 words 364 us, 1,024 (that
+// step) 340, 2,048 405; L = 128: 512 words 734, 896 (that step) 656, 1,216 672, 2,048 822.  Five million
+// points, L = 50: 672 -> 586.  A million points of 200 floats (four waves; 1,024 words less a cut -> 2,048): 1,705 ->
+// 1,596 distances per search, build 262 -> 250 ms, 10,000 queries at L = 50 2,055 -> 1,935 us, at L = 200
+// 4,025 -> 3,554; 4,096 words, a wave less: 266 ms, 2,004 and 4,129.
+//
+// More than 2^22 points: a table of 224 buckets (beams of 65 to 128) would need 21-bit tags, one of 304,
+// at six waves, still takes 16-bit tags up to 2^23 points: 20,000 queries on five million, L = 100, 1,776 -> 1,558
+// us (two million, where 16 bits suffice either way, 1,226 -> 1,237); beyond, the repeats saved are worth
+// the waves (10^8 points: search phase of a build 15.1 -> 14.7 s).
+//
+// Wider beams: 8 words per beam entry, rounded up to a power of two, but at most 1,024 words (512
+// above 512 entries), then adjusted to an occupancy step: measured at beams of 200 to 2,048 on a
+// hundred million points, where tables of 1,024 and 512 words answer 1.7 to 2.3 times the queries
+// per second of tables of 4,096 and 8,192.  The table is never cut below 3/4 of the power of two.
+constexpr u32 LDS_UNIT = 1280;
+static u32 register_waves(u32 nch, u32 nslot, bool own) {  // waves per SIMD, by the registers of the variants
+  if (nslot <= 2u)
+    return nch <= 1u ? 8u : nch <= 2u ? 7u : nch <= 4u ? (own ? 6u : 5u) : nch <= 6u || (nch == 7u && (own || nslot == 1u)) ? 5u : 4u;
+  return nch <= 2u ? 5u : nch <= 4u ? (own ? 5u : 4u) : 4u;
+}
+u32 search_hash_buckets(const DistCfg& cfg, u64 n, u32 L, u32 hash_bits, bool own) {
   if (hash_bits) return 1u << (hash_bits - 2u);
+  const u32 nslot = search_nslot_for(L);
+  if (L < 8u) return 128;  // (over after a few hops: not worth clearing more)
+  if (nslot <= 4u) {
+    u32 waves = register_waves((u32)cfg.nch, nslot, own);
+    if (nslot == 2u && n > (1ull << 22) && waves > 6u) waves = 6u;
+    const u32 share = 163840u / (4u * waves) / LDS_UNIT * LDS_UNIT;
+    const u32 nb = (share - search_lds_bytes(L, 0)) / 16u;
+    return nb < 512u ? nb : 512u;
+  }
   u32 want = 8u * L, bits = 9;
   while ((1u << bits) < want && bits < (L > 512u ? 9u : 10u)) ++bits;
   const u32 full = 1u << (bits - 2u);

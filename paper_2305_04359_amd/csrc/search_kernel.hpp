@@ -323,7 +323,6 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
   const int lane = threadIdx.x;
   const u32 qi = blockIdx.x;
   const u32 nb = a.hash_buckets;
-  const u32 hsize = 4u * nb;  // table size in 32-bit words
   uint4* bucket = reinterpret_cast<uint4*>(hash);
   constexpr bool compact = TAG16;                     // eight 16-bit tags per bucket
   const bool tags21 = !TAG16 && a.tag_width == 21u;  // six 21-bit tags per bucket
@@ -343,7 +342,11 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
   const QueryRegs<KIND, VEC, NCH> Q =
       load_query<KIND, VEC, NCH>(a.queries + (u64)qrow * a.qrow_bytes, T.npieces, lane);
 
-  for (u32 i = lane; i < hsize; i += 64) hash[i] = NONE_ID;
+  if constexpr (NCH == 1) {
+    for (u32 i = lane; i < 4u * nb; i += 64) hash[i] = NONE_ID;
+  } else {  // (larger tables; the small one gains nothing)
+    for (u32 i = lane; i < nb; i += 64) bucket[i] = make_uint4(NONE_ID, NONE_ID, NONE_ID, NONE_ID);
+  }
   if (a.batch_counters != nullptr && qi == 0 && lane == 0) zero_batch_counters(a.batch_counters);
 
   u64 A[NSLOT];

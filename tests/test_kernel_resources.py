@@ -56,3 +56,18 @@ def test_own_start_searches_keep_eight_waves(kernels):
     start vertices of their own: one-slot beams leave room for eight waves per SIMD."""
     found = {a: f for a, f in _named(kernels, "search_kernel").items() if a[:4] in ((2, 16, 2, 1), (3, 16, 2, 1)) and a[6]}
     assert found and all(f["vgpr_count"] <= 64 for f in found.values())
+
+
+def test_filter_sizes_match_the_registers(kernels):
+    """The visited filter takes the LDS that the waves of search_kernel<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK>
+    leave to each other: the waves per SIMD that search.hip assumes are those of the registers, give or take one
+    where variants differ."""
+    def assumed(nch, nslot, own):
+        if nslot <= 2:
+            return 8 if nch == 1 else 7 if nch == 2 else (6 if own else 5) if nch == 4 else 5 if nch == 6 or (nch == 7 and (own or nslot == 1)) else 4
+        return 5 if nch <= 2 else (5 if own else 4) if nch == 4 else 4
+
+    for a, f in _named(kernels, "search_kernel").items():
+        if a[3] <= 4 and a[5]:
+            waves = min(8, 512 // (-(-f["vgpr_count"] // 8) * 8))
+            assert abs(waves - assumed(a[2], a[3], a[6])) <= (2 if a[3] == 4 and a[4] else 1), (a, f)
