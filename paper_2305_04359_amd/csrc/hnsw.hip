@@ -167,6 +167,7 @@ int make_walk(ann_hnsw* h, hipStream_t st) {
     y.R = h->m;
     walk.push_back(y);
   }
+  if (h->walk.p != nullptr) HIP_TRY(hipDeviceSynchronize());  // a search, on whatever stream, may still read the old table
   HIP_TRY(h->walk.alloc(walk.size() * sizeof(DescendLayer)));
   HIP_TRY(hipMemcpy(h->walk.p, walk.data(), walk.size() * sizeof(DescendLayer), hipMemcpyHostToDevice));
   return ANN_OK;
