@@ -444,7 +444,8 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
       need = nv[slots[i]] > need ? nv[slots[i]] : need;
       ids2[i] = ids_host[slots[i]];
     }
-    DevBuf ids2_d, slots_d, vis2, nvis2;
+    DevBuf ids2_d, slots_d, vis2, nvis2, pos2;
+    FailureWait wait;
     HIP_TRY(ids2_d.alloc((size_t)novf * 4));
     HIP_TRY(slots_d.alloc((size_t)novf * 4));
     HIP_TRY(vis2.alloc((size_t)novf * need * 8));
@@ -462,7 +463,6 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     sb.batch_counters = nullptr;
     sb.vis_where = nullptr;
     sb.counters = nullptr;
-    DevBuf pos2;
     if (starts) {
       // redone search i stands at the position of batch slot slots[i]
       std::vector<u32> p2(novf);
@@ -486,6 +486,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     u32 again = 0;
     HIP_TRY(hipMemcpyAsync(&again, small + 0, 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    wait.done = true;
     if (again != 0) return fail(ANN_EINTERNAL, "visited list overflowed again on retry");
     g->stats.redone += novf;
     HIP_TRY(hipMemsetAsync(small + 3, 0, 4, st));  // every lost list has been made up for
@@ -577,6 +578,7 @@ int graph_scratch(ann_graph* g, u64 b, u32 L, hipStream_t st, BatchScratch** out
     if (!g->scratch) return fail(ANN_ENOMEM, "host allocation failed");
     int rc = g->scratch->alloc(b, g->R, cap, g->spill_keys ? g->spill_keys : default_spill_keys(b));
     if (rc) {
+      (void)hipDeviceSynchronize();  // (part of it has been cleared on the stream)
       delete g->scratch;
       g->scratch = nullptr;
       return rc;
@@ -662,6 +664,7 @@ int new_graph(u64 n, u32 d, int dtype, int metric, u32 R, ann_graph** out) {
   if (e == hipSuccess) e = g->al.get(reinterpret_cast<void**>(&g->counters), COUNTER_COPIES * sizeof(DevCounters));
   if (e == hipSuccess) e = g->al.zero(g->counters, COUNTER_COPIES * sizeof(DevCounters));
   if (e != hipSuccess) {
+    (void)hipDeviceSynchronize();  // (the clearing may be queued)
     ann_graph_free(g);
     return fail(e == hipErrorOutOfMemory ? ANN_ENOMEM : ANN_EHIP, "graph allocation: %s", hipGetErrorString(e));
   }
@@ -683,6 +686,7 @@ int reserve_rows(ann_graph* g, u64 want, hipStream_t st) {
   if (e == hipSuccess) e = hipMemcpyAsync(meta, g->meta, (size_t)g->n * sizeof(u32), hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
+    (void)hipDeviceSynchronize();
     g->al.put(rows);
     g->al.put(meta);
     return fail(e == hipErrorOutOfMemory ? ANN_ENOMEM : ANN_EHIP, "graph growth: %s", hipGetErrorString(e));
@@ -918,6 +922,7 @@ int ann_insert_batch(ann_graph* g, const void* points_dev, const uint32_t* ids_h
   Allocator al = g->al;
   al.stream = stream;
   AllocScope scope(al);
+  FailureWait wait;  // (the graph keeps its scratch; a later call may enlarge it)
   BatchScratch* Sp = nullptr;
   rc = graph_scratch(g, b, L, st, &Sp);
   if (rc) return rc;
@@ -945,6 +950,7 @@ int ann_insert_batch(ann_graph* g, const void* points_dev, const uint32_t* ids_h
   rc = batch_insert(g, pts, ids_host, S.qidx.as<u32>(), b, L, alpha, S, tm, st, /*sync=*/true);
   if (rc) return rc;
   rc = finish_batches(g, S, tm, st);
+  wait.done = rc == ANN_OK;
   return rc == ANN_LOST_LIST ? fail(ANN_EINTERNAL, "a visited list was lost in a synchronised batch") : rc;
 } catch (...) {
   return annmi::on_exception();
@@ -1010,6 +1016,7 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   }
 
   const double t_order = now_ms();
+  FailureWait wait;  // (the graph keeps its scratch; a later call may enlarge it)
   rc = grow_graph(g, n_total, st);
   if (rc) return rc;
   const double t_grow = now_ms();
@@ -1034,6 +1041,7 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
     if (rc) return rc;
   }
   rc = finish_batches(g, S, tm, st);
+  wait.done = rc == ANN_OK;
   if (trace)
     fprintf(stderr, "ann_insert_points: order %.2f ms, growth %.2f ms, scratch %.2f ms, %zu batches %.2f ms\n",
             t_order - t_begin, t_grow - t_order, t_alloc - t_grow, bounds.size() - 1, now_ms() - t_alloc);
@@ -1109,6 +1117,9 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
       if (g) ann_graph_free(g);
     }
   } guard{g};
+  DevBuf order_dev;
+  BatchScratch S;
+  FailureWait wait;
   rc = check_insert_params(g, L, alpha);
   if (rc) return rc;
   g->collect = o.collect_stats != 0;
@@ -1134,9 +1145,7 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
   u64 bmax = 1;
   for (size_t r = 0; r + 1 < bounds.size(); ++r) bmax = bounds[r + 1] - bounds[r] > bmax ? bounds[r + 1] - bounds[r] : bmax;
 
-  DevBuf order_dev;
   HIP_TRY(order_dev.alloc(m * 4));
-  BatchScratch S;
   const u32 cap = g->visited_cap ? g->visited_cap : (4 * L > 256 ? 4 * L : 256);
   rc = S.alloc(bmax, R, cap, g->spill_keys ? g->spill_keys : default_spill_keys(bmax));
   if (rc) return rc;
@@ -1226,6 +1235,7 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
   if (trace)
     fprintf(stderr, "ann_build: graph alloc + start vertex %.2f ms, order %.2f ms, scratch %.2f ms, batches %.2f ms\n",
             t_start - t_begin, t_order - t_start, t_alloc - t_order, now_ms() - t_alloc);
+  wait.done = true;
   guard.g = nullptr;
   *out = g;
   return ANN_OK;

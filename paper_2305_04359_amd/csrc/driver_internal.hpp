@@ -105,6 +105,19 @@ struct DevBuf {
   }
 };
 
+// Stands behind the buffers of a call that queues work on them (so that it goes first): where the call ends early,
+// all that it queued, on side streams too, is waited for before the buffers go back.  hipFree waits
+// by itself; the caller's `free` is promised that nothing is left to run on what it gets.
+struct FailureWait {
+  bool done = false;  // set where the call has waited, or keeps its buffers
+  FailureWait() = default;
+  FailureWait(const FailureWait&) = delete;
+  FailureWait& operator=(const FailureWait&) = delete;
+  ~FailureWait() {
+    if (!done) (void)hipDeviceSynchronize();
+  }
+};
+
 // Page-locked host memory: small copies to and from it are queued without a staging copy, and the
 // device reads it when the copy runs, so its contents must stay until then.
 struct HostBuf {

@@ -1604,6 +1604,9 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
       if (g) ann_graph_free(g);
     }
   } guard{g};
+  HcCtx X;
+  DevBuf arcs, arcs_tmp, big_hist, uq_counts, lists, small, arena;
+  FailureWait wait;
   rc = check_insert_params(g, 1, alpha);
   if (rc) return rc;
   HIP_TRY(hipMemsetAsync(g->rows, 0xFF, (size_t)n * R * sizeof(u32), st));
@@ -1619,12 +1622,10 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
   u32 G = (u32)std::max<u64>(1, (32ull << 20) / n);
   if (G > T) G = T;
   mark("graph, points, start vertex");
-  HcCtx X;
   rc = hc_setup(X, g, pts, Ls, s, l, seed, G);
   if (rc) return rc;
   mark("buffers of a tree group");
   const u64 total = (u64)T * 2 * n;
-  DevBuf arcs, arcs_tmp, big_hist, uq_counts, lists, small, arena;
   HIP_TRY(arcs.alloc(total * 8));
   HIP_TRY(arcs_tmp.alloc(total * 8));
   HIP_TRY(hipMemsetAsync(arcs.p, 0xFF, total * 8, st));
@@ -1698,6 +1699,7 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
   u32 flags[4] = {0, 0, 0, 0};
   HIP_TRY(hipMemcpyAsync(flags, small.p, 16, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
+  wait.done = true;
   if (flags[2] != 0) return fail(ANN_EINTERNAL, "merge spill arena exhausted");
   mark("prune");
   g->stats.edges = nuniq;

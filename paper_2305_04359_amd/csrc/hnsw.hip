@@ -130,6 +130,7 @@ int make_layers(ann_hnsw* h, const void* points_dev, hipStream_t st) {
       }
     }
     DevBuf idsd;
+    FailureWait wait;
     HIP_TRY(idsd.alloc(nl * 4));
     HIP_TRY(hipMemcpyAsync(idsd.p, mine.data(), nl * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(h->down[l].alloc(nl * 4));
@@ -141,6 +142,7 @@ int make_layers(ann_hnsw* h, const void* points_dev, hipStream_t st) {
                        h->pts[l].as<unsigned char>());
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));  // idsd and the host vectors go out of scope
+    wait.done = true;
     h->entry_c[l] = (u32)(std::lower_bound(mine.begin(), mine.end(), h->entry) - mine.begin());
   }
   h->entry_c[0] = h->entry;
@@ -200,8 +202,27 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
     }
     for (u32 l = 1; l <= top; ++l) ins_off[l][r + 1] = ins_c[l].size();
   }
-  DevBuf order_dev;
+  // Two scratch areas and two streams: the upper layers of a batch do not depend on layer 0, so
+  // they run on a stream of their own, up to two batches ahead of the bottom layer's stream, and
+  // their small kernels fill the gaps the large ones leave.
+  constexpr int RING = 2;
+  struct UpStream {
+    hipStream_t s = nullptr;
+    hipEvent_t cur_ready[RING] = {}, cur_free[RING] = {}, setup = nullptr;
+    ~UpStream() {
+      if (s) (void)hipStreamDestroy(s);
+      for (auto& e : cur_ready)
+        if (e) (void)hipEventDestroy(e);
+      for (auto& e : cur_free)
+        if (e) (void)hipEventDestroy(e);
+      if (setup) (void)hipEventDestroy(setup);
+    }
+  };
+  DevBuf order_dev, cur_a[RING], cur_b[RING];
   std::vector<DevBuf> ins_c_dev(top + 1), ins_slot_dev(top + 1);
+  BatchScratch S0, Su;
+  UpStream us;
+  FailureWait wait;
   HIP_TRY(order_dev.alloc(cnt * 4));
   if (cnt) HIP_TRY(hipMemcpyAsync(order_dev.p, order.data(), cnt * 4, hipMemcpyHostToDevice, st));
   for (u32 l = 1; l <= top; ++l) {
@@ -214,11 +235,6 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
     }
   }
 
-  // Two scratch areas and two streams: the upper layers of a batch do not depend on layer 0, so
-  // they run on a stream of their own, up to two batches ahead of the bottom layer's stream, and
-  // their small kernels fill the gaps the large ones leave.
-  constexpr int RING = 2;
-  BatchScratch S0, Su;
   const u32 vcap = 4 * efc > 256 ? 4 * efc : 256;
   rc = S0.alloc(bmax, 2 * m, vcap, default_spill_keys(bmax));
   if (rc) return rc;
@@ -229,19 +245,6 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
     rc = Su.alloc(bup, m, vcap, default_spill_keys(bup), /*with_side=*/false);
     if (rc) return rc;
   }
-  struct UpStream {
-    hipStream_t s = nullptr;
-    hipEvent_t cur_ready[RING] = {}, cur_free[RING] = {}, setup = nullptr;
-    ~UpStream() {
-      if (s) (void)hipStreamDestroy(s);
-      for (auto& e : cur_ready)
-        if (e) (void)hipEventDestroy(e);
-      for (auto& e : cur_free)
-        if (e) (void)hipEventDestroy(e);
-      if (setup) (void)hipEventDestroy(setup);
-    }
-  } us;
-  DevBuf cur_a[RING], cur_b[RING];
   if (top > 0) {
     HIP_TRY(hipStreamCreateWithFlags(&us.s, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&us.setup, hipEventDisableTiming));
@@ -335,6 +338,7 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
     h->rounds = 0;
   }
   if (rc) return rc;
+  wait.done = true;
   return rc;
 }
 
@@ -365,6 +369,7 @@ int ann_hnsw_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dty
     ann_hnsw* h;
     ~Guard() { free_hnsw(h); }
   } guard{h};
+  FailureWait wait;
   h->al = al;
   h->n = n;
   h->d = d;
@@ -435,6 +440,7 @@ int ann_hnsw_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dty
   if (rc) return rc;
   rc = make_walk(h, st);
   if (rc) return rc;
+  wait.done = true;
   guard.h = nullptr;
   *out = h;
   return ANN_OK;
@@ -517,6 +523,7 @@ int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total
     rc = grow_graph(h->layer[l], nl1, st);
     if (rc) return rc;
     DevBuf npts, ndown, idsd;
+    FailureWait wait;
     HIP_TRY(npts.alloc(nl1 * d * esz));
     HIP_TRY(ndown.alloc(nl1 * 4));
     HIP_TRY(idsd.alloc(fresh.size() * 4));
@@ -530,6 +537,7 @@ int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total
                        npts.as<unsigned char>() + nl0 * d * esz);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipDeviceSynchronize());  // the old arrays may still be read; the host vectors go out of scope
+    wait.done = true;
     h->pts[l] = std::move(npts);
     h->down[l] = std::move(ndown);
   }

@@ -263,6 +263,7 @@ static hipError_t start_vertex_t(const T* x, u64 n, u32 d, hipStream_t s, u32* s
   const bool byte_words = sizeof(T) == 1 && d % 4 == 0 && d <= 4096;
   const u32 nwg = byte_words ? (u32)((n * 8 + 255) / 256) : (u32)((n + 255) / 256);
   DevBuf partial_b, colsum_b, wg_b;  // (from the calling thread's allocator)
+  FailureWait wait;
   hipError_t e;
   if ((e = partial_b.alloc((size_t)nblocks * d * sizeof(S))) != hipSuccess) return e;
   if ((e = colsum_b.alloc((size_t)d * sizeof(S))) != hipSuccess) return e;
@@ -294,6 +295,7 @@ static hipError_t start_vertex_t(const T* x, u64 n, u32 d, hipStream_t s, u32* s
   e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(start_out, best_id, sizeof(u32), hipMemcpyDeviceToHost, s);
   const hipError_t e2 = hipStreamSynchronize(s);  // also before the buffers go back
+  wait.done = e2 == hipSuccess;
   return e != hipSuccess ? e : e2;
 }
 

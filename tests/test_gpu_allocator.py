@@ -1,9 +1,9 @@
 """What the callbacks of the build options may rely on: when the library calls `free`, nothing that it queued
-is still to run on that memory."""
+is still to run on that memory, also where the call fails half-way."""
 import numpy as np
 import pytest
 
-from helpers import dev
+from helpers import dev, say
 
 pytestmark = pytest.mark.gpu
 
@@ -25,6 +25,58 @@ def _allocator(A, torch, stream):
             self.inner, self.free = give_back, A.FREE_FN(_free)
 
     return Watching()
+
+
+def _calls(A, pts):
+    """call -> (what is there before it, the call)"""
+    half = pts[:pts.shape[0] // 2]
+    return {
+        "build": (lambda al: None, lambda g, al: A.ann_build(pts, 16, 32, 1.2, seed=3, allocator=al)),
+        "insert": (lambda al: A.ann_build(half, 16, 32, 1.2, seed=3, allocator=al),
+                   lambda g, al: A.ann_insert_points(g, pts, 32, 1.2, seed=4)),
+        "layered": (lambda al: None, lambda g, al: A.ann_hnsw_build(pts, 8, 32, 1.2, seed=3, allocator=al)),
+        "layered insert": (lambda al: A.ann_hnsw_build(half, 8, 32, 1.2, seed=3, allocator=al),
+                           lambda g, al: A.ann_hnsw_insert_points(g, pts, 32, 1.2, seed=4)),
+        "cluster": (lambda al: None, lambda g, al: A.ann_hcnng_build(pts, 3, 100, 3, 10, 16, 1.2, seed=3, allocator=al)),
+    }
+
+
+@pytest.mark.parametrize("call", ["build", "insert", "layered", "layered insert", "cluster"])
+def test_memory_comes_back_idle(env, call):
+    """Padded byte rows (a copy of the points is one more allocation).  Work queued before the call keeps
+    everything that the call queues from running until somebody waits."""
+    torch, A, _ = env
+    pts = dev(torch, np.random.default_rng(5).integers(0, 256, (1500, 60)).astype(np.uint8))
+    before, act = _calls(A, pts)[call]
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        def once(k):
+            """with k allocations (None: all that it wants); returns how many the call made"""
+            al = _allocator(A, torch, stream)
+            g = before(al)
+            stream.synchronize()
+            had = al.allocs
+            if k is None:
+                made = act(g, al)
+            else:
+                al.fail_after = had + k
+                torch.cuda._sleep(5_000_000)  # some milliseconds
+                with pytest.raises(A.AnnError) as e:
+                    act(g, al)
+                assert e.value.code == -2
+                made = e = None
+            assert al.busy == 0, f"{al.busy} buffers came back with work queued"
+            n = al.allocs - had
+            stream.synchronize()  # (an object that is freed does not wait for the caller's searches)
+            del made, g
+            assert len(al.live) == 0 and al.allocs == al.frees
+            return n
+
+        total = once(None)
+        for k in range(total):
+            say(f"allocator {call}: dry after {k} of {total}")
+            assert once(k) == k
 
 
 def test_layered_insert_waits_for_searches(env):
