@@ -213,7 +213,7 @@ int resolve_points(const ann_graph* g, const void* points_dev, hipStream_t st, c
     g->pad_src = nullptr;
     g->pad_done = 0;
     const u64 want = g->cap > g->n ? g->cap : g->n;
-    HIP_TRY(g->al.get(&g->pad_buf, (size_t)want * g->pad_stride));
+    HIP_TRY(g->al.on(st).get(&g->pad_buf, (size_t)want * g->pad_stride));
     g->pad_cap = want;
   }
   if (g->pad_src != points_dev) g->pad_done = 0;
@@ -241,7 +241,7 @@ int resolve_queries(const ann_graph* g, const void* queries_dev, u64 nq, hipStre
       g->qpad_buf = nullptr;
       g->qpad_rows = 0;
     }
-    HIP_TRY(g->al.get(&g->qpad_buf, (size_t)nq * g->pad_stride));
+    HIP_TRY(g->al.on(st).get(&g->qpad_buf, (size_t)nq * g->pad_stride));
     g->qpad_rows = nq;
   }
   int rc = pad_rows(queries_dev, nq, g->d, g->qpad_buf, g->pad_stride, st);
@@ -679,8 +679,9 @@ int reserve_rows(ann_graph* g, u64 want, hipStream_t st) {
   if (want >= (1ull << 31)) return fail(ANN_EINVAL, "n must stay below 2^31");
   u32* rows = nullptr;
   u32* meta = nullptr;
-  hipError_t e = g->al.get(reinterpret_cast<void**>(&rows), (size_t)want * g->R * sizeof(u32));
-  if (e == hipSuccess) e = g->al.get(reinterpret_cast<void**>(&meta), (size_t)want * sizeof(u32));
+  const Allocator al = g->al.on(st);
+  hipError_t e = al.get(reinterpret_cast<void**>(&rows), (size_t)want * g->R * sizeof(u32));
+  if (e == hipSuccess) e = al.get(reinterpret_cast<void**>(&meta), (size_t)want * sizeof(u32));
   if (e == hipSuccess)
     e = hipMemcpyAsync(rows, g->rows, (size_t)g->n * g->R * sizeof(u32), hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(meta, g->meta, (size_t)g->n * sizeof(u32), hipMemcpyDeviceToDevice, st);
@@ -919,9 +920,7 @@ int ann_insert_batch(ann_graph* g, const void* points_dev, const uint32_t* ids_h
     }
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  Allocator al = g->al;
-  al.stream = stream;
-  AllocScope scope(al);
+  AllocScope scope(g->al.on(st));
   FailureWait wait;  // (the graph keeps its scratch; a later call may enlarge it)
   BatchScratch* Sp = nullptr;
   rc = graph_scratch(g, b, L, st, &Sp);
@@ -972,9 +971,7 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   if (n_total >= (1ull << 31)) return fail(ANN_EINVAL, "n must stay below 2^31");
   ann_build_opts o{};
   if (opts) o = *opts;
-  Allocator al = g->al;
-  al.stream = stream;
-  AllocScope scope(al);
+  AllocScope scope(g->al.on(static_cast<hipStream_t>(stream)));
   const u64 n_old = g->n, m = n_total - n_old;
   if (m == 0) return ANN_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);

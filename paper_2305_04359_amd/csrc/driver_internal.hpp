@@ -50,6 +50,12 @@ struct Allocator {
   hipError_t zero(void* p, size_t bytes) const {
     return alloc == nullptr ? hipMemset(p, 0, bytes) : hipMemsetAsync(p, 0, bytes, static_cast<hipStream_t>(stream));
   }
+  // the same allocator for a call on another stream than the object's first one
+  Allocator on(hipStream_t s) const {
+    Allocator a = *this;
+    a.stream = alloc != nullptr ? static_cast<void*>(s) : nullptr;
+    return a;
+  }
   void put(void* p) const {
     if (p == nullptr) return;
     if (free != nullptr)

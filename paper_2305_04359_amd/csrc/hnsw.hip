@@ -460,9 +460,7 @@ int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total
   const u64 n_old = h->n, mnew = n_total - n_old;
   if (mnew == 0) return ANN_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  Allocator al = h->al;
-  al.stream = stream;
-  AllocScope scope(al);
+  AllocScope scope(h->al.on(st));
   const u32 top = h->top, m = h->m, d = h->d;
   const u64 esz = h->dtype == ANN_F32 ? 4 : 1;
 
@@ -636,9 +634,7 @@ int ann_hnsw_search(const ann_hnsw* h, const void* points_dev, const void* queri
   if (h->top == 0) return query_launch(g0, p0, qs, nullptr, nq, k, L, eps, nullptr, ids_dev, dists_dev, st);
   if (h->qcur_cap < nq) {
     HIP_TRY(hipDeviceSynchronize());  // an earlier call, on whatever stream, may still use the old array
-    Allocator al = h->al;
-    al.stream = stream;
-    AllocScope scope(al);
+    AllocScope scope(h->al.on(st));
     HIP_TRY(h->qcur.alloc(nq * 4));
     h->qcur_cap = nq;
   }

@@ -1,5 +1,6 @@
 """What the callbacks of the build options may rely on: when the library calls `free`, nothing that it queued
-is still to run on that memory, also where the call fails half-way."""
+is still to run on that memory, also where the call fails half-way; `alloc` is asked for memory on the stream of
+the call that needs it, and what it gives is first used there."""
 import numpy as np
 import pytest
 
@@ -9,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _allocator(A, torch, stream):
-    """Counts what is alive, runs dry `left` allocations from now, looks at the stream when memory comes back."""
+    """Counts what is alive, runs dry where a test says so, looks at the stream when memory comes back."""
     from test_gpu_boundary import CountingAllocator
 
     class Watching(CountingAllocator):
@@ -99,3 +100,39 @@ def test_layered_insert_waits_for_searches(env):
         assert al.busy == 0 and torch.equal(ids, want)
         stream.synchronize()
         del h
+
+
+def test_alloc_names_the_stream_of_the_call(env):
+    """Searches and insertions on another stream than the build's: padded copies, grown rows, scratch, start vertices."""
+    from test_gpu_boundary import CountingAllocator
+    torch, A, _ = env
+    pts = dev(torch, np.random.default_rng(7).integers(0, 256, (1200, 60)).astype(np.uint8))
+    al = CountingAllocator(A, torch)
+    plain, asked = al.alloc, []
+
+    def _alloc(nbytes, stream, user):
+        asked.append(stream or 0)
+        return plain(nbytes, stream, user)
+
+    al.inner, al.alloc = plain, A.ALLOC_FN(_alloc)
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(first):
+        g = A.ann_build(pts[:600], 16, 32, 1.2, seed=3, allocator=al)
+        h = A.ann_hnsw_build(pts[:600], 8, 32, 1.2, seed=3, allocator=al)
+    assert set(asked) == {first.cuda_stream}
+    calls = {
+        "search": lambda: A.ann_search(g, pts[:600], pts[:100], 5, 20),
+        "reserve": lambda: A.ann_graph_reserve(g, 700),
+        "insert": lambda: A.ann_insert_points(g, pts, 32, 1.2, seed=4),
+        "layered search": lambda: A.ann_hnsw_search(h, pts[:600], pts[:100], 5, 20),
+        "layered insert": lambda: A.ann_hnsw_insert_points(h, pts, 32, 1.2, seed=4),
+    }
+    for name, call in calls.items():
+        del asked[:]
+        with torch.cuda.stream(second):
+            call()
+        assert asked and set(asked) == {second.cuda_stream}, name
+    torch.cuda.synchronize()
+    del g, h, calls, call
+    assert len(al.live) == 0
