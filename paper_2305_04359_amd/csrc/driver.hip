@@ -439,7 +439,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     HIP_TRY(hipMemcpy(slots.data(), S.ovf_list.p, (size_t)novf * 4, hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(nv.data(), S.nvis.p, (size_t)b * 4, hipMemcpyDeviceToHost));
     u32 need = 0;
-    std::vector<u32> ids2(novf);
+    std::vector<u32> ids2(novf), p2;
     for (u32 i = 0; i < novf; ++i) {
       need = nv[slots[i]] > need ? nv[slots[i]] : need;
       ids2[i] = ids_host[slots[i]];
@@ -450,8 +450,8 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     HIP_TRY(slots_d.alloc((size_t)novf * 4));
     HIP_TRY(vis2.alloc((size_t)novf * need * 8));
     HIP_TRY(nvis2.alloc((size_t)novf * 4));
-    HIP_TRY(hipMemcpy(ids2_d.p, ids2.data(), (size_t)novf * 4, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(slots_d.p, slots.data(), (size_t)novf * 4, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpyAsync(ids2_d.p, ids2.data(), (size_t)novf * 4, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(slots_d.p, slots.data(), (size_t)novf * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemsetAsync(small + 0, 0, 4, st));
     SearchArgs sb = sa;
     sb.qidx = ids2_d.as<u32>();
@@ -465,10 +465,10 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     sb.counters = nullptr;
     if (starts) {
       // redone search i stands at the position of batch slot slots[i]
-      std::vector<u32> p2(novf);
+      p2.resize(novf);
       for (u32 i = 0; i < novf; ++i) p2[i] = starts->slot_host ? starts->slot_host[slots[i]] : slots[i];
       HIP_TRY(pos2.alloc((size_t)novf * 4));
-      HIP_TRY(hipMemcpy(pos2.p, p2.data(), (size_t)novf * 4, hipMemcpyHostToDevice));
+      HIP_TRY(hipMemcpyAsync(pos2.p, p2.data(), (size_t)novf * 4, hipMemcpyHostToDevice, st));
       sb.slot = pos2.as<u32>();
     }
     HIP_TRY(launch_search(g->cfg, sb, st));
@@ -926,7 +926,7 @@ int ann_insert_batch(ann_graph* g, const void* points_dev, const uint32_t* ids_h
   rc = graph_scratch(g, b, L, st, &Sp);
   if (rc) return rc;
   BatchScratch& S = *Sp;
-  HIP_TRY(hipMemcpy(S.qidx.p, ids_host, (size_t)b * 4, hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpyAsync(S.qidx.p, ids_host, (size_t)b * 4, hipMemcpyHostToDevice, st));
   {
     // a point that has out-neighbours is in the graph already: searching from s would reach it
     // and it would become its own candidate

@@ -46,7 +46,7 @@ struct Allocator {
     return *p != nullptr ? hipSuccess : hipErrorOutOfMemory;
   }
   // Zeroes memory that `get` gave.  Memory of the caller's may still be read or written by work that was
-  // queued on its stream before it was handed on: the clearing goes behind that.
+  // queued on its stream before it was handed on: the clearing goes behind that, as every first use must.
   hipError_t zero(void* p, size_t bytes) const {
     return alloc == nullptr ? hipMemset(p, 0, bytes) : hipMemsetAsync(p, 0, bytes, static_cast<hipStream_t>(stream));
   }

@@ -171,7 +171,8 @@ int make_walk(ann_hnsw* h, hipStream_t st) {
   }
   if (h->walk.p != nullptr) HIP_TRY(hipDeviceSynchronize());  // a search, on whatever stream, may still read the old table
   HIP_TRY(h->walk.alloc(walk.size() * sizeof(DescendLayer)));
-  HIP_TRY(hipMemcpy(h->walk.p, walk.data(), walk.size() * sizeof(DescendLayer), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpyAsync(h->walk.p, walk.data(), walk.size() * sizeof(DescendLayer), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipStreamSynchronize(st));  // `walk` goes out of scope
   return ANN_OK;
 }
 

@@ -136,3 +136,50 @@ def test_alloc_names_the_stream_of_the_call(env):
     torch.cuda.synchronize()
     del g, h, calls, call
     assert len(al.live) == 0
+
+
+def test_memory_is_first_used_on_its_stream(env):
+    """Memory that comes with work of its last owner still queued on the stream: fills that run late.
+    Rows that are padded, a batch whose visited lists fit nowhere (more allocations), every builder."""
+    from test_gpu_boundary import CountingAllocator
+    torch, A, _ = env
+    pts = dev(torch, np.random.default_rng(8).integers(0, 256, (1500, 60)).astype(np.uint8))
+    half = pts[:700]
+    al = CountingAllocator(A, torch)
+    plain = al.alloc
+
+    def _alloc(nbytes, stream, user):
+        p = plain(nbytes, stream, user)
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream)):
+            torch.cuda._sleep(300_000)
+            al.live[p].fill_(0xA5)
+        return p
+
+    al.inner, al.alloc = plain, A.ALLOC_FN(_alloc)
+
+    def everything(a):
+        out = []
+        g = A.ann_build(half, 16, 40, 1.2, seed=3, allocator=a, visited_cap=16, spill_cap=1)
+        out.append(g.neighbors())
+        A.ann_insert_points(g, pts, 40, 1.2, seed=4)
+        out += [g.neighbors(), *A.ann_search(g, pts, pts[:300], 5, 20)]
+        first = A.ann_build(half, 16, 40, 1.2, seed=3, allocator=a, max_rounds=4)
+        ids = np.nonzero(first.neighbors()[:, 0] == 0xFFFFFFFF)[0].astype(np.uint32)
+        A.ann_insert_batch(first, half, ids[ids != first.info().start][:50], 40, 1.2)
+        out.append(first.neighbors())
+        h = A.ann_hnsw_build(half, 8, 40, 1.2, seed=3, allocator=a)
+        A.ann_hnsw_insert_points(h, pts, 40, 1.2, seed=4)
+        out += [l for i in range(h.info().top + 1) for l in h.layer(i)]
+        out += A.ann_hnsw_search(h, pts, pts[:300], 5, 20)
+        out.append(A.ann_hcnng_build(pts, 3, 100, 3, 10, 16, 1.2, seed=3, allocator=a).neighbors())
+        torch.cuda.synchronize()
+        return out
+
+    want = everything("torch")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        got = everything(al)
+    for w, x in zip(want, got):
+        assert torch.equal(w, x) if isinstance(w, torch.Tensor) else (w == x).all()
+    assert len(al.live) == 0
