@@ -284,6 +284,13 @@ int ann_graph_set_stats(ann_graph* g, int on);
  * chosen from the beam width).  For the sizing study of Sec. 4.5: results never
  * depend on it, only the number of repeated distance evaluations does.       */
 int ann_graph_set_filter_bits(ann_graph* g, uint32_t hash_bits);
+/* The filter that a launch of nq searches on this graph gets where every search has a
+ * wave of its own (for tests): its size in 32-bit words, the bits that a vertex takes in
+ * it, and the waves per SIMD that the registers of the kernel instance leave room
+ * for.  own_starts: searches with start vertices of their own (the layered index).
+ * Launches nothing.                                                              */
+int ann_search_filter(const ann_graph* g, uint64_t nq, uint32_t L, float eps, int own_starts, uint32_t* waves,
+                      uint32_t* words, uint32_t* tag_bits);
 void ann_graph_free(ann_graph* g);
 
 /* Stable LSD radix sort of `count` 64-bit keys by bits [32, 32+key_bits) only

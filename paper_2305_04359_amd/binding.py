@@ -77,6 +77,7 @@ EXPORTS = [
     "ann_build", "ann_insert_batch", "ann_insert_points", "ann_graph_reserve", "ann_search", "ann_search_eps", "ann_search_noalloc", "ann_start_vertex", "ann_graph_from_host",
     "ann_graph_copy_neighbors", "ann_graph_device_rows", "ann_graph_info", "ann_get_stats", "ann_graph_set_stats", "ann_graph_set_filter_bits",
     "ann_graph_free", "ann_sort_edges", "ann_last_error",
+    "ann_search_filter",
     "ann_hnsw_build", "ann_hnsw_insert_points", "ann_hnsw_from_host", "ann_hnsw_search", "ann_hnsw_info", "ann_hnsw_copy_levels", "ann_hnsw_layer_size",
     "ann_hnsw_copy_layer", "ann_hnsw_get_stats", "ann_hnsw_free",
     "ann_hcnng_build", "ann_hcnng_build_with", "ann_hcnng_tree_edges", "ann_hcnng_leaf_knn",
@@ -130,6 +131,8 @@ def lib():
         L.ann_graph_set_stats.argtypes = [vp, C.c_int]
         L.ann_graph_set_filter_bits.restype = C.c_int
         L.ann_graph_set_filter_bits.argtypes = [vp, u32]
+        L.ann_search_filter.restype = C.c_int
+        L.ann_search_filter.argtypes = [vp, u64, u32, C.c_float, C.c_int, C.POINTER(u32), C.POINTER(u32), C.POINTER(u32)]
         L.ann_graph_free.restype = None
         L.ann_graph_free.argtypes = [vp]
         L.ann_sort_edges.restype = C.c_int
@@ -305,6 +308,12 @@ class Graph:
 
     def set_filter_bits(self, hash_bits: int) -> None:
         _check(lib().ann_graph_set_filter_bits(self._h, int(hash_bits)))
+
+    def search_filter(self, nq, L, eps=-1.0, own_starts=False) -> tuple[int, int, int]:
+        """(waves per SIMD, words, bits per vertex) of the visited filter of a launch of nq searches (for tests)."""
+        v = [C.c_uint32() for _ in range(3)]
+        _check(lib().ann_search_filter(self._h, int(nq), int(L), float(eps), int(own_starts), *map(C.byref, v)))
+        return tuple(x.value for x in v)
 
     def neighbors(self) -> np.ndarray:
         gi = self.info()

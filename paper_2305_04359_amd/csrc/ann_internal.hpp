@@ -57,6 +57,7 @@ struct SearchArgs {
   // round(eps * 2^16), float kinds epsf
   long long eps16;
   float epsf;
+  // (the next three are the launch's, see search_set_filter)
   u32 hash_buckets;  // 16-byte buckets of the visited filter (any count from 4 to 2048)
   u32 id_bits;       // > 0: the filter stores tags of ids that fit in this many bits ...
   u32 tag_width;     // ... eight of 16 bits or six of 21 bits per bucket (0: four 32-bit ids)
@@ -77,7 +78,7 @@ struct SearchArgs {
   DevCounters* counters;  // may be null
   // for the host's choice of kernel
   u64 n;             // vertices of the graph
-  u32 filter_given;  // non-zero: the filter's size is the caller's choice and stays
+  u32 filter_given;  // non-zero: the filter's size is the caller's choice (log2 of its 32-bit words)
   u32 shares_chip;   // non-zero: other searches run beside these (parts of a batch)
 };
 
@@ -171,6 +172,12 @@ constexpr u32 STAGE_BUDGET = 10240;    // LDS bytes the prune kernels may spend 
 
 // launchers (each returns the hipGetLastError() of its launches)
 hipError_t launch_search(const DistCfg& cfg, const SearchArgs& a, hipStream_t s);
+// what a launch of one wave per search would be, without launching it (for tests)
+struct SearchPlan {
+  u32 waves;  // per SIMD, by the registers of the instance
+  u32 filter_words, tag_width;
+};
+hipError_t plan_search(const DistCfg& cfg, const SearchArgs& a, SearchPlan* plan);
 hipError_t launch_descend(const DistCfg& cfg, const DescendArgs& a, hipStream_t s);
 hipError_t launch_prune(const DistCfg& cfg, const PruneArgs& a, hipStream_t s);
 hipError_t launch_plan(const MergeArgs& a, hipStream_t s);
@@ -194,8 +201,6 @@ hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u6
 hipError_t start_vertex_device(const void* points, u64 n, u32 d, int dtype, hipStream_t s, u32* start_out);
 
 u32 search_lds_bytes(u32 L, u32 hash_buckets);
-// hash_bits: the caller's explicit choice, or 0; own: searches with start vertices of their own
-u32 search_hash_buckets(const DistCfg& cfg, u64 n, u32 L, u32 hash_bits, bool own);
 // how the visited filter stores vertices of a graph of n points: fills id_bits and tag_width
 void search_filter_mode(u64 n, u32 hash_buckets, u32* id_bits, u32* tag_width);
 

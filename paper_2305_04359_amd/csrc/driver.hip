@@ -326,8 +326,6 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   }
   sa.L = L;
   sa.k = 1;
-  sa.hash_buckets = search_hash_buckets(g->cfg, g->n, L, g->hash_bits, starts != nullptr);
-  search_filter_mode(g->n, sa.hash_buckets, &sa.id_bits, &sa.tag_width);
   sa.n = g->n;
   sa.filter_given = g->hash_bits;
   sa.batch_counters = small;
@@ -609,8 +607,6 @@ int query_launch(const ann_graph* g, const void* pts, const void* queries, const
   }
   sa.L = L;
   sa.k = k;
-  sa.hash_buckets = search_hash_buckets(g->cfg, g->n, L, g->hash_bits, starts != nullptr);
-  search_filter_mode(g->n, sa.hash_buckets, &sa.id_bits, &sa.tag_width);
   sa.n = g->n;
   sa.filter_given = g->hash_bits;
   sa.eps16 = eps >= 0.0f ? llround((double)eps * 65536.0) : -1;
@@ -825,6 +821,30 @@ int ann_graph_set_filter_bits(ann_graph* g, uint32_t hash_bits) {
   if (hash_bits && (hash_bits < 4 || hash_bits > 13)) return fail(ANN_EINVAL, "hash_bits must be in [4, 13]");
   g->hash_bits = hash_bits;
   return ANN_OK;
+}
+
+int ann_search_filter(const ann_graph* g, uint64_t nq, uint32_t L, float eps, int own_starts, uint32_t* waves,
+                      uint32_t* words, uint32_t* tag_bits) try {
+  if (!g || !waves || !words || !tag_bits) return fail(ANN_EINVAL, "null argument");
+  if (L < 1 || L > 2048) return fail(ANN_EINVAL, "L must be in [1, 2048]");
+  if (nq >= (1ull << 31)) return fail(ANN_EINVAL, "too many queries");
+  SearchArgs sa{};
+  sa.nq = (u32)nq;
+  sa.R = g->R;
+  sa.L = L;
+  sa.k = 1;
+  sa.n = g->n;
+  sa.filter_given = g->hash_bits;
+  sa.eps16 = eps >= 0.0f ? 0 : -1;
+  sa.starts = own_starts ? g->rows : nullptr;  // (that there are any is all that is looked at)
+  SearchPlan plan{};
+  HIP_TRY(plan_search(g->cfg, sa, &plan));
+  *waves = plan.waves;
+  *words = plan.filter_words;
+  *tag_bits = plan.tag_width ? plan.tag_width : 32;
+  return ANN_OK;
+} catch (...) {
+  return annmi::on_exception();
 }
 
 const uint32_t* ann_graph_device_rows(const ann_graph* g) { return g ? g->rows : nullptr; }

@@ -10,14 +10,21 @@ namespace annmi {
 u32 search_lds_bytes(u32 L, u32 hash_buckets) { return search_nslot_for(L) * 64 * 8 + 64 * 8 + hash_buckets * 16; }
 
 // Size of the visited filter.  An explicit hash_bits (log2 of the size in 32-bit words) is taken
-// as it is.  Otherwise, for beams of up to 256: all of the LDS that the waves a SIMD can hold by
-// their registers leave to each, up to 2,048 words: one wave less costs more than a larger table
+// as it is (search_set_filter).  Otherwise, for beams of up to 256: all of the LDS that the waves a SIMD can hold
+// by their registers leave to each, up to 2,048 words: one wave less costs more than a larger table
 // saves, and LDS below that step is free.  A compute unit hands out its 160 KB in units of 1,280 bytes.
+// `waves`: what the registers of the instance that is launched allow (search_instance_waves).
 // 10,000 queries, a million 128-d uint8 points (eight waves), R = 64, L = 50: 512 words 364 us, 1,024 (that
 // step) 340, 2,048 405; L = 128: 512 words 734, 896 (that step) 656, 1,216 672, 2,048 822.  Five million
-// points, L = 50: 672 -> 586.  A million points of 200 floats (four waves; 1,024 words less a cut -> 2,048): 1,705 ->
-// 1,596 distances per search, build 262 -> 250 ms, 10,000 queries at L = 50 2,055 -> 1,935 us, at L = 200
-// 4,025 -> 3,554; 4,096 words, a wave less: 266 ms, 2,004 and 4,129.
+// points, L = 50: 672 -> 586.  A million points of 200 floats (four waves): build 262 ms by 1,024 words, 250 by
+// 2,048 (that step), 266 by 4,096; 10,000 queries at L = 50 2,055, 1,935 and 2,004 us, and by 1,664, what five waves
+// would get, 0.4 % more than by 2,048; at L = 200 1,280 words 3,786, 1,920 (that step) 3,634.  Byte rows of 200 (six waves), 20,000 queries at L =
+// 128: 896 words 1,498 us (uint8) and 2,128 (int8), 1,216 (that step) 1,467 and 2,098, 1,344 1,538 and 2,183.
+//
+// Four slots (beams of 129 to 256): some instances hold seven waves, whose 640 words cost more in repeats than the
+// seventh wave brings: 20,000 queries, a million uint8 points, L = 200, eps = 0.25: seven waves 1,994 us, six (960
+// words) 1,768, five (1,280) 1,850; 500,000 points of 48 floats 1,601, 1,562, 1,649.  Instances whose registers
+// leave five are best at five: without the rule 1,925 us by 960 words, 1,845 by 1,280, 2,110 by 1,920.
 //
 // More than 2^22 points: a table of 224 buckets (beams of 65 to 128) would need 21-bit tags, one of 304,
 // at six waves, still takes 16-bit tags up to 2^23 points: 20,000 queries on five million, L = 100, 1,776 -> 1,558
@@ -29,18 +36,11 @@ u32 search_lds_bytes(u32 L, u32 hash_buckets) { return search_nslot_for(L) * 64 
 // hundred million points, where tables of 1,024 and 512 words answer 1.7 to 2.3 times the queries
 // per second of tables of 4,096 and 8,192.  The table is never cut below 3/4 of the power of two.
 constexpr u32 LDS_UNIT = 1280;
-static u32 register_waves(u32 nch, u32 nslot, bool own) {  // waves per SIMD, by the registers of the variants
-  if (nslot <= 2u)
-    return nch <= 1u ? 8u : nch <= 2u ? 7u : nch <= 4u ? (own ? 6u : 5u) : nch <= 6u || (nch == 7u && (own || nslot == 1u)) ? 5u : 4u;
-  return nch <= 2u ? 5u : nch <= 4u ? (own ? 5u : 4u) : 4u;
-}
-u32 search_hash_buckets(const DistCfg& cfg, u64 n, u32 L, u32 hash_bits, bool own) {
-  if (hash_bits) return 1u << (hash_bits - 2u);
+static u32 search_hash_buckets(u64 n, u32 L, u32 waves) {
   const u32 nslot = search_nslot_for(L);
   if (L < 8u) return 128;  // (over after a few hops: not worth clearing more)
   if (nslot <= 4u) {
-    u32 waves = register_waves((u32)cfg.nch, nslot, own);
-    if (nslot == 2u && n > (1ull << 22) && waves > 6u) waves = 6u;
+    if ((nslot == 4u || (nslot == 2u && n > (1ull << 22))) && waves > 6u) waves = 6u;
     const u32 share = 163840u / (4u * waves) / LDS_UNIT * LDS_UNIT;
     const u32 nb = (share - search_lds_bytes(L, 0)) / 16u;
     return nb < 512u ? nb : 512u;
@@ -50,10 +50,10 @@ u32 search_hash_buckets(const DistCfg& cfg, u64 n, u32 L, u32 hash_bits, bool ow
   const u32 full = 1u << (bits - 2u);
   const u32 base = search_lds_bytes(L, 0);
   const u32 lds_full = (search_lds_bytes(L, full) + 511u) & ~511u;
-  u32 waves = 163840u / lds_full;
-  waves = (waves + 3u) & ~3u;
-  if (waves > 32u) waves = 32u;
-  const u32 budget = (163840u / waves) & ~511u;
+  u32 resident = 163840u / lds_full;
+  resident = (resident + 3u) & ~3u;
+  if (resident > 32u) resident = 32u;
+  const u32 budget = (163840u / resident) & ~511u;
   if (budget <= base) return full;
   u32 nb = (budget - base) / 16u;
   if (nb < full - full / 4u) return full;
@@ -81,13 +81,19 @@ void search_filter_mode(u64 n, u32 hash_buckets, u32* id_bits, u32* tag_width) {
   }
 }
 
-template <int KIND, int VEC, int NCH>
-static hipError_t launch_plain(const SearchArgs& a, const VecTable& T, hipStream_t s) {
-  return launch_search_variant<KIND, VEC, NCH, false, false>(a, T, s);
+void search_set_filter(SearchArgs& a, u32 waves) {
+  a.hash_buckets = a.filter_given ? 1u << (a.filter_given - 2u) : search_hash_buckets(a.n, a.L, waves);
+  search_filter_mode(a.n, a.hash_buckets, &a.id_bits, &a.tag_width);
 }
 
-static hipError_t launch_search_plain(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s) {
-  ANN_DISPATCH_CFG(launch_plain, a, T, s);
+template <int KIND, int VEC, int NCH>
+static hipError_t launch_plain(const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan) {
+  return launch_search_variant<KIND, VEC, NCH, false, false>(a, T, s, plan);
+}
+
+static hipError_t launch_search_plain(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s,
+                                      SearchPlan* plan) {
+  ANN_DISPATCH_CFG(launch_plain, a, T, s, plan);
 }
 
 // How many waves share a search.  Up to 1,024 searches leave most of the chip idle, and each waits for
@@ -151,15 +157,25 @@ static bool search_ahead(const DistCfg& cfg, const SearchArgs& a) {
   return a.nq <= (graph > ONE_L2 ? 3072u : 2048u);
 }
 
+// one wave per search
+static hipError_t launch_search_alone(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s,
+                                      SearchPlan* plan) {
+  const bool own = a.starts != nullptr || a.next_start != nullptr;
+  if (own) return a.eps16 >= 0 ? launch_search_own_eps(cfg, a, T, s, plan) : launch_search_own(cfg, a, T, s, plan);
+  return a.eps16 >= 0 ? launch_search_eps(cfg, a, T, s, plan) : launch_search_plain(cfg, a, T, s, plan);
+}
+
 hipError_t launch_search(const DistCfg& cfg, const SearchArgs& a, hipStream_t s) {
   if (a.nq == 0) return hipSuccess;
   VecTable T{a.points, (u32)cfg.row_bytes, cfg.npieces};
   const u32 waves = search_waves(cfg, a);
   if (waves > 1u) return launch_search_wide(cfg, a, T, waves, s);
   if (search_ahead(cfg, a)) return launch_search_ahead(cfg, a, T, s);
-  const bool own = a.starts != nullptr || a.next_start != nullptr;
-  if (own) return a.eps16 >= 0 ? launch_search_own_eps(cfg, a, T, s) : launch_search_own(cfg, a, T, s);
-  return a.eps16 >= 0 ? launch_search_eps(cfg, a, T, s) : launch_search_plain(cfg, a, T, s);
+  return launch_search_alone(cfg, a, T, s, nullptr);
+}
+
+hipError_t plan_search(const DistCfg& cfg, const SearchArgs& a, SearchPlan* plan) {
+  return launch_search_alone(cfg, a, VecTable{a.points, (u32)cfg.row_bytes, cfg.npieces}, nullptr, plan);
 }
 
 }  // namespace annmi

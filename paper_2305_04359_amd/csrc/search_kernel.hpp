@@ -14,6 +14,7 @@
 // exactly while the table remembers up to twice as many vertices.  The bucket count need not be
 // a power of two; it is chosen so that the wave's LDS lands on an occupancy step.
 #pragma once
+#include <atomic>
 #include <cstddef>
 
 #include "ann_device.hpp"
@@ -521,9 +522,11 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
 
 // launches of the variants that other translation units compile: with the (1 + eps) rule
 // (search_eps.hip), with start vertices of their own (search_own.hip), with both (search_own_eps.hip)
-hipError_t launch_search_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
-hipError_t launch_search_own(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
-hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
+hipError_t launch_search_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan);
+hipError_t launch_search_own(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan);
+hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan);
+// the filter's size and layout for an instance whose registers leave room for `waves` waves per SIMD (search.hip)
+void search_set_filter(SearchArgs& a, u32 waves);
 // Several waves per search (search_wide.hip): rows of at most 64 ids, beams of at most 256, ids of
 // at most 24 bits (beam entries and the 16-bit tags of a filter of 512 buckets).
 constexpr u32 WIDE_BUCKETS = 512;
@@ -559,34 +562,59 @@ inline bool search_network(const SearchArgs& a) {
   return a.R >= 64u || (a.R > 32u && (a.L <= 24u || a.eps16 >= 0)) || a.nq <= 256u;
 }
 
-// One launch for a fixed choice of EPS and OWN; the beam slots and the filter layout are picked here.
-template <int KIND, int VEC, int NCH, bool EPS, bool OWN>
-inline hipError_t launch_search_variant(const SearchArgs& a, const VecTable& T, hipStream_t s) {
+// Waves per SIMD that the registers of one instance leave room for (0: the runtime does not say), asked for once.
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK>
+inline u32 search_instance_waves() {
+  static std::atomic<u32> known{0};
+  u32 waves = known.load(std::memory_order_relaxed);
+  if (waves == 0) {
+    hipFuncAttributes f{};
+    const auto kernel = search_kernel<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK>;
+    if (hipFuncGetAttributes(&f, reinterpret_cast<const void*>(kernel)) != hipSuccess || f.numRegs < 1) return 0;
+    waves = 512u / (((u32)f.numRegs + 7u) & ~7u);  // 512 registers per lane and SIMD, in units of 8
+    waves = waves > 8u ? 8u : waves < 1u ? 1u : waves;
+    known.store(waves, std::memory_order_relaxed);
+  }
+  return waves;
+}
+
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool OWN, bool NETWORK>
+inline hipError_t launch_search_instance(SearchArgs a, const VecTable& T, hipStream_t s, SearchPlan* plan) {
+  // (the size decides whether 16-bit tags do, and with them the instance)
+  u32 waves = search_instance_waves<KIND, VEC, NCH, NSLOT, EPS, true, OWN, NETWORK>();
+  if (waves != 0) search_set_filter(a, waves);
+  if (waves != 0 && a.tag_width != 16u) {
+    waves = search_instance_waves<KIND, VEC, NCH, NSLOT, EPS, false, OWN, NETWORK>();
+    if (waves != 0) search_set_filter(a, waves);
+  }
+  if (waves == 0) return hipErrorInvalidDeviceFunction;
+  if (plan != nullptr) {
+    *plan = SearchPlan{waves, 4u * a.hash_buckets, a.tag_width};
+    return hipSuccess;
+  }
   const u32 lds = search_lds_bytes(a.L, a.hash_buckets);
   const dim3 grid(a.nq), block(64);
-  const bool t16 = a.tag_width == 16u;
-#define ANN_LAUNCH_SEARCH(NS, NET)                                                                            \
-  if (t16)                                                                                                    \
-    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NS, EPS, true, OWN, NET>), grid, block, lds, s, a, T);  \
-  else                                                                                                        \
-    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NS, EPS, false, OWN, NET>), grid, block, lds, s, a, T)
+  if (a.tag_width == 16u)
+    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NSLOT, EPS, true, OWN, NETWORK>), grid, block, lds, s, a, T);
+  else
+    hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NSLOT, EPS, false, OWN, NETWORK>), grid, block, lds, s, a, T);
+  return hipGetLastError();
+}
+
+// One launch for a fixed choice of EPS and OWN; the beam slots are picked here.
+template <int KIND, int VEC, int NCH, bool EPS, bool OWN>
+inline hipError_t launch_search_variant(const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan) {
   constexpr bool NETWORK = search_network_compiled<KIND, NCH, OWN>;
   switch (search_nslot_for(a.L)) {
     case 1:
-      if (NETWORK && search_network(a)) {
-        ANN_LAUNCH_SEARCH(1, NETWORK);
-      } else {
-        ANN_LAUNCH_SEARCH(1, false);
-      }
-      break;
-    case 2: ANN_LAUNCH_SEARCH(2, false); break;
-    case 4: ANN_LAUNCH_SEARCH(4, false); break;
-    case 8: ANN_LAUNCH_SEARCH(8, false); break;
-    case 16: ANN_LAUNCH_SEARCH(16, false); break;
-    default: ANN_LAUNCH_SEARCH(32, false); break;
+      if (NETWORK && search_network(a)) return launch_search_instance<KIND, VEC, NCH, 1, EPS, OWN, NETWORK>(a, T, s, plan);
+      return launch_search_instance<KIND, VEC, NCH, 1, EPS, OWN, false>(a, T, s, plan);
+    case 2: return launch_search_instance<KIND, VEC, NCH, 2, EPS, OWN, false>(a, T, s, plan);
+    case 4: return launch_search_instance<KIND, VEC, NCH, 4, EPS, OWN, false>(a, T, s, plan);
+    case 8: return launch_search_instance<KIND, VEC, NCH, 8, EPS, OWN, false>(a, T, s, plan);
+    case 16: return launch_search_instance<KIND, VEC, NCH, 16, EPS, OWN, false>(a, T, s, plan);
+    default: return launch_search_instance<KIND, VEC, NCH, 32, EPS, OWN, false>(a, T, s, plan);
   }
-#undef ANN_LAUNCH_SEARCH
-  return hipGetLastError();
 }
 
 }  // namespace annmi

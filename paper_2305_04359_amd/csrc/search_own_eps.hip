@@ -6,12 +6,12 @@
 namespace annmi {
 
 template <int KIND, int VEC, int NCH>
-static hipError_t launch_own_eps(const SearchArgs& a, const VecTable& T, hipStream_t s) {
-  return launch_search_variant<KIND, VEC, NCH, true, true>(a, T, s);
+static hipError_t launch_own_eps(const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan) {
+  return launch_search_variant<KIND, VEC, NCH, true, true>(a, T, s, plan);
 }
 
-hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s) {
-  ANN_DISPATCH_CFG(launch_own_eps, a, T, s);
+hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan) {
+  ANN_DISPATCH_CFG(launch_own_eps, a, T, s, plan);
 }
 
 }  // namespace annmi

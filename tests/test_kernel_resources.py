@@ -58,16 +58,42 @@ def test_own_start_searches_keep_eight_waves(kernels):
     assert found and all(f["vgpr_count"] <= 64 for f in found.values())
 
 
-def test_filter_sizes_match_the_registers(kernels):
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,metric,d,nch", [
+    ("uint8", 0, 128, 1), ("uint8", 0, 200, 2), ("uint8", 0, 400, 4), ("int8", 0, 100, 1), ("int8", 0, 256, 2), ("int8", 0, 512, 4),
+    ("float32", 0, 48, 2), ("float32", 0, 100, 4), ("float32", 0, 144, 6), ("float32", 0, 200, 7), ("float32", 0, 256, 8),
+    ("float32", 1, 64, 2), ("float32", 1, 128, 4), ("float32", 1, 192, 6), ("float32", 1, 224, 7), ("float32", 1, 240, 8)])
+def test_filter_sizes_match_the_registers(kernels, env, dtype, metric, d, nch):
     """The visited filter takes the LDS that the waves of search_kernel<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK>
-    leave to each other: the waves per SIMD that search.hip assumes are those of the registers, give or take one
-    where variants differ."""
-    def assumed(nch, nslot, own):
-        if nslot <= 2:
-            return 8 if nch == 1 else 7 if nch == 2 else (6 if own else 5) if nch == 4 else 5 if nch == 6 or (nch == 7 and (own or nslot == 1)) else 4
-        return 5 if nch <= 2 else (5 if own else 4) if nch == 4 else 4
-
-    for a, f in _named(kernels, "search_kernel").items():
-        if a[3] <= 4 and a[5]:
-            waves = min(8, 512 // (-(-f["vgpr_count"] // 8) * 8))
-            assert abs(waves - assumed(a[2], a[3], a[6])) <= (2 if a[3] == 4 and a[4] else 1), (a, f)
+    leave to each other: what the library's rule gives for every instance, against the registers of its
+    metadata.  A compute unit has 160 KB, handed out in units of 1,280 bytes, and four SIMDs."""
+    import numpy as np
+    _, A, _ = env
+    found = _named(kernels, "search_kernel")
+    code = {"uint8": A.U8, "int8": A.I8, "float32": A.F32}[dtype]
+    kind = {"uint8": 0, "int8": 1, "float32": 2 + metric}[dtype]
+    seen = set()
+    for n, Rs in ((100, (32, 48, 64)), ((1 << 20) + 1, (1,)), ((1 << 22) + 1, (1,)), ((1 << 23) + 1, (1,))):
+        if n > 100 and (dtype, d) not in (("uint8", 128), ("uint8", 200), ("float32", 200)):
+            continue
+        for R in Rs:
+            g = A.ann_graph_from_host(np.full((n, R), 0xFFFFFFFF, np.uint32), d, code, metric, 0)
+            for L in (7, 8, 20, 60, 64, 65, 100, 128, 129, 200, 256):
+                for eps in (-1.0, 0.1):
+                    for own in (0, 1):
+                        for nq in (200, 20000):
+                            waves, words, bits = g.search_filter(nq, L, eps, own)
+                            nslot = 1 if L <= 64 else 2 if L <= 128 else 4
+                            net = nslot == 1 and (R >= 64 or R > 32 and (L <= 24 or eps >= 0) or nq <= 256)
+                            net = net and not (own and kind >= 2 and nch <= 2)
+                            a = (kind, 16, nch, nslot, int(eps >= 0), int(bits == 16), own, int(net))
+                            seen.add(a)
+                            # (where 16-bit tags do not fit the first instance's table, the other instance's decides)
+                            either = [a] + ([a[:5] + (0,) + a[6:]] if n > 100 else [])
+                            assert waves in [min(8, 512 // (-(-found[x]["vgpr_count"] // 8) * 8)) for x in either], (a, waves)
+                            if nslot == 4 or (nslot == 2 and n > 1 << 22):
+                                waves = min(waves, 6)
+                            share = 160 * 1024 // (4 * waves) // 1280 * 1280
+                            assert words == (512 if L < 8 else min(2048, (share - 512 * nslot - 512) // 16 * 4)), (a, n, words)
+                            assert bits == 16 or n > 100
+    assert {a[3:] for a in seen if a[5]} >= {a[3:] for a in found if a[0] == kind and a[2] == nch and a[3] <= 4 and a[5]}
