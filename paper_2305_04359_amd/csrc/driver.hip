@@ -89,9 +89,9 @@ bool make_cfg(uint32_t d, int dtype, int metric, DistCfg* cfg, std::string* why)
       return false;
     }
     // rows of 5 to 7 pieces per lane (132 to 224 floats) run instances of 6 or 7: a kernel's registers
-    // grow with the pieces, and the empty ones cost load and FMA slots (with the prune walk's rows
-    // requested ahead, builds at R = 64, L = 128: 60,000 points of 160 floats 102 -> 78 ms; the prune
-    // kernel no longer spills.  Batches of 10,000 queries on 200 floats are at the HBM rate either way).
+    // grow with the pieces, and the empty ones cost load and FMA slots (builds at R = 64, L = 128, when the prune
+    // walked on the vector units: 60,000 points of 160 floats 102 -> 78 ms.  Batches of 10,000 queries on 200
+    // floats are at the HBM rate either way).
     if (nch == 8 && per_lane < 8) nch = per_lane < 6 ? 6 : (int)per_lane;
   } else if (nch > 4) {
     *why = "u8/i8 rows above 512 bytes are not supported";

@@ -604,7 +604,10 @@ struct F32PruneOk {
 
 // Waves per SIMD of the prune kernel: what its walk's registers leave room for.  Byte rows above 128 bytes
 // hold a block, the next one and a slice of selected rows, 32 registers each; float rows a block of
-// candidates and a tile of selected rows, 8 * NCH registers each, beside 16 of products.
+// candidates and a tile of selected rows, 8 * NCH registers each, beside 16 of products.  Squared L2 with seven
+// pieces lacks five registers for three waves; they are put aside once per block of candidates, which costs
+// less than the third wave brings (prune of 300,000 points of 200 floats, R = 64: 18.8 ms, by two waves 19.3; of
+// a million at R = 32 20.8 and 22.1).
 template <int KIND, int VEC, int NCH>
 struct PruneWaves {
   static constexpr int value = F32PruneOk<KIND, VEC, NCH>::value ? (NCH <= 4 ? 4 : NCH <= 7 ? 3 : 2)

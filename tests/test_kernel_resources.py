@@ -58,6 +58,12 @@ def test_own_start_searches_keep_eight_waves(kernels):
     assert found and all(f["vgpr_count"] <= 64 for f in found.values())
 
 
+def test_spills(kernels):
+    """No kernel keeps registers in memory, but for the one whose third wave is worth it (PruneWaves)."""
+    spills = {k: f["vgpr_spill_count"] for k, f in kernels.items() if f["vgpr_spill_count"]}
+    assert set(spills) <= {("prune_kernel", (2, 16, 7))} and all(n <= 8 for n in spills.values()), spills
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,metric,d,nch", [
     ("uint8", 0, 128, 1), ("uint8", 0, 200, 2), ("uint8", 0, 400, 4), ("int8", 0, 100, 1), ("int8", 0, 256, 2), ("int8", 0, 512, 4),
