@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<K
       bitonic_sort_keys(cand, n2, lane);
       bool done = false;
       if constexpr (kMfma) {
-        if (a.use_mfma) {
+        if (MfmaPruneOk<KIND, VEC, NCH>::always || a.use_mfma) {
           kept = prune_sorted_mfma<KIND, VEC, NCH>(T, M, cand, total, a.R, a.a16, out, lane, pair_evals);
           done = true;
         }
@@ -1048,8 +1048,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<K
       }
       if constexpr (kF32)
         kept = prune_sorted_f32<KIND, VEC, NCH>(T, F, T.base + (u64)b * T.row_bytes, cand, total, a.R, a.af, out, lane, pair_evals);
-      else if (!done)
-        kept = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand, total, a.R, al, out, lane, pair_evals);
+      else if constexpr (!MfmaPruneOk<KIND, VEC, NCH>::always)
+        if (!done) kept = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand, total, a.R, al, out, lane, pair_evals);
     } else {
       // (the staged-vector areas are laid out for the walk in use; the minimum-search walk reads
       // the selected vectors from device memory when the matrix-core layout is active)
@@ -1109,7 +1109,7 @@ hipError_t launch_merge(const DistCfg& cfg, const MergeArgs& a, u32 grid, hipStr
 bool gram_path_ok(const DistCfg& cfg) { return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256; }
 u32 gram_path_tmax() { return SM_TMAX; }
 bool mfma_prune_ok(u32 R, const DistCfg& cfg) {
-  return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256 && mfma_lds_bytes(R, (u32)cfg.row_bytes) <= 24576u;
+  return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256 && mfma_lds_bytes(R, (u32)cfg.row_bytes) <= MFMA_LDS_MAX;
 }
 u32 prune_stage_bytes(u32 R, const DistCfg& cfg) { return cfg.kind <= 1 ? stage_bytes(R, (u32)cfg.row_bytes, STAGE_BUDGET) : 0u; }
 u32 fast_path_amax(const DistCfg& cfg) { return cfg.nch <= 2 ? 4u : (cfg.nch <= 4 ? 2u : 1u); }

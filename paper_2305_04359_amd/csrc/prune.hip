@@ -61,15 +61,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PruneWaves<K
     bool done = false;
     cnt = 0;
     if constexpr (kMfma) {
-      if (a.use_mfma) {
+      if (MfmaPruneOk<KIND, VEC, NCH>::always || a.use_mfma) {
         cnt = prune_sorted_mfma<KIND, VEC, NCH>(T, M, cand_lds, nv, a.R, a.a16, out, lane, pair_evals);
         done = true;
       }
     }
     if constexpr (kF32)
       cnt = prune_sorted_f32<KIND, VEC, NCH>(T, F, T.base + (u64)p * T.row_bytes, cand_lds, nv, a.R, a.af, out, lane, pair_evals);
-    else if (!done)
-      cnt = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand_lds, nv, a.R, al, out, lane, pair_evals);
+    else if constexpr (!MfmaPruneOk<KIND, VEC, NCH>::always)
+      if (!done) cnt = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand_lds, nv, a.R, al, out, lane, pair_evals);
   } else {
     for (u32 i = lane; i < nv; i += 64) vis[i] &= ~1ull;
     __syncthreads();

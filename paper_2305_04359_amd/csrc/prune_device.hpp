@@ -170,8 +170,9 @@ __device__ __forceinline__ bool removes_pieces(i32 thr, const QueryRegs<KIND, VE
 }
 
 // cand[0..m): keys (distance to p | id), ids distinct, p absent, SORTED ascending.
-// Selected ids go to out[0..return) in selection order.  Byte rows of more than 256 bytes come here; the
-// walks on the matrix cores further down take the others.  blk: LDS for 8 rows of st.stride bytes
+// Selected ids go to out[0..return) in selection order.  Byte rows of 257 to 512 bytes come here, and rows of up to
+// 128 bytes that are no multiple of 32 where R is above 128 (mfma_prune_ok: copies of the selected rows beyond
+// 24 KB of LDS); the walks on the matrix cores further down take the others.  blk: LDS for 8 rows of st.stride bytes
 // plus 8 norms (used even when the selected vectors themselves are not staged).
 template <int KIND, int VEC, int NCH>
 __device__ __forceinline__ u32 prune_sorted(const VecTable& T, const SelStage& st, unsigned char* blk,
@@ -352,6 +353,7 @@ constexpr u32 MM_BLOCK = 32;  // candidates per block
 template <int KIND, int VEC, int NCH>
 struct MfmaPruneOk {
   static constexpr bool value = KindTraits<KIND>::is_int && (8 * NCH * VEC <= 256);
+  static constexpr bool always = value && NCH == 2;  // at every R: the walk above is not compiled
 };
 
 // LDS areas of the matrix-core walk (all 16-byte aligned)
@@ -366,12 +368,14 @@ struct MfmaLds {
   i32* cthr;           // 32: removal thresholds of the block's candidates
   u32* cid;            // 32
 };
-__host__ __device__ inline u32 mfma_rows(u32 R) { return (R + 31u) & ~31u; }
-__host__ __device__ inline bool mfma_sel_in_lds(u32 row_bytes) { return row_bytes <= 128u && (row_bytes % 32u) != 0u; }
-__host__ __device__ inline u32 mfma_lds_bytes(u32 R, u32 row_bytes) {
+__host__ __device__ constexpr u32 mfma_rows(u32 R) { return (R + 31u) & ~31u; }
+__host__ __device__ constexpr bool mfma_sel_in_lds(u32 row_bytes) { return row_bytes <= 128u && (row_bytes % 32u) != 0u; }
+__host__ __device__ constexpr u32 mfma_lds_bytes(u32 R, u32 row_bytes) {
   return (mfma_sel_in_lds(row_bytes) ? mfma_rows(R) * mm_stride(row_bytes) : 0u) + mfma_rows(R) * 4u +
          MM_BLOCK * mm_stride(row_bytes) + 3u * MM_BLOCK * 4u;
 }
+constexpr u32 MFMA_LDS_MAX = 24576;  // beyond, the walk leaves room for too few waves
+static_assert(mfma_lds_bytes(512, 256) <= MFMA_LDS_MAX, "rows above 128 bytes have no other walk (MfmaPruneOk::always)");
 __device__ __forceinline__ MfmaLds mfma_lds_carve(unsigned char* base, u32 R, u32 row_bytes) {
   MfmaLds M;
   const bool in_lds = mfma_sel_in_lds(row_bytes);

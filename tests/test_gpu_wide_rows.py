@@ -23,3 +23,17 @@ def test_graphs_equal_the_oracles(env, d, dtype, lo, hi):
         og, start = O.build(O.Dataset(pts_h[:n], 0), R, L, alpha, seed=3, threads=0)
         g = A.ann_build(dev(torch, pts_h[:n]), R, L, alpha, seed=3)
         assert int(g.info().start) == start and (g.neighbors() == og).all()
+
+
+@pytest.mark.parametrize("d,R", [(80, 128), (80, 129), (112, 150), (96, 150), (144, 150), (256, 200), (272, 130)])
+def test_many_edges_per_vertex(env, d, R):
+    """Each walk of the prune where R is long: copies of the selected rows that fill their LDS or no longer fit it
+    (rows of 80 and 112 bytes on both sides of R = 128), rows read from device memory, rows above 256 bytes."""
+    torch, A, O = env
+    rng = np.random.default_rng(d + R)
+    pts_h = rng.integers(0, 256, (1200, d)).astype(np.uint8)  # (nothing clusters: few candidates are removed)
+    say(f"many edges d={d} R={R}")
+    og, start = O.build(O.Dataset(pts_h, 0), R, 220, 1.0, seed=3, threads=0)
+    g = A.ann_build(dev(torch, pts_h), R, 220, 1.0, seed=3)
+    assert int(g.info().start) == start and (g.neighbors() == og).all()
+    assert ((og != 0xFFFFFFFF).sum(1) > 32).any()
