@@ -427,9 +427,16 @@ int ann_hcnng_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dt
                     uint32_t T, uint32_t Ls, uint32_t s, uint32_t l, uint32_t R, float alpha, uint64_t seed,
                     void* stream, ann_graph** out);
 
-/* The same with the caller's allocator.  A build holds up to 250 bytes per
- * point and tree (32 million of them at a time) while it runs; hipMalloc and
- * hipFree of that size now and then take longer than the build itself.       */
+/* The same with the caller's allocator.  Beside the graph (and the padded points) a
+ * build holds while it runs, in bytes and apart from small tables,
+ *   (28 + 6 l + stride (1 + 128 / Ls) + 100 / Ls) G n  for the trees that are cut side by
+ *                 side, G = max(1, min(T, floor(2^25 / n))); stride = the bytes of a
+ *                 row rounded up to a multiple of 32; more where a group splits
+ *                 into more tiles of 32 points than that has room for
+ *   33 T n        for the edges of all T trees
+ *   48 n          and, where s T is above 4,096, 8 bytes per distinct edge
+ * which is 8.0 GB at n = 10^6 rows of 128 bytes, T = 30, Ls = 1000, l = 10.  hipMalloc
+ * and hipFree of that size now and then take longer than the build itself.       */
 typedef struct {
   ann_alloc_fn alloc;     /* device memory for the graph and all scratch; NULL =    */
   ann_free_fn free;       /* hipMalloc / hipFree; both or neither                   */

@@ -574,7 +574,10 @@ def ann_hnsw_search(index: Hnsw, points, queries, k, L, eps=-1.0, ids_out=None, 
 
 def ann_hcnng_build(points, T, Ls, s, l, R, alpha, seed=1, metric=L2SQ, allocator="torch") -> Graph:
     """The clustering-based builder of Sec. 4.3 over a device tensor of points.
-    The graph and the build's scratch are PyTorch's memory unless allocator=None."""
+    The graph and the build's scratch are PyTorch's memory unless allocator=None.  The scratch (8 GB for a
+    million rows of 128 bytes and 30 trees, see ann.h) stays in PyTorch's cache after the call, for the
+    next one or other tensors; torch.cuda.empty_cache() gives it back to the driver, and with allocator=None
+    it goes back by itself."""
     points = _dev2d(points, "points")
     o = HcnngOpts()
     al = _use_allocator(o, allocator)

@@ -183,3 +183,37 @@ def test_memory_is_first_used_on_its_stream(env):
     for w, x in zip(want, got):
         assert torch.equal(w, x) if isinstance(w, torch.Tensor) else (w == x).all()
     assert len(al.live) == 0
+
+
+@pytest.mark.parametrize("dtype,d,n,T,Ls,l", [("uint8", 128, 40000, 6, 1000, 10), ("int8", 40, 20000, 5, 100, 16), ("float32", 256, 20000, 4, 500, 16),
+                                             ("uint8", 128, 20000, 3, 8, 4)])
+def test_cluster_build_holds_what_the_header_says(env, dtype, d, n, T, Ls, l):
+    """ann_hcnng_opts names the bytes that a build holds while it runs."""
+    from test_gpu_boundary import CountingAllocator
+    torch, A, _ = env
+    rng = np.random.default_rng(9)
+    pts = dev(torch, rng.standard_normal((n, d)).astype(dtype) if dtype == "float32" else rng.integers(0, 100, (n, d)).astype(dtype))
+    al = CountingAllocator(A, torch)
+    plain, live, held = al.alloc, {}, [0]
+    give_back = al.free
+
+    def _alloc(nbytes, stream, user):
+        p = plain(nbytes, stream, user)
+        live[p] = nbytes
+        held[0] = max(held[0], sum(live.values()))
+        return p
+
+    def _free(ptr, user):
+        del live[ptr]
+        give_back(ptr, user)
+
+    al.inner, al.alloc, al.free = (plain, give_back), A.ALLOC_FN(_alloc), A.FREE_FN(_free)
+    R = 24
+    g = A.ann_hcnng_build(pts, T, Ls, 3, l, R, 1.2, seed=3, allocator=al)
+    row = d * pts.element_size()
+    stride, G = (row + 31) // 32 * 32, max(1, min(T, (1 << 25) // n))
+    said = (28 + 6 * l + stride * (1 + 128 / Ls) + 100 / Ls) * G * n + 33 * T * n + 48 * n
+    graph = n * (4 * R + 4) + (1 << 21)
+    padded = n * 2 * row if dtype != "float32" and d % 16 else 0
+    assert 0.9 * said < held[0] < 1.01 * said + graph + padded, (held[0], said)
+    del g
