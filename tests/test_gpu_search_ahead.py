@@ -70,7 +70,8 @@ def test_requests_ahead_start_vertices(env):
 
 @pytest.mark.parametrize("n", [(1 << 20) + 1, (1 << 22) + 1])
 def test_requests_ahead_many_points(env, n):
-    """Ids of 21 and 23 bits: 16-bit tags in this kernel's filter, in the smaller one for the first graph only."""
+    """Ids of 21 and 23 bits, the most that 16-bit tags hold in the filters of this kernel and of the one for
+    larger launches."""
     torch, A, _ = env
     g = torch.Generator(device="cuda")
     g.manual_seed(8)

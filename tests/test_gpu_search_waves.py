@@ -88,10 +88,10 @@ def test_four_waves_per_search(env):
                 assert torch.equal(i, ids[:nq]) and torch.equal(d, dists[:nq])
 
 
-@pytest.mark.parametrize("n", [(1 << 20) + 1, (1 << 22) + 1])
+@pytest.mark.parametrize("n", [(1 << 20) + 1, (1 << 22) + 1, (1 << 23) + 1])
 def test_waves_per_search_many_points(env, n):
-    """Ids of 21 and 23 bits: the several-waves kernel's filter keeps 16-bit tags, the one-wave kernel's
-    smaller one does so for the first graph only."""
+    """Ids of 21, 23 and 24 bits: the several-waves kernel's filter keeps 16-bit tags, the one-wave kernel's
+    smaller one does not for the last graph."""
     torch, A, _ = env
     g = torch.Generator(device="cuda")
     g.manual_seed(8)
