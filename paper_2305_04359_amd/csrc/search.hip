@@ -141,8 +141,8 @@ static u32 search_waves(const DistCfg& cfg, const SearchArgs& a) {
   return graph > LAST_LEVEL_CACHE ? 4 : 1;
 }
 
-// Whether the next hops' memory is requested ahead.  It costs registers (five waves per SIMD instead of eight)
-// and instructions (three entries of the beam looked up per hop, one in thirteen expansions undone), and
+// Whether the next hops' memory is requested ahead.  It costs registers and LDS (88 to 116 registers leave four or
+// five waves per SIMD, the filter of 480 buckets 18 waves on a compute unit, instead of 32) and instructions (three entries of the beam looked up per hop, one in thirteen expansions undone), and
 // hides one of a hop's two trips to memory: it pays while the chip is half empty.  Speed against one wave
 // each without it, uint8 and int8 rows, 5,000 to 500,000 points, R = 32 to 64:
 //  - 513 to 3,000 searches: 0.98 to 1.28 (2,000 uint8 searches at L = 128, R = 64: 233 -> 203 us on 100,000
