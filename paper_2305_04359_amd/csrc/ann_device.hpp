@@ -156,6 +156,8 @@ template <int KIND, int VEC, int NCH>
 struct QueryRegs {
   Piece<VEC> q[NCH];
   i32 qq;  // <q,q> for the integer kinds
+  static constexpr bool in_lds = false;
+  __device__ __forceinline__ Piece<VEC> piece(int u) const { return q[u]; }
 };
 
 // The pieces only (no arithmetic on them, so the loads can stay in flight) ...
@@ -196,8 +198,8 @@ __device__ __forceinline__ QueryRegs<KIND, VEC, NCH> load_query(const char* row,
 }
 
 // Distance key from the lane-local pieces of one row; all 8 lanes of the group get the result.
-template <int KIND, int VEC, int NCH>
-__device__ __forceinline__ u32 distance_key(const QueryRegs<KIND, VEC, NCH>& Q, const Piece<VEC> (&x)[NCH]) {
+template <int KIND, int VEC, int NCH, class Query>
+__device__ __forceinline__ u32 distance_key(const Query& Q, const Piece<VEC> (&x)[NCH]) {
   if constexpr (KIND == K_U8) {
     u32 xx = 0, qx = 0;
 #pragma unroll
@@ -221,11 +223,16 @@ __device__ __forceinline__ u32 distance_key(const QueryRegs<KIND, VEC, NCH>& Q, 
     return dkey_from_int(group_sum(xx - 2 * qx) + Q.qq);
   } else {
     float acc = 0.0f;
+    Piece<VEC> next = Q.piece(0);
 #pragma unroll
-    for (int u = 0; u < NCH; ++u)
+    for (int u = 0; u < NCH; ++u) {
+      const Piece<VEC> q = next;
+      if (u + 1 < NCH) next = Q.piece(u + 1);
+      // (one piece ahead and no more: left alone, the compiler reads all of them before the first sum)
+      if constexpr (Query::in_lds) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < VEC / 4; ++i) {
-        float a = __uint_as_float(Q.q[u].w[i]);
+        float a = __uint_as_float(q.w[i]);
         float b = __uint_as_float(x[u].w[i]);
         if constexpr (KIND == K_F32_L2) {
           float t = a - b;
@@ -234,6 +241,7 @@ __device__ __forceinline__ u32 distance_key(const QueryRegs<KIND, VEC, NCH>& Q, 
           acc = __builtin_fmaf(a, b, acc);
         }
       }
+    }
     acc = group_sum(acc);
     return dkey_from_float(KIND == K_F32_IP ? -acc : acc);
   }
@@ -256,8 +264,8 @@ __device__ __forceinline__ u32 cand_of_lane(int lane) { return (u32)(8 * (lane &
 // candidate reads candidate 0's row again (a line the pass fetches anyway) instead of being
 // masked off and handed zeros: no compare, branch or register clearing per pass; its result is
 // never looked at.
-template <int KIND, int VEC, int NCH, int PBX, bool FULL, class IdAt>
-__device__ __forceinline__ void eval_passes(const VecTable& T, const QueryRegs<KIND, VEC, NCH>& Q, IdAt id_at,
+template <int KIND, int VEC, int NCH, int PBX, bool FULL, class Query, class IdAt>
+__device__ __forceinline__ void eval_passes(const VecTable& T, const Query& Q, IdAt id_at,
                                             u32 cnt, u32 t0, int sub, u32 grp, u32& result) {
   Piece<VEC> x[PBX][NCH];
 #pragma unroll
@@ -286,8 +294,8 @@ __device__ __forceinline__ void eval_passes(const VecTable& T, const QueryRegs<K
   }
 }
 
-template <int KIND, int VEC, int NCH, bool FULL, class IdAt>
-__device__ __forceinline__ u32 eval_up_to_64_impl(const VecTable& T, const QueryRegs<KIND, VEC, NCH>& Q,
+template <int KIND, int VEC, int NCH, bool FULL, class Query, class IdAt>
+__device__ __forceinline__ u32 eval_up_to_64_impl(const VecTable& T, const Query& Q,
                                                   IdAt id_at, u32 cnt, int lane) {
   constexpr int PB = PassBatch<VEC, NCH>::value;
   const int sub = lane & (LPC - 1);
@@ -325,16 +333,16 @@ __device__ __forceinline__ u32 eval_up_to_64_impl(const VecTable& T, const Query
   return result;
 }
 
-template <int KIND, int VEC, int NCH, class IdAt>
-__device__ __forceinline__ u32 eval_up_to_64(const VecTable& T, const QueryRegs<KIND, VEC, NCH>& Q,
+template <int KIND, int VEC, int NCH, class Query, class IdAt>
+__device__ __forceinline__ u32 eval_up_to_64(const VecTable& T, const Query& Q,
                                              IdAt id_at, u32 cnt, int lane) {
   return eval_up_to_64_impl<KIND, VEC, NCH, false>(T, Q, id_at, cnt, lane);
 }
 
 // The same for callers that pass cnt >= 1 and whose id_at(0) is a vertex: rows that fill every
 // lane's pieces take the unmasked passes.
-template <int KIND, int VEC, int NCH, class IdAt>
-__device__ __forceinline__ u32 eval_up_to_64_full_rows(const VecTable& T, const QueryRegs<KIND, VEC, NCH>& Q,
+template <int KIND, int VEC, int NCH, class Query, class IdAt>
+__device__ __forceinline__ u32 eval_up_to_64_full_rows(const VecTable& T, const Query& Q,
                                                        IdAt id_at, u32 cnt, int lane) {
   if (T.npieces == (u32)(LPC * NCH)) return eval_up_to_64_impl<KIND, VEC, NCH, true>(T, Q, id_at, cnt, lane);
   return eval_up_to_64_impl<KIND, VEC, NCH, false>(T, Q, id_at, cnt, lane);

@@ -26,3 +26,20 @@
     }                                                                                          \
   } while (0)
 
+
+// The same for float rows with sketches (sketch_bytes): <KIND, NCH, SK>.
+#define ANN_DISPATCH_SKETCH(FN, ...)                                                           \
+  do {                                                                                         \
+    const int key_ = cfg.kind * 1000 + cfg.nch * 10 + (int)(sketch_bytes(cfg) / 128u);         \
+    switch (key_) {                                                                            \
+      case K_F32_L2 * 1000 + 41: return FN<K_F32_L2, 4, 1>(__VA_ARGS__);                       \
+      case K_F32_L2 * 1000 + 62: return FN<K_F32_L2, 6, 2>(__VA_ARGS__);                       \
+      case K_F32_L2 * 1000 + 72: return FN<K_F32_L2, 7, 2>(__VA_ARGS__);                       \
+      case K_F32_L2 * 1000 + 82: return FN<K_F32_L2, 8, 2>(__VA_ARGS__);                       \
+      case K_F32_IP * 1000 + 41: return FN<K_F32_IP, 4, 1>(__VA_ARGS__);                       \
+      case K_F32_IP * 1000 + 62: return FN<K_F32_IP, 6, 2>(__VA_ARGS__);                       \
+      case K_F32_IP * 1000 + 72: return FN<K_F32_IP, 7, 2>(__VA_ARGS__);                       \
+      case K_F32_IP * 1000 + 82: return FN<K_F32_IP, 8, 2>(__VA_ARGS__);                       \
+      default: return hipErrorInvalidConfiguration;                                            \
+    }                                                                                          \
+  } while (0)

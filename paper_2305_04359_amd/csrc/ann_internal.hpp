@@ -80,6 +80,7 @@ struct SearchArgs {
   u64 n;             // vertices of the graph
   u32 filter_given;  // non-zero: the filter's size is the caller's choice (log2 of its 32-bit words)
   u32 shares_chip;   // non-zero: other searches run beside these (parts of a batch)
+  const char* sketch;  // sketches of the vertices (sketch_bytes each), or null
 };
 
 // The walk of a query through the upper layers of the layered index (Sec. 4.2): a search with
@@ -178,6 +179,14 @@ struct SearchPlan {
   u32 filter_words, tag_width;
 };
 hipError_t plan_search(const DistCfg& cfg, const SearchArgs& a, SearchPlan* plan);
+// sketches of float rows (sketch.hpp): bytes of one (0: rows of this kind have none), and the ones of the rows
+// first .. first + count - 1 of an array
+u32 sketch_bytes(const DistCfg& cfg);
+constexpr u32 SEARCH_SKETCH_BEAM = 128;  // the longest beam of a search that reads sketches
+constexpr u32 SEARCH_SKETCH_MIN = 1024;  // launches of more searches than this read them
+// whether making them for all n rows is repaid by that many searches (queries, or the searches of an insertion)
+bool search_sketch_pays(const DistCfg& cfg, u64 n, u64 searches, u32 L, bool query);
+hipError_t launch_sketch_rows(const DistCfg& cfg, const void* rows, u64 first, u64 count, void* out, hipStream_t s);
 hipError_t launch_descend(const DistCfg& cfg, const DescendArgs& a, hipStream_t s);
 hipError_t launch_prune(const DistCfg& cfg, const PruneArgs& a, hipStream_t s);
 hipError_t launch_plan(const MergeArgs& a, hipStream_t s);

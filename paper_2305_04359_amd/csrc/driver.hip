@@ -238,6 +238,7 @@ int resolve_queries(const ann_graph* g, const void* queries_dev, u64 nq, hipStre
       // an earlier call, on whatever stream it was issued, may still read the old buffer
       HIP_TRY(hipDeviceSynchronize());
       g->al.put(g->qpad_buf);
+  g->al.put(g->sketch_buf);
       g->qpad_buf = nullptr;
       g->qpad_rows = 0;
     }
@@ -280,6 +281,49 @@ void collect_phase_times(ann_graph* g, PhaseTimer& tm) {
 
 // batches of at least this many points run step 1 in three parts (see batch_insert)
 constexpr u64 STEP1_PARTS_MIN = 8192;
+
+// Sketches of the graph's points for the searches of this call, `searches` in all (see search_sketch_pays): into
+// `buf`, and g->sketch until the caller takes it down.  Without the memory the searches do without.
+int make_sketches(ann_graph* g, const void* points, u64 searches, u32 L, DevBuf& buf, hipStream_t st) {
+  g->sketch = nullptr;
+  if (!search_sketch_pays(g->cfg, g->n, searches, L, false)) return ANN_OK;
+  if (buf.alloc(g->n * sketch_bytes(g->cfg)) != hipSuccess) {
+    (void)hipGetLastError();
+    return ANN_OK;
+  }
+  HIP_TRY(launch_sketch_rows(g->cfg, points, 0, g->n, buf.p, st));
+  g->sketch = buf.p;
+  return ANN_OK;
+}
+
+// The same for a call that answers nq queries: made anew by every call, in memory that the graph keeps.
+int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStream_t st, const void** out) {
+  *out = nullptr;
+  if (nq <= SEARCH_SKETCH_MIN || !search_sketch_pays(g->cfg, g->n, nq, L, true)) return ANN_OK;
+  // (a captured call must not allocate, and what it captures may outlive the memory)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return ANN_OK;
+  }
+  if (g->sketch_cap < g->n) {
+    if (g->sketch_buf) {
+      HIP_TRY(hipDeviceSynchronize());  // earlier calls may still read the old ones
+      g->al.put(g->sketch_buf);
+      g->sketch_buf = nullptr;
+      g->sketch_cap = 0;
+    }
+    if (g->al.on(st).get(&g->sketch_buf, (size_t)g->n * sketch_bytes(g->cfg)) != hipSuccess) {
+      (void)hipGetLastError();
+      g->sketch_buf = nullptr;
+      return ANN_OK;
+    }
+    g->sketch_cap = g->n;
+  }
+  HIP_TRY(launch_sketch_rows(g->cfg, points, 0, g->n, g->sketch_buf, st));
+  *out = g->sketch_buf;
+  return ANN_OK;
+}
 
 // BatchInsert(P') of Alg. 3 for the b ids in ids_host (device copy made here).
 // With `sync` the host waits after step 1 and redoes, with as much room as they need, the searches
@@ -328,6 +372,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   sa.k = 1;
   sa.n = g->n;
   sa.filter_given = g->hash_bits;
+  sa.sketch = static_cast<const char*>(g->sketch);
   sa.batch_counters = small;
   sa.eps16 = -1;
   sa.epsf = 0.0f;
@@ -589,8 +634,9 @@ int graph_scratch(ann_graph* g, u64 b, u32 L, hipStream_t st, BatchScratch** out
 }
 
 int query_launch(const ann_graph* g, const void* pts, const void* queries, const u32* qidx, u64 nq, u32 k, u32 L,
-                 float eps, const StartsArgs* starts, u32* out_ids, void* out_dists, hipStream_t st) {
+                 float eps, const StartsArgs* starts, u32* out_ids, void* out_dists, hipStream_t st, const void* sketch) {
   SearchArgs sa{};
+  sa.sketch = static_cast<const char*>(sketch);
   sa.points = static_cast<const char*>(pts);
   sa.graph = g->rows;
   sa.queries = static_cast<const char*>(queries);
@@ -1033,6 +1079,8 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   }
 
   const double t_order = now_ms();
+  DevBuf sketches;
+  SketchScope held{g};
   FailureWait wait;  // (the graph keeps its scratch; a later call may enlarge it)
   rc = grow_graph(g, n_total, st);
   if (rc) return rc;
@@ -1046,6 +1094,8 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   if (rc) return rc;
   const void* pts = nullptr;
   rc = resolve_points(g, points_dev, st, &pts);
+  if (rc) return rc;
+  rc = make_sketches(g, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, sketches, st);
   if (rc) return rc;
   const double t_alloc = now_ms();
   // Every batch waits on the host after step 1 (the check for visited lists that fit nowhere):
@@ -1134,7 +1184,8 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
       if (g) ann_graph_free(g);
     }
   } guard{g};
-  DevBuf order_dev;
+  DevBuf order_dev, sketches;
+  SketchScope held{g};
   BatchScratch S;
   FailureWait wait;
   rc = check_insert_params(g, L, alpha);
@@ -1218,6 +1269,8 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
   const void* pts = nullptr;
   rc = resolve_points(g, points_dev, st, &pts);
   if (rc) return rc;
+  rc = make_sketches(g, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, sketches, st);
+  if (rc) return rc;
 
   const double t_alloc = now_ms();
   // First try: every batch is issued without waiting for the previous one.  A search whose
@@ -1281,7 +1334,10 @@ int ann_search_eps(const ann_graph* g, const void* points_dev, const void* queri
   if (rc_) return rc_;
   rc_ = resolve_queries(g, queries_dev, nq, st_, &qsp);
   if (rc_) return rc_;
-  rc_ = query_launch(g, pts, qsp, nullptr, nq, k, L, eps, nullptr, ids_dev, dists_dev, st_);
+  const void* sketch = nullptr;
+  rc_ = query_sketches(g, pts, nq, L, st_, &sketch);
+  if (rc_) return rc_;
+  rc_ = query_launch(g, pts, qsp, nullptr, nq, k, L, eps, nullptr, ids_dev, dists_dev, st_, sketch);
   if (rc_) return rc_;
   return ANN_OK;
 } catch (...) {

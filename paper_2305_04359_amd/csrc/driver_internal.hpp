@@ -179,6 +179,11 @@ struct ann_graph {
   mutable annmi::u64 pad_done = 0;  // leading rows of pad_src that pad_buf holds
   mutable void* qpad_buf = nullptr;
   mutable annmi::u64 qpad_rows = 0;
+  // sketches of the points (float rows) for the searches of the call that is running, or null
+  const void* sketch = nullptr;
+  // memory for the ones that a call of ann_search makes, and the rows it has room for
+  mutable void* sketch_buf = nullptr;
+  mutable annmi::u64 sketch_cap = 0;
   // scratch of the insertions that follow the build (ann_insert_batch, ann_insert_points), kept
   // between calls: allocating and freeing it costs more than a batch of ten thousand points
   annmi::BatchScratch* scratch = nullptr;
@@ -306,6 +311,14 @@ struct StartsArgs {
   const u32* down = nullptr;
 };
 
+// takes the sketches of a call down at its end
+struct SketchScope {
+  ann_graph* g;
+  ~SketchScope() { g->sketch = nullptr; }
+};
+int make_sketches(ann_graph* g, const void* points, u64 searches, u32 L, DevBuf& buf, hipStream_t st);
+int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStream_t st, const void** out);
+
 int new_graph(u64 n, u32 d, int dtype, int metric, u32 R, ann_graph** out);
 int check_insert_params(const ann_graph* g, uint32_t L, float alpha);
 // the graph gets the vertices n..n_total-1, with empty rows (its arrays grow when they have to)
@@ -320,6 +333,7 @@ int finish_batches(ann_graph* g, BatchScratch& S, PhaseTimer& tm, hipStream_t st
 // One launch of the query search over `g` (points and queries already resolved to what the
 // kernels read); `starts` as in batch_insert; out_ids / out_dists may be null.
 int query_launch(const ann_graph* g, const void* pts, const void* queries, const u32* qidx, u64 nq, u32 k, u32 L,
-                 float eps, const StartsArgs* starts, u32* out_ids, void* out_dists, hipStream_t st);
+                 float eps, const StartsArgs* starts, u32* out_ids, void* out_dists, hipStream_t st,
+                 const void* sketch = nullptr);
 
 }  // namespace annmi

@@ -36,13 +36,13 @@ u32 search_lds_bytes(u32 L, u32 hash_buckets) { return search_nslot_for(L) * 64 
 // hundred million points, where tables of 1,024 and 512 words answer 1.7 to 2.3 times the queries
 // per second of tables of 4,096 and 8,192.  The table is never cut below 3/4 of the power of two.
 constexpr u32 LDS_UNIT = 1280;
-static u32 search_hash_buckets(u64 n, u32 L, u32 waves) {
+static u32 search_hash_buckets(u64 n, u32 L, u32 waves, u32 lds_more) {
   const u32 nslot = search_nslot_for(L);
   if (L < 8u) return 128;  // (over after a few hops: not worth clearing more)
   if (nslot <= 4u) {
     if ((nslot == 4u || (nslot == 2u && n > (1ull << 22))) && waves > 6u) waves = 6u;
     const u32 share = 163840u / (4u * waves) / LDS_UNIT * LDS_UNIT;
-    const u32 nb = (share - search_lds_bytes(L, 0)) / 16u;
+    const u32 nb = (share - search_lds_bytes(L, 0) - lds_more) / 16u;
     return nb < 512u ? nb : 512u;
   }
   u32 want = 8u * L, bits = 9;
@@ -81,8 +81,8 @@ void search_filter_mode(u64 n, u32 hash_buckets, u32* id_bits, u32* tag_width) {
   }
 }
 
-void search_set_filter(SearchArgs& a, u32 waves) {
-  a.hash_buckets = a.filter_given ? 1u << (a.filter_given - 2u) : search_hash_buckets(a.n, a.L, waves);
+void search_set_filter(SearchArgs& a, u32 waves, u32 lds_more) {
+  a.hash_buckets = a.filter_given ? 1u << (a.filter_given - 2u) : search_hash_buckets(a.n, a.L, waves, lds_more);
   search_filter_mode(a.n, a.hash_buckets, &a.id_bits, &a.tag_width);
 }
 
@@ -171,6 +171,11 @@ hipError_t launch_search(const DistCfg& cfg, const SearchArgs& a, hipStream_t s)
   const u32 waves = search_waves(cfg, a);
   if (waves > 1u) return launch_search_wide(cfg, a, T, waves, s);
   if (search_ahead(cfg, a)) return launch_search_ahead(cfg, a, T, s);
+  if (a.sketch != nullptr && a.L <= SEARCH_SKETCH_BEAM) {
+    const bool own = a.starts != nullptr || a.next_start != nullptr;
+    if (!own) return a.eps16 >= 0 ? launch_search_sketch_eps(cfg, a, T, s) : launch_search_sketch(cfg, a, T, s);
+    if (a.eps16 < 0) return launch_search_sketch_own(cfg, a, T, s);
+  }
   return launch_search_alone(cfg, a, T, s, nullptr);
 }
 

@@ -16,9 +16,11 @@
 #pragma once
 #include <atomic>
 #include <cstddef>
+#include <type_traits>
 
 #include "ann_device.hpp"
 #include "ann_internal.hpp"
+#include "sketch.hpp"
 #include "wave_sort.hpp"
 
 namespace annmi {
@@ -307,19 +309,44 @@ __device__ __forceinline__ void zero_batch_counters(u32* c) {
   c[11] = 0;
 }
 
+// The query of a search in registers, or (SK > 0) in LDS.
+template <int KIND, int VEC, int NCH>
+struct SearchQuery : QueryRegs<KIND, VEC, NCH> {
+  __device__ __forceinline__ SearchQuery(const QueryRegs<KIND, VEC, NCH>& Q, Piece<VEC>*, int)
+      : QueryRegs<KIND, VEC, NCH>(Q) {}
+};
+template <int KIND, int VEC, int NCH>
+struct SearchQueryLds {
+  const Piece<VEC>* mine;
+  __device__ __forceinline__ SearchQueryLds(const QueryRegs<KIND, VEC, NCH>& Q, Piece<VEC>* lds, int lane) {
+    if (lane < LPC) {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u) lds[LPC * u + lane] = Q.q[u];
+    }
+    __syncthreads();
+    mine = lds + (lane & (LPC - 1));
+  }
+  static constexpr bool in_lds = true;
+  __device__ __forceinline__ Piece<VEC> piece(int u) const { return mine[LPC * u]; }
+};
+
 // EPS: the (1 + eps) rule is compiled in.  TAG16: the filter holds 16-bit tags (graphs of up to
 // a few million points); the other two layouts share the second variant, so that their code does
 // not weigh on the registers of the first.
 // OWN: every search has a start vertex of its own and reports the closest vertex it found (the
 // layered index); compiled apart so that the flat graph's searches do not carry its arguments.
 // NETWORK: see beam_insert.
-template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK>
-__global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
+// SK: 16-byte pieces per lane of the vertices' sketches (0: there are none).  Once the beam is full, a row's
+// candidates whose sketch puts them certainly beyond the beam's last entry are dropped unread.
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK>
+__device__ __forceinline__ void search_one(const SearchArgs& a, const VecTable& T, const SketchTable& K) {
   extern __shared__ __align__(16) unsigned char smem[];
   u64* beam = reinterpret_cast<u64*>(smem);
   u64* skeys = beam + NSLOT * 64;  // survivors of one batch of candidates
   u32* cid = reinterpret_cast<u32*>(skeys);  // the batch's ids: dead once its keys are formed
-  u32* hash = reinterpret_cast<u32*>(skeys + 64);  // 16-byte aligned
+  // (SK) the query, which lives in LDS: a row that must be read is the rarer case, and the registers are waves
+  Piece<VEC>* qlds = reinterpret_cast<Piece<VEC>*>(skeys + 64);
+  u32* hash = reinterpret_cast<u32*>(qlds + (SK > 0 ? LPC * (NCH + 2 * SK) : 0));  // 16-byte aligned
 
   const int lane = threadIdx.x;
   const u32 qi = blockIdx.x;
@@ -340,8 +367,17 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
   const u32 L = a.L;
 
   const u32 qrow = a.qidx ? a.qidx[qi] : qi;
-  const QueryRegs<KIND, VEC, NCH> Q =
+  const QueryRegs<KIND, VEC, NCH> Qr =
       load_query<KIND, VEC, NCH>(a.queries + (u64)qrow * a.qrow_bytes, T.npieces, lane);
+  using Query = std::conditional_t<(SK > 0), SearchQueryLds<KIND, VEC, NCH>, SearchQuery<KIND, VEC, NCH>>;
+  const Query Q(Qr, qlds, lane);
+  SketchQuery SQ;
+  u32 sk_last = 0;  // where this lane reads the last of a sketch's pieces: its own, or that of the group's last lane
+  if constexpr (SK > 0) {
+    SQ = sketch_query<KIND, NCH, SK>(Qr, reinterpret_cast<uint4*>(qlds + LPC * NCH), lane);
+    const u32 sub = (u32)lane & (LPC - 1);
+    sk_last = (SK - 1) * 128u + (sub + 32u * (SK - 1) < T.npieces ? sub : LPC - 1u) * 16u;
+  }
 
   if constexpr (NCH == 1) {
     for (u32 i = lane; i < 4u * nb; i += 64) hash[i] = NONE_ID;
@@ -360,7 +396,14 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
     if (a.starts != nullptr) st = a.starts[a.slot != nullptr ? a.slot[qi] : qi];
   }
   {
-    u32 dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [st](u32) { return st; }, 1u, lane);
+    u32 dk;
+    if constexpr (SK > 0) {
+      if (lane == 0) cid[0] = st;
+      __syncthreads();
+      dk = eval_rows<KIND, NCH>(T, Q, cid, 1u, lane);
+    } else {
+      dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [st](u32) { return st; }, 1u, lane);
+    }
     dk = readlane_u32(dk, 0);
     if (lane == 0) {
       A[0] = make_key(dk, st);
@@ -382,6 +425,10 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
 
   u32 size = 1, nv = 0, evals = 1;
   u32 n_pass = 0, n_surv = 0, n_ins = 0;  // statistics only
+  // SK: whether fewer than half of the last row's new candidates entered the beam.  On the way in from the
+  // start vertex most do, and reading the sketches first would only put more bytes and another trip to
+  // memory in front of them.
+  bool sparse = false;
   // where the visited list goes: the search's own slot, later perhaps a spill chunk
   u64* vptr = a.vis != nullptr ? a.vis + (u64)qi * a.vis_cap : nullptr;
   u32 vcap = a.vis_cap;
@@ -467,25 +514,50 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
         }
       }
       const u64 fm = ballot(fresh);
-      const u32 m = __builtin_popcountll(fm);
+      u32 m = __builtin_popcountll(fm);
       if (m) {
         const u32 rank = __builtin_popcountll(fm & lanemask_lt(lane));
         if (fresh) cid[rank] = x;
         __syncthreads();
+        const u32 met = m;
+        if constexpr (SK > 0) {
+          evals += m;
+          if (size == L && sparse) {
+            const u32 cand = cand_of_lane(lane);
+            const bool keep = !sketch_drops<KIND, SK>(K, SQ, beam_worst<NSLOT, 1>(A, L, size), cid, m, sk_last, lane) && cand < m;
+            const u64 km = ballot(keep);
+            const u32 kid = cid[cand];  // (below m where it is kept)
+            __syncthreads();
+            m = __builtin_popcountll(km);
+            if (m) {
+              if (keep) cid[__builtin_popcountll(km & lanemask_lt(lane))] = kid;
+              __syncthreads();
+            }
+          }
+        }
+        if (SK > 0 && m == 0) {
+          sparse = true;
+          if (present != ~0ull) break;
+          continue;
+        }
+        const u32 before = n_surv;
         // (the variants with start vertices of their own sit at the register count that eight
         // waves per SIMD allow: the second code path of the full-row passes would cost them a wave)
         u32 dk;
-        if constexpr (OWN)
+        if constexpr (SK > 0)
+          dk = eval_rows<KIND, NCH>(T, Q, cid, m, lane);
+        else if constexpr (OWN)
           dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [cid](u32 c) { return cid[c]; }, m, lane);
         else
           dk = eval_up_to_64_full_rows<KIND, VEC, NCH>(T, Q, [cid](u32 c) { return cid[c]; }, m, lane);
         const u32 c = cand_of_lane(lane);
         u64 mykey = c < m ? make_key(dk, cid[c]) : KEY_INF;
         __syncthreads();
-        evals += m;
+        if constexpr (SK == 0) evals += m;
         n_pass += (m + 7u) >> 3;
 
         beam_insert<NSLOT, NETWORK>(A, beam, skeys, mykey, L, size, n_surv, n_ins, lane, [] { __syncthreads(); });
+        if constexpr (SK > 0) sparse = 2u * (n_surv - before) < met;
       }
       if (present != ~0ull) break;  // rows are compact: the first gap ends the row
     }
@@ -519,14 +591,31 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
   }
 }
 
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK>
+__global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
+  search_one<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK, 0>(a, T, SketchTable{});
+}
+
+// On rows with sketches.  A search waits for memory 70 % of its time, so registers go to waves: the query and
+// its planes live in LDS (read once per pass of 8 to 32 candidates), and the bound keeps the compiler from spending the
+// registers again.  200 floats: four waves with the query in registers 198 ms a build, five 188; a sixth would spill.
+constexpr int sketch_waves(int NCH) { return NCH <= 4 ? 6 : NCH <= 7 ? 5 : 4; }
+template <int KIND, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK>
+__global__ __launch_bounds__(64, sketch_waves(NCH)) void search_sketch_kernel(SearchArgs a, VecTable T, SketchTable K) {
+  search_one<KIND, 16, NCH, NSLOT, EPS, TAG16, OWN, NETWORK, SK>(a, T, K);
+}
 
 // launches of the variants that other translation units compile: with the (1 + eps) rule
 // (search_eps.hip), with start vertices of their own (search_own.hip), with both (search_own_eps.hip)
 hipError_t launch_search_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan);
 hipError_t launch_search_own(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan);
 hipError_t launch_search_own_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s, SearchPlan* plan);
+// the same on rows with sketches (sketch.hip, sketch_eps.hip, sketch_own.hip)
+hipError_t launch_search_sketch(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
+hipError_t launch_search_sketch_eps(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
+hipError_t launch_search_sketch_own(const DistCfg& cfg, const SearchArgs& a, const VecTable& T, hipStream_t s);
 // the filter's size and layout for an instance whose registers leave room for `waves` waves per SIMD (search.hip)
-void search_set_filter(SearchArgs& a, u32 waves);
+void search_set_filter(SearchArgs& a, u32 waves, u32 lds_more = 0);
 // Several waves per search (search_wide.hip): rows of at most 64 ids, beams of at most 256, ids of
 // at most 24 bits (beam entries and the 16-bit tags of a filter of 512 buckets).
 constexpr u32 WIDE_BUCKETS = 512;
@@ -563,14 +652,18 @@ inline bool search_network(const SearchArgs& a) {
 }
 
 // Waves per SIMD that the registers of one instance leave room for (0: the runtime does not say), asked for once.
-template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK>
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK = 0>
 inline u32 search_instance_waves() {
   static std::atomic<u32> known{0};
   u32 waves = known.load(std::memory_order_relaxed);
   if (waves == 0) {
     hipFuncAttributes f{};
-    const auto kernel = search_kernel<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK>;
-    if (hipFuncGetAttributes(&f, reinterpret_cast<const void*>(kernel)) != hipSuccess || f.numRegs < 1) return 0;
+    const void* kernel;
+    if constexpr (SK > 0)
+      kernel = reinterpret_cast<const void*>(search_sketch_kernel<KIND, NCH, NSLOT, EPS, TAG16, OWN, NETWORK, SK>);
+    else
+      kernel = reinterpret_cast<const void*>(search_kernel<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK>);
+    if (hipFuncGetAttributes(&f, kernel) != hipSuccess || f.numRegs < 1) return 0;
     waves = 512u / (((u32)f.numRegs + 7u) & ~7u);  // 512 registers per lane and SIMD, in units of 8
     waves = waves > 8u ? 8u : waves < 1u ? 1u : waves;
     known.store(waves, std::memory_order_relaxed);
@@ -578,26 +671,34 @@ inline u32 search_instance_waves() {
   return waves;
 }
 
-template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool OWN, bool NETWORK>
+template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool OWN, bool NETWORK, int SK = 0>
 inline hipError_t launch_search_instance(SearchArgs a, const VecTable& T, hipStream_t s, SearchPlan* plan) {
+  constexpr u32 more = SK > 0 ? LPC * (NCH + 2 * SK) * VEC : 0;  // LDS beside that of every search: the query and its planes
   // (the size decides whether 16-bit tags do, and with them the instance)
-  u32 waves = search_instance_waves<KIND, VEC, NCH, NSLOT, EPS, true, OWN, NETWORK>();
-  if (waves != 0) search_set_filter(a, waves);
+  u32 waves = search_instance_waves<KIND, VEC, NCH, NSLOT, EPS, true, OWN, NETWORK, SK>();
+  if (waves != 0) search_set_filter(a, waves, more);
   if (waves != 0 && a.tag_width != 16u) {
-    waves = search_instance_waves<KIND, VEC, NCH, NSLOT, EPS, false, OWN, NETWORK>();
-    if (waves != 0) search_set_filter(a, waves);
+    waves = search_instance_waves<KIND, VEC, NCH, NSLOT, EPS, false, OWN, NETWORK, SK>();
+    if (waves != 0) search_set_filter(a, waves, more);
   }
   if (waves == 0) return hipErrorInvalidDeviceFunction;
   if (plan != nullptr) {
     *plan = SearchPlan{waves, 4u * a.hash_buckets, a.tag_width};
     return hipSuccess;
   }
-  const u32 lds = search_lds_bytes(a.L, a.hash_buckets);
+  const u32 lds = search_lds_bytes(a.L, a.hash_buckets) + more;
   const dim3 grid(a.nq), block(64);
-  if (a.tag_width == 16u)
+  if constexpr (SK > 0) {
+    const SketchTable K{a.sketch};
+    if (a.tag_width == 16u)
+      hipLaunchKernelGGL((search_sketch_kernel<KIND, NCH, NSLOT, EPS, true, OWN, NETWORK, SK>), grid, block, lds, s, a, T, K);
+    else
+      hipLaunchKernelGGL((search_sketch_kernel<KIND, NCH, NSLOT, EPS, false, OWN, NETWORK, SK>), grid, block, lds, s, a, T, K);
+  } else if (a.tag_width == 16u) {
     hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NSLOT, EPS, true, OWN, NETWORK>), grid, block, lds, s, a, T);
-  else
+  } else {
     hipLaunchKernelGGL((search_kernel<KIND, VEC, NCH, NSLOT, EPS, false, OWN, NETWORK>), grid, block, lds, s, a, T);
+  }
   return hipGetLastError();
 }
 
@@ -614,6 +715,18 @@ inline hipError_t launch_search_variant(const SearchArgs& a, const VecTable& T, 
     case 8: return launch_search_instance<KIND, VEC, NCH, 8, EPS, OWN, false>(a, T, s, plan);
     case 16: return launch_search_instance<KIND, VEC, NCH, 16, EPS, OWN, false>(a, T, s, plan);
     default: return launch_search_instance<KIND, VEC, NCH, 32, EPS, OWN, false>(a, T, s, plan);
+  }
+}
+
+// The same on rows with sketches (beams of up to SEARCH_SKETCH_BEAM).
+template <int KIND, int NCH, int SK, bool EPS, bool OWN>
+inline hipError_t launch_search_sketched(const SearchArgs& a, const VecTable& T, hipStream_t s) {
+  switch (search_nslot_for(a.L)) {
+    case 1:
+      if (search_network(a)) return launch_search_instance<KIND, 16, NCH, 1, EPS, OWN, true, SK>(a, T, s, nullptr);
+      return launch_search_instance<KIND, 16, NCH, 1, EPS, OWN, false, SK>(a, T, s, nullptr);
+    case 2: return launch_search_instance<KIND, 16, NCH, 2, EPS, OWN, false, SK>(a, T, s, nullptr);
+    default: return hipErrorInvalidConfiguration;
   }
 }
 

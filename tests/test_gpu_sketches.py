@@ -1,0 +1,113 @@
+"""Searches over sketches of float rows: graphs and results are those of searches without them, bit for bit."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(torch, n, d, kind, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    c = torch.randn((256, d), generator=g, device="cuda")
+    x = c[torch.randint(256, (n,), generator=g, device="cuda")] + 0.4 * torch.randn((n, d), generator=g, device="cuda")
+    if kind == "far":  # a cloud far from the origin: the bounds are wide against the distances
+        x += 30.0
+    elif kind == "unit":
+        x /= x.norm(dim=1, keepdim=True)
+    elif kind == "odd":  # rows that no bound covers, and rows that the rounding serves badly
+        s = 7919
+        x[0::s] = 0.0
+        x[1::s] *= 1e13
+        x[2::s] *= 1e-13
+        x[3::s, 0] = 50.0
+        x[4::s, d - 1] = float("inf")
+        x[5::s] = x[7:8]
+        x[6::s] *= 3e-39
+    return x
+
+
+class _Refusing:
+    """An allocator that has no memory for one size (that of the sketches: no array of rows may have it)."""
+
+    def __init__(self, A, nbytes):
+        self.inner = A.TorchAllocator()
+        self.refused = 0
+
+        def alloc(size, stream, user):
+            if size == nbytes:
+                self.refused += 1
+                return None
+            return self.inner.alloc(size, stream, user)
+
+        self.alloc = A.ALLOC_FN(alloc)
+        self.free = self.inner.free
+
+    def fill(self, opts):
+        opts.alloc = C.cast(self.alloc, C.c_void_p)
+        opts.free = C.cast(self.free, C.c_void_p)
+        opts.alloc_user = None
+
+
+# both sizes of a sketch; 20, 25, 31 (no piece to spare beside the scale), 40, 48, 49, 56, 57 and 63 pieces of 16 bytes;
+# one and two slots of the beam, the sorting network
+@pytest.mark.parametrize("d,metric,kind,R,L", [
+    (80, "l2", "far", 48, 20), (100, "ip", "unit", 64, 64), (124, "l2", "odd", 48, 96), (160, "ip", "odd", 32, 128),
+    (192, "l2", "unit", 48, 32), (196, "ip", "far", 48, 65), (224, "l2", "odd", 40, 128), (228, "ip", "unit", 32, 48),
+    (252, "l2", "far", 48, 100)])
+def test_sketches_change_nothing(env, d, metric, kind, R, L):
+    torch, A, _ = env
+    sk = 128 if d < 128 else 256
+    n = (272 << 20) // (4 * d)
+    x = _points(torch, n, d, kind, d)
+    m = A.L2SQ if metric == "l2" else A.MIPS
+    refusing = _Refusing(A, n * sk)
+    kw = dict(seed=3, metric=m, batch_cap=20_000, max_rounds=16)
+    g = A.ann_build(x, R, L, 1.0, **kw)
+    h = A.ann_build(x, R, L, 1.0, allocator=refusing, **kw)
+    assert refusing.refused == 1
+    assert np.array_equal(g.neighbors(), h.neighbors()) and g.info().start == h.info().start
+    q = _points(torch, 20_001, d, "odd" if kind == "odd" else "unit" if metric == "ip" else kind, d + 1)
+    for eps in (-1.0, 0.1):
+        a = A.ann_search_eps(g, x, q, 10, L, eps)
+        b = A.ann_search_eps(h, x, q, 10, L, eps)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32))
+    assert refusing.refused == 3
+
+
+def test_streamed_and_layered(env):
+    torch, A, _ = env
+    n, d = 345_000, 200
+    x = _points(torch, n, d, "unit", 5)
+    out = []
+    for refuse in (False, True):
+        al = _Refusing(A, n * 256) if refuse else "torch"
+        g = A.ann_build(x[:300_000], 32, 64, 1.0, seed=2, metric=A.MIPS, allocator=al)
+        A.ann_insert_points(g, x, 64, 1.0, seed=4)
+        h = A.ann_hnsw_build(x, 16, 64, 1.0, seed=6, metric=A.MIPS, allocator=al)
+        r = A.ann_hnsw_search(h, x, x[:30_000], 10, 40)
+        out.append((g.neighbors(), h.layer(0)[1], r[0].cpu().numpy(), r[1].cpu().numpy()))
+        if refuse:
+            assert al.refused == 3  # the insertion, the layered build, the queries on it
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+def test_captured_queries_do_without(env):
+    """A call under capture neither allocates nor leaves memory of the graph's in what it captured."""
+    torch, A, _ = env
+    n, d = 350_000, 200
+    x = _points(torch, n, d, "unit", 8)
+    g = A.ann_build(x, 32, 32, 1.0, seed=2, metric=A.MIPS, batch_cap=20_000, max_rounds=16)
+    q = x[:20_000].contiguous()
+    want = A.ann_search(g, x, q, 10, 32)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = A.ann_search(g, x, q, 10, 32)
+    for _ in range(3):
+        got[0].zero_()
+        got[1].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
