@@ -723,11 +723,23 @@ __device__ __forceinline__ void lds_steps(u64* ek, u32 P, u32 k2, u32 jtop, u32 
 // sorted by (distance, smaller position, larger position) in LDS.  The sorted pairs, as
 // (smaller << 16 | larger), replace the head of the leaf's part of knn_d (from knn_d[off * l]);
 // their number goes to pair_cnt[leaf].
+//
+// A thread keeps its NK keys in registers.  A histogram over PAIR_SPANS equal spans between the leaf's least and
+// greatest distance (most pairs lie in a tenth of them) says how many keys lie below a distance, about; that number
+// deals the keys into PAIR_BUCKETS buckets of two to four each, and a key's place is its bucket's first plus the
+// bucket's keys below it, which it counts itself.  Where a bucket holds more than PAIR_CROWD keys (many equal distances)
+// the leaf is sorted by the bitonic network instead, whose 91 steps took 49 us for a leaf of 8,192
+// keys, waiting for LDS and barriers.  30 trees of a million points: 8.1 -> 4.1 ms (5.7 with
+// the lists looked up in memory).
+constexpr u32 PAIR_SPANS = 1024, PAIR_BUCKETS = 2048, PAIR_CROWD = 48;
+template <int NK>
 __global__ __launch_bounds__(1024) void hc_pairs_kernel(const u32* leaf_list, const u32* leaf_off, u32 l,
                                                        const unsigned short* knn_pos, i32* knn_d, u32* pair_cnt) {
   extern __shared__ __align__(16) unsigned char hc_smem[];
-  __shared__ u32 kept;
-  u64* ek = reinterpret_cast<u64*>(hc_smem);
+  __shared__ u32 first[PAIR_BUCKETS + 1];  // counts, then the buckets' first places
+  __shared__ u32 below[PAIR_SPANS + 1];    // counts, then the keys below the span
+  __shared__ u32 least, greatest, crowd, wave_total[16];
+  u64* ek = reinterpret_cast<u64*>(hc_smem);  // 1024 * NK
   const u32 leaf = leaf_list[blockIdx.x];  // the launch's leaves: those of one size class
   const u32 off = leaf_off[leaf];
   const u32 cnt = leaf_off[leaf + 1] - off;
@@ -738,43 +750,147 @@ __global__ __launch_bounds__(1024) void hc_pairs_kernel(const u32* leaf_list, co
   const u32 tid = threadIdx.x;
   const int lane = (int)(tid & 63u);
   const u32 k = l < cnt - 1u ? l : cnt - 1u;
-  const u32 E = cnt * k;
-  if (tid == 0) kept = 0;
+  const u32 E = cnt * k;  // at most 1024 * NK
+  for (u32 i = tid; i < PAIR_BUCKETS; i += 1024) first[i] = 0;
+  below[tid] = 0;
+  if (tid == 0) {
+    least = 0xFFFFFFFFu;
+    greatest = 0;
+    crowd = 0;
+  }
+  // The lists go through LDS (where the sorted keys will be), two entries per word: that a list holds a point
+  // is looked up in half as many places as there are pairs, and by single entries from memory it was most of
+  // the kernel's time.
+  unsigned short* lists = reinterpret_cast<unsigned short*>(hc_smem);
+  const u32 words = (l + 1u) / 2u;  // per list
+  for (u32 i = tid; i < cnt * 2u * words; i += 1024) {
+    const u32 a = i / (2u * words), j = i - a * 2u * words;
+    lists[i] = j < k ? knn_pos[(u64)(off + a) * l + j] : (unsigned short)0xFFFFu;
+  }
+  u64 key[NK];
+  u32 lo = 0xFFFFFFFFu, hi = 0;
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {  // (the distances, requested together)
+    const u32 e = tid + 1024u * q, a = e / k;
+    key[q] = e < E ? (u64)(u32)knn_d[(u64)(off + a) * l + (e - a * k)] << 32 : KEY_INF;
+  }
   __syncthreads();
-  for (u32 e0 = tid - (u32)lane; e0 < E; e0 += 1024) {  // whole waves: the ballot below needs every lane
-    const u32 e = e0 + (u32)lane;
-    bool keep = false;
-    u64 key = KEY_INF;
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    const u32 e = tid + 1024u * q;
     if (e < E) {
-      const u32 a = e / k, j = e - a * k;
-      const u64 o = (u64)(off + a) * l + j;
-      const u32 b = knn_pos[o];
-      keep = true;
-      if (a > b) {
-        // does b list a?  Eight entries of b's list at a time, all requested before the first is
-        // looked at (entries past the list's end repeat its last one)
-        const unsigned short* lb = knn_pos + (u64)(off + b) * l;
-        for (u32 t0 = 0; t0 < k; t0 += 8) {
-          unsigned short w[8];
-#pragma unroll
-          for (u32 t = 0; t < 8; ++t) w[t] = lb[t0 + t < k ? t0 + t : k - 1u];
-#pragma unroll
-          for (u32 t = 0; t < 8; ++t) keep = keep && w[t] != a;
+      const u32 a = e / k, j = e - a * k, b = lists[a * 2u * words + j];
+      bool keep = true;
+      if (a > b) {  // does b list a?
+        const u32* lb = reinterpret_cast<const u32*>(lists) + b * words;
+        for (u32 t = 0; t < words; ++t) {
+          const u32 w = lb[t];
+          keep = keep && (w & 0xFFFFu) != a && (w >> 16) != a;
         }
       }
       const u32 u = a < b ? a : b, v = a < b ? b : a;
-      key = ((u64)(u32)knn_d[o] << 32) | (u << 16) | v;
+      const u32 d = (u32)(key[q] >> 32);
+      key[q] = keep ? ((u64)d << 32) | (u << 16) | v : KEY_INF;
+      if (keep) {
+        lo = d < lo ? d : lo;
+        hi = d > hi ? d : hi;
+      }
     }
-    const u64 m = ballot(keep);
-    u32 base = 0;
-    if (lane == 0 && m != 0ull) base = atomicAdd(&kept, (u32)__builtin_popcountll(m));
-    base = readlane_u32(base, 0);
-    if (keep) ek[base + (u32)__builtin_popcountll(m & lanemask_lt(lane))] = key;
+  }
+#pragma unroll
+  for (int step = 32; step >= 1; step >>= 1) {
+    const u32 olo = (u32)__shfl_xor((int)lo, step, 64), ohi = (u32)__shfl_xor((int)hi, step, 64);
+    lo = olo < lo ? olo : lo;
+    hi = ohi > hi ? ohi : hi;
   }
   __syncthreads();
-  const u32 M = kept;
+  if (lane == 0) {
+    atomicMin(&least, lo);
+    atomicMax(&greatest, hi);
+  }
+  __syncthreads();
+  const u32 from = least;
+  const float scale = (float)PAIR_SPANS / ((float)(greatest - from) + 1.0f);
+  auto span_at = [&](u64 x) { return (float)((u32)(x >> 32) - from) * scale; };
+  auto span_of = [&](float f) { return (u32)f < PAIR_SPANS - 1u ? (u32)f : PAIR_SPANS - 1u; };
+#pragma unroll
+  for (int q = 0; q < NK; ++q)
+    if (key[q] != KEY_INF) atomicAdd(&below[span_of(span_at(key[q]))], 1u);
+  __syncthreads();
+  // inclusive sum of one number per thread over the workgroup
+  auto scan = [&](u32 x) {
+#pragma unroll
+    for (int step = 1; step < 64; step <<= 1) {
+      const u32 o = (u32)__shfl_up((int)x, step, 64);
+      if (lane >= step) x += o;
+    }
+    if (lane == 63) wave_total[tid >> 6] = x;
+    __syncthreads();
+    for (u32 w = 0; w < (tid >> 6); ++w) x += wave_total[w];
+    __syncthreads();
+    return x;
+  };
+  const u32 upto = scan(below[tid]);
+  below[tid + 1u] = upto;
+  if (tid == 0) below[0] = 0;
+  __syncthreads();
+  const u32 M = below[PAIR_SPANS];
+  // a key's bucket, by the keys below its span and its way through it: conversions, products and truncations are
+  // monotone, so buckets are in the order of the distances
+  const float spread = (float)PAIR_BUCKETS / (float)(M ? M : 1u);
+  u32 at[NK];  // bucket << 16 | number in it
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    at[q] = 0;
+    if (key[q] != KEY_INF) {
+      const float f = span_at(key[q]);
+      const u32 sp = span_of(f), b0 = below[sp], b1 = below[sp + 1u];
+      float way = f - (float)sp;
+      way = way < 1.0f ? way : 1.0f;
+      u32 b = (u32)(((float)b0 + way * (float)(b1 - b0)) * spread);
+      b = b < PAIR_BUCKETS - 1u ? b : PAIR_BUCKETS - 1u;
+      at[q] = (b << 16) | atomicAdd(&first[b], 1u);
+    }
+  }
+  __syncthreads();
+  // exclusive scan of the counts, two per thread
+  const u32 c0 = first[2u * tid], c1 = first[2u * tid + 1u];
+  if (c0 > PAIR_CROWD || c1 > PAIR_CROWD) crowd = 1;
+  const u32 run = scan(c0 + c1) - c0 - c1;
+  first[2u * tid] = run;
+  first[2u * tid + 1u] = run + c0;
+  if (tid == 1023u) first[PAIR_BUCKETS] = M;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NK; ++q)
+    if (key[q] != KEY_INF) ek[first[at[q] >> 16] + (at[q] & 0xFFFFu)] = key[q];
+  __syncthreads();
+  u32* out = reinterpret_cast<u32*>(knn_d) + (u64)off * l;
+  if (tid == 0) pair_cnt[leaf] = M;
+  if (crowd == 0) {
+#pragma unroll
+    for (int q = 0; q < NK; ++q) {
+      if (key[q] != KEY_INF) {
+        const u32 b = at[q] >> 16, s0 = first[b], s1 = first[b + 1u], me = s0 + (at[q] & 0xFFFFu);
+        u32 place = s0;
+        for (u32 t = s0; t < s1; ++t) {
+          const u64 other = ek[t];
+          place += other < key[q] || (other == key[q] && t < me) ? 1u : 0u;
+        }
+        at[q] = place;
+      }
+    }
+    __syncthreads();
+    u32* sorted = reinterpret_cast<u32*>(hc_smem);
+#pragma unroll
+    for (int q = 0; q < NK; ++q)
+      if (key[q] != KEY_INF) sorted[at[q]] = (u32)key[q];
+    __syncthreads();
+    for (u32 e = tid; e < M; e += 1024) out[e] = sorted[e];
+    return;
+  }
   u32 P = 64;
-  while (P < M) P <<= 1;  // within the launch's LDS: the host sized it for the largest leaf
+  while (P < M) P <<= 1;  // at most 1024 * NK, a power of two
   for (u32 e = M + tid; e < P; e += 1024) ek[e] = KEY_INF;
   __syncthreads();
   // bitonic sort; the steps whose partners lie within 64 consecutive keys (more than half of all
@@ -859,22 +975,34 @@ __global__ __launch_bounds__(1024) void hc_pairs_kernel(const u32* leaf_list, co
     }
     __syncthreads();
   }
-  u32* out = reinterpret_cast<u32*>(knn_d) + (u64)off * l;
   for (u32 e = tid; e < M; e += 1024) out[e] = (u32)ek[e];
-  if (tid == 0) pair_cnt[leaf] = M;
 }
 
 // Second half, one wavefront per leaf: Kruskal's scan over the sorted pairs with the degree bound
-// s.  A pair whose ends are connected, or one of whose ends is full, stays so: the wave tests 64
-// pairs at once against the state so far and walks through the survivors in order.  Accepted
-// pairs go, as two arcs (point << 32 | neighbour), to arcs[2 * (off - leaf) ...] (a leaf of cnt
+// s, 64 pairs at a time.  A pair whose ends are connected, or one of whose ends is full, stays so.  Of the pairs
+// that are left, all those are accepted at once that no earlier one can change: no earlier one shares
+// a point with it (the degrees), and one of its two trees is touched by no earlier one (that tree
+// stays apart from the other, whatever becomes of those); nor can it change an earlier one, for the same reason.
+// Which is the first of a chunk to touch a tree or a point is found by a minimum over lane numbers in LDS,
+// in tables so small that strangers share entries: that only sends a pair into another round.  The first pair that is
+// left always passes.  A tree that no earlier pair touches goes under the other's root, the smaller under the
+// larger where there is a choice (as far as the sizes are known: a root's word holds what it had when it last
+// took part in such a choice).
+// Accepted pairs go, as two arcs (point << 32 | neighbour), to arcs[2 * (off - leaf) ...] (a leaf of cnt
 // points accepts at most cnt - 1; unused entries keep what they hold).
+//
+// What bounds it is the chain of LDS trips.  One pair after another, and every point put under its root
+// before each chunk, took 5.6 ms for 30 trees of a million points; so 1.8.
+constexpr u32 ROOT = 0x8000u;  // parent words: a root's has this bit and the size of its tree
+constexpr u32 MARKS = 256;
 __global__ __launch_bounds__(64) void hc_kruskal_kernel(const u64* keys, const u32* leaf_off, u32 l, u32 s,
                                                         const i32* knn_d, const u32* pair_cnt, u64* arcs) {
   __shared__ unsigned short parent_lds[HC_MAX_LS];
   __shared__ unsigned char deg_lds[HC_MAX_LS];
+  __shared__ u32 tree_mark[MARKS], point_mark[MARKS], ring_lds[128];
   volatile unsigned short* parent = parent_lds;
   volatile unsigned char* deg = deg_lds;
+  volatile u32* ring = ring_lds;
   const u32 leaf = blockIdx.x;
   const u32 off = leaf_off[leaf];
   const u32 cnt = leaf_off[leaf + 1] - off;
@@ -883,82 +1011,98 @@ __global__ __launch_bounds__(64) void hc_kruskal_kernel(const u64* keys, const u
   const u32 E = pair_cnt[leaf];
   const u32* pairs = reinterpret_cast<const u32*>(knn_d) + (u64)off * l;
   for (u32 i = (u32)lane; i < cnt; i += 64) {
-    parent[i] = (unsigned short)i;
+    parent[i] = (unsigned short)(ROOT | 1u);
     deg[i] = 0;
   }
-  __builtin_amdgcn_wave_barrier();
-  u64* out = arcs + 2ull * (off - leaf);
-  u32 accepted = 0;
-  // The accepted pairs wait in the lanes' registers, one per lane, and leave 64 at a time: the
-  // ids' loads then overlap, and none of them sits in the chain of dependent steps.
-  u32 mine = 0;
-  auto write_out = [&](u32 first, u32 count) {
-    if ((u32)lane < count) {
-      const u64 gu = keys[off + (mine >> 16)] & 0xFFFFFFFFull, gv = keys[off + (mine & 0xFFFFu)] & 0xFFFFFFFFull;
-      out[2 * (first + (u32)lane)] = (gu << 32) | gv;
-      out[2 * (first + (u32)lane) + 1] = (gv << 32) | gu;
-    }
+  for (u32 i = (u32)lane; i < MARKS; i += 64) tree_mark[i] = point_mark[i] = 0xFFFFFFFFu;
+  auto order_lds = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
-  bool flat = true;  // every point stands directly under its root
+  order_lds();
+  u64* out = arcs + 2ull * (off - leaf);
+  u32 accepted = 0, written = 0;
+  // The accepted pairs leave 64 at a time, so that the ids' loads overlap and stay out of the chain of
+  // dependent steps.
+  auto write_out = [&](u32 count) {
+    if ((u32)lane < count) {
+      const u32 mine = ring[(written + (u32)lane) & 127u];
+      const u64 gu = keys[off + (mine >> 16)] & 0xFFFFFFFFull, gv = keys[off + (mine & 0xFFFFu)] & 0xFFFFFFFFull;
+      out[2 * (written + (u32)lane)] = (gu << 32) | gv;
+      out[2 * (written + (u32)lane) + 1] = (gv << 32) | gu;
+    }
+    written += count;
+  };
+  u32 turn = 0x3FFFFFFu;  // falls with every round, so that a round's marks lie below all earlier ones
+  u32 ahead = (u32)lane < E ? pairs[lane] : 0u, last = 0xFFFFFFFFu;  // (no pair: its ends are one point)
   for (u32 c = 0; c < E && accepted < cnt - 1u; c += 64) {
-    if (!flat) {
-      // the links made while the last 64 pairs were scanned are the only ones a search has to
-      // follow afterwards (without this the chains grow as long as the leaf)
-      for (u32 i = (u32)lane; i < cnt; i += 64) {
-        u32 r = i;
-        while (parent[r] != r) r = parent[r];
-        __builtin_amdgcn_wave_barrier();
-        parent[i] = (unsigned short)r;
-      }
-      __builtin_amdgcn_wave_barrier();
-      flat = true;
-    }
-    const u32 e = c + (u32)lane;
-    const u32 pr = e < E ? pairs[e] : 0u;
-    const bool dup = e > 0 && e < E && pr == pairs[e - 1];
+    const u32 e = c + (u32)lane, pr = ahead;
+    ahead = e + 64u < E ? pairs[e + 64u] : 0u;  // the next chunk's, requested early
+    const u32 left = (u32)__shfl_up((int)pr, 1, 64);
+    const bool dup = pr == (lane == 0 ? last : left);
+    last = readlane_u32(pr, 63);
     const u32 u = pr >> 16, v = pr & 0xFFFFu;
-    bool ok = e < E && !dup;
-    if (ok) ok = deg[u] < s && deg[v] < s;
-    u32 pu = 0, pv = 0;  // the ends' roots as the chunk starts (flat: parents are roots)
-    if (ok) {
-      pu = parent[u];
-      pv = parent[v];
-      ok = pu != pv;
-    }
-    u64 mask = ballot(ok);
-    while (mask != 0ull) {
-      const int j = __builtin_ctzll(mask);
-      mask &= mask - 1ull;
-      // every lane repeats the same step on the same LDS words; the four reads a step starts
-      // with do not wait for one another, and only links made within this chunk add to them
-      const u32 uu = readlane_u32(u, j), vv = readlane_u32(v, j);
-      u32 ru = readlane_u32(pu, j), rv = readlane_u32(pv, j);
-      const unsigned char du = deg[uu], dv = deg[vv];
-      u32 nu = parent[ru], nv = parent[rv];
-      if (du < s && dv < s) {
-        while (nu != ru) {
-          ru = nu;
-          nu = parent[ru];
+    bool act = e < E && !dup;
+    u32 ru = u, rv = v;
+    u64 taken = 0;  // the chunk's accepted pairs
+    bool entered = false;
+    for (;;) {
+      u32 pu = 0, pv = 0;
+      if (act) {
+        pu = parent[ru];
+        pv = parent[rv];
+        const u32 du = deg[u], dv = deg[v];
+        while (!(pu & ROOT)) {
+          ru = pu;
+          pu = parent[ru];
         }
-        while (nv != rv) {
-          rv = nv;
-          nv = parent[rv];
+        while (!(pv & ROOT)) {
+          rv = pv;
+          pv = parent[rv];
         }
-        if (ru != rv) {
-          __builtin_amdgcn_wave_barrier();  // every lane has read before any lane writes
-          parent[ru] = (unsigned short)rv;
-          deg[uu] = du + 1;
-          deg[vv] = dv + 1;
-          if (lane == (int)(accepted & 63u)) mine = (uu << 16) | vv;
-          ++accepted;
-          if ((accepted & 63u) == 0) write_out(accepted - 64u, 64u);
-          flat = false;
-        }
+        act = ru != rv && du < s && dv < s;
       }
-      __builtin_amdgcn_wave_barrier();
+      order_lds();
+      if (!entered && act) {  // the way is as short for whoever asks next
+        if (ru != u) parent[u] = (unsigned short)ru;
+        if (rv != v) parent[v] = (unsigned short)rv;
+      }
+      entered = true;
+      if (ballot(act) == 0ull) break;
+      const u32 sign = (turn << 6) | (u32)lane;
+      --turn;
+      if (act) {
+        atomicMin(&tree_mark[ru % MARKS], sign);
+        atomicMin(&tree_mark[rv % MARKS], sign);
+        atomicMin(&point_mark[u % MARKS], sign);
+        atomicMin(&point_mark[v % MARKS], sign);
+      }
+      order_lds();
+      bool take = false, own_u = false, own_v = false;
+      if (act) {
+        own_u = *(volatile u32*)&tree_mark[ru % MARKS] == sign;
+        own_v = *(volatile u32*)&tree_mark[rv % MARKS] == sign;
+        take = (own_u || own_v) && *(volatile u32*)&point_mark[u % MARKS] == sign &&
+               *(volatile u32*)&point_mark[v % MARKS] == sign;
+      }
+      order_lds();
+      if (take) {
+        const bool under_v = own_u && (!own_v || (pu & ~ROOT) <= (pv & ~ROOT));
+        parent[under_v ? ru : rv] = (unsigned short)(under_v ? rv : ru);
+        if (own_u && own_v) parent[under_v ? rv : ru] = (unsigned short)(ROOT | ((pu & ~ROOT) + (pv & ~ROOT)));
+        deg[u] = (unsigned char)(deg[u] + 1u);
+        deg[v] = (unsigned char)(deg[v] + 1u);
+        act = false;
+      }
+      taken |= ballot(take);
+      order_lds();
     }
+    if ((taken >> lane) & 1ull) ring[(accepted + (u32)__builtin_popcountll(taken & lanemask_lt(lane))) & 127u] = pr;
+    accepted += (u32)__builtin_popcountll(taken);
+    order_lds();
+    if (accepted - written >= 64u) write_out(64u);
   }
-  write_out(accepted & ~63u, accepted & 63u);
+  write_out(accepted - written);
 }
 
 // ---- repeated keys out of a sorted array --------------------------------------------------
@@ -1407,11 +1551,10 @@ int hc_leaves(HcCtx& X, u32 G, const std::vector<Leaf>& leaves, u64* arcs, hipSt
       const u32 cntc = first_of[c + 1] - first_of[c];
       if (!cntc) continue;
       const u32 lds = limit[c] * 8;
-      HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(hc_pairs_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      hipLaunchKernelGGL(hc_pairs_kernel, dim3(cntc), dim3(1024), lds, st, X.leaf_list.as<u32>() + first_of[c],
-                         X.leaf_off.as<u32>(), X.l, X.knn_pos.as<unsigned short>(), X.knn_d.as<i32>(),
-                         X.pair_cnt.as<u32>());
+      const auto kernel = c == 0 ? hc_pairs_kernel<4> : c == 1 ? hc_pairs_kernel<8> : hc_pairs_kernel<16>;
+      HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      hipLaunchKernelGGL(kernel, dim3(cntc), dim3(1024), lds, st, X.leaf_list.as<u32>() + first_of[c], X.leaf_off.as<u32>(),
+                         X.l, X.knn_pos.as<unsigned short>(), X.knn_d.as<i32>(), X.pair_cnt.as<u32>());
     }
   }
   hipLaunchKernelGGL(hc_kruskal_kernel, dim3(nleaves), dim3(64), 0, st, X.final_keys.as<u64>(), X.leaf_off.as<u32>(), X.l,

@@ -1,0 +1,36 @@
+"""A leaf's pair sort and tree scan where they can go wrong: leaves of every size class (up to 4,096, 8,192 and 16,384
+pairs), one entry per list up to sixteen, distances that crowd into one bucket (equal points, few
+distinct values), a far point that stretches the span, trees whose points fill up (s = 1).  The accepted pairs are
+the oracle's, in its order."""
+import numpy as np
+import pytest
+
+from helpers import dev, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(kind, n, d, rng):
+    x = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    if kind == "equal":
+        x[:] = x[0]
+    elif kind == "few":  # distances take a handful of values
+        x = rng.integers(0, 2, (n, d)).astype(np.uint8)
+    elif kind == "far":  # one dense cloud, one point far away
+        x = (100 + rng.integers(0, 3, (n, d))).astype(np.uint8)
+        x[n // 2] = 255
+    elif kind == "half":  # every other point the same one
+        x[::2] = x[1]
+    return x
+
+
+@pytest.mark.parametrize("kind", ["spread", "equal", "few", "far", "half"])
+def test_leaves_equal_the_oracles(env, kind):
+    torch, A, O = env
+    for n, l, s, d in ((2, 3, 3, 8), (3, 1, 1, 8), (64, 10, 3, 16), (65, 16, 2, 16), (409, 10, 3, 32), (410, 10, 3, 32),
+                       (819, 10, 255, 20), (820, 10, 1, 20), (1024, 1, 3, 8), (1024, 4, 3, 64), (1023, 15, 3, 128), (1024, 16, 3, 128)):
+        say(f"cluster pairs {kind} n={n} l={l} s={s}")
+        x = _points(kind, n, d, np.random.default_rng(n + l))
+        _, off, edges = A.ann_hcnng_tree_edges(dev(torch, x), 1024, s, l, 5, 0)
+        want = O.hcnng_leaf(O.Dataset(x, 0), np.arange(n), s, l)
+        assert len(off) == 2 and np.array_equal(np.asarray(edges), np.asarray(want)), (n, l, s)
