@@ -206,6 +206,15 @@ u64 radix_hist_entries(u64 count);
 hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u64 count, u32 key_bits, hipStream_t s,
                             u32 first_bit = 32);
 
+// Grouping of a batch's reversed edges, planned in the same go: group_split deals the keys into 2^low_bits buckets
+// (bucket_total: their sizes, in `hist`), launch_group_plan groups each bucket into a.keys and files the segments.
+constexpr u32 GROUP_HIGH_BITS = 11;  // at most this many destination bits are left to the second half
+bool group_split_plan(u64 count, u32 key_bits, u32* low_bits);  // false: radix_sort_edges and launch_plan serve these
+u64 group_hist_entries(u64 count);
+hipError_t group_split(const u64* keys, u64* out, u32* hist, u64 hist_entries, u64 count, u32 low_bits, const u32** bucket_total,
+                       hipStream_t s);
+hipError_t launch_group_plan(const MergeArgs& a, const u64* in, const u32* bucket_total, u32 low_bits, u32 high_bits, hipStream_t s);
+
 // start vertex (point nearest the mean)
 hipError_t start_vertex_device(const void* points, u64 n, u32 d, int dtype, hipStream_t s, u32* start_out);
 

@@ -537,8 +537,15 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   tm.mark(2, st);
 
   // step 2a: bring equal destinations together
-  HIP_TRY(radix_sort_edges(S.edges.as<u64>(), S.edges_tmp.as<u64>(), S.hist.as<u32>(), radix_hist_entries(S.bmax * R), E,
-                           bits_for(g->n), st));
+  const u32 key_bits = bits_for(g->n);
+  const u64 hist_entries = group_hist_entries(S.bmax * R);
+  u32 low_bits = 0;
+  const u32* bucket_total = nullptr;
+  const bool grouped = group_split_plan(E, key_bits, &low_bits);
+  if (grouped)
+    HIP_TRY(group_split(S.edges.as<u64>(), S.edges_tmp.as<u64>(), S.hist.as<u32>(), hist_entries, E, low_bits, &bucket_total, st));
+  else
+    HIP_TRY(radix_sort_edges(S.edges.as<u64>(), S.edges_tmp.as<u64>(), S.hist.as<u32>(), hist_entries, E, key_bits, st));
   tm.mark(3, st);
 
   // step 2b: cut the keys into segments of equal destination; append where the row has room,
@@ -570,7 +577,10 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   ma.a16 = a16;
   ma.af = alpha;
   ma.counters = ctr;
-  HIP_TRY(launch_plan(ma, st));
+  if (grouped)
+    HIP_TRY(launch_group_plan(ma, S.edges_tmp.as<u64>(), bucket_total, low_bits, key_bits - low_bits, st));
+  else
+    HIP_TRY(launch_plan(ma, st));
   // grid-stride kernels over work lists whose lengths stay on the device: enough waves to fill
   // the chip, no more (idle workgroups are not free)
   const u64 want = E < 8192 ? E : 8192;

@@ -230,7 +230,7 @@ struct BatchScratch {
     HIP_TRY(nvis.alloc(b * 4));
     HIP_TRY(edges.alloc(E * 8));
     HIP_TRY(edges_tmp.alloc(E * 8));
-    HIP_TRY(hist.alloc(radix_hist_entries(E) * 4));
+    HIP_TRY(hist.alloc(group_hist_entries(E) * 4));
     HIP_TRY(lists.alloc(3 * E * sizeof(MergeItem)));
     HIP_TRY(small.alloc(64));
     HIP_TRY(small.al.zero(small.p, 64));

@@ -34,6 +34,47 @@ __device__ __forceinline__ u32 make_meta(u32 deg, u32 clean) { return deg | (cle
 // ---------------------------------------------------------------------------------------------
 // planning: one thread per edge key; the first key of each segment does the work
 // ---------------------------------------------------------------------------------------------
+// What becomes of the segment of cnt keys from keys[i0] on, all of them edges to b: appended here where the row has room
+// (returns -1), else the work list it belongs on: 0 fast, 1 gram, 2 generic with a long candidate list, 3
+// generic with a list of up to 512.  `m` receives the row's meta word as it was.
+__device__ __forceinline__ int plan_segment(const MergeArgs& a, u32 b, u64 i0, u32 cnt, u32* stat_lds, u32& m) {
+  m = a.meta[b];
+  const u32 deg = meta_deg(m), clean = meta_clean(m);
+  if (!a.force_prune && deg + cnt <= a.R) {
+    u32* row = a.graph + (u64)b * a.R;
+    for (u32 j = 0; j < cnt; ++j) row[deg + j] = (u32)(a.keys[i0 + j] & 0xFFFFFFFFull);
+    a.meta[b] = make_meta(deg + cnt, clean);
+    if (a.counters != nullptr) {
+      atomicAdd(&stat_lds[0], 1u);
+      atomicAdd(&stat_lds[1], cnt);
+    }
+    return -1;
+  }
+  const u32 fresh = deg - clean + cnt;
+  int kind = 2;
+  if (a.force_prune)
+    kind = (a.gram_ok && deg + cnt <= a.gram_tmax) ? 1 : 2;  // (the fast path presumes a clean prefix)
+  else if (clean <= 64 && fresh <= a.fast_amax)
+    kind = 0;
+  else if (a.gram_ok && deg + cnt <= a.gram_tmax)
+    kind = 1;
+  return kind == 2 && deg + cnt <= a.medium_max ? 3 : kind;
+}
+// One global atomic per work list and workgroup; the order of a list has no influence on any result, every segment is
+// processed on its own.
+__device__ __forceinline__ void plan_reserve(const MergeArgs& a, const u32* cnt_lds, u32* base_lds, const u32* stat_lds) {
+  if (threadIdx.x < 4 && cnt_lds[threadIdx.x] != 0)
+    base_lds[threadIdx.x] = atomicAdd(&a.list_count[threadIdx.x], cnt_lds[threadIdx.x]);
+  if (a.counters != nullptr && threadIdx.x == 0 && stat_lds[0] != 0) {
+    atomicAdd(&block_counters(a.counters)->appends, (unsigned long long)stat_lds[0]);
+    atomicAdd(&block_counters(a.counters)->edges, (unsigned long long)stat_lds[1]);
+  }
+}
+__device__ __forceinline__ void plan_file(const MergeArgs& a, int kind, u32 at_, u64 i0, u32 cnt, u32 b, u32 m) {
+  const long long at = (long long)at_;
+  a.list_items[kind][kind == 3 ? -at : at] = MergeItem{(u32)i0, cnt, b, m};
+}
+
 __global__ __launch_bounds__(256) void plan_kernel(MergeArgs a) {
   __shared__ u32 cnt_lds[4];
   __shared__ u32 base_lds[4];
@@ -43,7 +84,7 @@ __global__ __launch_bounds__(256) void plan_kernel(MergeArgs a) {
   __syncthreads();
 
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-  int kind = -1;  // 0 fast, 1 gram, 2 generic with a long candidate list, 3 generic with a list of up to 512
+  int kind = -1;
   u32 slot = 0, cnt = 0, b = 0, m = 0;
   if (i < a.nkeys) {
     b = (u32)(a.keys[i] >> 32);
@@ -64,45 +105,134 @@ __global__ __launch_bounds__(256) void plan_kernel(MergeArgs a) {
           hi = mid;
       }
       cnt = (u32)(hi - i);
-      m = a.meta[b];
-      const u32 deg = meta_deg(m), clean = meta_clean(m);
-      if (!a.force_prune && deg + cnt <= a.R) {
-        u32* row = a.graph + (u64)b * a.R;
-        for (u32 j = 0; j < cnt; ++j) row[deg + j] = (u32)(a.keys[i + j] & 0xFFFFFFFFull);
-        a.meta[b] = make_meta(deg + cnt, clean);
-        if (a.counters != nullptr) {
-          atomicAdd(&stat_lds[0], 1u);
-          atomicAdd(&stat_lds[1], cnt);
-        }
-      } else {
-        const u32 fresh = deg - clean + cnt;
-        if (a.force_prune)
-          kind = (a.gram_ok && deg + cnt <= a.gram_tmax) ? 1 : 2;  // (the fast path presumes a clean prefix)
-        else if (clean <= 64 && fresh <= a.fast_amax)
-          kind = 0;
-        else if (a.gram_ok && deg + cnt <= a.gram_tmax)
-          kind = 1;
-        else
-          kind = 2;
-        if (kind == 2 && deg + cnt <= a.medium_max) kind = 3;
-        slot = atomicAdd(&cnt_lds[kind], 1u);
-      }
+      kind = plan_segment(a, b, i, cnt, stat_lds, m);
+      if (kind >= 0) slot = atomicAdd(&cnt_lds[kind], 1u);
     }
   }
   __syncthreads();
-  // one global atomic per work list and workgroup; the order of a list has no influence on any
-  // result, every segment is processed on its own
-  if (threadIdx.x < 4 && cnt_lds[threadIdx.x] != 0)
-    base_lds[threadIdx.x] = atomicAdd(&a.list_count[threadIdx.x], cnt_lds[threadIdx.x]);
-  if (a.counters != nullptr && threadIdx.x == 0 && stat_lds[0] != 0) {
-    atomicAdd(&block_counters(a.counters)->appends, (unsigned long long)stat_lds[0]);
-    atomicAdd(&block_counters(a.counters)->edges, (unsigned long long)stat_lds[1]);
+  plan_reserve(a, cnt_lds, base_lds, stat_lds);
+  __syncthreads();
+  if (kind >= 0) plan_file(a, kind, base_lds[kind] + slot, i, cnt, b, m);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Grouping and planning of a batch in one: the keys come dealt into buckets by the low bits of their
+// destination (group_split), one workgroup per bucket groups its keys by the other bits, at most GROUP_HIGH_BITS, and plans
+// the segments, whose lengths it has just counted.  Equal destinations need to stand together, in the order of the batch;
+// the order of the groups has no influence on any result.  It replaces the second pass of the radix sort
+// (three launches) and the planning launch: GROUP_MEASURED.
+// Four waves, each over its own quarter of the bucket, rank as the radix sort does (sort.hip), with counters of each wave's own.
+// ---------------------------------------------------------------------------------------------
+constexpr u32 GROUP_WAVES = 4;
+__global__ __launch_bounds__(64 * GROUP_WAVES) void group_plan_kernel(MergeArgs a, const u64* in, u64* out, const u32* bucket_total,
+                                                                      u32 low_bits, u32 high_bits) {
+  extern __shared__ u32 count[];  // GROUP_WAVES x 2^high_bits, then 2^high_bits: where a segment's filing stands
+  __shared__ u32 cnt_lds[4], base_lds[4], stat_lds[2], part[GROUP_WAVES], wave_sum[GROUP_WAVES];
+  const u32 t = threadIdx.x, lane = t & 63u, w = t >> 6, digits = 1u << high_bits, buckets = 1u << low_bits;
+  u32* mine = count + w * digits;
+  u32* filed = count + GROUP_WAVES * digits;
+  if (t < 4) cnt_lds[t] = 0;
+  if (t < 2) stat_lds[t] = 0;
+  const u32 c = bucket_total[blockIdx.x];
+  if (c == 0) return;
+  // the bucket's first key: those of all buckets before it
+  u32 before = 0;
+  for (u32 i = t; i < buckets; i += 64u * GROUP_WAVES) before += i < blockIdx.x ? bucket_total[i] : 0u;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) before += (u32)__shfl_xor((int)before, off, 64);
+  if (lane == 0) part[w] = before;
+  for (u32 i = lane; i < digits; i += 64) mine[i] = 0;
+  __syncthreads();
+  u64 base = 0;
+#pragma unroll
+  for (u32 v = 0; v < GROUP_WAVES; ++v) base += part[v];
+  // this wave's quarter, whole rows of 64
+  const u32 rows = (c + 63u) / 64u, per = (rows + GROUP_WAVES - 1u) / GROUP_WAVES * 64u;
+  const u32 lo = w * per < c ? w * per : c, hi = lo + per < c ? lo + per : c;
+  for (u32 i = lo + lane; i < hi; i += 64) atomicAdd(&mine[(u32)(in[base + i] >> 32) >> low_bits], 1u);
+  __syncthreads();
+  // first places, digit by digit and in a digit wave by wave: a thread owns PL digits
+  const u32 PL = (digits + 64u * GROUP_WAVES - 1u) / (64u * GROUP_WAVES);
+  u32 total = 0;
+  for (u32 j = 0; j < PL; ++j)
+    if (PL * t + j < digits)
+      for (u32 v = 0; v < GROUP_WAVES; ++v) total += count[v * digits + PL * t + j];
+  u32 incl = total;
+#pragma unroll
+  for (u32 off = 1; off < 64; off <<= 1) {
+    const u32 o = (u32)__shfl_up((int)incl, off, 64);
+    if (lane >= off) incl += o;
+  }
+  if (lane == 63) wave_sum[w] = incl;
+  __syncthreads();
+  u32 run = incl - total;
+  for (u32 v = 0; v < w; ++v) run += wave_sum[v];
+  const u32 first_run = run;
+  for (u32 j = 0; j < PL; ++j) {
+    if (PL * t + j >= digits) break;
+    for (u32 v = 0; v < GROUP_WAVES; ++v) {
+      const u32 x = count[v * digits + PL * t + j];
+      count[v * digits + PL * t + j] = run;
+      run += x;
+    }
   }
   __syncthreads();
-  if (kind >= 0) {
-    const long long at = (long long)(base_lds[kind] + slot);
-    a.list_items[kind][kind == 3 ? -at : at] = MergeItem{(u32)i, cnt, b, m};
+  for (u32 i0 = lo; i0 < hi; i0 += 64) {
+    const u32 i = i0 + lane;
+    const bool valid = i < hi;
+    const u64 key = valid ? in[base + i] : 0ull;
+    const u32 dg = (u32)(key >> 32) >> low_bits;
+    u64 match = ballot(valid);
+    for (u32 bit = 0; bit < high_bits; ++bit) {
+      const bool one = (dg >> bit) & 1u;
+      const u64 bm = ballot(one);
+      match &= one ? bm : ~bm;
+    }
+    u32 dst = 0;
+    if (valid) dst = mine[dg] + (u32)__builtin_popcountll(match & lanemask_lt((int)lane));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid && (match >> lane) == 1ull) mine[dg] += (u32)__builtin_popcountll(match);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid) out[base + dst] = key;
   }
+  __syncthreads();  // (also before the appends read the keys back)
+  // after the walk the last wave's counter of a digit is the end of its segment
+  u32 from = first_run;
+  for (u32 j = 0; j < PL; ++j) {
+    const u32 dg = PL * t + j;
+    if (dg >= digits) break;
+    const u32 to = count[(GROUP_WAVES - 1u) * digits + dg];
+    if (to > from) {
+      u32 m;
+      const int kind = plan_segment(a, (dg << low_bits) | blockIdx.x, base + from, to - from, stat_lds, m);
+      filed[dg] = kind < 0 ? 0xFFFFFFFFu : ((u32)kind << 30) | atomicAdd(&cnt_lds[kind], 1u);
+    }
+    from = to;
+  }
+  __syncthreads();
+  plan_reserve(a, cnt_lds, base_lds, stat_lds);
+  __syncthreads();
+  from = first_run;
+  for (u32 j = 0; j < PL; ++j) {
+    const u32 dg = PL * t + j;
+    if (dg >= digits) break;
+    const u32 to = count[(GROUP_WAVES - 1u) * digits + dg];
+    if (to > from && filed[dg] != 0xFFFFFFFFu) {
+      const u32 b = (dg << low_bits) | blockIdx.x, kind = filed[dg] >> 30;
+      plan_file(a, (int)kind, base_lds[kind] + (filed[dg] & 0x3FFFFFFFu), base + from, to - from, b, a.meta[b]);
+    }
+    from = to;
+  }
+}
+
+hipError_t launch_group_plan(const MergeArgs& a, const u64* in, const u32* bucket_total, u32 low_bits, u32 high_bits,
+                             hipStream_t s) {
+  const u32 lds = (GROUP_WAVES + 1u) * (4u << high_bits);
+  hipLaunchKernelGGL(group_plan_kernel, dim3(1u << low_bits), dim3(64 * GROUP_WAVES), lds, s, a, in, const_cast<u64*>(a.keys),
+                     bucket_total, low_bits, high_bits);
+  return hipGetLastError();
 }
 
 hipError_t launch_plan(const MergeArgs& a, hipStream_t s) {

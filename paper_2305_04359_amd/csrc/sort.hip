@@ -33,6 +33,8 @@ u64 radix_hist_entries(u64 count) {
   return RS_RADIX * (tiles + 1);
 }
 
+// DROP: keys of all ones (unused slots) are left out.
+template <bool DROP>
 __global__ __launch_bounds__(64) void rs_hist_kernel(const u64* keys, u64 count, u64 tile_keys, u32 tiles,
                                                      u32 shift, u32 mask, u32* hist) {
   __shared__ u32 cnt[RS_RADIX];
@@ -48,7 +50,7 @@ __global__ __launch_bounds__(64) void rs_hist_kernel(const u64* keys, u64 count,
     for (u32 q = 0; q < 4; ++q) k4[q] = i0 + 64u * q < hi ? keys[i0 + 64u * q] : 0ull;
 #pragma unroll
     for (u32 q = 0; q < 4; ++q)
-      if (i0 + 64u * q < hi) atomicAdd(&cnt[(u32)(k4[q] >> shift) & mask], 1u);
+      if (i0 + 64u * q < hi && !(DROP && k4[q] == KEY_INF)) atomicAdd(&cnt[(u32)(k4[q] >> shift) & mask], 1u);
   }
   __syncthreads();
   for (u32 i = lane; i < RS_RADIX; i += 64) hist[(u64)i * tiles + blockIdx.x] = cnt[i];
@@ -86,6 +88,7 @@ __global__ __launch_bounds__(256) void rs_rowscan_kernel(u32* hist, u32 tiles, u
 // digit for itself (an exclusive scan of 1,024 numbers in LDS costs a microsecond; a kernel of
 // its own for it cost six, and a "last workgroup does it" ticket inside the row scan more still:
 // RS_RADIX atomics on one address).
+template <bool DROP>
 __global__ __launch_bounds__(64) void rs_scatter_kernel(const u64* keys, u64* out, u64 count, u64 tile_keys,
                                                         u32 tiles, u32 shift, u32 mask, u32 nbits,
                                                         const u32* hist, const u32* digit_total) {
@@ -126,8 +129,8 @@ __global__ __launch_bounds__(64) void rs_scatter_kernel(const u64* keys, u64* ou
       const u64 i0 = i4 + 64u * q;
       if (i0 >= hi) break;  // uniform
       const u64 i = i0 + lane;
-      const bool valid = i < hi;
       const u64 key = k4[q];
+      const bool valid = i < hi && !(DROP && key == KEY_INF);
       const u32 dg = (u32)(key >> shift) & mask;
       u64 match = ballot(valid);
       for (u32 b = 0; b < nbits; ++b) {
@@ -279,10 +282,10 @@ hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u6
     const u32 nb = key_bits - done < per ? key_bits - done : per;
     const u32 shift = first_bit + done;
     const u32 mask = (1u << nb) - 1u;
-    hipLaunchKernelGGL(rs_hist_kernel, dim3(tiles), dim3(64), 0, s, src, count, tile_keys, tiles, shift, mask, hist);
+    hipLaunchKernelGGL(rs_hist_kernel<false>, dim3(tiles), dim3(64), 0, s, src, count, tile_keys, tiles, shift, mask, hist);
     u32* digit_total = hist + (u64)RS_RADIX * tiles;
     hipLaunchKernelGGL(rs_rowscan_kernel, dim3(RS_RADIX), dim3(256), 0, s, hist, tiles, digit_total);
-    hipLaunchKernelGGL(rs_scatter_kernel, dim3(tiles), dim3(64), 0, s, src, dst, count, tile_keys, tiles, shift,
+    hipLaunchKernelGGL(rs_scatter_kernel<false>, dim3(tiles), dim3(64), 0, s, src, dst, count, tile_keys, tiles, shift,
                        mask, nb, hist, digit_total);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -293,6 +296,40 @@ hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u6
   }
   if (src != keys) return hipMemcpyAsync(keys, src, count * sizeof(u64), hipMemcpyDeviceToDevice, s);
   return hipSuccess;
+}
+
+// The first half of grouping a batch's keys (the second: group_plan_kernel in merge.hip): one stable pass over the
+// low bits of the destinations, unused slots left out.
+bool group_split_plan(u64 count, u32 key_bits, u32* low_bits) {
+  if (count <= RS_ONE_MAX || key_bits > RS_DIGIT_BITS + GROUP_HIGH_BITS) return false;
+  // buckets of about 512 keys, so that there are some hundreds of workgroups
+  u32 low = key_bits > GROUP_HIGH_BITS - 1u ? key_bits - (GROUP_HIGH_BITS - 1u) : 1u;
+  while (low < RS_DIGIT_BITS && low < key_bits - 1u && (count >> low) > 512u) ++low;
+  *low_bits = low < RS_DIGIT_BITS ? low : RS_DIGIT_BITS;
+  return true;
+}
+// a wave's tile: a batch of a few thousand points needs more of them than rs_tile_keys gives
+static u64 group_tile_keys(u64 count) { return count <= (1u << 18) ? 256 : count <= (1u << 19) ? 512 : rs_tile_keys(count); }
+u64 group_hist_entries(u64 count) {
+  if (count <= RS_ONE_MAX) return radix_hist_entries(count);
+  const u64 tk = group_tile_keys(count), tiles = (count + tk - 1) / tk, most = radix_hist_entries(count);
+  // (no larger for a smaller count: sizes below the lines take up to 1,024 tiles)
+  const u64 need = RS_RADIX * ((tiles < 1024 ? 1024 : tiles) + 1);
+  return need > most ? need : most;
+}
+hipError_t group_split(const u64* keys, u64* out, u32* hist, u64 hist_entries, u64 count, u32 low_bits, const u32** bucket_total,
+                       hipStream_t s) {
+  const u64 tile_keys = group_tile_keys(count);
+  const u32 tiles = (u32)((count + tile_keys - 1) / tile_keys);
+  if ((u64)RS_RADIX * (tiles + 1u) > hist_entries) return hipErrorInvalidValue;
+  const u32 mask = (1u << low_bits) - 1u;
+  u32* digit_total = hist + (u64)RS_RADIX * tiles;
+  hipLaunchKernelGGL(rs_hist_kernel<true>, dim3(tiles), dim3(64), 0, s, keys, count, tile_keys, tiles, 32u, mask, hist);
+  hipLaunchKernelGGL(rs_rowscan_kernel, dim3(RS_RADIX), dim3(256), 0, s, hist, tiles, digit_total);
+  hipLaunchKernelGGL(rs_scatter_kernel<true>, dim3(tiles), dim3(64), 0, s, keys, out, count, tile_keys, tiles, 32u, mask, low_bits,
+                     hist, digit_total);
+  *bucket_total = digit_total;
+  return hipGetLastError();
 }
 
 }  // namespace annmi
