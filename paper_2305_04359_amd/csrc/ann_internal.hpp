@@ -162,6 +162,7 @@ struct MergeArgs {
   long long a16;
   float af;
   DevCounters* counters;
+  u32 launches;     // re-prune launches: 1 (all kinds in one), 2 (all but the longest lists), 0 (one per kind, side by side)
   u32 force_prune;  // non-zero: every segment is pruned, also where row and segment fit in R (the
                     // clustering-based builder, Sec. 4.3; rows start empty there)
 };
@@ -194,6 +195,7 @@ hipError_t launch_merge(const DistCfg& cfg, const MergeArgs& a, u32 grid, hipStr
                         hipStream_t s_generic, hipStream_t s_medium);
 hipError_t launch_meta_from_rows(const u32* graph, u64 n, u32 R, u32* meta, hipStream_t s);
 hipError_t launch_meta_forget_clean(u64 n, u32* meta, hipStream_t s);
+u32 merge_launches(const DistCfg& cfg, u64 batch);  // MergeArgs.launches of a batch
 bool gram_path_ok(const DistCfg& cfg);
 u32 gram_path_tmax();
 u32 fast_path_amax(const DistCfg& cfg);
@@ -214,6 +216,10 @@ u64 group_hist_entries(u64 count);
 hipError_t group_split(const u64* keys, u64* out, u32* hist, u64 hist_entries, u64 count, u32 low_bits, const u32** bucket_total,
                        hipStream_t s);
 hipError_t launch_group_plan(const MergeArgs& a, const u64* in, const u32* bucket_total, u32 low_bits, u32 high_bits, hipStream_t s);
+
+// Few keys: sorted and planned by one workgroup (a.keys is where `keys` is).
+bool sort_and_plan_ok(u64 count);
+hipError_t launch_sort_and_plan(const MergeArgs& a, u64* keys, u32 key_bits, hipStream_t s);
 
 // start vertex (point nearest the mean)
 hipError_t start_vertex_device(const void* points, u64 n, u32 d, int dtype, hipStream_t s, u32* start_out);

@@ -541,8 +541,10 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   const u64 hist_entries = group_hist_entries(S.bmax * R);
   u32 low_bits = 0;
   const u32* bucket_total = nullptr;
-  const bool grouped = group_split_plan(E, key_bits, &low_bits);
-  if (grouped)
+  const bool grouped = group_split_plan(E, key_bits, &low_bits), few = sort_and_plan_ok(E);
+  if (few) {
+    // (sorted below, where they are planned)
+  } else if (grouped)
     HIP_TRY(group_split(S.edges.as<u64>(), S.edges_tmp.as<u64>(), S.hist.as<u32>(), hist_entries, E, low_bits, &bucket_total, st));
   else
     HIP_TRY(radix_sort_edges(S.edges.as<u64>(), S.edges_tmp.as<u64>(), S.hist.as<u32>(), hist_entries, E, key_bits, st));
@@ -567,7 +569,8 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   // does not apply (float rows, long rows) and in batches of millions of points: there they get
   // a kernel instance of their own; elsewhere one more launch per batch would cost more than
   // the few rows gain
-  ma.medium_max = (!ma.gram_ok || E >= (1ull << 22)) ? MERGE_MEDIUM_MAX : 0u;
+  ma.launches = merge_launches(g->cfg, b);
+  ma.medium_max = (!ma.gram_ok || ma.launches == 2 || E >= (1ull << 22)) ? MERGE_MEDIUM_MAX : 0u;
   ma.stage_bytes = prune_stage_bytes(R, g->cfg);
   ma.use_mfma = mfma_prune_ok(R, g->cfg) ? 1u : 0u;
   ma.arena = S.arena.as<u64>();
@@ -577,7 +580,9 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   ma.a16 = a16;
   ma.af = alpha;
   ma.counters = ctr;
-  if (grouped)
+  if (few)
+    HIP_TRY(launch_sort_and_plan(ma, S.edges.as<u64>(), key_bits, st));
+  else if (grouped)
     HIP_TRY(launch_group_plan(ma, S.edges_tmp.as<u64>(), bucket_total, low_bits, key_bits - low_bits, st));
   else
     HIP_TRY(launch_plan(ma, st));
@@ -585,7 +590,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   // the chip, no more (idle workgroups are not free)
   const u64 want = E < 8192 ? E : 8192;
   // (a small batch's kernels are over before a wait between streams has been served)
-  if (S.side[0] != nullptr && b >= 2048) {
+  if (S.side[0] != nullptr && b >= 2048 && ma.launches == 0) {
     HIP_TRY(hipEventRecord(S.ev_plan, st));
     const int nside = ma.medium_max ? 3 : 2;
     if (nside == 3) {

@@ -23,58 +23,14 @@
 #include "ann_device.hpp"
 #include "ann_internal.hpp"
 #include "ann_dispatch.hpp"
+#include "plan_device.hpp"
 #include "prune_device.hpp"
 
 namespace annmi {
 
-__device__ __forceinline__ u32 meta_deg(u32 m) { return m & 0xFFFFu; }
-__device__ __forceinline__ u32 meta_clean(u32 m) { return m >> 16; }
-__device__ __forceinline__ u32 make_meta(u32 deg, u32 clean) { return deg | (clean << 16); }
-
 // ---------------------------------------------------------------------------------------------
 // planning: one thread per edge key; the first key of each segment does the work
 // ---------------------------------------------------------------------------------------------
-// What becomes of the segment of cnt keys from keys[i0] on, all of them edges to b: appended here where the row has room
-// (returns -1), else the work list it belongs on: 0 fast, 1 gram, 2 generic with a long candidate list, 3
-// generic with a list of up to 512.  `m` receives the row's meta word as it was.
-__device__ __forceinline__ int plan_segment(const MergeArgs& a, u32 b, u64 i0, u32 cnt, u32* stat_lds, u32& m) {
-  m = a.meta[b];
-  const u32 deg = meta_deg(m), clean = meta_clean(m);
-  if (!a.force_prune && deg + cnt <= a.R) {
-    u32* row = a.graph + (u64)b * a.R;
-    for (u32 j = 0; j < cnt; ++j) row[deg + j] = (u32)(a.keys[i0 + j] & 0xFFFFFFFFull);
-    a.meta[b] = make_meta(deg + cnt, clean);
-    if (a.counters != nullptr) {
-      atomicAdd(&stat_lds[0], 1u);
-      atomicAdd(&stat_lds[1], cnt);
-    }
-    return -1;
-  }
-  const u32 fresh = deg - clean + cnt;
-  int kind = 2;
-  if (a.force_prune)
-    kind = (a.gram_ok && deg + cnt <= a.gram_tmax) ? 1 : 2;  // (the fast path presumes a clean prefix)
-  else if (clean <= 64 && fresh <= a.fast_amax)
-    kind = 0;
-  else if (a.gram_ok && deg + cnt <= a.gram_tmax)
-    kind = 1;
-  return kind == 2 && deg + cnt <= a.medium_max ? 3 : kind;
-}
-// One global atomic per work list and workgroup; the order of a list has no influence on any result, every segment is
-// processed on its own.
-__device__ __forceinline__ void plan_reserve(const MergeArgs& a, const u32* cnt_lds, u32* base_lds, const u32* stat_lds) {
-  if (threadIdx.x < 4 && cnt_lds[threadIdx.x] != 0)
-    base_lds[threadIdx.x] = atomicAdd(&a.list_count[threadIdx.x], cnt_lds[threadIdx.x]);
-  if (a.counters != nullptr && threadIdx.x == 0 && stat_lds[0] != 0) {
-    atomicAdd(&block_counters(a.counters)->appends, (unsigned long long)stat_lds[0]);
-    atomicAdd(&block_counters(a.counters)->edges, (unsigned long long)stat_lds[1]);
-  }
-}
-__device__ __forceinline__ void plan_file(const MergeArgs& a, int kind, u32 at_, u64 i0, u32 cnt, u32 b, u32 m) {
-  const long long at = (long long)at_;
-  a.list_items[kind][kind == 3 ? -at : at] = MergeItem{(u32)i0, cnt, b, m};
-}
-
 __global__ __launch_bounds__(256) void plan_kernel(MergeArgs a) {
   __shared__ u32 cnt_lds[4];
   __shared__ u32 base_lds[4];
@@ -105,7 +61,8 @@ __global__ __launch_bounds__(256) void plan_kernel(MergeArgs a) {
           hi = mid;
       }
       cnt = (u32)(hi - i);
-      kind = plan_segment(a, b, i, cnt, stat_lds, m);
+      m = a.meta[b];
+      kind = plan_segment(a, b, m, cnt, stat_lds, [&](u32 j) { return (u32)(a.keys[i + j] & 0xFFFFFFFFull); });
       if (kind >= 0) slot = atomicAdd(&cnt_lds[kind], 1u);
     }
   }
@@ -120,7 +77,8 @@ __global__ __launch_bounds__(256) void plan_kernel(MergeArgs a) {
 // destination (group_split), one workgroup per bucket groups its keys by the other bits, at most GROUP_HIGH_BITS, and plans
 // the segments, whose lengths it has just counted.  Equal destinations need to stand together, in the order of the batch;
 // the order of the groups has no influence on any result.  It replaces the second pass of the radix sort
-// (three launches) and the planning launch: GROUP_MEASURED.
+// (three launches) and the planning launch: a build of a million points at R = 64 79.3 ->
+// 76.7 ms, batches of 3,000 points 420 -> 403 us each.
 // Four waves, each over its own quarter of the bucket, rank as the radix sort does (sort.hip), with counters of each wave's own.
 // ---------------------------------------------------------------------------------------------
 constexpr u32 GROUP_WAVES = 4;
@@ -205,8 +163,8 @@ __global__ __launch_bounds__(64 * GROUP_WAVES) void group_plan_kernel(MergeArgs 
     if (dg >= digits) break;
     const u32 to = count[(GROUP_WAVES - 1u) * digits + dg];
     if (to > from) {
-      u32 m;
-      const int kind = plan_segment(a, (dg << low_bits) | blockIdx.x, base + from, to - from, stat_lds, m);
+      const u32 b = (dg << low_bits) | blockIdx.x;
+      const int kind = plan_segment(a, b, a.meta[b], to - from, stat_lds, [&](u32 k) { return (u32)(a.keys[base + from + k] & 0xFFFFFFFFull); });
       filed[dg] = kind < 0 ? 0xFFFFFFFFu : ((u32)kind << 30) | atomicAdd(&cnt_lds[kind], 1u);
     }
     from = to;
@@ -453,53 +411,67 @@ __device__ __forceinline__ u32 fast_item(const MergeArgs& a, const VecTable& T, 
     return kept;
 }
 
+// what a workgroup's re-prunes add to the counters
+struct MergeStats {
+  unsigned long long rep = 0, edges = 0, pair = 0;
+  __device__ __forceinline__ void add(const MergeArgs& a, int lane) const {
+    if (a.counters != nullptr && lane == 0 && rep) {
+      atomicAdd(&block_counters(a.counters)->reprunes, rep);
+      atomicAdd(&block_counters(a.counters)->edges, edges);
+      atomicAdd(&block_counters(a.counters)->prune_evals, pair);
+    }
+  }
+};
+
+template <int NCH>
+struct FastLds {
+  static constexpr int AMAX = FastAMax<NCH>::value;
+  u32 ids[64 + AMAX];    // clean ids by row position, then the new ids
+  u32 dk[1 + AMAX][64];  // distance keys by row position: to b, to each new entry
+};
+
+template <int KIND, int VEC, int NCH>
+__device__ __forceinline__ void merge_fast_one(const MergeArgs& a, const VecTable& T, FastLds<NCH>& L, u32 it, int lane,
+                                               MergeStats& stats) {
+  constexpr int AMAX = FastAMax<NCH>::value;
+  const AlphaParam al{a.a16, a.af};
+  const MergeItem item = a.list_items[0][it];
+  const u32 i0 = item.i0, cnt = item.cnt, b = item.b, m = item.meta;
+  const u32 deg = meta_deg(m), clean = meta_clean(m);
+  const u32 stale = deg - clean;  // appended since the last prune
+  const u32 na = stale + cnt;     // 1 <= na <= AMAX
+  u32* row = a.graph + (u64)b * a.R;
+  // uniform dispatch on the number of new entries
+#define ANN_FAST_CASE(N)                                                                              \
+  case N:                                                                                             \
+    if constexpr (AMAX >= N)                                                                          \
+      (void)fast_item<KIND, VEC, NCH, N>(a, T, al, L.ids, L.dk, b, i0, clean, stale, row, a.R, lane); \
+    break;
+  switch (na) {
+    ANN_FAST_CASE(1)
+    ANN_FAST_CASE(2)
+    ANN_FAST_CASE(3)
+    ANN_FAST_CASE(4)
+    ANN_FAST_CASE(5)
+    ANN_FAST_CASE(6)
+    ANN_FAST_CASE(7)
+    ANN_FAST_CASE(8)
+    default: break;
+  }
+#undef ANN_FAST_CASE
+  ++stats.rep;
+  stats.edges += cnt;
+  stats.pair += (unsigned long long)(clean + na) * (na + 1);
+}
+
 template <int KIND, int VEC, int NCH>
 __global__ __launch_bounds__(64) void merge_fast_kernel(MergeArgs a, VecTable T) {
-  constexpr int AMAX = FastAMax<NCH>::value;
-  __shared__ u32 ids_lds[64 + AMAX];    // clean ids by row position, then the new ids
-  __shared__ u32 dk_lds[1 + AMAX][64];  // distance keys by row position: to b, to each new entry
-
+  __shared__ FastLds<NCH> lds;
   const int lane = threadIdx.x;
   const u32 nitems = a.list_count[0];
-  const AlphaParam al{a.a16, a.af};
-  unsigned long long n_rep = 0, n_edges = 0, n_pair = 0;
-
-  for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const MergeItem item = a.list_items[0][it];
-    const u32 i0 = item.i0, cnt = item.cnt, b = item.b, m = item.meta;
-    const u32 deg = meta_deg(m), clean = meta_clean(m);
-    const u32 stale = deg - clean;  // appended since the last prune
-    const u32 na = stale + cnt;     // 1 <= na <= AMAX
-    u32* row = a.graph + (u64)b * a.R;
-    u32 kept = 0;
-    // uniform dispatch on the number of new entries
-#define ANN_FAST_CASE(N)                                                                                     \
-  case N:                                                                                                    \
-    if constexpr (AMAX >= N)                                                                                 \
-      kept = fast_item<KIND, VEC, NCH, N>(a, T, al, ids_lds, dk_lds, b, i0, clean, stale, row, a.R, lane);   \
-    break;
-    switch (na) {
-      ANN_FAST_CASE(1)
-      ANN_FAST_CASE(2)
-      ANN_FAST_CASE(3)
-      ANN_FAST_CASE(4)
-      ANN_FAST_CASE(5)
-      ANN_FAST_CASE(6)
-      ANN_FAST_CASE(7)
-      ANN_FAST_CASE(8)
-      default: break;
-    }
-#undef ANN_FAST_CASE
-    (void)kept;
-    ++n_rep;
-    n_edges += cnt;
-    n_pair += (unsigned long long)(clean + na) * (na + 1);
-  }
-  if (a.counters != nullptr && lane == 0 && n_rep) {
-    atomicAdd(&block_counters(a.counters)->reprunes, n_rep);
-    atomicAdd(&block_counters(a.counters)->edges, n_edges);
-    atomicAdd(&block_counters(a.counters)->prune_evals, n_pair);
-  }
+  MergeStats stats;
+  for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) merge_fast_one<KIND, VEC, NCH>(a, T, lds, it, lane, stats);
+  stats.add(a, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -902,37 +874,41 @@ __device__ __forceinline__ u32 reprune_small_int(const VecTable& T, const QueryR
 // ---------------------------------------------------------------------------------------------
 // gram path kernel
 // ---------------------------------------------------------------------------------------------
+template <int NCH>
+struct GramLds {
+  __align__(16) unsigned char Xs[SM_TMAX * mm_stride(128u * NCH)];
+  SmallLds small;
+};
+
+template <int KIND, int VEC, int NCH>
+__device__ __forceinline__ void merge_gram_one(const MergeArgs& a, const VecTable& T, GramLds<NCH>& L, u32 it, int lane,
+                                               MergeStats& stats) {
+  const MergeItem item = a.list_items[1][it];
+  const u32 i0 = item.i0, cnt = item.cnt, b = item.b;
+  const u32 deg = meta_deg(item.meta), clean = meta_clean(item.meta);
+  const u32 total = deg + cnt;
+  u32* row = a.graph + (u64)b * a.R;
+  for (u32 j = lane; j < total; j += 64)
+    L.small.uid[j] = j < deg ? row[j] : (u32)(a.keys[i0 + (j - deg)] & 0xFFFFFFFFull);
+  __syncthreads();
+  const QueryRegs<KIND, VEC, NCH> Qb = load_query<KIND, VEC, NCH>(T.base + (u64)b * T.row_bytes, T.npieces, lane);
+  const u32 kept = reprune_small_int<KIND, VEC, NCH>(T, Qb, L.Xs, L.small, total, clean, a.R, a.a16, row, lane);
+  if (lane == 0) a.meta[b] = make_meta(kept, kept);
+  ++stats.rep;
+  stats.edges += cnt;
+  // pairs whose distance was formed: all of them, or only those with a new entry in them
+  stats.pair += total - clean <= 32u ? (unsigned long long)(total - clean) * total : (unsigned long long)total * (total + 1) / 2;
+}
+
 template <int KIND, int VEC, int NCH>
 __global__ __launch_bounds__(64) void merge_gram_kernel(MergeArgs a, VecTable T) {
-  constexpr bool kOk = KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value;
-  if constexpr (kOk) {
-    __shared__ __align__(16) unsigned char Xs[SM_TMAX * mm_stride(128u * NCH)];
-    __shared__ SmallLds small;
+  if constexpr (KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value) {
+    __shared__ GramLds<NCH> lds;
     const int lane = threadIdx.x;
     const u32 nitems = a.list_count[1];
-    unsigned long long n_rep = 0, n_edges = 0, n_pair = 0;
-    for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) {
-      const MergeItem item = a.list_items[1][it];
-      const u32 i0 = item.i0, cnt = item.cnt, b = item.b;
-      const u32 deg = meta_deg(item.meta), clean = meta_clean(item.meta);
-      const u32 total = deg + cnt;
-      u32* row = a.graph + (u64)b * a.R;
-      for (u32 j = lane; j < total; j += 64)
-        small.uid[j] = j < deg ? row[j] : (u32)(a.keys[i0 + (j - deg)] & 0xFFFFFFFFull);
-      __syncthreads();
-      const QueryRegs<KIND, VEC, NCH> Qb = load_query<KIND, VEC, NCH>(T.base + (u64)b * T.row_bytes, T.npieces, lane);
-      const u32 kept = reprune_small_int<KIND, VEC, NCH>(T, Qb, Xs, small, total, clean, a.R, a.a16, row, lane);
-      if (lane == 0) a.meta[b] = make_meta(kept, kept);
-      ++n_rep;
-      n_edges += cnt;
-      // pairs whose distance was formed: all of them, or only those with a new entry in them
-      n_pair += total - clean <= 32u ? (unsigned long long)(total - clean) * total : (unsigned long long)total * (total + 1) / 2;
-    }
-    if (a.counters != nullptr && lane == 0 && n_rep) {
-      atomicAdd(&block_counters(a.counters)->reprunes, n_rep);
-      atomicAdd(&block_counters(a.counters)->edges, n_edges);
-      atomicAdd(&block_counters(a.counters)->prune_evals, n_pair);
-    }
+    MergeStats stats;
+    for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) merge_gram_one<KIND, VEC, NCH>(a, T, lds, it, lane, stats);
+    stats.add(a, lane);
   }
 }
 
@@ -1084,10 +1060,9 @@ __device__ __forceinline__ u32 reprune_new_f32(const VecTable& T, const F32Lds& 
 // buffer three waves fit a compute unit, with the small one sixteen.
 // (Byte rows above 128 bytes: left alone, the compiler takes registers for one wave per SIMD.)
 template <int KIND, int VEC, int NCH, u32 CAP>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<KIND>::is_int && NCH == 2 ? 2 : 1))) void merge_generic_kernel(MergeArgs a, VecTable T) {
+__device__ __forceinline__ void merge_generic_one(const MergeArgs& a, const VecTable& T, u64* cand_lds, unsigned char* smem, u32 it,
+                                                  int lane, MergeStats& stats) {
   constexpr int LIST = CAP == MERGE_SPILL_MIN ? 2 : 3;
-  __shared__ u64 cand_lds[CAP];
-  extern __shared__ __align__(16) unsigned char smem[];
   constexpr bool kF32 = F32PruneOk<KIND, VEC, NCH>::value;
   u32* out = reinterpret_cast<u32*>(smem);  // R entries
   SelStage st;
@@ -1099,107 +1074,139 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<K
   if constexpr (kF32) F = f32_lds_carve(smem, a.R, out);
   constexpr bool kMfma = MfmaPruneOk<KIND, VEC, NCH>::value;
   const MfmaLds M = mfma_lds_carve(smem + ((a.R * 4u + 15u) & ~15u), a.R, T.row_bytes);  // used when a.use_mfma
-
-  const int lane = threadIdx.x;
-  const u32 nitems = a.list_count[LIST];
-  if (blockIdx.x >= nitems) return;
   const AlphaParam al{a.a16, a.af};
-  unsigned long long n_rep = 0, n_edges = 0, n_pair = 0;
+  const MergeItem item = a.list_items[LIST][LIST == 3 ? -(long long)it : (long long)it];
+  const u32 i0 = item.i0, cnt = item.cnt, b = item.b;
+  const u32 deg = meta_deg(item.meta);
+  const u32 total = deg + cnt;
+  u32* row = a.graph + (u64)b * a.R;
+  // a clean prefix and few new entries (meta holds no prefix where one cannot be relied on)
+  const u32 clean = meta_clean(item.meta);
+  const bool by_new = kF32 && CAP == MERGE_MEDIUM_MAX && clean > 0 && total - clean <= F32_NEW_MAX && total <= F32_LIST_MAX;
 
-  for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const MergeItem item = a.list_items[LIST][LIST == 3 ? -(long long)it : (long long)it];
-    const u32 i0 = item.i0, cnt = item.cnt, b = item.b;
-    const u32 deg = meta_deg(item.meta);
-    const u32 total = deg + cnt;
-    u32* row = a.graph + (u64)b * a.R;
-    // a clean prefix and few new entries (meta holds no prefix where one cannot be relied on)
-    const u32 clean = meta_clean(item.meta);
-    const bool by_new = kF32 && CAP == MERGE_MEDIUM_MAX && clean > 0 && total - clean <= F32_NEW_MAX && total <= F32_LIST_MAX;
-
-    // candidate list U = N_out(b) followed by the new sources
-    u64* cand;
-    const bool in_lds = total <= CAP;
-    if (in_lds) {
-      cand = cand_lds;
-    } else {
-      unsigned long long off = 0;
-      if (lane == 0) off = atomicAdd(a.arena_top, (unsigned long long)total);
-      off = readlane_u64(off, 0);
-      if (off + total > a.arena_cap) {  // cannot happen with the arena sized by the host
-        if (lane == 0) *a.error_flag = 1u;
-        continue;
-      }
-      cand = a.arena + off;
+  // candidate list U = N_out(b) followed by the new sources
+  u64* cand;
+  const bool in_lds = total <= CAP;
+  if (in_lds) {
+    cand = cand_lds;
+  } else {
+    unsigned long long off = 0;
+    if (lane == 0) off = atomicAdd(a.arena_top, (unsigned long long)total);
+    off = readlane_u64(off, 0);
+    if (off + total > a.arena_cap) {  // cannot happen with the arena sized by the host
+      if (lane == 0) *a.error_flag = 1u;
+      return;
     }
-    for (u32 j = lane; j < total; j += 64) {
-      const u32 id = j < deg ? row[j] : (u32)(a.keys[i0 + (j - deg)] & 0xFFFFFFFFull);
-      cand[j] = make_key(0u, id);
-    }
-    __syncthreads();
-
-    // distances d(b, x) for every x in U
-    const QueryRegs<KIND, VEC, NCH> Q = load_query<KIND, VEC, NCH>(T.base + (u64)b * T.row_bytes, T.npieces, lane);
-    for (u32 base = 0; base < total; base += 64) {
-      const u32 c64 = total - base < 64u ? total - base : 64u;
-      const u64* cb = cand + base;
-      const u32 dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [cb](u32 i) { return key_id(cb[i]); }, c64, lane);
-      const u32 c = cand_of_lane(lane);
-      const u32 id = c < c64 ? key_id(cb[c]) : 0u;
-      __syncthreads();
-      if (c < c64) cand[base + c] = make_key(dk, id) | (by_new && base + c >= clean ? 1ull : 0ull);
-    }
-    __syncthreads();
-
-    u32 pair_evals = total;
-    u32 kept;
-    if (in_lds) {
-      u32 n2 = 64;
-      while (n2 < total) n2 <<= 1;
-      for (u32 j = total + lane; j < n2; j += 64) cand[j] = KEY_INF;
-      __syncthreads();
-      bitonic_sort_keys(cand, n2, lane);
-      bool done = false;
-      if constexpr (kMfma) {
-        if (MfmaPruneOk<KIND, VEC, NCH>::always || a.use_mfma) {
-          kept = prune_sorted_mfma<KIND, VEC, NCH>(T, M, cand, total, a.R, a.a16, out, lane, pair_evals);
-          done = true;
-        }
-      }
-      if constexpr (kF32 && CAP == MERGE_MEDIUM_MAX) {
-        if (by_new) {
-          kept = reprune_new_f32<KIND, NCH>(T, F, T.base + (u64)b * T.row_bytes, cand, total, a.R, a.af, row, lane);
-          if (lane == 0) a.meta[b] = make_meta(kept, kept);
-          __syncthreads();
-          ++n_rep;
-          n_edges += cnt;
-          n_pair += (unsigned long long)total * (total - clean + 1u);
-          continue;
-        }
-      }
-      if constexpr (kF32)
-        kept = prune_sorted_f32<KIND, VEC, NCH>(T, F, T.base + (u64)b * T.row_bytes, cand, total, a.R, a.af, out, lane, pair_evals);
-      else if constexpr (!MfmaPruneOk<KIND, VEC, NCH>::always)
-        if (!done) kept = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand, total, a.R, al, out, lane, pair_evals);
-    } else {
-      // (the staged-vector areas are laid out for the walk in use; the minimum-search walk reads
-      // the selected vectors from device memory when the matrix-core layout is active)
-      SelStage st2 = st;
-      if (a.use_mfma) st2.vec = nullptr;
-      kept = prune_unsorted<KIND, VEC, NCH>(T, st2, cand, total, a.R, al, out, lane, pair_evals);
-    }
-    __syncthreads();
-    for (u32 j = lane; j < a.R; j += 64) row[j] = j < kept ? out[j] : NONE_ID;
-    if (lane == 0) a.meta[b] = make_meta(kept, kept);
-    __syncthreads();
-    ++n_rep;
-    n_edges += cnt;
-    n_pair += pair_evals;
+    cand = a.arena + off;
   }
-  if (a.counters != nullptr && lane == 0 && n_rep) {
-    atomicAdd(&block_counters(a.counters)->reprunes, n_rep);
-    atomicAdd(&block_counters(a.counters)->edges, n_edges);
-    atomicAdd(&block_counters(a.counters)->prune_evals, n_pair);
+  for (u32 j = lane; j < total; j += 64) {
+    const u32 id = j < deg ? row[j] : (u32)(a.keys[i0 + (j - deg)] & 0xFFFFFFFFull);
+    cand[j] = make_key(0u, id);
   }
+  __syncthreads();
+
+  // distances d(b, x) for every x in U
+  const QueryRegs<KIND, VEC, NCH> Q = load_query<KIND, VEC, NCH>(T.base + (u64)b * T.row_bytes, T.npieces, lane);
+  for (u32 base = 0; base < total; base += 64) {
+    const u32 c64 = total - base < 64u ? total - base : 64u;
+    const u64* cb = cand + base;
+    const u32 dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [cb](u32 i) { return key_id(cb[i]); }, c64, lane);
+    const u32 c = cand_of_lane(lane);
+    const u32 id = c < c64 ? key_id(cb[c]) : 0u;
+    __syncthreads();
+    if (c < c64) cand[base + c] = make_key(dk, id) | (by_new && base + c >= clean ? 1ull : 0ull);
+  }
+  __syncthreads();
+
+  u32 pair_evals = total;
+  u32 kept;
+  if (in_lds) {
+    u32 n2 = 64;
+    while (n2 < total) n2 <<= 1;
+    for (u32 j = total + lane; j < n2; j += 64) cand[j] = KEY_INF;
+    __syncthreads();
+    bitonic_sort_keys(cand, n2, lane);
+    bool done = false;
+    if constexpr (kMfma) {
+      if (MfmaPruneOk<KIND, VEC, NCH>::always || a.use_mfma) {
+        kept = prune_sorted_mfma<KIND, VEC, NCH>(T, M, cand, total, a.R, a.a16, out, lane, pair_evals);
+        done = true;
+      }
+    }
+    if constexpr (kF32 && CAP == MERGE_MEDIUM_MAX) {
+      if (by_new) {
+        kept = reprune_new_f32<KIND, NCH>(T, F, T.base + (u64)b * T.row_bytes, cand, total, a.R, a.af, row, lane);
+        if (lane == 0) a.meta[b] = make_meta(kept, kept);
+        __syncthreads();
+        ++stats.rep;
+        stats.edges += cnt;
+        stats.pair += (unsigned long long)total * (total - clean + 1u);
+        return;
+      }
+    }
+    if constexpr (kF32)
+      kept = prune_sorted_f32<KIND, VEC, NCH>(T, F, T.base + (u64)b * T.row_bytes, cand, total, a.R, a.af, out, lane, pair_evals);
+    else if constexpr (!MfmaPruneOk<KIND, VEC, NCH>::always)
+      if (!done) kept = prune_sorted<KIND, VEC, NCH>(T, st, blk, cand, total, a.R, al, out, lane, pair_evals);
+  } else {
+    // (the staged-vector areas are laid out for the walk in use; the minimum-search walk reads
+    // the selected vectors from device memory when the matrix-core layout is active)
+    SelStage st2 = st;
+    if (a.use_mfma) st2.vec = nullptr;
+    kept = prune_unsorted<KIND, VEC, NCH>(T, st2, cand, total, a.R, al, out, lane, pair_evals);
+  }
+  __syncthreads();
+  for (u32 j = lane; j < a.R; j += 64) row[j] = j < kept ? out[j] : NONE_ID;
+  if (lane == 0) a.meta[b] = make_meta(kept, kept);
+  __syncthreads();
+  ++stats.rep;
+  stats.edges += cnt;
+  stats.pair += pair_evals;
+}
+
+template <int KIND, int VEC, int NCH, u32 CAP>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<KIND>::is_int && NCH == 2 ? 2 : 1))) void merge_generic_kernel(MergeArgs a, VecTable T) {
+  __shared__ u64 cand_lds[CAP];
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x;
+  const u32 nitems = a.list_count[CAP == MERGE_SPILL_MIN ? 2 : 3];
+  MergeStats stats;
+  for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) merge_generic_one<KIND, VEC, NCH, CAP>(a, T, cand_lds, smem, it, lane, stats);
+  stats.add(a, lane);
+}
+
+// All three kinds in one launch, for batches with few segments: three launches one after the other take 24 us in a batch
+// of 200 points, this one 14.  A workgroup has the LDS and the registers of the largest kind: with the buffer of 4,096 keys
+// three share a compute unit, with that of 512 (CAP; longer lists have a launch of their own) eight.  The longest lists
+// first; merge_launches says where this pays.
+template <int KIND, int VEC, int NCH, u32 CAP>
+__global__ __launch_bounds__(64) void merge_all_kernel(MergeArgs a, VecTable T) {
+  if constexpr (KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x;
+    const u32 nfast = a.list_count[0], ngram = a.list_count[1], nlong = a.list_count[CAP == MERGE_SPILL_MIN ? 2 : 3];
+    MergeStats stats;
+    for (u32 it = blockIdx.x; it < nlong + ngram + nfast; it += gridDim.x) {
+      if (it < nlong)
+        merge_generic_one<KIND, VEC, NCH, CAP>(a, T, reinterpret_cast<u64*>(smem), smem + CAP * 8u, it, lane, stats);
+      else if (it < nlong + ngram)
+        merge_gram_one<KIND, VEC, NCH>(a, T, *reinterpret_cast<GramLds<NCH>*>(smem), it - nlong, lane, stats);
+      else
+        merge_fast_one<KIND, VEC, NCH>(a, T, *reinterpret_cast<FastLds<NCH>*>(smem), it - nlong - ngram, lane, stats);
+      __syncthreads();
+    }
+    stats.add(a, lane);
+  }
+}
+template <int KIND, int VEC, int NCH, u32 CAP>
+static hipError_t launch_merge_all(const MergeArgs& a, const VecTable& T, u32 grid, u32 lds, hipStream_t s) {
+  u32 all = CAP * 8u + lds;
+  all = all > sizeof(GramLds<NCH>) ? all : (u32)sizeof(GramLds<NCH>);
+  const auto kernel = merge_all_kernel<KIND, VEC, NCH, CAP>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)all);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), all, s, a, T);
+  return hipGetLastError();
 }
 
 // The three kernels work on disjoint rows, so they may run side by side: s_gram and s_generic are
@@ -1212,6 +1219,14 @@ static hipError_t launch_merge_t(const MergeArgs& a, const VecTable& T, u32 grid
   const u32 lds = F32PruneOk<KIND, VEC, NCH>::value ? f32_lds_bytes(a.R, T.npieces)
                   : a.use_mfma ? ((a.R * 4u + 15u) & ~15u) + mfma_lds_bytes(a.R, T.row_bytes)
                             : ((a.R * 8u + 15u) & ~15u) + 8u * stage_stride(T.row_bytes) + 32u + a.stage_bytes;
+  if constexpr (KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value) {
+    if (a.launches == 1)
+      return launch_merge_all<KIND, VEC, NCH, MERGE_SPILL_MIN>(a, T, grid < 1024u ? grid : 1024u, lds, s);
+    if (a.launches == 2) {
+      hipLaunchKernelGGL((merge_generic_kernel<KIND, VEC, NCH, MERGE_SPILL_MIN>), dim3(grid < 1024u ? grid : 1024u), dim3(64), lds, s, a, T);
+      return launch_merge_all<KIND, VEC, NCH, MERGE_MEDIUM_MAX>(a, T, grid < 4096u ? grid : 4096u, lds, s);
+    }
+  }
   const u32 grid_generic = (grid < 1024u || a.force_prune) ? grid : 1024u;
   hipLaunchKernelGGL((merge_generic_kernel<KIND, VEC, NCH, MERGE_SPILL_MIN>), dim3(grid_generic), dim3(64), lds,
                      s_generic, a, T);
@@ -1234,6 +1249,23 @@ hipError_t launch_merge(const DistCfg& cfg, const MergeArgs& a, u32 grid, hipStr
   if (grid == 0) return hipSuccess;
   VecTable T{a.points, (u32)cfg.row_bytes, cfg.npieces};
   ANN_DISPATCH_CFG(launch_merge_t, a, T, grid, s, s_gram, s_generic, s_medium);
+}
+
+// Batches of byte rows whose re-prunes go in one launch or two, on one stream; in larger ones each kind has a launch, and from
+// 2,048 points on a stream.  What counts is how many rows there are to prune, four to five per point: in one launch
+// three workgroups share a compute unit, in two eight.  Whole builds, side by side or one after the other as
+// before / in one launch / in two:
+//  - rows of up to 128 bytes, batches of 900 points (45,000, R = 64, L = 64) 10.7 / 9.3 ms; 1,600 (R = 64) 18.3 /
+//    16.9 / 16.9; 1,800 (int8, R = 48) 17.9 in one, 16.4 in two; 2,000 (R = 32) 20.5 and 19.6; 3,000 (int8, R = 64) 24.2 /
+//    26.7 / 24.0; 4,000 (R = 32) 30.8 in one, 27.3 in two; 4,000 (layered, R = 64) 28.1 / 28.7 / 27.7; 8,000 (R = 32) 30.4 / - /
+//    31.2; 20,000 (R = 64) 76.7 / - / 90.6.
+//  - rows of up to 256 bytes (256 registers): 1,200 points (200 bytes, R = 64) 17.1 / 14.5; 1,900 (256 bytes)
+//    19.0 / 18.0 / 17.2; 2,400 (200 bytes, R = 48) 20.4 / - / 19.0; 3,000 (R = 32) 23.9 / - / 24.7.
+u32 merge_launches(const DistCfg& cfg, u64 batch) {
+  if (!gram_path_ok(cfg)) return 0;
+  const bool narrow = cfg.nch == 1;
+  if (batch <= (narrow ? 1024u : 1280u)) return 1;
+  return batch <= (narrow ? 4096u : 2560u) ? 2 : 0;
 }
 
 bool gram_path_ok(const DistCfg& cfg) { return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256; }

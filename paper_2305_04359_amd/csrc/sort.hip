@@ -10,6 +10,7 @@
 // wide, so 20 destination bits (a million points) take two passes.
 #include "ann_device.hpp"
 #include "ann_internal.hpp"
+#include "plan_device.hpp"
 
 namespace annmi {
 
@@ -158,11 +159,15 @@ __global__ __launch_bounds__(64) void rs_scatter_kernel(const u64* keys, u64* ou
 // through LDS.  Bound by the chain of LDS round trips of a wave's rows.  6,400 keys
 // on 14 bits: 37 us in six launches, 13.5 us here; 1,024 keys 7 us, 4,096 keys 11 us (build of 10,000
 // points, R = 32: 9.65 -> 8.30 ms).
+//
+// PLAN: the keys are a batch's reversed edges, sorted by all bits of their destination, and the segments are planned in
+// the same launch: a thread looks at the keys it holds after the last pass, and finds the end of a segment that starts with
+// one of them in LDS.
 constexpr u64 RS_ONE_MAX = 64ull * 12 * 16;
 
-template <int WAVES, int ROWS>
+template <int WAVES, int ROWS, bool PLAN>
 __global__ __launch_bounds__(64 * WAVES) void rs_one_kernel(u64* keys, u32 count, u32 first_bit, u32 key_bits,
-                                                            u32 npass) {
+                                                            u32 npass, MergeArgs a) {
   constexpr u32 D = RS_RADIX;
   constexpr u32 N = 64u * ROWS * WAVES;
   constexpr u32 PL = D / (64u * WAVES);  // digits a thread owns in the scan
@@ -246,6 +251,62 @@ __global__ __launch_bounds__(64 * WAVES) void rs_one_kernel(u64* keys, u32 count
 #pragma unroll
   for (u32 q = 0; q < (u32)ROWS; ++q)
     if (i0 + 64u * q < count) keys[i0 + 64u * q] = k[q];
+  if constexpr (PLAN) {
+    __shared__ u32 cnt_lds[4], base_lds[4], stat_lds[2];
+    if (t < 4) cnt_lds[t] = 0;
+    if (t < 2) stat_lds[t] = 0;
+    __syncthreads();
+    u32 filed[ROWS], cnt[ROWS], m[ROWS];
+#pragma unroll
+    for (u32 q = 0; q < (u32)ROWS; ++q) {  // (all meta words requested before the first segment is measured)
+      const u32 i = i0 + 64u * q, b = (u32)(k[q] >> 32);
+      const bool head = i < count && b != NONE_ID && (i == 0 || (u32)(xch[i - 1u] >> 32) != b);
+      cnt[q] = head ? 1u : 0u;
+      m[q] = a.meta[head ? b : 0u];
+    }
+#pragma unroll
+    for (u32 q = 0; q < (u32)ROWS; ++q) {
+      filed[q] = NONE_ID;
+      if (cnt[q] == 0) continue;
+      const u32 i = i0 + 64u * q, b = (u32)(k[q] >> 32);
+      u32 lo = i, step = 1;  // gallop, then bisect
+      while (i + step < count && (u32)(xch[i + step] >> 32) == b) {
+        lo = i + step;
+        step <<= 1;
+      }
+      u32 hi = i + step < count ? i + step : count;
+      while (hi - lo > 1) {
+        const u32 mid = (lo + hi) >> 1;
+        if ((u32)(xch[mid] >> 32) == b)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      cnt[q] = hi - i;
+      const int kind = plan_segment(a, b, m[q], cnt[q], stat_lds, [&](u32 j) { return (u32)xch[i + j]; });
+      if (kind >= 0) filed[q] = ((u32)kind << 30) | atomicAdd(&cnt_lds[kind], 1u);
+    }
+    __syncthreads();
+    plan_reserve(a, cnt_lds, base_lds, stat_lds);
+    __syncthreads();
+#pragma unroll
+    for (u32 q = 0; q < (u32)ROWS; ++q)
+      if (filed[q] != NONE_ID) {
+        const u32 b = (u32)(k[q] >> 32), kind = filed[q] >> 30;
+        plan_file(a, (int)kind, base_lds[kind] + (filed[q] & 0x3FFFFFFFu), i0 + 64u * q, cnt[q], b, m[q]);
+      }
+  }
+}
+
+// One workgroup plans 1,024 keys in 3 us and so saves a launch; 6,400 keys, which are 25 workgroups' work, in 11, where the
+// launch of its own takes 5.
+constexpr u64 RS_PLAN_MAX = 64ull * 4 * 4;
+bool sort_and_plan_ok(u64 count) { return count <= RS_PLAN_MAX; }
+hipError_t launch_sort_and_plan(const MergeArgs& a, u64* keys, u32 key_bits, hipStream_t s) {
+  if (a.nkeys == 0) return hipSuccess;
+  const u32 npass = (key_bits + RS_DIGIT_BITS - 1) / RS_DIGIT_BITS;
+  hipLaunchKernelGGL((rs_one_kernel<4, 4, true>), dim3(1), dim3(256), 0, s, keys, (u32)a.nkeys, 32u, key_bits, npass, a);
+  return hipGetLastError();
 }
 
 hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u64 count, u32 key_bits,
@@ -260,7 +321,7 @@ hipError_t radix_sort_edges(u64* keys, u64* tmp, u32* hist, u64 hist_entries, u6
   // has room for all of them (18 us a sort in the layered build, where layers overlap; 9 us so).
   if (count <= RS_ONE_MAX) {
 #define RS_ONE(W, ROWS) \
-  hipLaunchKernelGGL((rs_one_kernel<W, ROWS>), dim3(1), dim3(64 * W), 0, s, keys, (u32)count, first_bit, key_bits, npass)
+  hipLaunchKernelGGL((rs_one_kernel<W, ROWS, false>), dim3(1), dim3(64 * W), 0, s, keys, (u32)count, first_bit, key_bits, npass, MergeArgs{})
     if (count <= 64u * 4 * 4)
       RS_ONE(4, 4);
     else if (count <= 64u * 8 * 8)
