@@ -9,11 +9,11 @@
 // every lane keeping the best of the candidates it sees for its own point); one workgroup per
 // leaf sorts the leaf's candidate pairs in LDS, and one wavefront per leaf runs Kruskal's scan
 // with the degree bound, 64 pairs at a time (a pair that fails once fails for good, so the wave
-// tests 64 in parallel and only the survivors are taken in order; the scan is a chain of
-// dependent LDS reads, so thousands of leaves are scanned side by side).
-// At the end the arcs of all trees are sorted by (point, neighbour), repeated ones dropped, and
-// every point's neighbours pruned with the alpha rule of Sec. 4.1 by the re-prune kernel of the
-// flat graph's BatchInsert.
+// tests 64 in parallel and accepts at once all that no earlier one can change; the scan is a chain of
+// dependent LDS trips, so thousands of leaves are scanned side by side).
+// At the end every point's neighbours of all trees, each once (found where the trees left them, in places of the
+// point's own, or, with many trees or a large degree bound, by sorting all arcs), are
+// pruned with the alpha rule of Sec. 4.1 by the re-prune kernel of the flat graph's BatchInsert.
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
@@ -22,6 +22,7 @@
 
 #include "ann_device.hpp"
 #include "driver_internal.hpp"
+#include "plan_device.hpp"
 
 using namespace annmi;
 
@@ -988,21 +989,25 @@ __global__ __launch_bounds__(1024) void hc_pairs_kernel(const u32* leaf_list, co
 // left always passes.  A tree that no earlier pair touches goes under the other's root, the smaller under the
 // larger where there is a choice (as far as the sizes are known: a root's word holds what it had when it last
 // took part in such a choice).
-// Accepted pairs go, as two arcs (point << 32 | neighbour), to arcs[2 * (off - leaf) ...] (a leaf of cnt
-// points accepts at most cnt - 1; unused entries keep what they hold).
+// SLOTS false: accepted pairs go, as two arcs (point << 32 | neighbour), to arcs[2 * (off - leaf) ...] (a leaf of cnt
+// points accepts at most cnt - 1; unused entries keep what they hold).  SLOTS true: to the ends' own places, slots[(tree
+// * n + point) * s + k] for a point's k-th neighbour in that tree.
 //
 // What bounds it is the chain of LDS trips.  One pair after another, and every point put under its root
 // before each chunk, took 5.6 ms for 30 trees of a million points; so 1.8.
 constexpr u32 ROOT = 0x8000u;  // parent words: a root's has this bit and the size of its tree
 constexpr u32 MARKS = 256;
+template <bool SLOTS>
 __global__ __launch_bounds__(64) void hc_kruskal_kernel(const u64* keys, const u32* leaf_off, u32 l, u32 s,
-                                                        const i32* knn_d, const u32* pair_cnt, u64* arcs) {
+                                                        const i32* knn_d, const u32* pair_cnt, u64* arcs, u32* slots, u32 n) {
   __shared__ unsigned short parent_lds[HC_MAX_LS];
   __shared__ unsigned char deg_lds[HC_MAX_LS];
   __shared__ u32 tree_mark[MARKS], point_mark[MARKS], ring_lds[128];
+  __shared__ unsigned short place_lds[SLOTS ? 128 : 1];  // which neighbours the ends are of each other
   volatile unsigned short* parent = parent_lds;
   volatile unsigned char* deg = deg_lds;
   volatile u32* ring = ring_lds;
+  volatile unsigned short* place = place_lds;
   const u32 leaf = blockIdx.x;
   const u32 off = leaf_off[leaf];
   const u32 cnt = leaf_off[leaf + 1] - off;
@@ -1028,8 +1033,15 @@ __global__ __launch_bounds__(64) void hc_kruskal_kernel(const u64* keys, const u
     if ((u32)lane < count) {
       const u32 mine = ring[(written + (u32)lane) & 127u];
       const u64 gu = keys[off + (mine >> 16)] & 0xFFFFFFFFull, gv = keys[off + (mine & 0xFFFFu)] & 0xFFFFFFFFull;
-      out[2 * (written + (u32)lane)] = (gu << 32) | gv;
-      out[2 * (written + (u32)lane) + 1] = (gv << 32) | gu;
+      if constexpr (SLOTS) {
+        const u32 k = place[(written + (u32)lane) & 127u];
+        u32* tree = slots + (u64)(off / n) * n * s;
+        tree[gu * s + (k >> 8)] = (u32)gv;
+        tree[gv * s + (k & 0xFFu)] = (u32)gu;
+      } else {
+        out[2 * (written + (u32)lane)] = (gu << 32) | gv;
+        out[2 * (written + (u32)lane) + 1] = (gv << 32) | gu;
+      }
     }
     written += count;
   };
@@ -1045,13 +1057,15 @@ __global__ __launch_bounds__(64) void hc_kruskal_kernel(const u64* keys, const u
     bool act = e < E && !dup;
     u32 ru = u, rv = v;
     u64 taken = 0;  // the chunk's accepted pairs
+    u32 du = 0, dv = 0;
     bool entered = false;
     for (;;) {
       u32 pu = 0, pv = 0;
       if (act) {
         pu = parent[ru];
         pv = parent[rv];
-        const u32 du = deg[u], dv = deg[v];
+        du = deg[u];
+        dv = deg[v];
         while (!(pu & ROOT)) {
           ru = pu;
           pu = parent[ru];
@@ -1090,14 +1104,18 @@ __global__ __launch_bounds__(64) void hc_kruskal_kernel(const u64* keys, const u
         const bool under_v = own_u && (!own_v || (pu & ~ROOT) <= (pv & ~ROOT));
         parent[under_v ? ru : rv] = (unsigned short)(under_v ? rv : ru);
         if (own_u && own_v) parent[under_v ? rv : ru] = (unsigned short)(ROOT | ((pu & ~ROOT) + (pv & ~ROOT)));
-        deg[u] = (unsigned char)(deg[u] + 1u);
-        deg[v] = (unsigned char)(deg[v] + 1u);
+        deg[u] = (unsigned char)(du + 1u);
+        deg[v] = (unsigned char)(dv + 1u);
         act = false;
       }
       taken |= ballot(take);
       order_lds();
     }
-    if ((taken >> lane) & 1ull) ring[(accepted + (u32)__builtin_popcountll(taken & lanemask_lt(lane))) & 127u] = pr;
+    if ((taken >> lane) & 1ull) {
+      const u32 at = (accepted + (u32)__builtin_popcountll(taken & lanemask_lt(lane))) & 127u;
+      ring[at] = pr;
+      if constexpr (SLOTS) place[at] = (unsigned short)(du << 8 | dv);
+    }
     accepted += (u32)__builtin_popcountll(taken);
     order_lds();
     if (accepted - written >= 64u) write_out(64u);
@@ -1111,6 +1129,83 @@ constexpr u32 UQ_TILE = 2048;  // keys per workgroup of 256 threads
 __device__ __forceinline__ bool uq_keep(const u64* keys, u64 i, u64 n) {
   return i < n && keys[i] != KEY_INF && (i == 0 || keys[i] != keys[i - 1]);
 }
+
+// The neighbours that up to COLLECT_MAX slots (trees times s) name for each point, each once, as the keys and work list items
+// of the final prune: in place of sorting all arcs by point and neighbour, eight passes over 480 MB for 30
+// trees of a million points.  A workgroup stages the slots of 64 points, which lie together tree by tree, in LDS; a wave
+// takes a point, and an id's first appearance is found in a small hash table in LDS.  Which place a point's keys
+// get among the others' depends on timing and has no influence on any result.  30 trees of a million points: sort, removal of
+// repeated arcs and planning 6.6 ms, this 0.56 (and 0.6 more in the scan of the trees, whose writes go to the
+// points' own places).
+constexpr u32 COLLECT_MAX = 96, COLLECT_POINTS = 64, COLLECT_WAVES = 4, COLLECT_HASH = 256;
+__global__ __launch_bounds__(64 * COLLECT_WAVES) void hc_collect_kernel(MergeArgs a, const u32* slots, u32 n, u32 T, u32 s, u64* keys,
+                                                                        u32* key_count) {
+  __shared__ u32 ids[COLLECT_POINTS][COLLECT_MAX + 1];
+  __shared__ u32 table_lds[COLLECT_WAVES][COLLECT_HASH];
+  __shared__ u32 found[COLLECT_POINTS], before[COLLECT_POINTS], cnt_lds[4], base_lds[4], stat_lds[2], key_base;
+  const u32 t = threadIdx.x, lane = t & 63u, w = t >> 6;
+  const u32 p0 = blockIdx.x * COLLECT_POINTS, np = n - p0 < COLLECT_POINTS ? n - p0 : COLLECT_POINTS;
+  if (t < 4) cnt_lds[t] = 0;
+  if (t < 2) stat_lds[t] = 0;
+  for (u32 tree = w; tree < T; tree += COLLECT_WAVES) {
+    const u32* in = slots + ((u64)tree * n + p0) * s;
+    for (u32 i = lane; i < np * s; i += 64) ids[i / s][tree * s + i % s] = in[i];
+  }
+  __syncthreads();
+  u32* table = table_lds[w];
+  const u32 m = T * s;  // at most COLLECT_MAX
+  for (u32 p = w; p < np; p += COLLECT_WAVES) {
+    for (u32 i = lane; i < COLLECT_HASH; i += 64) table[i] = NONE_ID;
+    const u32 x[2] = {lane < m ? ids[p][lane] : NONE_ID, lane + 64u < m ? ids[p][lane + 64u] : NONE_ID};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    u32 c = 0;
+#pragma unroll
+    for (u32 q = 0; q < 2; ++q) {
+      bool fresh = false;
+      if (x[q] != NONE_ID) {
+        // (at most 96 of 256 places are taken, so there is an end)
+        for (u32 h = (x[q] * 0x9E3779B1u) >> 24;; h = (h + 1u) & (COLLECT_HASH - 1u)) {
+          const u32 was = atomicCAS(&table[h], NONE_ID, x[q]);
+          fresh = was == NONE_ID;
+          if (fresh || was == x[q]) break;
+        }
+      }
+      const u64 fm = ballot(fresh);
+      if (fresh) ids[p][c + (u32)__builtin_popcountll(fm & lanemask_lt((int)lane))] = x[q];
+      c += (u32)__builtin_popcountll(fm);
+    }
+    if (lane == 0) found[p] = c;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  if (w == 0) {
+    const u32 c = lane < np ? found[lane] : 0u;
+    u32 incl = c;
+#pragma unroll
+    for (u32 off = 1; off < 64; off <<= 1) {
+      const u32 o = (u32)__shfl_up((int)incl, off, 64);
+      if (lane >= off) incl += o;
+    }
+    before[lane] = incl - c;
+    if (lane == 63) key_base = atomicAdd(key_count, incl);
+  }
+  int kind = -1;
+  u32 slot = 0;
+  __syncthreads();
+  if (t < np && found[t] != 0) {
+    kind = plan_segment(a, p0 + t, 0u, found[t], stat_lds, [](u32) { return 0u; });  // (force_prune: nothing is appended)
+    slot = atomicAdd(&cnt_lds[kind], 1u);
+  }
+  for (u32 p = w; p < np; p += COLLECT_WAVES)
+    for (u32 i = lane; i < found[p]; i += 64) keys[key_base + before[p] + i] = ((u64)(p0 + p) << 32) | ids[p][i];
+  __syncthreads();
+  plan_reserve(a, cnt_lds, base_lds, stat_lds);
+  __syncthreads();
+  if (kind >= 0) plan_file(a, kind, base_lds[kind] + slot, key_base + before[t], found[t], p0 + t, 0u);
+}
+
 
 __global__ __launch_bounds__(256) void uq_count_kernel(const u64* keys, u64 n, u32* counts) {
   __shared__ u32 total;
@@ -1453,8 +1548,8 @@ int hc_partition(HcCtx& X, u32 tree0, u32 G, std::vector<Leaf>& leaves, hipStrea
 }
 
 // Leaves -> nearest neighbours -> degree-bounded trees, for a whole group; the accepted pairs of
-// the group's j-th leaf land, as arcs, at arcs[2 * (goff_j - j) ...].
-int hc_leaves(HcCtx& X, u32 G, const std::vector<Leaf>& leaves, u64* arcs, hipStream_t st) {
+// the group's j-th leaf land, as arcs, at arcs[2 * (goff_j - j) ...], or, where `slots` is given, there.
+int hc_leaves(HcCtx& X, u32 G, const std::vector<Leaf>& leaves, u64* arcs, u32* slots, hipStream_t st) {
   const u64 N = (u64)G * X.n;
   const u32 nleaves = (u32)leaves.size();
   // leaf_off[nleaves + 1] | tile_of_leaf[nleaves + 1]: where a leaf's points and its tiles of 32 begin
@@ -1557,8 +1652,12 @@ int hc_leaves(HcCtx& X, u32 G, const std::vector<Leaf>& leaves, u64* arcs, hipSt
                          X.l, X.knn_pos.as<unsigned short>(), X.knn_d.as<i32>(), X.pair_cnt.as<u32>());
     }
   }
-  hipLaunchKernelGGL(hc_kruskal_kernel, dim3(nleaves), dim3(64), 0, st, X.final_keys.as<u64>(), X.leaf_off.as<u32>(), X.l,
-                     X.s, X.knn_d.as<i32>(), X.pair_cnt.as<u32>(), arcs);
+  if (slots != nullptr)
+    hipLaunchKernelGGL(hc_kruskal_kernel<true>, dim3(nleaves), dim3(64), 0, st, X.final_keys.as<u64>(), X.leaf_off.as<u32>(), X.l,
+                       X.s, X.knn_d.as<i32>(), X.pair_cnt.as<u32>(), nullptr, slots, (u32)X.n);
+  else
+    hipLaunchKernelGGL(hc_kruskal_kernel<false>, dim3(nleaves), dim3(64), 0, st, X.final_keys.as<u64>(), X.leaf_off.as<u32>(), X.l,
+                       X.s, X.knn_d.as<i32>(), X.pair_cnt.as<u32>(), arcs, nullptr, (u32)X.n);
   HIP_TRY(hipGetLastError());
   return ANN_OK;
 }
@@ -1643,7 +1742,7 @@ static int hc_one_tree(const void* points_dev, uint64_t n, uint32_t d, ann_dtype
   std::vector<Leaf> leaves;
   rc = hc_partition(X, tree, 1, leaves, st);
   if (rc) return rc;
-  rc = hc_leaves(X, 1, leaves, arcs.as<u64>(), st);
+  rc = hc_leaves(X, 1, leaves, arcs.as<u64>(), nullptr, st);
   if (rc) return rc;
   std::vector<u64> hk(n), ha(2 * n);
   HIP_TRY(hipMemcpyAsync(hk.data(), X.final_keys.p, n * 8, hipMemcpyDeviceToHost, st));
@@ -1769,9 +1868,17 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
   if (rc) return rc;
   mark("buffers of a tree group");
   const u64 total = (u64)T * 2 * n;
-  HIP_TRY(arcs.alloc(total * 8));
+  // s neighbours per tree and point at most: with few of them every point has a place for each (4 T s n bytes, no more
+  // than the arcs), and nothing is sorted
+  const bool by_slots = s <= 4u && (u64)T * s <= COLLECT_MAX;
+  if (by_slots) {
+    HIP_TRY(arcs.alloc((u64)T * s * n * 4));
+    HIP_TRY(hipMemsetAsync(arcs.p, 0xFF, (u64)T * s * n * 4, st));
+  } else {
+    HIP_TRY(arcs.alloc(total * 8));
+    HIP_TRY(hipMemsetAsync(arcs.p, 0xFF, total * 8, st));
+  }
   HIP_TRY(arcs_tmp.alloc(total * 8));
-  HIP_TRY(hipMemsetAsync(arcs.p, 0xFF, total * 8, st));
   mark("arc buffers");
   std::vector<Leaf> leaves;
   for (u32 t = 0; t < T; t += G) {
@@ -1779,30 +1886,33 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
     rc = hc_partition(X, t, Gc, leaves, st);
     if (rc) return rc;
     mark("cluster trees");
-    rc = hc_leaves(X, Gc, leaves, arcs.as<u64>() + (u64)t * 2 * n, st);
+    rc = by_slots ? hc_leaves(X, Gc, leaves, nullptr, arcs.as<u32>() + (u64)t * s * n, st)
+                  : hc_leaves(X, Gc, leaves, arcs.as<u64>() + (u64)t * 2 * n, nullptr, st);
     if (rc) return rc;
     mark("leaves");
     g->stats.rounds += Gc;
   }
-  // all arcs by (point, neighbour): the neighbour bits first, then, stably, the point bits; the
-  // unused entries (all ones) end up behind every point
-  const u64 he = radix_hist_entries(total);
-  HIP_TRY(big_hist.alloc(he * 4));
-  const u32 idb = bits_to_hold(n);
-  HIP_TRY(radix_sort_edges(arcs.as<u64>(), arcs_tmp.as<u64>(), big_hist.as<u32>(), he, total, idb, st, 0));
-  HIP_TRY(radix_sort_edges(arcs.as<u64>(), arcs_tmp.as<u64>(), big_hist.as<u32>(), he, total, idb, st, 32));
-  // each (point, neighbour) once
-  const u32 ntiles = (u32)((total + UQ_TILE - 1) / UQ_TILE);
-  HIP_TRY(uq_counts.alloc(((size_t)ntiles + 1) * 4));
-  hipLaunchKernelGGL(uq_count_kernel, dim3(ntiles), dim3(256), 0, st, arcs.as<u64>(), total, uq_counts.as<u32>());
-  hipLaunchKernelGGL(uq_scan_kernel, dim3(1), dim3(1024), 0, st, uq_counts.as<u32>(), ntiles);
-  hipLaunchKernelGGL(uq_scatter_kernel, dim3(ntiles), dim3(256), 0, st, arcs.as<u64>(), total, uq_counts.as<u32>(),
-                     arcs_tmp.as<u64>());
-  HIP_TRY(hipGetLastError());
   u32 nuniq = 0;
-  HIP_TRY(hipMemcpyAsync(&nuniq, uq_counts.as<u32>() + ntiles, 4, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  mark("arcs sorted, each once");
+  if (!by_slots) {
+    // all arcs by (point, neighbour): the neighbour bits first, then, stably, the point bits; the
+    // unused entries (all ones) end up behind every point
+    const u64 he = radix_hist_entries(total);
+    HIP_TRY(big_hist.alloc(he * 4));
+    const u32 idb = bits_to_hold(n);
+    HIP_TRY(radix_sort_edges(arcs.as<u64>(), arcs_tmp.as<u64>(), big_hist.as<u32>(), he, total, idb, st, 0));
+    HIP_TRY(radix_sort_edges(arcs.as<u64>(), arcs_tmp.as<u64>(), big_hist.as<u32>(), he, total, idb, st, 32));
+    // each (point, neighbour) once
+    const u32 ntiles = (u32)((total + UQ_TILE - 1) / UQ_TILE);
+    HIP_TRY(uq_counts.alloc(((size_t)ntiles + 1) * 4));
+    hipLaunchKernelGGL(uq_count_kernel, dim3(ntiles), dim3(256), 0, st, arcs.as<u64>(), total, uq_counts.as<u32>());
+    hipLaunchKernelGGL(uq_scan_kernel, dim3(1), dim3(1024), 0, st, uq_counts.as<u32>(), ntiles);
+    hipLaunchKernelGGL(uq_scatter_kernel, dim3(ntiles), dim3(256), 0, st, arcs.as<u64>(), total, uq_counts.as<u32>(),
+                       arcs_tmp.as<u64>());
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(&nuniq, uq_counts.as<u32>() + ntiles, 4, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    mark("arcs sorted, each once");
+  }
   // prune(p, neighbours, R) for every point: the re-prune kernel of BatchInsert on empty rows
   HIP_TRY(hipMemsetAsync(g->meta, 0, (size_t)n * sizeof(u32), st));
   HIP_TRY(lists.alloc(3 * n * sizeof(MergeItem)));
@@ -1821,7 +1931,8 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
   u32* sm = small.as<u32>();
   ma.list_count = sm + 8;
   for (int c = 0; c < 3; ++c) ma.list_items[c] = lists.as<MergeItem>() + (u64)c * n;
-  ma.list_items[3] = ma.list_items[2] + (n - 1);  // (not filled here: every list is pruned by the large instance)
+  ma.list_items[3] = ma.list_items[2] + (n - 1);
+  ma.medium_max = gram_path_ok(g->cfg) ? 0u : MERGE_MEDIUM_MAX;
   ma.fast_amax = fast_path_amax(g->cfg);
   ma.gram_ok = gram_path_ok(g->cfg) ? 1u : 0u;
   ma.gram_tmax = gram_path_tmax();
@@ -1836,7 +1947,17 @@ int ann_hcnng_build_with(const void* points_dev, uint64_t n, uint32_t d, ann_dty
   ma.counters = nullptr;
   ma.force_prune = 1;
   g->clean_alpha = alpha;
-  HIP_TRY(launch_plan(ma, st));
+  if (by_slots) {
+    u32* key_count = sm + 12;
+    hipLaunchKernelGGL(hc_collect_kernel, dim3((u32)((n + COLLECT_POINTS - 1) / COLLECT_POINTS)), dim3(64 * COLLECT_WAVES), 0, st, ma,
+                       arcs.as<u32>(), (u32)n, T, s, arcs_tmp.as<u64>(), key_count);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(&nuniq, key_count, 4, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    mark("neighbours, each once");
+  } else {
+    HIP_TRY(launch_plan(ma, st));
+  }
   const u64 want = nuniq < 8192 ? nuniq : 8192;
   HIP_TRY(launch_merge(g->cfg, ma, (u32)(want ? want : 1), st, st, st, st));
   u32 flags[4] = {0, 0, 0, 0};

@@ -34,3 +34,18 @@ def test_leaves_equal_the_oracles(env, kind):
         _, off, edges = A.ann_hcnng_tree_edges(dev(torch, x), 1024, s, l, 5, 0)
         want = O.hcnng_leaf(O.Dataset(x, 0), np.arange(n), s, l)
         assert len(off) == 2 and np.array_equal(np.asarray(edges), np.asarray(want)), (n, l, s)
+
+
+@pytest.mark.parametrize("n,T,s,Ls,dtype", [(64, 32, 3, 20, "u8"), (65, 24, 4, 30, "u8"), (700, 33, 3, 50, "u8"), (700, 25, 4, 64, "u8"),
+                                            (701, 3, 5, 60, "u8"), (127, 96, 1, 9, "u8"), (640, 1, 2, 33, "u8"), (2, 4, 3, 5, "u8"),
+                                            (700, 32, 3, 50, "f32"), (300, 40, 3, 50, "f32")])
+def test_neighbours_of_all_trees(env, n, T, s, Ls, dtype):
+    """Trees times s at 96 and beyond, s at 4 and beyond, points around a workgroup's 64: graphs equal the oracle's."""
+    torch, A, O = env
+    say(f"cluster collect n={n} T={T} s={s}")
+    rng = np.random.default_rng(n + T)
+    x = rng.integers(0, 256, (n, 32)).astype(np.uint8)
+    if dtype == "f32":  # whole numbers: the distances are exact in fp32
+        x = x.astype(np.float32)
+    g = A.ann_hcnng_build(dev(torch, x), T, Ls, s, 10, 24, 1.2, seed=3)
+    assert np.array_equal(g.neighbors(), O.hcnng_build(O.Dataset(x, 0), T, Ls, s, 10, 24, 1.2, seed=3, threads=0))
