@@ -339,7 +339,7 @@ struct SearchQueryLds {
 // SK: 16-byte pieces per lane of the vertices' sketches (0: there are none).  Once the beam is full, a row's
 // candidates whose sketch puts them certainly beyond the beam's last entry are dropped unread.
 template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK>
-__device__ __forceinline__ void search_one(const SearchArgs& a, const VecTable& T, const SketchTable& K) {
+__device__ __forceinline__ void search_one(SearchArgs a, VecTable T, SketchTable K) {
   extern __shared__ __align__(16) unsigned char smem[];
   u64* beam = reinterpret_cast<u64*>(smem);
   u64* skeys = beam + NSLOT * 64;  // survivors of one batch of candidates

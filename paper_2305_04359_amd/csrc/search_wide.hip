@@ -146,7 +146,9 @@ __device__ __forceinline__ const SearchArgs& args_here() {
 // holds the kernel to 128 registers, and three float instances of 8 pieces per lane spill 2 to 7 of
 // them.  Free to take up to 139 they do not spill, but beyond 384 searches a second generation
 // waits for the first (300,000 points of 256 floats, R = 32, 512 searches, L = 100: 556 -> 810 us).
-template <int KIND, int VEC, int NCH, int NSLOT>
+//
+// FIRST: the first wave, whose chain the search is, goes before the waves that work ahead (launch_wide_slots).
+template <int KIND, int VEC, int NCH, int NSLOT, bool FIRST>
 __global__ __launch_bounds__(64 * WIDE_MAX_WAVES, 4) void search_wide_kernel(SearchArgs a, VecTable T, u32 nlists) {
   extern __shared__ __align__(16) unsigned char smem[];
   u64* lists = reinterpret_cast<u64*>(smem);  // nlists x 64
@@ -234,6 +236,7 @@ __global__ __launch_bounds__(64 * WIDE_MAX_WAVES, 4) void search_wide_kernel(Sea
       }
     }
   } else {
+    if constexpr (FIRST) __builtin_amdgcn_s_setprio(3);
     u32 st = a.start;
     if (a.starts != nullptr) st = a.starts[a.slot != nullptr ? a.slot[qi] : qi];
     const u32 dk = readlane_u32(eval_up_to_64<KIND, VEC, NCH>(T, Q, [st](u32) { return st; }, 1u, lane), 0);
@@ -413,6 +416,18 @@ __global__ __launch_bounds__(64 * WIDE_MAX_WAVES, 4) void search_wide_kernel(Sea
   }
 }
 
+template <int KIND, int VEC, int NCH, int NSLOT>
+static void launch_wide_slots(const SearchArgs& a, const VecTable& T, u32 nlists, dim3 grid, dim3 block, u32 lds, hipStream_t s) {
+  // The first wave before the others: where four waves and more share a SIMD (500 searches on 300,000 points, R = 48, L = 64,
+  // 125.5 -> 119.5 us, on float rows 174.6 -> 169.5, 900 on 900,000 points 153.8 -> 151.6; builds of 25,000 points 14.3 ->
+  // 13.9 ms), and in the upper layers of a layered build, beside which the bottom layer searches (200,000 points: 27.4 ->
+  // 26.6 ms).  With fewer searches it only holds up the waves it will wait for (300 on 500,000 points 153.8 -> 155.4 us).
+  if (a.nq > 384u || (a.starts != nullptr && a.vis != nullptr))
+    hipLaunchKernelGGL((search_wide_kernel<KIND, VEC, NCH, NSLOT, true>), grid, block, lds, s, a, T, nlists);
+  else
+    hipLaunchKernelGGL((search_wide_kernel<KIND, VEC, NCH, NSLOT, false>), grid, block, lds, s, a, T, nlists);
+}
+
 template <int KIND, int VEC, int NCH>
 static hipError_t launch_wide(const SearchArgs& a, const VecTable& T, u32 waves, hipStream_t s) {
   const u32 nlists = waves * 4u < WIDE_MAX_LISTS ? waves * 4u : WIDE_MAX_LISTS;
@@ -420,9 +435,9 @@ static hipError_t launch_wide(const SearchArgs& a, const VecTable& T, u32 waves,
   const u32 lds = nlists * 64u * 8u + (u32)sizeof(WideCtrl) + a.hash_buckets * 16u;
   const dim3 grid(a.nq), block(waves * 64u);
   switch (ns) {
-    case 1: hipLaunchKernelGGL((search_wide_kernel<KIND, VEC, NCH, 1>), grid, block, lds, s, a, T, nlists); break;
-    case 2: hipLaunchKernelGGL((search_wide_kernel<KIND, VEC, NCH, 2>), grid, block, lds, s, a, T, nlists); break;
-    case 4: hipLaunchKernelGGL((search_wide_kernel<KIND, VEC, NCH, 4>), grid, block, lds, s, a, T, nlists); break;
+    case 1: launch_wide_slots<KIND, VEC, NCH, 1>(a, T, nlists, grid, block, lds, s); break;
+    case 2: launch_wide_slots<KIND, VEC, NCH, 2>(a, T, nlists, grid, block, lds, s); break;
+    case 4: launch_wide_slots<KIND, VEC, NCH, 4>(a, T, nlists, grid, block, lds, s); break;
     default: return hipErrorInvalidConfiguration;
   }
   return hipGetLastError();
