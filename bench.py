@@ -245,15 +245,19 @@ def other_phases(st, w):
     phase times (all against the HBM peak; none of them is the dominant kernel).
     prune (step 1): the vectors of V are gathered once (|V| = hops), V is written by the search and
     read here (2 x 8 B per entry), the new row is written.  sort: every pass reads and writes the
-    8-byte keys.  merge (step 2): a touched row is read and written; a re-pruned row's old entries
+    8-byte keys; ids of up to 21 bits take one pass here, and the grouping of its buckets, another
+    read and write, in the merge phase.  merge (step 2): a touched row is read and written; a re-pruned row's old entries
     and its new sources are gathered (R vectors + one per new edge: an upper bound, rows are not
     always full and appended edges need no vector)."""
     row_bytes = w.d * w.points.dtype.itemsize
-    passes = (int(w.n).bit_length() + 9) // 10  # ten key bits per pass over the destination's bits
+    bits = int(w.n).bit_length()
+    grouped = bits <= 21
+    passes = 1 if grouped else (bits + 9) // 10  # ten key bits per pass over the destination's bits
     b = {
         "prune": st["hops"] * (row_bytes + 16) + st["prunes"] * 4 * w.R,
         "sort": passes * 2 * 8 * st["edges"],
-        "merge": (st["reprunes"] + st["appends"]) * 2 * 4 * w.R + (st["reprunes"] * w.R + st["edges"]) * row_bytes,
+        "merge": (st["reprunes"] + st["appends"]) * 2 * 4 * w.R + (st["reprunes"] * w.R + st["edges"]) * row_bytes
+        + (2 * 8 * st["edges"] if grouped else 0),
     }
     out = {}
     for k, v in b.items():

@@ -122,7 +122,8 @@ typedef struct {
 typedef struct {
   uint64_t searches;    /* greedy searches run                                   */
   uint64_t hops;        /* vertices processed, summed over searches (|V|)        */
-  uint64_t evals;       /* distances taken in searches, re-evaluations included; where
+  uint64_t evals;       /* distances taken in searches, re-evaluations and the ones that a
+                           row's 8-bit sketch settled included; where
                            several waves share a search, also those taken ahead of
                            their turn (their number depends on timing)            */
   uint64_t prunes;      /* step-1 prunes                                         */
@@ -436,9 +437,9 @@ int ann_hcnng_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dt
  *                 side, G = max(1, min(T, floor(2^25 / n))); stride = the bytes of a
  *                 row rounded up to a multiple of 32; more where a group splits
  *                 into more tiles of 32 points than that has room for
- *   33 T n        for the edges of all T trees
+ *   33 T n        for the edges of all T trees; (16 + 4 s) T n where s <= 4 and s T <= 96
  *   48 n          and, where s T is above 4,096, 8 bytes per distinct edge
- * which is 8.0 GB at n = 10^6 rows of 128 bytes, T = 30, Ls = 1000, l = 10.  hipMalloc
+ * which is 7.9 GB at n = 10^6 rows of 128 bytes, T = 30, Ls = 1000, s = 3, l = 10.  hipMalloc
  * and hipFree of that size now and then take longer than the build itself.       */
 typedef struct {
   ann_alloc_fn alloc;     /* device memory for the graph and all scratch; NULL =    */

@@ -306,6 +306,7 @@ int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStr
     (void)hipGetLastError();
     return ANN_OK;
   }
+  std::lock_guard<std::mutex> hold(g->sketch_lock);
   if (g->sketch_cap < g->n) {
     if (g->sketch_buf) {
       HIP_TRY(hipDeviceSynchronize());  // earlier calls may still read the old ones
@@ -318,6 +319,9 @@ int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStr
       g->sketch_buf = nullptr;
       return ANN_OK;
     }
+    // whatever the memory's last owner queued is over before any call, on whatever stream, uses it (once: later calls
+    // write the same bytes again)
+    HIP_TRY(hipStreamSynchronize(st));
     g->sketch_cap = g->n;
   }
   HIP_TRY(launch_sketch_rows(g->cfg, points, 0, g->n, g->sketch_buf, st));

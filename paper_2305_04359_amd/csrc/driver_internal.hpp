@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <ctime>
+#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -184,6 +185,7 @@ struct ann_graph {
   // memory for the ones that a call of ann_search makes, and the rows it has room for
   mutable void* sketch_buf = nullptr;
   mutable annmi::u64 sketch_cap = 0;
+  mutable std::mutex sketch_lock;
   // scratch of the insertions that follow the build (ann_insert_batch, ann_insert_points), kept
   // between calls: allocating and freeing it costs more than a batch of ten thousand points
   annmi::BatchScratch* scratch = nullptr;
