@@ -336,10 +336,12 @@ struct SearchQueryLds {
 // OWN: every search has a start vertex of its own and reports the closest vertex it found (the
 // layered index); compiled apart so that the flat graph's searches do not carry its arguments.
 // NETWORK: see beam_insert.
+// (Arguments by reference: by value the byte instances take 65 to 79 registers for 62 to 64 and lose one wave per SIMD or two;
+// a build of 331,958 int8 points at R = 32 39.4 -> 41.4 ms.)
 // SK: 16-byte pieces per lane of the vertices' sketches (0: there are none).  Once the beam is full, a row's
 // candidates whose sketch puts them certainly beyond the beam's last entry are dropped unread.
 template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK>
-__device__ __forceinline__ void search_one(SearchArgs a, VecTable T, SketchTable K) {
+__device__ __forceinline__ void search_one(const SearchArgs& a, const VecTable& T, const SketchTable& K) {
   extern __shared__ __align__(16) unsigned char smem[];
   u64* beam = reinterpret_cast<u64*>(smem);
   u64* skeys = beam + NSLOT * 64;  // survivors of one batch of candidates
