@@ -336,266 +336,13 @@ struct SearchQueryLds {
 // OWN: every search has a start vertex of its own and reports the closest vertex it found (the
 // layered index); compiled apart so that the flat graph's searches do not carry its arguments.
 // NETWORK: see beam_insert.
-// (Arguments by reference: by value the byte instances take 65 to 79 registers for 62 to 64 and lose one wave per SIMD or two;
-// a build of 331,958 int8 points at R = 32 39.4 -> 41.4 ms.)
 // SK: 16-byte pieces per lane of the vertices' sketches (0: there are none).  Once the beam is full, a row's
 // candidates whose sketch puts them certainly beyond the beam's last entry are dropped unread.
-template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK>
-__device__ __forceinline__ void search_one(const SearchArgs& a, const VecTable& T, const SketchTable& K) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  u64* beam = reinterpret_cast<u64*>(smem);
-  u64* skeys = beam + NSLOT * 64;  // survivors of one batch of candidates
-  u32* cid = reinterpret_cast<u32*>(skeys);  // the batch's ids: dead once its keys are formed
-  // (SK) the query, which lives in LDS: a row that must be read is the rarer case, and the registers are waves
-  Piece<VEC>* qlds = reinterpret_cast<Piece<VEC>*>(skeys + 64);
-  u32* hash = reinterpret_cast<u32*>(qlds + (SK > 0 ? LPC * (NCH + 2 * SK) : 0));  // 16-byte aligned
-
-  const int lane = threadIdx.x;
-  const u32 qi = blockIdx.x;
-  const u32 nb = a.hash_buckets;
-  uint4* bucket = reinterpret_cast<uint4*>(hash);
-  constexpr bool compact = TAG16;                     // eight 16-bit tags per bucket
-  const bool tags21 = !TAG16 && a.tag_width == 21u;  // six 21-bit tags per bucket
-  const bool tagged = compact || tags21;
-  const u32 idmask = tagged ? ((1u << a.id_bits) - 1u) : 0u;
-  const u32 tagmask = tagged ? ((1u << (a.id_bits - (31u - (u32)__builtin_clz(nb)))) - 1u) : 0u;
-  // bucket = floor(y' * nb / 2^24) with y' the top 24 bits of y (y shifted up if it has fewer),
-  // as the high part of a 24 x 24-bit product: y' * (nb << 8) >> 32
-  const u32 yshl = tagged && a.id_bits < 24u ? 24u - a.id_bits : 0u;
-  const u32 yshr = tagged && a.id_bits > 24u ? a.id_bits - 24u : 0u;
-  const u32 nb8 = nb << 8;
-  auto bucket_of_y = [=](u32 y) { return umulhi24((y << yshl) >> yshr, nb8); };
-  auto bucket_of_id = [=](u32 x) { return umulhi24((x * 0x9E3779B1u) >> 8, nb8); };
-  const u32 L = a.L;
-
-  const u32 qrow = a.qidx ? a.qidx[qi] : qi;
-  const QueryRegs<KIND, VEC, NCH> Qr =
-      load_query<KIND, VEC, NCH>(a.queries + (u64)qrow * a.qrow_bytes, T.npieces, lane);
-  using Query = std::conditional_t<(SK > 0), SearchQueryLds<KIND, VEC, NCH>, SearchQuery<KIND, VEC, NCH>>;
-  const Query Q(Qr, qlds, lane);
-  SketchQuery SQ;
-  u32 sk_last = 0;  // where this lane reads the last of a sketch's pieces: its own, or that of the group's last lane
-  if constexpr (SK > 0) {
-    SQ = sketch_query<KIND, NCH, SK>(Qr, reinterpret_cast<uint4*>(qlds + LPC * NCH), lane);
-    const u32 sub = (u32)lane & (LPC - 1);
-    sk_last = (SK - 1) * 128u + (sub + 32u * (SK - 1) < T.npieces ? sub : LPC - 1u) * 16u;
-  }
-
-  if constexpr (NCH == 1) {
-    for (u32 i = lane; i < 4u * nb; i += 64) hash[i] = NONE_ID;
-  } else {  // (larger tables; the small one gains nothing)
-    for (u32 i = lane; i < nb; i += 64) bucket[i] = make_uint4(NONE_ID, NONE_ID, NONE_ID, NONE_ID);
-  }
-  if (a.batch_counters != nullptr && qi == 0 && lane == 0) zero_batch_counters(a.batch_counters);
-
-  u64 A[NSLOT];
-#pragma unroll
-  for (int s = 0; s < NSLOT; ++s) A[s] = KEY_INF;
-
-  // beam <- {s}
-  u32 st = a.start;
-  if constexpr (OWN) {
-    if (a.starts != nullptr) st = a.starts[a.slot != nullptr ? a.slot[qi] : qi];
-  }
-  {
-    u32 dk;
-    if constexpr (SK > 0) {
-      if (lane == 0) cid[0] = st;
-      __syncthreads();
-      dk = eval_rows<KIND, NCH>(T, Q, cid, 1u, lane);
-    } else {
-      dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [st](u32) { return st; }, 1u, lane);
-    }
-    dk = readlane_u32(dk, 0);
-    if (lane == 0) {
-      A[0] = make_key(dk, st);
-      beam[0] = A[0];  // the LDS copy of the beam is kept current (processed flags aside)
-    }
-  }
-  __syncthreads();
-  if (lane == 0) {
-    if (compact) {
-      const u32 y = mix_id(st, idmask, a.id_bits);
-      hash[4u * bucket_of_y(y)] = 0xFFFF0000u | (y & tagmask);
-    } else if (tags21) {
-      const u32 y = mix_id(st, idmask, a.id_bits);
-      hash[4u * bucket_of_y(y)] = 0xFFE00000u | (y & tagmask);
-    } else {
-      hash[4u * bucket_of_id(st)] = st;
-    }
-  }
-
-  u32 size = 1, nv = 0, evals = 1;
-  u32 n_pass = 0, n_surv = 0, n_ins = 0;  // statistics only
-  // SK: whether fewer than half of the last row's new candidates entered the beam.  On the way in from the
-  // start vertex most do, and reading the sketches first would only put more bytes and another trip to
-  // memory in front of them.
-  bool sparse = false;
-  // where the visited list goes: the search's own slot, later perhaps a spill chunk
-  u64* vptr = a.vis != nullptr ? a.vis + (u64)qi * a.vis_cap : nullptr;
-  u32 vcap = a.vis_cap;
-  if (a.vis_where != nullptr && lane == 0) a.vis_where[qi] = ~0ull;
-
-  for (;;) {
-    // p* <- closest unprocessed member of the beam
-    int pos = -1;
-    u64 pk = 0;
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-      if (pos < 0) {
-        const u64 m = ballot(A[s] != KEY_INF && !(A[s] & 1ull));
-        if (m) {
-          const int l = __builtin_ctzll(m);
-          pos = s * 64 + l;
-          pk = readlane_u64(A[s], l);
-          if (lane == l) A[s] |= 1ull;
-        }
-      }
-    }
-    if (pos < 0) break;
-    // (1 + eps) rule of Sec. 4.5: p* is searched only while its distance is within the bound of
-    // the beam's k-th entry; the beam is sorted and that entry never moves away, so the first
-    // failure ends the search.
-    if (EPS && size >= a.k) {  // compiled in only for searches that use the rule
-      const bool beyond = beyond_eps<KIND>(pk, beam_entry<NSLOT>(A, a.k - 1u), a);
-      if (beyond) break;  // (p* keeps its flag: nothing reads it once the search is over)
-    }
-    const u32 pstar = key_id(pk);
-    visited_append(a, qi, vptr, vcap, nv, pk, lane);
-    ++nv;
-
-    // beam <- beam U N_out(p*), keep the L closest
-    const u32* row = a.graph + (u64)pstar * a.R;
-    for (u32 base = 0; base < a.R; base += 64) {
-      const u32 j = base + lane;
-      const u32 x = j < a.R ? row[j] : NONE_ID;
-      bool fresh = x != NONE_ID;
-      const u64 present = ballot(fresh);
-      if (fresh) {
-        if (compact) {
-          const u32 y = mix_id(x, idmask, a.id_bits);
-          const u32 h = bucket_of_y(y);
-          const u32 tag = y & tagmask;
-          const u32 tt = tag | (tag << 16);
-          const uint4 e = bucket[h];
-          // some 16-bit half equal to the tag?  (halves of e ^ tt that are zero)
-          const u32 mz = pk_min_u16(pk_min_u16(e.x ^ tt, e.y ^ tt), pk_min_u16(e.z ^ tt, e.w ^ tt));
-          if ((mz & 0xFFFFu) == 0u || (mz >> 16) == 0u)
-            fresh = false;
-          else  // shift the bucket by one tag, newest in front
-            bucket[h] = make_uint4((e.x << 16) | tag, (e.y << 16) | (e.x >> 16), (e.z << 16) | (e.y >> 16),
-                                   (e.w << 16) | (e.z >> 16));
-        } else if (tags21) {
-          // a bucket is two 64-bit words of three 21-bit tags each (an empty slot is all ones,
-          // which no tag of at most 20 bits equals), newest in front
-          constexpr u32 M21 = 0x1FFFFFu;
-          const u32 y = mix_id(x, idmask, a.id_bits);
-          const u32 h = bucket_of_y(y);
-          const u32 tag = y & tagmask;
-          const uint4 e = bucket[h];
-          const u32 f0 = e.x & M21, f1 = __builtin_amdgcn_alignbit(e.y, e.x, 21) & M21, f2 = (e.y >> 10) & M21;
-          const u32 f3 = e.z & M21, f4 = __builtin_amdgcn_alignbit(e.w, e.z, 21) & M21, f5 = (e.w >> 10) & M21;
-          const u32 ma = (f0 ^ tag) < (f1 ^ tag) ? (f0 ^ tag) : (f1 ^ tag);
-          const u32 mb = (f2 ^ tag) < (f3 ^ tag) ? (f2 ^ tag) : (f3 ^ tag);
-          const u32 mc = (f4 ^ tag) < (f5 ^ tag) ? (f4 ^ tag) : (f5 ^ tag);
-          const u32 mab = ma < mb ? ma : mb;
-          if ((mab < mc ? mab : mc) == 0u)
-            fresh = false;
-          else
-            bucket[h] = make_uint4((e.x << 21) | tag, __builtin_amdgcn_alignbit(e.y, e.x, 11), (e.z << 21) | f2,
-                                   __builtin_amdgcn_alignbit(e.w, e.z, 11));
-        } else {
-          const u32 h = bucket_of_id(x);
-          const uint4 e = bucket[h];
-          const u32 m01 = (e.x ^ x) < (e.y ^ x) ? (e.x ^ x) : (e.y ^ x);
-          const u32 m23 = (e.z ^ x) < (e.w ^ x) ? (e.z ^ x) : (e.w ^ x);
-          if ((m01 < m23 ? m01 : m23) == 0u)
-            fresh = false;
-          else
-            bucket[h] = make_uint4(x, e.x, e.y, e.z);
-        }
-      }
-      const u64 fm = ballot(fresh);
-      u32 m = __builtin_popcountll(fm);
-      if (m) {
-        const u32 rank = __builtin_popcountll(fm & lanemask_lt(lane));
-        if (fresh) cid[rank] = x;
-        __syncthreads();
-        const u32 met = m;
-        if constexpr (SK > 0) {
-          evals += m;
-          if (size == L && sparse) {
-            const u32 cand = cand_of_lane(lane);
-            const bool keep = !sketch_drops<KIND, SK>(K, SQ, beam_worst<NSLOT, 1>(A, L, size), cid, m, sk_last, lane) && cand < m;
-            const u64 km = ballot(keep);
-            const u32 kid = cid[cand];  // (below m where it is kept)
-            __syncthreads();
-            m = __builtin_popcountll(km);
-            if (m) {
-              if (keep) cid[__builtin_popcountll(km & lanemask_lt(lane))] = kid;
-              __syncthreads();
-            }
-          }
-        }
-        if (SK > 0 && m == 0) {
-          sparse = true;
-          if (present != ~0ull) break;
-          continue;
-        }
-        const u32 before = n_surv;
-        // (the variants with start vertices of their own sit at the register count that eight
-        // waves per SIMD allow: the second code path of the full-row passes would cost them a wave)
-        u32 dk;
-        if constexpr (SK > 0)
-          dk = eval_rows<KIND, NCH>(T, Q, cid, m, lane);
-        else if constexpr (OWN)
-          dk = eval_up_to_64<KIND, VEC, NCH>(T, Q, [cid](u32 c) { return cid[c]; }, m, lane);
-        else
-          dk = eval_up_to_64_full_rows<KIND, VEC, NCH>(T, Q, [cid](u32 c) { return cid[c]; }, m, lane);
-        const u32 c = cand_of_lane(lane);
-        u64 mykey = c < m ? make_key(dk, cid[c]) : KEY_INF;
-        __syncthreads();
-        if constexpr (SK == 0) evals += m;
-        n_pass += (m + 7u) >> 3;
-
-        beam_insert<NSLOT, NETWORK>(A, beam, skeys, mykey, L, size, n_surv, n_ins, lane, [] { __syncthreads(); });
-        if constexpr (SK > 0) sparse = 2u * (n_surv - before) < met;
-      }
-      if (present != ~0ull) break;  // rows are compact: the first gap ends the row
-    }
-  }
-
-  if (a.nvis != nullptr && lane == 0) a.nvis[qi] = nv;
-  if constexpr (OWN) {
-    // The three pointers this needs are read from the kernel's argument block here, not through
-    // `a`: arguments named in the code are all fetched into scalar registers at the kernel's
-    // start and would occupy six of them for the whole search.
-    if (lane == 0) {
-      const char* kp = (const char*)__builtin_amdgcn_kernarg_segment_ptr();
-      u32* next = *reinterpret_cast<u32* const volatile*>(kp + offsetof(SearchArgs, next_start));
-      if (next != nullptr) {
-        const u32* slot = *reinterpret_cast<const u32* const volatile*>(kp + offsetof(SearchArgs, slot));
-        const u32* down = *reinterpret_cast<const u32* const volatile*>(kp + offsetof(SearchArgs, down));
-        // the beam's first entry is the closest vertex the search visited (it always holds one)
-        const u32 best = key_id(A[0]);
-        next[slot != nullptr ? slot[qi] : qi] = down != nullptr ? down[best] : best;
-      }
-    }
-  }
-  write_results<KIND, NSLOT>(A, a, qi, lane);
-  if (a.counters != nullptr && lane == 0) {
-    atomicAdd(&block_counters(a.counters)->searches, 1ull);
-    atomicAdd(&block_counters(a.counters)->hops, (unsigned long long)nv);
-    atomicAdd(&block_counters(a.counters)->evals, (unsigned long long)evals);
-    atomicAdd(&block_counters(a.counters)->passes, (unsigned long long)n_pass);
-    atomicAdd(&block_counters(a.counters)->survivors, (unsigned long long)n_surv);
-    atomicAdd(&block_counters(a.counters)->insert_hops, (unsigned long long)n_ins);
-  }
-}
-
 template <int KIND, int VEC, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK>
 __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
-  search_one<KIND, VEC, NCH, NSLOT, EPS, TAG16, OWN, NETWORK, 0>(a, T, SketchTable{});
+  constexpr int SK = 0;
+  constexpr SketchTable K{};
+#include "search_body.inc"
 }
 
 // On rows with sketches.  A search waits for memory 70 % of its time, so registers go to waves: the query and
@@ -604,7 +351,8 @@ __global__ __launch_bounds__(64) void search_kernel(SearchArgs a, VecTable T) {
 constexpr int sketch_waves(int NCH) { return NCH <= 4 ? 6 : NCH <= 7 ? 5 : 4; }
 template <int KIND, int NCH, int NSLOT, bool EPS, bool TAG16, bool OWN, bool NETWORK, int SK>
 __global__ __launch_bounds__(64, sketch_waves(NCH)) void search_sketch_kernel(SearchArgs a, VecTable T, SketchTable K) {
-  search_one<KIND, 16, NCH, NSLOT, EPS, TAG16, OWN, NETWORK, SK>(a, T, K);
+  constexpr int VEC = 16;
+#include "search_body.inc"
 }
 
 // launches of the variants that other translation units compile: with the (1 + eps) rule
