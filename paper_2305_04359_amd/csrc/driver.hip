@@ -238,7 +238,6 @@ int resolve_queries(const ann_graph* g, const void* queries_dev, u64 nq, hipStre
       // an earlier call, on whatever stream it was issued, may still read the old buffer
       HIP_TRY(hipDeviceSynchronize());
       g->al.put(g->qpad_buf);
-  g->al.put(g->sketch_buf);
       g->qpad_buf = nullptr;
       g->qpad_rows = 0;
     }
@@ -822,6 +821,7 @@ void ann_graph_free(ann_graph* g) {
   g->al.put(g->counters);
   g->al.put(g->pad_buf);
   g->al.put(g->qpad_buf);
+  g->al.put(g->sketch_buf);
   delete g->scratch;
   delete g;
 }

@@ -111,3 +111,41 @@ def test_captured_queries_do_without(env):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def test_sketch_memory_goes_back(env):
+    """What a query call took for sketches is the graph's until it grows or is freed, and then goes back."""
+    from test_gpu_boundary import CountingAllocator
+    torch, A, _ = env
+    n, d = 345_000, 200
+    x = _points(torch, n, d, "unit", 5)
+    q = x[:20_000].contiguous()
+    kw = dict(seed=2, metric=A.MIPS, batch_cap=20_000, max_rounds=16)
+
+    al = CountingAllocator(A, torch)
+    g = A.ann_build(x, 32, 32, 1.0, allocator=al, **kw)
+    built = len(al.live)
+    A.ann_search(g, x, q, 10, 32)
+    A.ann_search(g, x, q, 10, 32)
+    assert len(al.live) == built + 1
+    torch.cuda.synchronize()
+    del g
+    assert len(al.live) == 0 and al.allocs == al.frees
+
+    al = CountingAllocator(A, torch)
+    g = A.ann_build(x[:340_000], 32, 32, 1.0, allocator=al, **kw)
+    A.ann_search(g, x[:340_000], q, 10, 32)
+    A.ann_insert_points(g, x, 32, 1.0, seed=4)
+    A.ann_search(g, x, q, 10, 32)
+    torch.cuda.synchronize()
+    del g
+    assert len(al.live) == 0 and al.allocs == al.frees
+
+    al = CountingAllocator(A, torch)
+    h = A.ann_hnsw_build(x, 16, 32, 1.0, allocator=al, **kw)
+    built = len(al.live)
+    A.ann_hnsw_search(h, x, q, 10, 32)
+    assert len(al.live) == built + 2  # the sketches, the queries' start vertices
+    torch.cuda.synchronize()
+    del h
+    assert len(al.live) == 0 and al.allocs == al.frees
