@@ -34,7 +34,8 @@
  *     the padded copies named above, room for the 8-bit sketches of f32 rows
  *     that a large call of ann_search makes for itself (128 bytes per row of
  *     80 to 124 elements, 256 per row of 160 to 252; without that memory the
- *     call does without them), and the scratch of ann_insert_batch /
+ *     call does without them; it goes back before the graph grows, too), and
+ *     the scratch of ann_insert_batch /
  *     ann_insert_points (sized for the largest batch so far).  The memory
  *     comes from hipMalloc / hipFree, or from the `alloc` / `free` callbacks
  *     of ann_build_opts / ann_hnsw_opts / ann_hcnng_opts, which the object

@@ -306,25 +306,38 @@ int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStr
     return ANN_OK;
   }
   std::lock_guard<std::mutex> hold(g->sketch_lock);
-  if (g->sketch_cap < g->n) {
-    if (g->sketch_buf) {
-      HIP_TRY(hipDeviceSynchronize());  // earlier calls may still read the old ones
-      g->al.put(g->sketch_buf);
-      g->sketch_buf = nullptr;
-      g->sketch_cap = 0;
-    }
-    if (g->al.on(st).get(&g->sketch_buf, (size_t)g->n * sketch_bytes(g->cfg)) != hipSuccess) {
+  if (g->sketch_buf == nullptr) {
+    void* buf = nullptr;
+    hipEvent_t given = nullptr;
+    const Allocator al = g->al.on(st);
+    hipError_t e = hipEventCreateWithFlags(&given, hipEventDisableTiming);
+    if (e == hipSuccess) e = al.get(&buf, (size_t)g->n * sketch_bytes(g->cfg));
+    if (e == hipSuccess) e = hipEventRecord(given, st);
+    if (e != hipSuccess) {
       (void)hipGetLastError();
-      g->sketch_buf = nullptr;
+      g->al.put(buf);
+      if (given) (void)hipEventDestroy(given);
       return ANN_OK;
     }
-    // whatever the memory's last owner queued is over before any call, on whatever stream, uses it (once: later calls
-    // write the same bytes again)
-    HIP_TRY(hipStreamSynchronize(st));
-    g->sketch_cap = g->n;
+    g->sketch_buf = buf;
+    g->sketch_given = given;
   }
+  // what the memory's last owner queued is over before any call, on whatever stream, writes to it (later calls write the
+  // same bytes again)
+  HIP_TRY(hipStreamWaitEvent(st, g->sketch_given, 0));
   HIP_TRY(launch_sketch_rows(g->cfg, points, 0, g->n, g->sketch_buf, st));
   *out = g->sketch_buf;
+  return ANN_OK;
+}
+
+// That memory goes back before the graph grows: it has room for the old points.
+int release_query_sketches(ann_graph* g) {
+  if (g->sketch_buf == nullptr) return ANN_OK;
+  HIP_TRY(hipDeviceSynchronize());  // earlier calls, on whatever stream, may still read it
+  g->al.put(g->sketch_buf);
+  g->sketch_buf = nullptr;
+  (void)hipEventDestroy(g->sketch_given);
+  g->sketch_given = nullptr;
   return ANN_OK;
 }
 
@@ -762,6 +775,8 @@ int reserve_rows(ann_graph* g, u64 want, hipStream_t st) {
 
 // The graph gets the vertices n..n_total-1, with empty rows.
 int grow_graph(ann_graph* g, u64 n_total, hipStream_t st) {
+  const int rc_sketch = release_query_sketches(g);
+  if (rc_sketch) return rc_sketch;
   if (n_total > g->cap) {
     // at least half as much again, so that a stream of small additions copies the rows rarely
     u64 want = g->cap + g->cap / 2;
@@ -822,6 +837,7 @@ void ann_graph_free(ann_graph* g) {
   g->al.put(g->pad_buf);
   g->al.put(g->qpad_buf);
   g->al.put(g->sketch_buf);
+  if (g->sketch_given) (void)hipEventDestroy(g->sketch_given);
   delete g->scratch;
   delete g;
 }

@@ -182,9 +182,9 @@ struct ann_graph {
   mutable annmi::u64 qpad_rows = 0;
   // sketches of the points (float rows) for the searches of the call that is running, or null
   const void* sketch = nullptr;
-  // memory for the ones that a call of ann_search makes, and the rows it has room for
+  // memory for the ones that a call of ann_search makes, room for n points, and where the call that took it stood then
   mutable void* sketch_buf = nullptr;
-  mutable annmi::u64 sketch_cap = 0;
+  mutable hipEvent_t sketch_given = nullptr;
   mutable std::mutex sketch_lock;
   // scratch of the insertions that follow the build (ann_insert_batch, ann_insert_points), kept
   // between calls: allocating and freeing it costs more than a batch of ten thousand points

@@ -149,3 +149,49 @@ def test_sketch_memory_goes_back(env):
     torch.cuda.synchronize()
     del h
     assert len(al.live) == 0 and al.allocs == al.frees
+
+
+def test_queries_do_not_wait(env):
+    """A query call returns while its stream is busy, the first one and the first one after an insertion too; its
+    sketches stand behind the late work of their memory's last owner, also for a call on another stream."""
+    from test_gpu_boundary import CountingAllocator
+    torch, A, _ = env
+    n, d = 345_000, 200
+    x = _points(torch, n, d, "unit", 5)
+    q = x[:20_000].contiguous()
+    old = x[:340_000]
+    al = CountingAllocator(A, torch)
+    plain = al.alloc
+
+    def _alloc(nbytes, stream, user):
+        p = plain(nbytes, stream, user)
+        if late and nbytes >= 340_000 * 256:
+            with torch.cuda.stream(torch.cuda.ExternalStream(stream)):
+                torch.cuda._sleep(20_000_000)
+                al.live[p].fill_(0xA5)
+        return p
+
+    late = False
+    al.inner, al.alloc = plain, A.ALLOC_FN(_alloc)
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    build = dict(seed=2, metric=A.MIPS, batch_cap=20_000, max_rounds=16)
+    g, h = A.ann_build(old, 32, 32, 1.0, allocator=al, **build), A.ann_build(old, 32, 32, 1.0, **build)
+    for pts in (old, x):
+        if pts is x:
+            A.ann_insert_points(g, x, 32, 1.0, seed=4)
+            A.ann_insert_points(h, x, 32, 1.0, seed=4)
+        want = A.ann_search(h, pts, q, 10, 32)
+        torch.cuda.synchronize()
+        late = True
+        with torch.cuda.stream(first):
+            torch.cuda._sleep(100_000_000)
+            before = torch.cuda.Event()
+            before.record()
+            a = A.ann_search(g, pts, q, 10, 32)
+            assert not before.query()
+        with torch.cuda.stream(second):
+            b = A.ann_search(g, pts, q, 10, 32)
+        torch.cuda.synchronize()
+        late = False
+        for got in (a, b):
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
