@@ -281,17 +281,31 @@ void collect_phase_times(ann_graph* g, PhaseTimer& tm) {
 // batches of at least this many points run step 1 in three parts (see batch_insert)
 constexpr u64 STEP1_PARTS_MIN = 8192;
 
-// Sketches of the graph's points for the searches of this call, `searches` in all (see search_sketch_pays): into
-// `buf`, and g->sketch until the caller takes it down.  Without the memory the searches do without.
-int make_sketches(ann_graph* g, const void* points, u64 searches, u32 L, DevBuf& buf, hipStream_t st) {
+static thread_local SketchScope* running_sketches = nullptr;
+SketchScope::SketchScope(ann_graph* of) : g(of), outer(running_sketches) { running_sketches = this; }
+SketchScope::~SketchScope() {
   g->sketch = nullptr;
+  running_sketches = outer;
+}
+bool give_back_sketches() {
+  SketchScope* S = running_sketches;
+  if (S == nullptr || S->buf.p == nullptr || hipDeviceSynchronize() != hipSuccess) return false;
+  S->g->sketch = nullptr;
+  S->buf.release();
+  return true;
+}
+
+// Sketches of the graph's points for the searches of this call, `searches` in all (see search_sketch_pays): g->sketch
+// until the call is over.  Without the memory the searches do without.
+int make_sketches(SketchScope& S, const void* points, u64 searches, u32 L, hipStream_t st) {
+  ann_graph* g = S.g;
   if (!search_sketch_pays(g->cfg, g->n, searches, L, false)) return ANN_OK;
-  if (buf.alloc(g->n * sketch_bytes(g->cfg)) != hipSuccess) {
+  if (S.buf.alloc(g->n * sketch_bytes(g->cfg)) != hipSuccess) {
     (void)hipGetLastError();
     return ANN_OK;
   }
-  HIP_TRY(launch_sketch_rows(g->cfg, points, 0, g->n, buf.p, st));
-  g->sketch = buf.p;
+  HIP_TRY(launch_sketch_rows(g->cfg, points, 0, g->n, S.buf.p, st));
+  g->sketch = S.buf.p;
   return ANN_OK;
 }
 
@@ -330,8 +344,9 @@ int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStr
   return ANN_OK;
 }
 
-// That memory goes back before the graph grows: it has room for the old points.
-int release_query_sketches(ann_graph* g) {
+// That memory goes back before the graph grows (it has room for the old points) and where other memory of the object
+// is to be taken.
+int release_query_sketches(const ann_graph* g) {
   if (g->sketch_buf == nullptr) return ANN_OK;
   HIP_TRY(hipDeviceSynchronize());  // earlier calls, on whatever stream, may still read it
   g->al.put(g->sketch_buf);
@@ -505,14 +520,22 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
     }
     DevBuf ids2_d, slots_d, vis2, nvis2, pos2;
     FailureWait wait;
-    HIP_TRY(ids2_d.alloc((size_t)novf * 4));
-    HIP_TRY(slots_d.alloc((size_t)novf * 4));
-    HIP_TRY(vis2.alloc((size_t)novf * need * 8));
-    HIP_TRY(nvis2.alloc((size_t)novf * 4));
+    auto room = [](DevBuf& d, size_t bytes) {
+      const hipError_t e = d.alloc(bytes);
+      if (e != hipErrorOutOfMemory || !give_back_sketches()) return e;
+      (void)hipGetLastError();
+      return d.alloc(bytes);
+    };
+    HIP_TRY(room(ids2_d, (size_t)novf * 4));
+    HIP_TRY(room(slots_d, (size_t)novf * 4));
+    HIP_TRY(room(vis2, (size_t)novf * need * 8));
+    HIP_TRY(room(nvis2, (size_t)novf * 4));
+    if (starts) HIP_TRY(room(pos2, (size_t)novf * 4));
     HIP_TRY(hipMemcpyAsync(ids2_d.p, ids2.data(), (size_t)novf * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(slots_d.p, slots.data(), (size_t)novf * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemsetAsync(small + 0, 0, 4, st));
     SearchArgs sb = sa;
+    sb.sketch = static_cast<const char*>(g->sketch);  // (they may just have gone)
     sb.qidx = ids2_d.as<u32>();
     sb.nq = novf;
     sb.vis = vis2.as<u64>();
@@ -526,7 +549,6 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
       // redone search i stands at the position of batch slot slots[i]
       p2.resize(novf);
       for (u32 i = 0; i < novf; ++i) p2[i] = starts->slot_host ? starts->slot_host[slots[i]] : slots[i];
-      HIP_TRY(pos2.alloc((size_t)novf * 4));
       HIP_TRY(hipMemcpyAsync(pos2.p, p2.data(), (size_t)novf * 4, hipMemcpyHostToDevice, st));
       sb.slot = pos2.as<u32>();
     }
@@ -648,6 +670,8 @@ int graph_scratch(ann_graph* g, u64 b, u32 L, hipStream_t st, BatchScratch** out
     g->scratch = nullptr;
   }
   if (!g->scratch) {
+    const int rc_sketch = release_query_sketches(g);  // (their memory may be what the scratch needs)
+    if (rc_sketch) return rc_sketch;
     g->scratch = new (std::nothrow) BatchScratch();
     if (!g->scratch) return fail(ANN_ENOMEM, "host allocation failed");
     int rc = g->scratch->alloc(b, g->R, cap, g->spill_keys ? g->spill_keys : default_spill_keys(b));
@@ -750,6 +774,8 @@ int new_graph(u64 n, u32 d, int dtype, int metric, u32 R, ann_graph** out) {
 int reserve_rows(ann_graph* g, u64 want, hipStream_t st) {
   if (want <= g->cap) return ANN_OK;
   if (want >= (1ull << 31)) return fail(ANN_EINVAL, "n must stay below 2^31");
+  const int rc_sketch = release_query_sketches(g);  // (their memory may be what the rows need)
+  if (rc_sketch) return rc_sketch;
   u32* rows = nullptr;
   u32* meta = nullptr;
   const Allocator al = g->al.on(st);
@@ -1114,8 +1140,7 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   }
 
   const double t_order = now_ms();
-  DevBuf sketches;
-  SketchScope held{g};
+  SketchScope sketches(g);
   FailureWait wait;  // (the graph keeps its scratch; a later call may enlarge it)
   rc = grow_graph(g, n_total, st);
   if (rc) return rc;
@@ -1130,7 +1155,7 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   const void* pts = nullptr;
   rc = resolve_points(g, points_dev, st, &pts);
   if (rc) return rc;
-  rc = make_sketches(g, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, sketches, st);
+  rc = make_sketches(sketches, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, st);
   if (rc) return rc;
   const double t_alloc = now_ms();
   // Every batch waits on the host after step 1 (the check for visited lists that fit nowhere):
@@ -1219,8 +1244,8 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
       if (g) ann_graph_free(g);
     }
   } guard{g};
-  DevBuf order_dev, sketches;
-  SketchScope held{g};
+  DevBuf order_dev;
+  SketchScope sketches(g);
   BatchScratch S;
   FailureWait wait;
   rc = check_insert_params(g, L, alpha);
@@ -1304,7 +1329,7 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
   const void* pts = nullptr;
   rc = resolve_points(g, points_dev, st, &pts);
   if (rc) return rc;
-  rc = make_sketches(g, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, sketches, st);
+  rc = make_sketches(sketches, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, st);
   if (rc) return rc;
 
   const double t_alloc = now_ms();

@@ -313,13 +313,21 @@ struct StartsArgs {
   const u32* down = nullptr;
 };
 
-// takes the sketches of a call down at its end
+// The sketches of a building call: taken down at its end, or before, where something that the call cannot do without
+// finds no memory.
 struct SketchScope {
   ann_graph* g;
-  ~SketchScope() { g->sketch = nullptr; }
+  DevBuf buf;
+  SketchScope* outer;  // of a call that this one is made from (by an allocator's callback)
+  explicit SketchScope(ann_graph* of);
+  SketchScope(const SketchScope&) = delete;
+  SketchScope& operator=(const SketchScope&) = delete;
+  ~SketchScope();
 };
-int make_sketches(ann_graph* g, const void* points, u64 searches, u32 L, DevBuf& buf, hipStream_t st);
+int make_sketches(SketchScope& S, const void* points, u64 searches, u32 L, hipStream_t st);
+bool give_back_sketches();  // those of the call that this thread is in; false: there are none
 int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStream_t st, const void** out);
+int release_query_sketches(const ann_graph* g);
 
 int new_graph(u64 n, u32 d, int dtype, int metric, u32 R, ann_graph** out);
 int check_insert_params(const ann_graph* g, uint32_t L, float alpha);

@@ -219,8 +219,8 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
       if (setup) (void)hipEventDestroy(setup);
     }
   };
-  DevBuf order_dev, cur_a[RING], cur_b[RING], sketches;
-  SketchScope held{h->layer[0]};
+  DevBuf order_dev, cur_a[RING], cur_b[RING];
+  SketchScope sketches(h->layer[0]);
   std::vector<DevBuf> ins_c_dev(top + 1), ins_slot_dev(top + 1);
   BatchScratch S0, Su;
   UpStream us;
@@ -270,7 +270,7 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
     rc = resolve_points(h->layer[l], h->pts[l].p, st, &lp[l]);
     if (rc) return rc;
   }
-  rc = make_sketches(h->layer[0], lp[0], bmax > SEARCH_SKETCH_MIN ? cnt : 0, efc, sketches, st);
+  rc = make_sketches(sketches, lp[0], bmax > SEARCH_SKETCH_MIN ? cnt : 0, efc, st);
   if (rc) return rc;
 
   for (int attempt = may_restart ? 0 : 1; attempt < 2; ++attempt) {
@@ -635,18 +635,20 @@ int ann_hnsw_search(const ann_hnsw* h, const void* points_dev, const void* queri
   if (rc) return rc;
   rc = resolve_queries(g0, queries_dev, nq, st, &qs);
   if (rc) return rc;
-  const void* sketch = nullptr;
+  if (h->top != 0 && h->qcur_cap < nq) {
+    HIP_TRY(hipDeviceSynchronize());  // an earlier call, on whatever stream, may still use the old array
+    AllocScope scope(h->al.on(st));
+    rc = release_query_sketches(g0);  // (their memory may be what the array needs)
+    if (rc) return rc;
+    HIP_TRY(h->qcur.alloc(nq * 4));
+    h->qcur_cap = nq;
+  }
+  const void* sketch = nullptr;  // (in memory that nothing else of this call wants)
   if (h->top == 0 || !(eps >= 0.0f)) {  // (no instances with start vertices of their own and the (1 + eps) rule)
     rc = query_sketches(g0, p0, nq, L, st, &sketch);
     if (rc) return rc;
   }
   if (h->top == 0) return query_launch(g0, p0, qs, nullptr, nq, k, L, eps, nullptr, ids_dev, dists_dev, st, sketch);
-  if (h->qcur_cap < nq) {
-    HIP_TRY(hipDeviceSynchronize());  // an earlier call, on whatever stream, may still use the old array
-    AllocScope scope(h->al.on(st));
-    HIP_TRY(h->qcur.alloc(nq * 4));
-    h->qcur_cap = nq;
-  }
   // the upper layers in one launch, then the bottom layer from where each query arrived
   DescendArgs da{};
   da.queries = static_cast<const char*>(qs);

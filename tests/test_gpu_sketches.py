@@ -195,3 +195,88 @@ def test_queries_do_not_wait(env):
         late = False
         for got in (a, b):
             assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+class _Limited:
+    """An allocator that refuses one size or, from start() on, to hold more than `limit` bytes; counts the most it held
+    from there on."""
+
+    def __init__(self, A, limit=None, refuse=None):
+        self.inner = A.TorchAllocator()
+        self.size, self.held, self.most, self.limit, self.started = {}, 0, 0, limit, False
+
+        def alloc(nbytes, stream, user):
+            if nbytes == refuse or (self.started and limit is not None and self.held + nbytes > self.limit):
+                return None
+            p = self.inner.alloc(nbytes, stream, user)
+            self.size[p] = nbytes
+            self.held += nbytes
+            self.most = max(self.most, self.held)
+            return p
+
+        def free(ptr, user):
+            self.held -= self.size.pop(ptr)
+            self.inner.free(ptr, user)
+
+        self.alloc, self.free = A.ALLOC_FN(alloc), A.FREE_FN(free)
+
+    def start(self, room=0):
+        self.started, self.most = True, self.held
+        if self.limit is not None:
+            self.limit = max(self.limit, self.held + room)
+
+    def fill(self, opts):
+        opts.alloc = C.cast(self.alloc, C.c_void_p)
+        opts.free = C.cast(self.free, C.c_void_p)
+        opts.alloc_user = None
+
+
+BUILD = dict(seed=2, batch_cap=20_000, max_rounds=16)
+
+
+def _lost_lists(A, x, al):
+    """visited lists that fit nowhere: their searches are repeated in memory that the build asks for then"""
+    al.start()
+    g = A.ann_build(x, 32, 64, 1.0, seed=2, metric=A.MIPS, allocator=al, batch_cap=60_000, visited_cap=16, spill_cap=1)
+    return [g.neighbors()]
+
+
+def _layered_queries(A, x, al):
+    h = A.ann_hnsw_build(x, 16, 32, 1.0, metric=A.MIPS, allocator=al, **BUILD)
+    al.start(room=x.shape[0] * 256)  # for the sketches or for what the call cannot do without
+    return [t.cpu().numpy() for t in A.ann_hnsw_search(h, x, x[:20_000], 10, 32)]
+
+
+def _insertion(A, x, al):
+    old = x[:340_000]
+    g = A.ann_build(old, 32, 32, 1.0, metric=A.MIPS, allocator=al, **BUILD)
+    A.ann_search(g, old, x[:20_000], 10, 32)
+    al.start()
+    A.ann_insert_points(g, x, 32, 1.0, seed=4)
+    return [g.neighbors()]
+
+
+def _batch(A, x, al):
+    g = A.ann_build(x, 32, 32, 1.0, metric=A.MIPS, allocator=al, **BUILD)
+    A.ann_search(g, x, x[:20_000], 10, 32)
+    ids = np.nonzero(g.neighbors()[:, 0] == 0xFFFFFFFF)[0].astype(np.uint32)
+    al.start()
+    A.ann_insert_batch(g, x, ids[ids != g.info().start][:40_000], 32, 1.0)
+    return [g.neighbors()]
+
+
+@pytest.mark.parametrize("calls,n", [(_lost_lists, 135_000), (_layered_queries, 345_000), (_insertion, 345_000), (_batch, 345_000)])
+def test_what_fits_without_sketches_fits(env, calls, n):
+    """Sketches take memory that nothing else wants: a call that succeeds where there is none for them succeeds
+    where there is just as much in all."""
+    torch, A, _ = env
+    x = _points(torch, n, 200, "unit", 5)
+    without = _Limited(A, refuse=(340_000 if calls is _insertion else n) * 256)
+    want = calls(A, x, without)
+    torch.cuda.synchronize()
+    limited = _Limited(A, limit=without.most)
+    got = calls(A, x, limited)
+    for a, b in zip(want, got):
+        assert np.array_equal(a, b)
+    torch.cuda.synchronize()
+    assert limited.held == 0
