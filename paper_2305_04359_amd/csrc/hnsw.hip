@@ -640,6 +640,7 @@ int ann_hnsw_search(const ann_hnsw* h, const void* points_dev, const void* queri
     AllocScope scope(h->al.on(st));
     rc = release_query_sketches(g0);  // (their memory may be what the array needs)
     if (rc) return rc;
+    h->qcur_cap = 0;  // (the old array is gone also where there is no room for the new one)
     HIP_TRY(h->qcur.alloc(nq * 4));
     h->qcur_cap = nq;
   }

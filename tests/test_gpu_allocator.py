@@ -102,6 +102,23 @@ def test_layered_insert_waits_for_searches(env):
         del h
 
 
+def test_layered_queries_after_one_that_failed(env):
+    """A call that finds no room for its start vertices has given up the smaller array of the calls before."""
+    torch, A, _ = env
+    pts = dev(torch, np.random.default_rng(10).integers(0, 256, (1000, 64)).astype(np.uint8))
+    al = _allocator(A, torch, torch.cuda.current_stream())
+    h = A.ann_hnsw_build(pts, 8, 32, 1.2, seed=3, allocator=al)
+    assert h.info().top > 0
+    want, _ = A.ann_hnsw_search(h, pts, pts[:50], 5, 20)
+    al.fail_after = al.allocs
+    with pytest.raises(A.AnnError) as e:
+        A.ann_hnsw_search(h, pts, pts[:500], 5, 20)
+    assert e.value.code == -2
+    al.fail_after = None
+    ids, _ = A.ann_hnsw_search(h, pts, pts[:50], 5, 20)
+    assert torch.equal(ids, want)
+
+
 def test_alloc_names_the_stream_of_the_call(env):
     """Searches and insertions on another stream than the build's: padded copies, grown rows, scratch, start vertices."""
     from test_gpu_boundary import CountingAllocator
