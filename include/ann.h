@@ -360,7 +360,10 @@ int ann_hnsw_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dty
  * ann_hnsw_from_host) but is at most the index's highest layer, whose entry
  * point stays.  opts: batch_cap, order (n_total - n new ids), level (n_total -
  * n levels, in place of the rule), max_rounds.  seed drives the order.  Every
- * batch waits on the host once; blocks until done.                           */
+ * batch waits on the host once; blocks until done.  After an error the index
+ * is as it was, or holds some of the new points (as ann_insert_points), or,
+ * where memory ran out while its layers grew, can only be freed: further calls
+ * on it return ANN_EINVAL.                                                   */
 int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total, uint32_t efc, float alpha,
                            uint64_t seed, const ann_hnsw_opts* opts, void* stream);
 

@@ -35,12 +35,18 @@ struct ann_hnsw {
   std::vector<DevBuf> down;           // down[l], l >= 1: n_l ids one layer below
   std::vector<u32> entry_c;           // the entry point's id on every layer
   DevBuf walk;  // the upper layers, from the top, as the descent kernel reads them (DescendLayer)
+  // an insertion is growing the layers, or failed while it was: they don't fit one another nor the walk
+  bool growing = false;
   // where each query of a call enters the bottom layer
   mutable DevBuf qcur;
   mutable u64 qcur_cap = 0;
 };
 
 namespace {
+
+int check_whole(const ann_hnsw* h) {
+  return h->growing ? fail(ANN_EINVAL, "an insertion failed before the layers of this index had grown: it can only be freed") : ANN_OK;
+}
 
 u64 level_draw(u64 seed, u64 id) {  // the (id+1)-th output of SplitMix64(seed)
   u64 z = seed + (id + 1) * 0x9E3779B97F4A7C15ull;
@@ -455,7 +461,9 @@ int ann_hnsw_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dty
 int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total, uint32_t efc, float alpha,
                            uint64_t seed, const ann_hnsw_opts* opts, void* stream) try {
   if (!h || !points_dev) return fail(ANN_EINVAL, "null argument");
-  int rc = check_insert_params(h->layer[0], efc, alpha);
+  int rc = check_whole(h);
+  if (rc) return rc;
+  rc = check_insert_params(h->layer[0], efc, alpha);
   if (rc) return rc;
   if (n_total < h->n) return fail(ANN_EINVAL, "n_total is below the number of points in the index");
   if (n_total >= (1ull << 31)) return fail(ANN_EINVAL, "n must stay below 2^31");
@@ -502,9 +510,10 @@ int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total
 
   // the layers grow: new members go behind the old ones (their ids are larger), so every vertex
   // keeps its number on every layer
-  h->level.insert(h->level.end(), lv.begin(), lv.end());
   rc = grow_graph(h->layer[0], n_total, st);
-  if (rc) return rc;
+  if (rc) return rc;  // (nothing has changed)
+  h->growing = true;
+  h->level.insert(h->level.end(), lv.begin(), lv.end());
   for (u32 l = 1; l <= top; ++l) {
     std::vector<u32> fresh;
     for (u64 i = 0; i < mnew; ++i)
@@ -546,6 +555,7 @@ int ann_hnsw_insert_points(ann_hnsw* h, const void* points_dev, uint64_t n_total
   h->n = n_total;
   rc = make_walk(h, st);
   if (rc) return rc;
+  h->growing = false;
   return run_batches(h, points_dev, order, bounds, efc, alpha, o.max_rounds, h->layer[0]->collect, /*may_restart=*/false,
                      st);
 } catch (...) {
@@ -627,11 +637,13 @@ int ann_hnsw_search(const ann_hnsw* h, const void* points_dev, const void* queri
   if (k < 1 || k > L) return fail(ANN_EINVAL, "need 1 <= k <= L");
   if (L > 2048) return fail(ANN_EINVAL, "L must be at most 2048");
   if (nq >= (1ull << 31)) return fail(ANN_EINVAL, "too many queries");
+  int rc = check_whole(h);
+  if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const ann_graph* g0 = h->layer[0];
   const void* p0 = nullptr;
   const void* qs = nullptr;
-  int rc = resolve_points(g0, points_dev, st, &p0);
+  rc = resolve_points(g0, points_dev, st, &p0);
   if (rc) return rc;
   rc = resolve_queries(g0, queries_dev, nq, st, &qs);
   if (rc) return rc;
@@ -692,6 +704,8 @@ int ann_hnsw_copy_levels(const ann_hnsw* h, uint32_t* level_host) try {
 
 int ann_hnsw_layer_size(const ann_hnsw* h, uint32_t layer, uint64_t* count) try {
   if (!h || !count) return fail(ANN_EINVAL, "null argument");
+  const int rc = check_whole(h);
+  if (rc) return rc;
   if (layer > h->top) return fail(ANN_EINVAL, "no such layer");
   *count = h->layer[layer]->n;
   return ANN_OK;
@@ -701,6 +715,8 @@ int ann_hnsw_layer_size(const ann_hnsw* h, uint32_t layer, uint64_t* count) try 
 
 int ann_hnsw_copy_layer(const ann_hnsw* h, uint32_t layer, uint32_t* ids_host, uint32_t* rows_host) try {
   if (!h || !ids_host || !rows_host) return fail(ANN_EINVAL, "null argument");
+  const int rc = check_whole(h);
+  if (rc) return rc;
   if (layer > h->top) return fail(ANN_EINVAL, "no such layer");
   const ann_graph* g = h->layer[layer];
   HIP_TRY(hipMemcpy(rows_host, g->rows, (size_t)g->n * g->R * sizeof(u32), hipMemcpyDeviceToHost));

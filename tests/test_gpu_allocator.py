@@ -119,6 +119,49 @@ def test_layered_queries_after_one_that_failed(env):
     assert torch.equal(ids, want)
 
 
+def test_layered_index_after_an_insertion_that_failed(env):
+    """Wherever an insertion runs dry, the index answers as before, answers over the points that it holds, or refuses."""
+    torch, A, _ = env
+    pts = dev(torch, np.random.default_rng(11).integers(0, 256, (1500, 60)).astype(np.uint8))
+    stream = torch.cuda.current_stream()
+
+    def once(k):
+        al = _allocator(A, torch, stream)
+        h = A.ann_hnsw_build(pts[:600], 8, 32, 1.2, seed=3, allocator=al)
+        assert h.info().top > 0
+        want, _ = A.ann_hnsw_search(h, pts, pts[:50], 5, 20)
+        had = al.allocs
+        al.fail_after = None if k is None else had + k
+        try:
+            A.ann_hnsw_insert_points(h, pts, 32, 1.2, seed=4)
+            assert k is None
+            return al.allocs - had
+        except A.AnnError as e:
+            assert e.code == -2
+        al.fail_after = None
+        try:
+            ids, _ = A.ann_hnsw_search(h, pts, pts[:50], 5, 20)
+            h.layer(1)
+        except A.AnnError as e:
+            assert e.code == -1 and k > 1 and "can only be freed" in str(e)
+            for again in (lambda: h.layer(1), lambda: A.ann_hnsw_insert_points(h, pts, 32, 1.2, seed=4)):
+                with pytest.raises(A.AnnError):
+                    again()
+            return "refused"
+        if h.info().n == 600:
+            assert k < 2 and torch.equal(ids, want)  # (the bottom layer's rows and degrees)
+        else:
+            assert h.info().n == 1500 and (ids >= 0).all() and (ids < 1500).all()
+        return "answered"
+
+    total = once(None)
+    seen = set()
+    for k in range(total):
+        say(f"layered insertion dry after {k} of {total}")
+        seen.add(once(k))
+    assert seen == {"refused", "answered"}
+
+
 def test_alloc_names_the_stream_of_the_call(env):
     """Searches and insertions on another stream than the build's: padded copies, grown rows, scratch, start vertices."""
     from test_gpu_boundary import CountingAllocator
