@@ -836,8 +836,10 @@ __global__ __launch_bounds__(1024) void hc_pairs_kernel(const u32* leaf_list, co
   if (tid == 0) below[0] = 0;
   __syncthreads();
   const u32 M = below[PAIR_SPANS];
-  // a key's bucket, by the keys below its span and its way through it: conversions, products and truncations are
-  // monotone, so buckets are in the order of the distances
+  // a key's bucket, by the keys below its span and its way through it, in [0, 1]: conversions, products, sums and
+  // truncations are monotone, so buckets are in the order of the distances.  (The way is one fused operation: where the
+  // span's number came from a product that was rounded up, it is less than 0, and the bucket might be one that
+  // keys of the span before come after.)
   const float spread = (float)PAIR_BUCKETS / (float)(M ? M : 1u);
   u32 at[NK];  // bucket << 16 | number in it
 #pragma unroll
@@ -847,7 +849,7 @@ __global__ __launch_bounds__(1024) void hc_pairs_kernel(const u32* leaf_list, co
       const float f = span_at(key[q]);
       const u32 sp = span_of(f), b0 = below[sp], b1 = below[sp + 1u];
       float way = f - (float)sp;
-      way = way < 1.0f ? way : 1.0f;
+      way = __builtin_fminf(__builtin_fmaxf(way, 0.0f), 1.0f);
       u32 b = (u32)(((float)b0 + way * (float)(b1 - b0)) * spread);
       b = b < PAIR_BUCKETS - 1u ? b : PAIR_BUCKETS - 1u;
       at[q] = (b << 16) | atomicAdd(&first[b], 1u);

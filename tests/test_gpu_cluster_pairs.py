@@ -49,3 +49,25 @@ def test_neighbours_of_all_trees(env, n, T, s, Ls, dtype):
         x = x.astype(np.float32)
     g = A.ann_hcnng_build(dev(torch, x), T, Ls, s, 10, 24, 1.2, seed=3)
     assert np.array_equal(g.neighbors(), O.hcnng_build(O.Dataset(x, 0), T, Ls, s, 10, 24, 1.2, seed=3, threads=0))
+
+
+def test_order_across_spans(env):
+    """Two of 512 pairs share a point that takes one neighbour.  Their distances lie on both sides of the line between two
+    spans of the pair sort, three units in the last place apart, such that the larger one's product with the scale is
+    less than a whole number by less than its rounding, in a span that 261 pairs share, right behind one that the smaller one has
+    for itself (pairs that lie far apart from all others; their first coordinate keeps them so)."""
+    torch, A, O = env
+    f = np.float32
+    close = [f(1.1101452112197876), f(1.1101453304290771)]  # the first wins
+    span = int(np.frombuffer(f(929955008.0 * 929955008.0).tobytes(), np.uint32)[0] - 0x3F800000) / 1024
+    at = [span * 0.999 * i / 249 for i in range(249)] + [span * (4.001 + 0.99 * i / 260) for i in range(260)]
+    alone = [f(np.sqrt(np.frombuffer(np.uint32(0x3F800000 + int(k)).tobytes(), f)[0])) for k in at] + [f(929955008.0)]
+    rows = [(0.0, -close[0]), (0.0, 0.0), (0.0, close[1])]
+    for i, gap in enumerate(alone):
+        rows += [((i + 1) * 2.0 ** 40, 0.0), ((i + 1) * 2.0 ** 40, gap)]
+    x = np.zeros((len(rows), 4), f)
+    x[:, :2] = rows
+    _, off, edges = A.ann_hcnng_tree_edges(dev(torch, x), 1024, 1, 1, 5, 0)
+    want = O.hcnng_leaf(O.Dataset(x, 0), np.arange(len(x)), 1, 1)
+    assert len(off) == 2 and len(want) == 511
+    assert np.array_equal(np.asarray(edges), np.asarray(want))
