@@ -135,7 +135,7 @@ typedef struct {
   uint64_t redone;      /* searches redone because the visited list fit nowhere  */
   uint64_t restarts;    /* builds started over in synchronised mode for that     */
   uint64_t rounds;
-  uint64_t passes;      /* searches: 8-vertex distance passes                    */
+  uint64_t passes;      /* searches: 8-vertex distance passes over whole rows    */
   uint64_t survivors;   /* searches: candidates inserted into a beam             */
   uint64_t insert_hops; /* searches: hops that inserted at least one candidate   */
   /* device time per phase.  A batch of 8,192 points or more runs step 1 in three parts side by
@@ -290,7 +290,8 @@ int ann_graph_set_stats(ann_graph* g, int on);
  * depend on it, only the number of repeated distance evaluations does.       */
 int ann_graph_set_filter_bits(ann_graph* g, uint32_t hash_bits);
 /* The filter that a launch of nq searches on this graph gets where every search has a
- * wave of its own (for tests): its size in 32-bit words, the bits that a vertex takes in
+ * wave of its own and reads rows only (for tests; searches that read 8-bit sketches first
+ * hold their query in LDS too and get less): its size in 32-bit words, the bits that a vertex takes in
  * it, and the waves per SIMD that the registers of the kernel instance leave room
  * for.  own_starts: searches with start vertices of their own (the layered index).
  * Launches nothing.                                                              */

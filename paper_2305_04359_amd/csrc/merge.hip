@@ -1,9 +1,10 @@
 // Step 2 of BatchInsert (Alg. 3 of the paper): for every existing point b that was chosen by
 // batch points, N_out(b) <- N_out(b) U N, and prune(b, N_out(b), R) if that exceeds R.
 //
-// The sorted edge keys are cut into segments of equal destination by a planning kernel, which
+// The edge keys, grouped by destination, are cut into segments of equal destination by a planning kernel, which
 // appends directly where the row has room and otherwise files the segment under one of three
-// kinds of re-prune, each served by its own kernel (one wavefront per row):
+// kinds of re-prune (one wavefront per row), each served by a kernel of its own, in smaller batches of
+// byte rows two or all three of them by one (merge_launches):
 //
 //   fast     the row still starts with the output of its last prune (its "clean prefix": sorted
 //            by distance to b and free of pairs where one removes the other, which is what prune

@@ -7,7 +7,9 @@
 // One wavefront owns a tile of consecutive keys and walks it 64 keys at a time, so ranking inside
 // a tile needs no cross-wave coordination: a key's rank among equal digits of its 64-key row is
 // a popcount over a match mask built from one ballot per digit bit.  Digits are up to 10 bits
-// wide, so 20 destination bits (a million points) take two passes.
+// wide.  Equal destinations need only stand together, so where their bits are at most 21 one pass
+// does (group_split), and merge.hip groups each of its buckets; more bits take all passes.  At most
+// 12,288 keys are sorted by one workgroup.
 #include "ann_device.hpp"
 #include "ann_internal.hpp"
 #include "plan_device.hpp"
