@@ -29,6 +29,23 @@ def test_batches_equal_the_oracles(env, n, d, R, batch):
     assert g.info().start == s and np.array_equal(g.neighbors(), want)
 
 
+# thirty thousand edges to one vertex: most of a batch in one bucket, whatever its size
+@pytest.mark.parametrize("n", [40_000, 1 << 20])
+def test_a_crowded_destination(env, n):
+    torch, A, O = env
+    say(f"grouping crowded destination n={n}")
+    R, d = 16, 16
+    rng = np.random.default_rng(4)
+    pts_h = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    s = n - 1
+    g = A.ann_graph_from_host(np.full((n, R), 0xFFFFFFFF, np.uint32), d, A.U8, A.L2SQ, s)
+    want = O.empty_graph(n, R)
+    ids = rng.permutation(n - 1)[:30_000].astype(np.uint32)
+    A.ann_insert_batch(g, dev(torch, pts_h), ids, 32, 1.2)
+    O.batch_insert(O.Dataset(pts_h, 0), want, s, ids, 32, 1.2, threads=0)
+    assert np.array_equal(g.neighbors(), want)
+
+
 # every edge of a batch to one vertex, ids of 20, 21 and 22 bits (the last: the radix sort), rows that fill up
 @pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21])
 def test_one_destination(env, n):

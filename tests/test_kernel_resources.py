@@ -58,6 +58,14 @@ def test_own_start_searches_keep_eight_waves(kernels):
     assert found and all(f["vgpr_count"] <= 64 for f in found.values())
 
 
+def test_sketched_searches_keep_their_waves(kernels):
+    """search_sketch_kernel<KIND, NCH, NSLOT, EPS, TAG16, OWN, NETWORK, SK>: six waves per SIMD at four pieces per lane,
+    five at six and seven, four at eight."""
+    waves = {4: 6, 6: 5, 7: 5, 8: 4}
+    for a, f in _named(kernels, "search_sketch_kernel").items():
+        assert 512 // (-(-f["vgpr_count"] // 8) * 8) >= waves[a[1]], a
+
+
 def test_spills(kernels):
     """No kernel keeps registers in memory, but for the one whose third wave is worth it (PruneWaves)."""
     spills = {k: f["vgpr_spill_count"] for k, f in kernels.items() if f["vgpr_spill_count"]}
