@@ -156,13 +156,13 @@ def query_point(torch, A, O, w, g_stats, pts, qs, qs_stream, k, setting, gt, kth
     """One operating point of the query path: rate on the workload's queries (one launch is about
     one generation of wavefronts: a latency) and on a stream of distinct queries (the throughput),
     plain and tie-aware recall, and the roofline of the search kernel on the stream: per query
-    hops * 4R (adjacency rows) + DISTINCT distance evaluations * row bytes + k * 8 (results), hops
+    hops * 4R (adjacency rows) + DISTINCT distance evaluations * row bytes + k * 8 (results; with
+    sketches as in vector_bytes, and every row read and its sketch written once per call), hops
     and evaluations from the library's counters, the distinct share from the oracle's search of a
     sample of the same queries (the kernel's visited filter is lossy and counts repeats too)."""
     if setting is None:
         return None
     L, eps, _ = setting
-    row_bytes = w.d * w.points.dtype.itemsize
     ms, ids, dists = time_search(torch, A, g_stats, pts, qs, k, L, reps=5, eps=eps)
     ids_h = ids[:gt_rows].cpu().numpy().view(np.uint32)
     out = {"L": L, "eps": eps, "recall": round(recall(ids_h, gt), 4),
@@ -175,9 +175,11 @@ def query_point(torch, A, O, w, g_stats, pts, qs, qs_stream, k, setting, gt, kth
     nqs = qs_stream.shape[0]
     hops = (st1["hops"] - st0["hops"]) / (nlaunch * nqs)
     evals = (st1["evals"] - st0["evals"]) / (nlaunch * nqs)
+    survivors = (st1["survivors"] - st0["survivors"]) / (nlaunch * nqs)
+    sketch = sketch_bytes(w, L, nqs)
     distinct = 1.0
     if O is not None and graph_rows is not None:
-        ns = min(1000, qs.shape[0])
+        ns = min(4096, qs.shape[0])  # (launches of up to 3,072 also count what their kernels expand ahead of its turn)
         ost = O.Stats()
         O.search_batch(O.Dataset(w.points, w.metric), graph_rows, start, w.queries[:ns], k, L, threads=0, stats=ost,
                        eps=-1.0 if eps is None else eps)
@@ -186,16 +188,37 @@ def query_point(torch, A, O, w, g_stats, pts, qs, qs_stream, k, setting, gt, kth
         torch.cuda.synchronize()
         sb = g_stats.stats()
         distinct = min(1.0, ost.evals / max(1, sb["evals"] - sa["evals"]))
-    per_query = hops * 4 * w.R + evals * distinct * row_bytes + 8 * k
+    per_query = hops * 4 * w.R + vector_bytes(w, sketch, evals * distinct, survivors) + 8 * k
+    if sketch:
+        per_query += w.n * (w.d * 4 + sketch) / nqs
     achieved = per_query * nqs / (ms_s / 1e3) / 1e9
     out["qps_stream"] = round(nqs / ms_s * 1e3, 1)
     out["stream_queries"] = nqs
-    out["roofline_query"] = {"bound": "hbm", "kernel": "search_kernel (queries)", "achieved": round(achieved, 1),
+    out["roofline_query"] = {"bound": "hbm", "kernel": f"{'search_sketch_kernel' if sketch else 'search_kernel'} (queries)",
+                             "achieved": round(achieved, 1),
                              "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                              "hops_per_query": round(hops, 2), "evals_per_query": round(evals, 2),
                              "distinct_eval_fraction": round(distinct, 4), "bytes_per_query": int(per_query),
                              "launch_ms": round(ms_s, 4), **working_set(w)}
     return out
+
+
+def sketch_bytes(w, L, queries=0):
+    """Bytes of a float row's 8-bit sketch where the library's searches read it before the row (beams of 16 to
+    128; builds over 100 MB of rows and more, calls of more than 1,024 queries on 256 MB and more), else 0."""
+    row = w.d * 4
+    if w.points.dtype != np.float32 or not 16 <= L <= 128 or w.n * row < (256 << 20 if queries else 100 << 20):
+        return 0
+    if queries and queries <= 1024:
+        return 0
+    return 128 if 80 <= w.d < 128 else 256 if 160 <= w.d < 256 else 0
+
+
+def vector_bytes(w, sketch, distinct_evals, survivors):
+    """What a search has to gather for its distances: the row of every candidate, or, with sketches, the sketch of
+    every candidate and the rows of those that enter the beam."""
+    row = w.d * w.points.dtype.itemsize
+    return distinct_evals * sketch + survivors * row if sketch else distinct_evals * row
 
 
 def working_set(w):
@@ -208,21 +231,21 @@ def working_set(w):
 
 def build_roofline(st, w, distinct_frac, traffic, distinct_known=True):
     """Roofline of the dominant kernel, the build's beam search.  Algorithmic bytes = hops * 4R
-    (adjacency rows) + DISTINCT distance evaluations * row bytes (gathered vectors) + 8 * hops
-    (visited list).  One launch here is the searches of one batch.  A batch of 8,192 points or more
+    (adjacency rows) + DISTINCT distance evaluations * row bytes (gathered vectors; with sketches as in
+    vector_bytes) + 8 * hops (visited list).  One launch here is the searches of one batch.  A batch of 8,192 points or more
     issues them as three kernel dispatches side by side on three streams (a part that is through
     prunes while the others still search), and the launch's time is the span from the first
     dispatch's start to the last one's end (HIP events the library records on those streams).
     The dispatches' own durations (they overlap) are reported beside it: their average is what a
     kernel trace of the same build shows per dispatch."""
-    row_bytes = w.d * w.points.dtype.itemsize
-    srch_bytes = st["hops"] * (4 * w.R + 8) + st["evals"] * distinct_frac * row_bytes
+    sketch = sketch_bytes(w, w.L)
+    srch_bytes = st["hops"] * (4 * w.R + 8) + vector_bytes(w, sketch, st["evals"] * distinct_frac, st["survivors"])
     srch_s = st["ms_search"] / 1e3
     achieved = srch_bytes / srch_s / 1e9 if srch_s > 0 else 0.0
     nd = max(1, int(st.get("search_launches", 0)) or int(st["rounds"]))
     nb = max(1, int(st["rounds"]))
     return {
-        "bound": "hbm", "kernel": "search_kernel (build, step 1 of BatchInsert)",
+        "bound": "hbm", "kernel": f"{'search_sketch_kernel' if sketch else 'search_kernel'} (build, step 1 of BatchInsert)",
         "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
         # one launch = the searches of one batch; achieved = bytes_per_launch / avg_launch_ms
