@@ -69,8 +69,8 @@ __global__ __launch_bounds__(256) void sketch_rows_kernel(const char* rows, u64 
 // points of 64 floats 583 -> 658 us, 5,000 on 500,000 points of 128 764 -> 994.)
 u32 sketch_bytes(const DistCfg& cfg) {
   if (cfg.kind != K_F32_L2 && cfg.kind != K_F32_IP) return 0;
-  if (cfg.npieces >= 20u && cfg.npieces < 32u) return 128;
-  return cfg.npieces >= 40u && cfg.npieces < 64u ? 256 : 0;
+  if (cfg.npieces >= SKETCH_PIECES<1> && cfg.npieces < 32u) return 128;
+  return cfg.npieces >= SKETCH_PIECES<2> && cfg.npieces < 64u ? 256 : 0;
 }
 
 // Sketches pay where the rows lie beyond the 256 MB of the last-level cache.  A million points of 200 floats under the

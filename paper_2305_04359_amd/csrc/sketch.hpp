@@ -28,6 +28,11 @@
 namespace annmi {
 
 constexpr float SKETCH_LEAST = 1e-12f, SKETCH_MOST = 1e12f;
+// Rows with a sketch of 128 SK bytes have at least so many pieces (sketch_bytes: 20 to 31, 40 to 63), so that every lane
+// of a group has pieces in each 16-byte part that it holds.
+template <int SK>
+constexpr u32 SKETCH_PIECES = SK == 1 ? 20 : 40;
+static_assert(SKETCH_PIECES<1> >= (u32)LPC && SKETCH_PIECES<2> >= 32u + (u32)LPC);
 
 struct SketchTable {
   const char* base;  // 128 * SK bytes per vertex
@@ -141,8 +146,6 @@ __device__ __forceinline__ void sketch_passes(const SketchTable& K, const Sketch
 #pragma unroll
   for (int s = 0; s < SK; ++s) {
     const uint4 h = S.mine[2 * s * LPC], l = S.mine[(2 * s + 1) * LPC];
-    // (what a lane reads for want of pieces of its own does not count, nor does the last lane's meta)
-    const bool mine = s + 1 < SK || last_off == (u32)((SK - 1) * 128 + sub * 16);
 #pragma unroll
     for (int tt = 0; tt < PBX; ++tt) {
       const uint4 w = x[tt][s];
@@ -158,9 +161,8 @@ __device__ __forceinline__ void sketch_passes(const SketchTable& K, const Sketch
         i32 v = __builtin_amdgcn_sdot4((i32)w.x, (i32)w.x, 0, false);
         v = __builtin_amdgcn_sdot4((i32)w.y, (i32)w.y, v, false);
         v = __builtin_amdgcn_sdot4((i32)w.z, (i32)w.z, v, false);
-        const i32 last = s + 1 == SK && sub == LPC - 1 ? 0 : (i32)w.w;
-        v = __builtin_amdgcn_sdot4(last, last, v, false);
-        vv[tt] += mine ? v : 0;
+        const i32 last = s + 1 == SK && sub == LPC - 1 ? 0 : (i32)w.w;  // (scale and bound do not count)
+        vv[tt] += __builtin_amdgcn_sdot4(last, last, v, false);
       }
     }
   }
