@@ -204,12 +204,9 @@ def query_point(torch, A, O, w, g_stats, pts, qs, qs_stream, k, setting, gt, kth
 
 
 def sketch_bytes(w, L, queries=0):
-    """Bytes of a float row's 8-bit sketch where the library's searches read it before the row (beams of 16 to
-    128; builds over 100 MB of rows and more, calls of more than 1,024 queries on 256 MB and more), else 0."""
-    row = w.d * 4
-    if w.points.dtype != np.float32 or not 16 <= L <= 128 or w.n * row < (256 << 20 if queries else 100 << 20):
-        return 0
-    if queries and queries <= 1024:
+    """Bytes of a float row's 8-bit sketch where the library's searches read it before the row, else 0: beams of
+    16 to 128, 256 MB of rows and more, launches of some thousand searches (the library's own rule weighs what they save)."""
+    if w.points.dtype != np.float32 or not 16 <= L <= 128 or w.n * w.d * 4 < 256 << 20 or 0 < queries < 6000:
         return 0
     return 128 if 80 <= w.d < 128 else 256 if 160 <= w.d < 256 else 0
 

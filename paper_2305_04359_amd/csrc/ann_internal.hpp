@@ -185,8 +185,12 @@ hipError_t plan_search(const DistCfg& cfg, const SearchArgs& a, SearchPlan* plan
 u32 sketch_bytes(const DistCfg& cfg);
 constexpr u32 SEARCH_SKETCH_BEAM = 128;  // the longest beam of a search that reads sketches
 constexpr u32 SEARCH_SKETCH_MIN = 1024;  // launches of more searches than this read them
-// whether making them for all n rows is repaid by that many searches (queries, or the searches of an insertion)
-bool search_sketch_pays(const DistCfg& cfg, u64 n, u64 searches, u32 L, bool query);
+// the launches of a call that searches over them (L: their beam), and whether making them for all n rows is repaid
+struct SketchUse {
+  u64 largest = 0, gaining = 0;
+  void launch(u64 searches, u32 L);
+};
+bool search_sketch_pays(const DistCfg& cfg, u64 n, u32 L, const SketchUse& use, bool build);
 hipError_t launch_sketch_rows(const DistCfg& cfg, const void* rows, u64 first, u64 count, void* out, hipStream_t s);
 hipError_t launch_descend(const DistCfg& cfg, const DescendArgs& a, hipStream_t s);
 hipError_t launch_prune(const DistCfg& cfg, const PruneArgs& a, hipStream_t s);

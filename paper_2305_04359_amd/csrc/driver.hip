@@ -295,11 +295,13 @@ bool give_back_sketches() {
   return true;
 }
 
-// Sketches of the graph's points for the searches of this call, `searches` in all (see search_sketch_pays): g->sketch
-// until the call is over.  Without the memory the searches do without.
-int make_sketches(SketchScope& S, const void* points, u64 searches, u32 L, hipStream_t st) {
+// Sketches of the graph's points for the searches of this call (see search_sketch_pays): g->sketch until the call is
+// over.  Without the memory the searches do without.
+int make_sketches(SketchScope& S, const void* points, const std::vector<u64>& bounds, u32 L, bool build, hipStream_t st) {
   ann_graph* g = S.g;
-  if (!search_sketch_pays(g->cfg, g->n, searches, L, false)) return ANN_OK;
+  SketchUse use;
+  for (size_t r = 0; r + 1 < bounds.size(); ++r) use.launch(bounds[r + 1] - bounds[r], L);
+  if (!search_sketch_pays(g->cfg, g->n, L, use, build)) return ANN_OK;
   if (S.buf.alloc(g->n * sketch_bytes(g->cfg)) != hipSuccess) {
     (void)hipGetLastError();
     return ANN_OK;
@@ -312,7 +314,9 @@ int make_sketches(SketchScope& S, const void* points, u64 searches, u32 L, hipSt
 // The same for a call that answers nq queries: made anew by every call, in memory that the graph keeps.
 int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStream_t st, const void** out) {
   *out = nullptr;
-  if (nq <= SEARCH_SKETCH_MIN || !search_sketch_pays(g->cfg, g->n, nq, L, true)) return ANN_OK;
+  SketchUse use;
+  use.launch(nq, L);
+  if (!search_sketch_pays(g->cfg, g->n, L, use, false)) return ANN_OK;
   // (a captured call must not allocate, and what it captures may outlive the memory)
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
@@ -1155,7 +1159,7 @@ int ann_insert_points(ann_graph* g, const void* points_dev, uint64_t n_total, ui
   const void* pts = nullptr;
   rc = resolve_points(g, points_dev, st, &pts);
   if (rc) return rc;
-  rc = make_sketches(sketches, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, st);
+  rc = make_sketches(sketches, pts, bounds, L, false, st);
   if (rc) return rc;
   const double t_alloc = now_ms();
   // Every batch waits on the host after step 1 (the check for visited lists that fit nowhere):
@@ -1329,7 +1333,7 @@ int ann_build(const void* points_dev, uint64_t n, uint32_t d, ann_dtype dtype, a
   const void* pts = nullptr;
   rc = resolve_points(g, points_dev, st, &pts);
   if (rc) return rc;
-  rc = make_sketches(sketches, pts, bmax > SEARCH_SKETCH_MIN ? m : 0, L, st);
+  rc = make_sketches(sketches, pts, bounds, L, true, st);
   if (rc) return rc;
 
   const double t_alloc = now_ms();

@@ -324,7 +324,8 @@ struct SketchScope {
   SketchScope& operator=(const SketchScope&) = delete;
   ~SketchScope();
 };
-int make_sketches(SketchScope& S, const void* points, u64 searches, u32 L, hipStream_t st);
+// batches: bounds[r] to bounds[r + 1]; build: of a whole build, not of an insertion
+int make_sketches(SketchScope& S, const void* points, const std::vector<u64>& bounds, u32 L, bool build, hipStream_t st);
 bool give_back_sketches();  // those of the call that this thread is in; false: there are none
 int query_sketches(const ann_graph* g, const void* points, u64 nq, u32 L, hipStream_t st, const void** out);
 int release_query_sketches(const ann_graph* g);

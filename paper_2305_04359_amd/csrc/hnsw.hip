@@ -276,7 +276,7 @@ int run_batches(ann_hnsw* h, const void* points_dev, const std::vector<u32>& ord
     rc = resolve_points(h->layer[l], h->pts[l].p, st, &lp[l]);
     if (rc) return rc;
   }
-  rc = make_sketches(sketches, lp[0], bmax > SEARCH_SKETCH_MIN ? cnt : 0, efc, st);
+  rc = make_sketches(sketches, lp[0], bounds, efc, may_restart, st);
   if (rc) return rc;
 
   for (int attempt = may_restart ? 0 : 1; attempt < 2; ++attempt) {

@@ -76,22 +76,43 @@ u32 sketch_bytes(const DistCfg& cfg) {
 // Sketches pay where the rows lie beyond the 256 MB of the last-level cache.  A million points of 200 floats under the
 // inner product: build at R = 64, L = 128 251 -> 188 ms, 10,000 queries at L = 50 1,930 -> 1,310 us, of which
 // making the sketches 175 (1.06 GB moved at 6 TB/s); the searches fetch 6.7 GB where they fetched 12.
-//  - Builds gain before their rows fill that cache, which the graph and the visited lists share: 300,000 points of
-//    200 floats (240 MB) 74.7 -> 62.4 ms, 150,000 in an insertion (120 MB) 62.2 -> 54.8; 200,000 of 160 at L = 64 (128
-//    MB) about 1 %, 110,000 of 100 at L = 64 (44 MB) 24.7 -> 25.7.  Queries on rows that fit do not (200,000 points of
-//    160 floats, sketches apart, 229 and 228 us).
-//  - What searches save has to repay the sketches of all n rows.  A search takes about 24 L + 400 distances, a third
-//    of which need the row after all: queries whose bytes saved are 1.9 times those spent lose 2 % (4,000 on
-//    500,000 points of 160 floats, L = 40), 2.8 times gain a third (10,000 on a million of 100, L = 30: 1,031 ->
-//    773 us), 14 times 1.7 (50,000 on 700,000 of 180, L = 20: 5,203 -> 3,049 us).
+//  - Queries and insertions make them anew for every call, and what its searches save has to repay that.  A search takes
+//    about 24 L + 400 distances, of which 30 % + L / 500 need the row after all; the first 2,000 + 32 L of a launch save
+//    nothing (they wait for their own chains, which the sketches make longer); and what is saved counts by the
+//    share of the rows that the cache can't hold, a tenth if all but fits.  Where that makes half of the bytes that
+//    the making moves, 1,112 calls (100 to 252 floats, 300 to 800 MB, L = 24 to 128, 1,500 to 40,000 queries, R = 40
+//    and 56) are at most 2 % slower than without and up to 45 % faster; below it calls lose up to 27 % (2,000 queries on
+//    700,000 points of 124 floats, L = 128: 524 -> 665 us).  Of 596 other calls (drawn from 80 to 252 floats, 260
+//    to 1,300 MB, with and without the (1 + eps) rule) three lose more than 3 %, up to 17: two that the rule ends early, one at
+//    L = 17; all gain 23 % in the mean.  Insertions of 1,200 to 60,000 points: at most 4 % slower and up to 22 % faster;
+//    below 256 MB of rows nearly all lose (2,500 on 128 MB 5 to 13 %).
+//  - Builds search over them in dozens of launches.  On 256 MB of rows and more: 1 % slower (160 floats, L = 128, 320 MB)
+//    to 26 % faster.  Below, what counts is that the query lies in LDS and leaves registers to waves.  Rows of 256-byte
+//    sketches gain from 100 MB on (200 floats, R = 56, L = 128: 38.9 -> 36.9 ms at 128 MB, 55.6 -> 45.9 at 200), but those
+//    of less than three sketches at beams of up to 64 lose 2 to 3 % below 150 MB.  Rows of 128-byte sketches have
+//    six waves per SIMD for five: they gain where that spares a batch's searches a generation of waves (285,000 points of 112
+//    floats, batches of 5,669: 42.7 -> 37.1 ms) and lose 1 to 6 % where it doesn't (335,000, 6,696: 30.8 -> 31.6).
 //  - Beams above 128: more entries, so more of a row's candidates may enter, and four waves per SIMD (20,000 queries, 500,000
 //    points of 160 floats, L = 200: 3,793 -> 4,100 us).
 //  - Below a beam of 16 a search is over soon after its beam has filled.
-bool search_sketch_pays(const DistCfg& cfg, u64 n, u64 searches, u32 L, bool query) {
-  const u64 sk = sketch_bytes(cfg), row = cfg.row_bytes;
-  if (sk == 0 || L > SEARCH_SKETCH_BEAM || L < 16u) return false;
-  if (n * row < (query ? 256ull << 20 : 100ull << 20)) return false;
-  return searches * (24u * L + 400u) * (13u * row / 20u - sk) >= n * (row + sk) * 5u / 2u;
+void SketchUse::launch(u64 searches, u32 L) {
+  const u64 idle = 2000u + 32u * L;
+  largest = searches > largest ? searches : largest;
+  gaining += searches > idle ? searches - idle : 0;
+}
+bool search_sketch_pays(const DistCfg& cfg, u64 n, u32 L, const SketchUse& use, bool build) {
+  constexpr u64 cache = 256ull << 20, simds = 1024;
+  const u64 sk = sketch_bytes(cfg), row = cfg.row_bytes, bytes = n * row;
+  if (sk == 0 || L > SEARCH_SKETCH_BEAM || L < 16u || use.largest <= SEARCH_SKETCH_MIN) return false;
+  if (build && bytes < cache) {
+    if (sk == 128u) return bytes >= 100ull << 20 && (use.largest - 1u) / (5u * simds) != (use.largest - 1u) / (sketch_waves(4) * simds);
+    return bytes >= (L > 64u || row >= 3u * sk ? 100ull << 20 : 150ull << 20);
+  }
+  if (build) return true;
+  if (bytes < cache) return false;
+  const double saved = (double)row * (0.7 - L / 500.0) - (double)sk;
+  const double beyond = 1.1 - (double)cache / (double)bytes;
+  return (double)use.gaining * (24.0 * L + 400.0) * saved * beyond >= 0.5 * (double)n * (double)(row + sk);
 }
 
 hipError_t launch_sketch_rows(const DistCfg& cfg, const void* rows, u64 first, u64 count, void* out, hipStream_t s) {

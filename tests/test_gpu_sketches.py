@@ -280,3 +280,24 @@ def test_what_fits_without_sketches_fits(env, calls, n):
         assert np.array_equal(a, b)
     torch.cuda.synchronize()
     assert limited.held == 0
+
+
+def test_few_searches_make_no_sketches(env):
+    """Calls whose searches would not repay the sketches ask for no memory for them: few queries with wide beams, insertions
+    into rows that the cache holds; with enough of them they do."""
+    torch, A, _ = env
+    n, d = (272 << 20) // 400, 100
+    x = _points(torch, n, d, "unit", 9)
+    refusing = _Refusing(A, n * 128)
+    g = A.ann_build(x, 40, 32, 1.0, seed=2, allocator=refusing, batch_cap=20_000, max_rounds=16)
+    assert refusing.refused == 1
+    for nq, L, made in ((1500, 64, 0), (3000, 128, 0), (5000, 128, 0), (20_000, 10, 0), (20_000, 129, 0), (30_000, 64, 1)):
+        before = refusing.refused
+        A.ann_search(g, x, x[:nq], 10, L)
+        assert refusing.refused - before == made, (nq, L)
+    n = 300_010  # (no other array has the size of the sketches)
+    for m, L in ((2500, 128), (6000, 64), (40_000, 64)):
+        refusing = _Refusing(A, n * 128)
+        g = A.ann_build(x[:n - m], 40, 16, 1.0, seed=2, allocator=refusing, batch_cap=20_000)
+        A.ann_insert_points(g, x[:n], L, 1.0, seed=3)
+        assert refusing.refused == 0, (m, L)
