@@ -162,7 +162,7 @@ struct MergeArgs {
   long long a16;
   float af;
   DevCounters* counters;
-  u32 launches;     // re-prune launches: 1 (all kinds in one), 2 (all but the longest lists), 0 (one per kind, side by side)
+  u32 launches;     // re-prune launches: 1 (all kinds in one), 2 (all but the longest lists), 3 (nor the fast kind), 0 (one per kind, side by side)
   u32 force_prune;  // non-zero: every segment is pruned, also where row and segment fit in R (the
                     // clustering-based builder, Sec. 4.3; rows start empty there)
 };

@@ -612,7 +612,7 @@ int batch_insert(ann_graph* g, const void* points, const u32* ids_host, const u3
   // a kernel instance of their own; elsewhere one more launch per batch would cost more than
   // the few rows gain
   ma.launches = merge_launches(g->cfg, b);
-  ma.medium_max = (!ma.gram_ok || ma.launches == 2 || E >= (1ull << 22)) ? MERGE_MEDIUM_MAX : 0u;
+  ma.medium_max = (!ma.gram_ok || ma.launches >= 2 || E >= (1ull << 22)) ? MERGE_MEDIUM_MAX : 0u;
   ma.stage_bytes = prune_stage_bytes(R, g->cfg);
   ma.use_mfma = mfma_prune_ok(R, g->cfg) ? 1u : 0u;
   ma.arena = S.arena.as<u64>();

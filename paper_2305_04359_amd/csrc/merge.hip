@@ -1182,14 +1182,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KindTraits<K
 
 // All three kinds in one launch, for batches with few segments: three launches one after the other take 24 us in a batch
 // of 200 points, this one 14.  A workgroup has the LDS and the registers of the largest kind: with the buffer of 4,096 keys
-// three share a compute unit, with that of 512 (CAP; longer lists have a launch of their own) eight.  The longest lists
-// first; merge_launches says where this pays.
+// three share a compute unit, with that of 512 (CAP; longer lists have a launch of their own) eight, or five on rows
+// above 128 bytes, whose gram buffers are 32 KB.  The fast kind needs neither and has its own launch (launches == 3) where its
+// items are many.  The longest lists first; merge_launches says where this pays.
 template <int KIND, int VEC, int NCH, u32 CAP>
 __global__ __launch_bounds__(64) void merge_all_kernel(MergeArgs a, VecTable T) {
   if constexpr (KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x;
-    const u32 nfast = a.list_count[0], ngram = a.list_count[1], nlong = a.list_count[CAP == MERGE_SPILL_MIN ? 2 : 3];
+    const u32 nfast = a.launches == 3 ? 0u : a.list_count[0], ngram = a.list_count[1], nlong = a.list_count[CAP == MERGE_SPILL_MIN ? 2 : 3];
     MergeStats stats;
     for (u32 it = blockIdx.x; it < nlong + ngram + nfast; it += gridDim.x) {
       if (it < nlong)
@@ -1227,9 +1228,12 @@ static hipError_t launch_merge_t(const MergeArgs& a, const VecTable& T, u32 grid
   if constexpr (KindTraits<KIND>::is_int && SmallPathOk<VEC, NCH>::value) {
     if (a.launches == 1)
       return launch_merge_all<KIND, VEC, NCH, MERGE_SPILL_MIN>(a, T, grid < 1024u ? grid : 1024u, lds, s);
-    if (a.launches == 2) {
+    if (a.launches >= 2) {
       hipLaunchKernelGGL((merge_generic_kernel<KIND, VEC, NCH, MERGE_SPILL_MIN>), dim3(grid < 1024u ? grid : 1024u), dim3(64), lds, s, a, T);
-      return launch_merge_all<KIND, VEC, NCH, MERGE_MEDIUM_MAX>(a, T, grid < 4096u ? grid : 4096u, lds, s);
+      const hipError_t e = launch_merge_all<KIND, VEC, NCH, MERGE_MEDIUM_MAX>(a, T, grid < 4096u ? grid : 4096u, lds, s);
+      if (a.launches == 2 || e != hipSuccess) return e;
+      hipLaunchKernelGGL((merge_fast_kernel<KIND, VEC, NCH>), dim3(grid), dim3(64), 0, s, a, T);
+      return hipGetLastError();
     }
   }
   const u32 grid_generic = (grid < 1024u || a.force_prune) ? grid : 1024u;
@@ -1256,21 +1260,23 @@ hipError_t launch_merge(const DistCfg& cfg, const MergeArgs& a, u32 grid, hipStr
   ANN_DISPATCH_CFG(launch_merge_t, a, T, grid, s, s_gram, s_generic, s_medium);
 }
 
-// Batches of byte rows whose re-prunes go in one launch or two, on one stream; in larger ones each kind has a launch, and from
-// 2,048 points on a stream.  What counts is how many rows there are to prune, four to five per point: in one launch
-// three workgroups share a compute unit, in two eight.  Whole builds, side by side or one after the other as
-// before / in one launch / in two:
-//  - rows of up to 128 bytes, batches of 900 points (45,000, R = 64, L = 64) 10.7 / 9.3 ms; 1,600 (R = 64) 18.3 /
-//    16.9 / 16.9; 1,800 (int8, R = 48) 17.9 in one, 16.4 in two; 2,000 (R = 32) 20.5 and 19.6; 3,000 (int8, R = 64) 24.2 /
-//    26.7 / 24.0; 4,000 (R = 32) 30.8 in one, 27.3 in two; 4,000 (layered, R = 64) 28.1 / 28.7 / 27.7; 8,000 (R = 32) 30.4 / - /
-//    31.2; 20,000 (R = 64) 76.7 / - / 90.6.
-//  - rows of up to 256 bytes (256 registers): 1,200 points (200 bytes, R = 64) 17.1 / 14.5; 1,900 (256 bytes)
-//    19.0 / 18.0 / 17.2; 2,400 (200 bytes, R = 48) 20.4 / - / 19.0; 3,000 (R = 32) 23.9 / - / 24.7.
+// Batches of byte rows whose re-prunes go in one launch, in two, or in three (two and the fast kind), on one stream; in larger
+// ones each kind has a launch, and from 2,048 points on a stream.  What counts is how many rows there are to prune, four to
+// five per point, and of what kind: the fast ones want many waves per compute unit (joined, they get eight or five), the longest
+// lists want the 512-key buffer.  Whole builds, each kind apart / in one launch / in two / in three:
+//  - rows of up to 128 bytes, uint8 and int8 of 128 at R = 40: batches of 1,020 points 10.2 / 9.6 / 9.8 / 10.2 ms and
+//    12.0 / 11.7 / 10.8 / 11.1; 2,800 14.2 / - / 13.2 / 13.6 and 17.1 / - / 17.2 / 17.0; 4,000 17.5 / - / 17.0 / 17.0 and
+//    21.9 / - / 23.7 / 22.9 (at R = 104 46.1 / - / 39.1 / 38.0); 5,200 19.9 / - / 19.9 / 19.6 and 25.8 / - / 29.7 / 28.3.
+//  - rows of up to 256 bytes (256 registers), uint8 of 200 and int8 of 256 at R = 48 and 64: batches of 400 points 9.1 / 8.4 / 8.6
+//    / 9.0, 14.9 / 13.9 / 14.0 / 14.5 and 10.8 / 10.1 / 9.6 / 9.8, 16.7 / 16.7 / 15.5 / 15.6; 1,000 11.2 / 10.1 / 10.2 / 10.7, 17.8 /
+//    16.7 / 16.5 / 16.8 and 14.4 / 15.4 / 13.5 / 13.1, 22.1 / 25.3 / 22.2 / 21.1; 1,700 13.4 / - / 11.9 / 12.4, 20.0 / -
+//    / 18.4 / 18.8 and 18.7 / - / 19.3 / 17.4, 27.3 / - / 29.2 / 26.3; 2,500 15.3 / - / 14.9 / 14.8, 22.3 / - / 21.2 / 21.6 and 21.9 / -
+//    / 28.0 / 24.0, 31.6 / - / 38.0 / 32.9 (int8 of 140: 17.8 / - / 19.0 / 17.9, 29.1 / - / 31.6 / 29.6);
+//    3,200 17.8 / - / 18.5 / 17.8 and 25.4 / - / 33.1 / 27.6.
 u32 merge_launches(const DistCfg& cfg, u64 batch) {
   if (!gram_path_ok(cfg)) return 0;
-  const bool narrow = cfg.nch == 1;
-  if (batch <= (narrow ? 1024u : 1280u)) return 1;
-  return batch <= (narrow ? 4096u : 2560u) ? 2 : 0;
+  if (cfg.nch == 1) return batch <= 1024u ? 1 : batch <= 3072u ? 2 : batch <= 4096u ? 3 : 0;
+  return batch <= 512u ? 1 : batch <= 1536u ? 2 : batch <= 2560u ? 3 : 0;
 }
 
 bool gram_path_ok(const DistCfg& cfg) { return cfg.kind <= 1 && 8 * cfg.nch * cfg.vec <= 256; }

@@ -14,12 +14,14 @@ def _points(n, d, rng):
     return np.clip(c[rng.integers(0, 40, n)] + rng.normal(0, 14, (n, d)), 0, 255).astype(np.uint8)
 
 
-# batches of 1,024 / 1,025 and 4,096 / 4,097 points on rows of up to 128 bytes, of 1,280 / 1,281 and 2,560 / 2,561 on wider
-# ones; 1,024, 1,032 and 12,288, 12,320 keys; 10, 11, 12 and 15 bits of an id
+# batches of 1,024 / 1,025, 3,072 / 3,073 and 4,096 / 4,097 points on rows of up to 128 bytes, of 512 / 513, 1,536 / 1,537 and
+# 2,560 / 2,561 on wider ones; 1,024, 1,032 and 12,288, 12,320 keys; 10, 11, 12 and 15 bits of an id
 @pytest.mark.parametrize("n,d,R,batch", [
     (700, 20, 8, 128), (700, 20, 8, 129), (3000, 32, 16, 768), (3000, 32, 16, 770), (1023, 16, 32, 500), (1025, 16, 32, 500),
-    (2049, 128, 24, 1024), (2049, 128, 24, 1025), (17_000, 24, 12, 4096), (17_000, 24, 12, 4097), (5000, 200, 20, 1280),
-    (5000, 200, 20, 1281), (8000, 136, 12, 2560), (8000, 136, 12, 2561), (20_000, 64, 64, 20_000)])
+    (2049, 128, 24, 1024), (2049, 128, 24, 1025), (17_000, 24, 12, 4096), (17_000, 24, 12, 4097), (3000, 150, 20, 512),
+    (3000, 150, 20, 513), (5000, 200, 20, 1280), (5000, 200, 20, 1281), (5000, 200, 20, 1536), (5000, 200, 20, 1537),
+    (8000, 136, 12, 2560), (8000, 136, 12, 2561), (14_000, 40, 12, 3072), (14_000, 40, 12, 3073),
+    (9000, 180, 100, 2400), (20_000, 64, 64, 20_000)])
 def test_batches_equal_the_oracles(env, n, d, R, batch):
     torch, A, O = env
     say(f"grouping n={n} d={d} R={R} batch={batch}")
